@@ -134,21 +134,23 @@ __device__ __forceinline__ double block_sum_all(double v, double *sh) {
     return s;
 }
 
-__device__ __forceinline__ void block_sum2_all(double &a, double &b, double *sh) {
-    a = wave_sum(a);
-    b = wave_sum(b);
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = (blockDim.x + 63) >> 6;
-    __syncthreads();
-    if (lane == 0) {
-        sh[w] = a;
-        sh[32 + w] = b;
+// sums of a and b over a workgroup of NW wavefronts, valid in every thread
+// (fixed order): one barrier, on a buffer sh (2 NW doubles) that the previous
+// reduction did not use
+template <int NW>
+__device__ __forceinline__ void block_sum2_dpp(double &a, double &b, double *sh) {
+    a = wave_sum_dpp(a);
+    b = wave_sum_dpp(b);
+    if ((threadIdx.x & 63) == 0) {
+        sh[threadIdx.x >> 6] = a;
+        sh[NW + (threadIdx.x >> 6)] = b;
     }
     __syncthreads();
-    a = 0.0;
-    b = 0.0;
-    for (int q = 0; q < nw; q++) {
+    a = b = 0.0;
+#pragma unroll
+    for (int q = 0; q < NW; q++) {
         a += sh[q];
-        b += sh[32 + q];
+        b += sh[NW + q];
     }
 }
 
@@ -690,16 +692,17 @@ __global__ void k_local_coarse15(const VolDesc *__restrict__ vd, int nvol, int s
 // coarsest level: Jacobi-PCG in one workgroup, unknowns owned by threads,
 // search direction shared through LDS
 // ---------------------------------------------------------------------------
-template <typename T, int NPT, int NB = 6>
-__global__ void __launch_bounds__(1024) k_coarse_pcg(int n, const long long *__restrict__ slot,
+template <typename T, int NW, int NPT, int NB = 6>
+__global__ void __launch_bounds__(64 * NW) k_coarse_pcg(int n, const long long *__restrict__ slot,
                                                      const int *__restrict__ col, const double *__restrict__ val,
                                                      const unsigned char *__restrict__ frozen, const T *__restrict__ b,
                                                      T *__restrict__ u, const int *__restrict__ cptr,
                                                      const int *__restrict__ cidx, double rtol, int maxit,
                                                      int *__restrict__ iters) {
-    __shared__ double p_sh[2048];
-    __shared__ double red[64];
-    const int tid = threadIdx.x, nt = blockDim.x;
+    constexpr int nt = 64 * NW;
+    __shared__ double p_sh[nt * NPT];
+    __shared__ double red[2][2 * NW];
+    const int tid = threadIdx.x;
     // every thread owns NPT unknowns; their matrix rows stay in registers
     double x[NPT], r[NPT], p[NPT], dinv[NPT], dg[NPT], av[NPT][NB];
     int ac[NPT][NB];
@@ -740,7 +743,7 @@ __global__ void __launch_bounds__(1024) k_coarse_pcg(int n, const long long *__r
         rz += r[s] * p[s];
         rr0 += r[s] * r[s];
     }
-    block_sum2_all(rz, rr0, red);
+    block_sum2_dpp<NW>(rz, rr0, red[1]);
     int it = 0;
     if (rr0 > 0.0) {
         const double stop = rtol * rtol * rr0;
@@ -759,7 +762,7 @@ __global__ void __launch_bounds__(1024) k_coarse_pcg(int n, const long long *__r
                 qv[s] = a;
                 pq += p[s] * a;
             }
-            block_sum2_all(pq, dummy, red);
+            block_sum2_dpp<NW>(pq, dummy, red[0]);
             const double alpha = rz / pq;
             double rr = 0.0, rz1 = 0.0;
 #pragma unroll
@@ -769,7 +772,7 @@ __global__ void __launch_bounds__(1024) k_coarse_pcg(int n, const long long *__r
                 rr += r[s] * r[s];
                 rz1 += r[s] * r[s] * dinv[s];
             }
-            block_sum2_all(rr, rz1, red);
+            block_sum2_dpp<NW>(rr, rz1, red[1]);
             if (rr <= stop) break;
             const double beta = rz1 / rz;
             rz = rz1;
@@ -1330,75 +1333,89 @@ __global__ void k_dirichlet_load(int N, double h, const double *__restrict__ k, 
 // tetrahedra only.  Fine element (cell c, permutation q) at a level with m
 // segments per macro edge lies in the macro tetrahedron of macro cell c / m
 // whose axis order sorts the element's centroid offsets in that macro cell.
-__device__ int macro_tet_of(int cx, int cy, int cz, int q, int m, int n_sub) {
-    const int C[3] = {cx / m, cy / m, cz / m};
+__device__ __forceinline__ int macro_tet_of(int cx, int cy, int cz, int p0, int p1, int p2, int m, int n_sub) {
+    const int C0 = cx / m, C1 = cy / m, C2 = cz / m;
     // centroid offsets in quarter units: 3, 2, 1 along the element's axes p0, p1, p2
-    int D[3] = {4 * (cx - m * C[0]), 4 * (cy - m * C[1]), 4 * (cz - m * C[2])};
-    D[kPermD[q][0]] += 3;
-    D[kPermD[q][1]] += 2;
-    D[kPermD[q][2]] += 1;
-    const int a0 = D[0] > D[1] ? (D[0] > D[2] ? 0 : 2) : (D[1] > D[2] ? 1 : 2);
-    const int a2 = D[0] < D[1] ? (D[0] < D[2] ? 0 : 2) : (D[1] < D[2] ? 1 : 2);
+    const int D0 = 4 * (cx - m * C0) + (p0 == 0 ? 3 : p1 == 0 ? 2 : 1);
+    const int D1 = 4 * (cy - m * C1) + (p0 == 1 ? 3 : p1 == 1 ? 2 : 1);
+    const int D2 = 4 * (cz - m * C2) + (p0 == 2 ? 3 : p1 == 2 ? 2 : 1);
+    const int a0 = D0 > D1 ? (D0 > D2 ? 0 : 2) : (D1 > D2 ? 1 : 2);
+    const int a2 = D0 < D1 ? (D0 < D2 ? 0 : 2) : (D1 < D2 ? 1 : 2);
     const int a1 = 3 - a0 - a2;
-    return 6 * (C[0] + n_sub * (C[1] + n_sub * C[2])) + perm_id(a0, a1);
+    return 6 * (C0 + n_sub * (C1 + n_sub * C2)) + perm_id(a0, a1);
+}
+__device__ __forceinline__ int macro_tet_of(int cx, int cy, int cz, int q, int m, int n_sub) {
+    return macro_tet_of(cx, cy, cz, kPermD[q][0], kPermD[q][1], kPermD[q][2], m, n_sub);
 }
 
 // edge weight over intact elements: k (or 1 with k == nullptr) of each
 // tetrahedron having the edge on its axis path, unless its macro
-// tetrahedron is faulty
-__device__ double edge_w_intact(const double *__restrict__ k, int N, double h, int x, int y, int z, int a, int m,
-                                int n_sub, const unsigned char *__restrict__ faulty) {
+// tetrahedron is faulty.  The axis is a template argument, so the six
+// elements of the edge are known at compile time.
+template <int A>
+__device__ __forceinline__ double edge_w_intact(const double *__restrict__ k, int N, double h, int x, int y, int z,
+                                                int m, int n_sub, const unsigned char *__restrict__ faulty) {
     double sum = 0.0;
-    const int P[3] = {x, y, z};
+#pragma unroll
     for (int dd = 0; dd < 8; dd++) {
         const int dl[3] = {dd & 1, (dd >> 1) & 1, (dd >> 2) & 1};
-        if (dl[a]) continue;
-        const int c[3] = {P[0] - dl[0], P[1] - dl[1], P[2] - dl[2]};
-        if (c[0] < 0 || c[1] < 0 || c[2] < 0 || c[0] >= N || c[1] >= N || c[2] >= N) continue;
+        if (dl[A]) continue;
+        const int c[3] = {x - dl[0], y - dl[1], z - dl[2]};
+        const bool in = c[0] >= 0 && c[1] >= 0 && c[2] >= 0 && c[0] < N && c[1] < N && c[2] < N;
         const int ns = dl[0] + dl[1] + dl[2];
+#pragma unroll
         for (int q = 0; q < 6; q++) {
-            bool ok = kPermD[q][ns] == a;
-            for (int s = 0; s < ns; s++) ok = ok && dl[kPermD[q][s]];
-            if (!ok || faulty[macro_tet_of(c[0], c[1], c[2], q, m, n_sub)]) continue;
+            constexpr int kP[6][3] = {{0, 1, 2}, {0, 2, 1}, {1, 0, 2}, {1, 2, 0}, {2, 0, 1}, {2, 1, 0}};
+            if (kP[q][ns] != A || (ns > 0 && !dl[kP[q][0]]) || (ns > 1 && !dl[kP[q][1]])) continue;
+            if (!in || faulty[macro_tet_of(c[0], c[1], c[2], kP[q][0], kP[q][1], kP[q][2], m, n_sub)]) continue;
             sum += k ? k[6LL * (c[0] + (long long)N * (c[1] + (long long)N * c[2])) + q] : 1.0;
         }
     }
     return sum * h / 6.0;
 }
 
-__global__ void k_ifc_weights_intact(int n_ifc, const int *__restrict__ xyz, int N, int m, int n_sub, double h,
-                                     const double *__restrict__ k, const unsigned char *__restrict__ faulty,
-                                     double *__restrict__ wi) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n_ifc) return;
-    const int x = xyz[3 * t], y = xyz[3 * t + 1], z = xyz[3 * t + 2];
-    const int X[3] = {x, y, z};
-    for (int a = 0; a < 3; a++) {
-        int Xm[3] = {x, y, z};
-        Xm[a] -= 1;
-        wi[(long long)(2 * a) * n_ifc + t] = X[a] < N ? edge_w_intact(k, N, h, x, y, z, a, m, n_sub, faulty) : 0.0;
-        wi[(long long)(2 * a + 1) * n_ifc + t] =
-            X[a] > 0 ? edge_w_intact(k, N, h, Xm[0], Xm[1], Xm[2], a, m, n_sub, faulty) : 0.0;
+// ... of the edge from node X along direction d (+x, -x, +y, -y, +z, -z)
+__device__ __forceinline__ double dir_w_intact(const double *__restrict__ k, int N, double h, int x, int y, int z, int d,
+                                               int m, int n_sub, const unsigned char *__restrict__ faulty) {
+    const int lo = d & 1;  // the edge starts one node below
+    switch (d >> 1) {
+    case 0: return edge_w_intact<0>(k, N, h, x - lo, y, z, m, n_sub, faulty);
+    case 1: return edge_w_intact<1>(k, N, h, x, y - lo, z, m, n_sub, faulty);
+    default: return edge_w_intact<2>(k, N, h, x, y, z - lo, m, n_sub, faulty);
     }
 }
 
-__global__ void k_coarse_vals_intact(int n, const int *__restrict__ pos, const int *__restrict__ col, int N, int m,
-                                     int n_sub, double h, const double *__restrict__ k,
-                                     const unsigned char *__restrict__ faulty, double *__restrict__ val) {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= n) return;
-    const int x = pos[3 * q], y = pos[3 * q + 1], z = pos[3 * q + 2];
+// one thread per master and direction (blockIdx.y): bound by the latency of
+// the element look-ups; six weights in a row per thread, with the axis known
+// at run time only, took 112 us on 534 k masters and 40 us on any smaller
+// level, against 54 us and a few
+__global__ void __launch_bounds__(256) k_ifc_weights_intact(int n_ifc, const int *__restrict__ xyz, int N, int m,
+                                                            int n_sub, double h, const double *__restrict__ k,
+                                                            const unsigned char *__restrict__ faulty,
+                                                            double *__restrict__ wi) {
+    const int t = blockIdx.x * blockDim.x + threadIdx.x, d = (int)blockIdx.y;
+    if (t >= n_ifc) return;
+    const int X[3] = {xyz[3 * t], xyz[3 * t + 1], xyz[3 * t + 2]};
+    const int Xa = d < 2 ? X[0] : d < 4 ? X[1] : X[2];
+    const bool has = (d & 1) ? Xa > 0 : Xa < N;
+    wi[(long long)d * n_ifc + t] = has ? dir_w_intact(k, N, h, X[0], X[1], X[2], d, m, n_sub, faulty) : 0.0;
+}
+
+// 8 lanes per unknown: lanes 0..5 a direction each, lane 0 the diagonal
+__global__ void __launch_bounds__(256) k_coarse_vals_intact(int n, const int *__restrict__ pos, const int *__restrict__ col,
+                                                            int N, int m, int n_sub, double h,
+                                                            const double *__restrict__ k,
+                                                            const unsigned char *__restrict__ faulty,
+                                                            double *__restrict__ val) {
+    const int t = blockIdx.x * blockDim.x + threadIdx.x, q = t >> 3, d = t & 7;
+    double w = 0.0;
+    if (q < n && d < 6) w = dir_w_intact(k, N, h, pos[3 * q], pos[3 * q + 1], pos[3 * q + 2], d, m, n_sub, faulty);
     double diag = 0.0;
-    for (int a = 0; a < 3; a++) {
-        int Xm[3] = {x, y, z};
-        Xm[a] -= 1;
-        const double wp = edge_w_intact(k, N, h, x, y, z, a, m, n_sub, faulty);
-        const double wm = edge_w_intact(k, N, h, Xm[0], Xm[1], Xm[2], a, m, n_sub, faulty);
-        diag += wp + wm;
-        val[7 * q + 1 + 2 * a] = col[7 * q + 1 + 2 * a] >= 0 ? -wp : 0.0;
-        val[7 * q + 2 + 2 * a] = col[7 * q + 2 + 2 * a] >= 0 ? -wm : 0.0;
-    }
-    val[7 * q] = diag;
+#pragma unroll
+    for (int a = 0; a < 3; a++) diag += __shfl(w, 2 * a, 8) + __shfl(w, 2 * a + 1, 8);
+    if (q >= n) return;
+    if (d < 6) val[7 * q + 1 + d] = col[7 * q + 1 + d] >= 0 ? -w : 0.0;
+    if (d == 0) val[7 * q] = diag;
 }
 
 // ---------------------------------------------------------------------------
@@ -1863,28 +1880,28 @@ template <typename T>
 void launch_coarse_pcg(hipStream_t s, int n, const long long *slot, const int *col, const double *val,
                        const unsigned char *frozen, const T *b, T *u, const int *cptr, const int *cidx, double rtol,
                        int maxit, int *iters) {
-    // up to 512 unknowns in a single wavefront; otherwise one unknown per
-    // thread in as few waves as possible (cheaper barriers)
-    if (n <= 64) {
-        hipLaunchKernelGGL((k_coarse_pcg_wave<T, 1>), dim3(1), dim3(64), 0, s, n, slot, col, val, frozen, b, u, cptr,
-                           cidx, rtol, maxit, iters);
-    } else if (n <= 128) {
-        hipLaunchKernelGGL((k_coarse_pcg_wave<T, 2>), dim3(1), dim3(64), 0, s, n, slot, col, val, frozen, b, u, cptr,
-                           cidx, rtol, maxit, iters);
-    } else if (n <= 256) {
-        hipLaunchKernelGGL((k_coarse_pcg_wave<T, 4>), dim3(1), dim3(64), 0, s, n, slot, col, val, frozen, b, u, cptr,
-                           cidx, rtol, maxit, iters);
-    } else if (n <= 512) {
-        hipLaunchKernelGGL((k_coarse_pcg_wave<T, 8>), dim3(1), dim3(64), 0, s, n, slot, col, val, frozen, b, u, cptr,
-                           cidx, rtol, maxit, iters);
-    } else if (n <= 1024) {
-        const int bs = n <= 64 ? 64 : n <= 128 ? 128 : n <= 256 ? 256 : n <= 512 ? 512 : 1024;
-        hipLaunchKernelGGL((k_coarse_pcg<T, 1>), dim3(1), dim3(bs), 0, s, n, slot, col, val, frozen, b, u, cptr, cidx,
-                           rtol, maxit, iters);
-    } else {
-        hipLaunchKernelGGL((k_coarse_pcg<T, 2>), dim3(1), dim3(1024), 0, s, n, slot, col, val, frozen, b, u, cptr, cidx,
-                           rtol, maxit, iters);
-    }
+    // up to 64 unknowns in a single wavefront; otherwise 4 or 8 wavefronts,
+    // up to 4 unknowns per thread.  Latency binds an iteration: the rows a
+    // lane walks and the reductions, each DPP moves within a wavefront and
+    // one barrier.  343 unknowns: 47 us in 4 wavefronts, 58 in one with 8 rows
+    // per lane; 1331 unknowns: 116 us in 8 wavefronts, 266 in 16 with LDS
+    // permutes and two barriers per reduction
+    auto run = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, dim3(1), dim3(threads), 0, s, n, slot, col, val, frozen, b, u, cptr, cidx, rtol,
+                           maxit, iters);
+    };
+    if (n <= 64)
+        run(k_coarse_pcg_wave<T, 1>, 64);
+    else if (n <= 256)
+        run(k_coarse_pcg<T, 4, 1>, 256);
+    else if (n <= 512)
+        run(k_coarse_pcg<T, 4, 2>, 256);
+    else if (n <= 1024)
+        run(k_coarse_pcg<T, 8, 2>, 512);
+    else if (n <= 1536)
+        run(k_coarse_pcg<T, 8, 3>, 512);
+    else
+        run(k_coarse_pcg<T, 8, 4>, 512);
 }
 
 template <typename T>
@@ -2115,20 +2132,21 @@ void launch_coarse_pcg15(hipStream_t s, int n, const long long *slot, const int 
                          const unsigned char *frozen, const T *b, T *u, const int *cptr, const int *cidx,
                          double rtol, int maxit, int *iters) {
     // 14 off-diagonal entries per row stay in registers: at most 2 rows per
-    // lane (more spill to scratch), so above 128 unknowns one row per thread
+    // lane (more spill to scratch)
+    auto run = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, dim3(1), dim3(threads), 0, s, n, slot, col, val, frozen, b, u, cptr, cidx, rtol,
+                           maxit, iters);
+    };
     if (n <= 64)
-        hipLaunchKernelGGL((k_coarse_pcg_wave<T, 1, 14>), dim3(1), dim3(64), 0, s, n, slot, col, val, frozen, b, u, cptr,
-                           cidx, rtol, maxit, iters);
-    else if (n <= 128)
-        hipLaunchKernelGGL((k_coarse_pcg_wave<T, 2, 14>), dim3(1), dim3(64), 0, s, n, slot, col, val, frozen, b, u, cptr,
-                           cidx, rtol, maxit, iters);
-    else if (n <= 1024) {
-        const int bs = n <= 256 ? 256 : n <= 512 ? 512 : 1024;
-        hipLaunchKernelGGL((k_coarse_pcg<T, 1, 14>), dim3(1), dim3(bs), 0, s, n, slot, col, val, frozen, b, u, cptr, cidx,
-                           rtol, maxit, iters);
-    } else
-        hipLaunchKernelGGL((k_coarse_pcg<T, 2, 14>), dim3(1), dim3(1024), 0, s, n, slot, col, val, frozen, b, u, cptr,
-                           cidx, rtol, maxit, iters);
+        run(k_coarse_pcg_wave<T, 1, 14>, 64);
+    else if (n <= 256)
+        run(k_coarse_pcg<T, 4, 1, 14>, 256);
+    else if (n <= 512)
+        run(k_coarse_pcg<T, 4, 2, 14>, 256);
+    else if (n <= 1024)
+        run(k_coarse_pcg<T, 8, 2, 14>, 512);
+    else
+        run(k_coarse_pcg<T, 16, 2, 14>, 1024);
 }
 
 template void launch_coarse_pcg15<double>(hipStream_t, int, const long long *, const int *, const double *,
@@ -2213,14 +2231,14 @@ void launch_coarse_vals(hipStream_t s, int n, const int *pos, const int *col, in
 void launch_ifc_weights_intact(hipStream_t s, int n_ifc, const int *ifc_xyz, int N, int m, int n_sub, double h,
                                const double *k, const unsigned char *faulty, double *wi) {
     if (n_ifc <= 0) return;
-    hipLaunchKernelGGL(k_ifc_weights_intact, dim3((n_ifc + 255) / 256), dim3(256), 0, s, n_ifc, ifc_xyz, N, m, n_sub, h,
+    hipLaunchKernelGGL(k_ifc_weights_intact, dim3((n_ifc + 255) / 256, 6), dim3(256), 0, s, n_ifc, ifc_xyz, N, m, n_sub, h,
                        k, faulty, wi);
 }
 
 void launch_coarse_vals_intact(hipStream_t s, int n, const int *pos, const int *col, int N, int m, int n_sub, double h,
                                const double *k, const unsigned char *faulty, double *val) {
     if (n <= 0) return;
-    hipLaunchKernelGGL(k_coarse_vals_intact, dim3((n + 255) / 256), dim3(256), 0, s, n, pos, col, N, m, n_sub, h, k,
+    hipLaunchKernelGGL(k_coarse_vals_intact, dim3((n + 31) / 32), dim3(256), 0, s, n, pos, col, N, m, n_sub, h, k,
                        faulty, val);
 }
 
