@@ -19,6 +19,7 @@
 
 #include "../../include/hhgr.h"
 #include "geometry.hpp"
+#include "grid.hpp"
 #include "kernels.hpp"
 #include "topology.hpp"
 
@@ -136,6 +137,14 @@ struct LevelDev {
     int fz_TJ = 0, fz_TK = 0;
     long long fz_black0 = 0;
     bool fz_on = false;  // the cycles use fused pairs on this level (autotuner: where faster)
+    // the cube with k = 1: u (two buffers, a sweep goes from one to the
+    // other) and b on the grid (grid.hpp), the frozen nodes of a
+    // Dirichlet-Dirichlet recovery, and the tiles of each kind of launch
+    double *gu[2] = {}, *gb = nullptr;
+    float *gu32[2] = {}, *gb32 = nullptr;
+    unsigned char *gfrz = nullptr;
+    GridTiles tl[2][3][3];  // [ns - 1][start][tail]
+    GridTiles tl_res;
 };
 
 template <typename T>
@@ -218,15 +227,22 @@ struct hhgr_ctx {
     double bnorm = 0.0;
     bool rhs_set = false, coeff_set = false;
     bool vk = false, mixed = false;
-    // graphs
+    // the cube with k = 1 keeps u and b on the grid: the finest u is buffer
+    // cur of its two
+    const GridOps *go = nullptr;
+    int cur = 0;
+    double *gpartial = nullptr;
+    double *gst = nullptr;  // sine transform of the coarsest level
+    long long *gslot = nullptr;  // grid index of every coarsest unknown
+    int *gcptr = nullptr, *gcidx = nullptr;
+    // graphs, by the buffer that the step starts from
     bool use_graph = false;
-    hipGraphExec_t gexec = nullptr;
-    bool graph_ok = false;
+    hipGraphExec_t gexec[2] = {};
     // local recovery: its kernels are small enough that launching them one
     // by one leaves the GPU waiting for the host, so its cycles replay a
     // captured graph, kept for one (tetrahedron, cycle count)
     hipGraphExec_t lgexec = nullptr;
-    int lg_tet = -1, lg_n = -1;
+    int lg_tet = -1, lg_n = -1, lg_cur = 0;
     std::vector<int> loc_tets;  // the tetrahedra whose local hierarchy vd_loc holds
     // unstructured mesh with a coefficient per tetrahedron (empty: k = 1):
     // the values, the master rows of every level and the coarsest rows
@@ -258,8 +274,14 @@ struct hhgr_batch {
     std::vector<hipEvent_t> ev;                // [0] fork, [1 + q] member join
     std::vector<hipEvent_t> evl;               // [2q] local fork, [2q + 1] local join
     std::vector<BatchDD> dd;
-    hipGraphExec_t gexec = nullptr;
-    std::vector<int> sig_in_graph;  // (member, mode) pairs the graph was captured for
+    // step graphs by the (member, mode, start buffer) triples they were
+    // captured for; a step on the grid swaps its buffers, so two serve in turn
+    struct Step {
+        std::vector<int> sig;
+        hipGraphExec_t x = nullptr;
+    };
+    Step step[2];
+    int step_next = 0;
     double *hnorm = nullptr;        // pinned, one per member
 };
 
@@ -341,6 +363,10 @@ void to_user(const hhgr_ctx &c, const LevelDev &D, const double *vec, double *us
     else
         launch_slots_to_user<double>(s, vint, c.tetinfo, D.m, D.N, ig, D.ifc_dof, vec, user);
 }
+
+// partial sums of a grid of N cells per axis: a workgroup for 4 rows, or the
+// tiles of a marching launch (a few thousand)
+size_t gpartial_len(int N) { return std::max<size_t>((size_t)N * N / 4 + 1, 65536); }
 
 // ----------------------------------------------------------------------------
 // layout of the workspace (sizing and carving share this code)
@@ -495,6 +521,18 @@ void carve(hhgr_ctx &c, Carver &cv) {
             D.lb = cv.take<double>((size_t)nf * T.C_pad);
             D.lr = cv.take<double>((size_t)nf * T.C_pad);
         }
+        if (c.go) {
+            const size_t n = (size_t)grid_len(T.N);
+            D.gu[0] = cv.take<double>(n);
+            D.gb = cv.take<double>(n);
+            if (l > c.Lc) D.gu[1] = cv.take<double>(n);
+            if (c.mixed) {
+                D.gu32[0] = cv.take<float>(n);
+                D.gb32 = cv.take<float>(n);
+                if (l > c.Lc) D.gu32[1] = cv.take<float>(n);
+            }
+            if (c.d.max_faults > 0 && l > c.Lc) D.gfrz = cv.take<unsigned char>(n);
+        }
         D.wi_dn = cv.take<double>(6 * (size_t)T.n_ifc);
         D.gidx_dn = cv.take<int>(T.gidx.size());
         if (l == c.L) D.gamma = cv.take<unsigned char>(T.n_ifc);
@@ -533,8 +571,19 @@ void carve(hhgr_ctx &c, Carver &cv) {
         c.kel = cv.take<double>(96 * (size_t)c.n_tets);
     }
     const TopoLevel &TL = tp.lev[c.L];
-    c.aux_u = cv.take<double>(TL.n_slots);
-    c.aux_b = cv.take<double>(TL.n_slots);
+    const size_t n_aux = std::max((size_t)TL.n_slots, c.go ? (size_t)grid_len(TL.N) : (size_t)0);
+    c.aux_u = cv.take<double>(n_aux);
+    c.aux_b = cv.take<double>(n_aux);
+    if (c.go) {
+        // a marching launch has at most a few thousand tiles, a row launch a
+        // workgroup for 4 rows
+        c.gpartial = cv.take<double>(gpartial_len(TL.N));
+        const int n = tp.lev[c.Lc].N - 1;
+        c.gst = cv.take<double>((size_t)n * n + n);
+        c.gslot = cv.take<long long>(c.cn);
+        c.gcptr = cv.take<int>(c.cn + 1);
+        c.gcidx = cv.take<int>(c.cn);
+    }
     if (c.vk) {
         c.user_u = cv.take<double>(c.n_dofs);
         c.user_l = cv.take<double>(c.n_dofs);
@@ -1144,6 +1193,211 @@ void cycle_and_norm(hhgr_ctx &c, const HView<double> &V, hipStream_t s, double *
     finest_residual<double>(c, V, (double *)nullptr, s, dst);
 }
 
+// ----------------------------------------------------------------------------
+// the cube with k = 1: cycles on the grid (grid.hpp)
+// ----------------------------------------------------------------------------
+template <typename T>
+T *gvec(const LevelDev &D, int q);
+template <>
+double *gvec<double>(const LevelDev &D, int q) {
+    return q < 2 ? D.gu[q] : D.gb;
+}
+template <>
+float *gvec<float>(const LevelDev &D, int q) {
+    return q < 2 ? D.gu32[q] : D.gb32;
+}
+
+void grid_ops_sweep(const GridOps &o, hipStream_t s, int ns, int start, int tail, const GridTiles &t,
+                    const GridSweep<double> &g) {
+    o.sweep64(s, ns, start, tail, t, g);
+}
+void grid_ops_sweep(const GridOps &o, hipStream_t s, int ns, int start, int tail, const GridTiles &t,
+                    const GridSweep<float> &g) {
+    o.sweep32(s, ns, start, tail, t, g);
+}
+
+// one V-cycle on level l: from zero, or from buffer q of the level's u;
+// returns the buffer that holds the result.  masked: the intact side of a
+// Dirichlet-Dirichlet recovery.  norm: the last launch leaves the squared
+// residual in gpartial (finest level, at least one post-smoothing sweep).
+template <typename T>
+int grid_cycle(hhgr_ctx &c, int l, bool zero, int q, bool masked, bool norm, hipStream_t s) {
+    const GridOps &o = *c.go;
+    LevelDev &D = c.lev[l];
+    T *const u[2] = {gvec<T>(D, 0), gvec<T>(D, 1)}, *const b = gvec<T>(D, 2);
+    if (l == c.Lc) {
+        if (masked)
+            launch_coarse_pcg<T>(s, c.cn, c.gslot, c.ccol, c.cval, c.cfrozen, b, u[0], c.gcptr, c.gcidx, kCoarseRtol,
+                                 kCoarseMaxit, c.citers);
+        else if constexpr (std::is_same<T, double>::value)
+            o.coarse64(s, D.N, c.gst, b, u[0]);
+        else
+            o.coarse32(s, D.N, c.gst, b, u[0]);
+        return 0;
+    }
+    const LevelDev &Dc = c.lev[l - 1];
+    GridSweep<T> g;
+    g.N = D.N;
+    g.h = D.h;
+    g.omega = c.d.omega;
+    g.b = b;
+    g.bc = gvec<T>(Dc, 2);
+    g.frz = masked ? D.gfrz : nullptr;
+    g.partial = c.gpartial;
+    auto sweep = [&](int ns, int start, int tail) {
+        g.u = u[q];
+        q = start == kGridFromZero ? 0 : 1 - q;
+        g.v = u[q];
+        const bool timed = c.timing && !masked && l == c.L && start != kGridProlong;
+        if (timed) timed_begin(c, s);
+        grid_ops_sweep(o, s, ns, start, tail, D.tl[ns - 1][start][tail], g);
+        if (timed) timed_end(c, s);
+    };
+    for (int k = 0; k < c.d.nu_pre;) {
+        // two sweeps in one launch only from zero: there the first pass reads
+        // b alone (N = 256: 105 us against 67 + 110; from u 275 against 105 + 110)
+        const int start = zero && k == 0 ? kGridFromZero : kGridFromU;
+        const int ns = start == kGridFromZero && c.d.nu_pre >= 2 ? 2 : 1;
+        k += ns;
+        sweep(ns, start, k == c.d.nu_pre ? kGridRestrict : kGridPlain);
+    }
+    if (c.d.nu_pre == 0) {
+        if (zero) {
+            q = 0;
+            launch_fill<T>(s, u[0], grid_len(D.N), T(0));
+        }
+        if constexpr (std::is_same<T, double>::value) {
+            o.plain_residual64(s, D.N, D.h, u[q], b, u[1 - q]);
+            o.plain_restrict64(s, D.N, u[1 - q], g.bc);
+        } else {
+            o.plain_residual32(s, D.N, D.h, u[q], b, u[1 - q]);
+            o.plain_restrict32(s, D.N, u[1 - q], g.bc);
+        }
+    }
+    g.ec = gvec<T>(Dc, grid_cycle<T>(c, l - 1, true, 0, masked, false, s));
+    for (int k = 0; k < c.d.nu_post; k++)
+        sweep(1, k == 0 ? kGridProlong : kGridFromU, norm && k == c.d.nu_post - 1 ? kGridNorm : kGridPlain);
+    if (c.d.nu_post == 0) {
+        if constexpr (std::is_same<T, double>::value)
+            o.plain_prolong64(s, D.N, u[q], g.ec, u[1 - q]);
+        else
+            o.plain_prolong32(s, D.N, u[q], g.ec, u[1 - q]);
+        q = 1 - q;
+    }
+    return q;
+}
+
+// ||b - A u||^2 of the finest level into *dst; r32: also r, rounded, as the
+// FP32 right-hand side; e: u += e first, in the level's other buffer
+void grid_residual(hhgr_ctx &c, bool masked, const float *e, float *r32, hipStream_t s, double *dst) {
+    LevelDev &D = c.lev[c.L];
+    GridResidual g;
+    g.N = D.N;
+    g.h = D.h;
+    g.u = D.gu[c.cur];
+    g.b = D.gb;
+    g.e = e;
+    g.v = D.gu[1 - c.cur];
+    g.r32 = r32;
+    g.frz = masked ? D.gfrz : nullptr;
+    g.partial = c.gpartial;
+    c.go->residual(s, D.tl_res, g);
+    if (e) c.cur = 1 - c.cur;
+    launch_reduce(s, c.gpartial, D.tl_res.blocks(), dst);
+}
+
+// one FP64 cycle or mixed refinement step, with the squared residual norm
+// to *dst (FP64: only if norm)
+void grid_step(hhgr_ctx &c, bool masked, bool norm, hipStream_t s, double *dst) {
+    LevelDev &D = c.lev[c.L];
+    if (c.mixed) {
+        const int q = grid_cycle<float>(c, c.L, true, 0, masked, false, s);
+        grid_residual(c, masked, D.gu32[q], D.gb32, s, dst);
+        return;
+    }
+    const bool tail = norm && c.d.nu_post > 0;
+    c.cur = grid_cycle<double>(c, c.L, false, c.cur, masked, tail, s);
+    if (tail)
+        launch_reduce(s, c.gpartial,
+                      D.tl[0][c.d.nu_post > 1 ? kGridFromU : kGridProlong][kGridNorm].blocks(), dst);
+    else if (norm)
+        grid_residual(c, masked, nullptr, nullptr, s, dst);
+}
+
+GridTets grid_tets(const hhgr_ctx &c, const std::vector<int> &tets) {
+    GridTets g;
+    g.n = (int)tets.size();
+    for (int q = 0; q < g.n; q++)
+        for (int a = 0; a < 3; a++) {
+            g.info[q][a] = c.topo->V0[tets[q]][a];
+            g.info[q][3 + a] = c.topo->perm[tets[q]][a];
+        }
+    return g;
+}
+
+// containers of the finest level (full: every node of the closures, else the
+// interior nodes)
+GridClosures grid_closures(const hhgr_ctx &c, const VolDesc *vd, int nvol, bool full) {
+    const LevelDev &D = c.lev[c.L];
+    GridClosures g;
+    g.vd = vd;
+    g.nvol = nvol;
+    g.list = full ? D.flist : D.ilist;
+    g.nlist = full ? D.nflist : D.nilist;
+    g.rowC = D.rowC;
+    g.tetinfo = c.tetinfo;
+    g.M = D.M;
+    g.N = D.N;
+    return g;
+}
+
+// the tetrahedra of vd_loc: closures of u (interiors zero) and b into slot
+// space for the local cycles; their interiors back to the grid
+void grid_to_local(hhgr_ctx &c, hipStream_t s) {
+    LevelDev &D = c.lev[c.L];
+    const GridClosures g = grid_closures(c, D.vd_loc, D.n_loc, true);
+    c.go->to_closures(s, g, true, D.gu[c.cur], D.u);
+    c.go->to_closures(s, g, false, D.gb, D.b);
+}
+void grid_from_local(hhgr_ctx &c, hipStream_t s) {
+    LevelDev &D = c.lev[c.L];
+    c.go->from_closures(s, grid_closures(c, D.vd_loc, D.n_loc, false), D.u, D.gu[c.cur]);
+}
+
+// transform matrix and eigenvalues of the coarsest level (see k_grid_coarse)
+std::vector<double> sine_table(int N) {
+    const int n = N - 1;
+    std::vector<double> st((size_t)n * n + n);
+    const double pi = 3.14159265358979323846;
+    for (int i = 0; i < n; i++) {
+        for (int j = 0; j < n; j++) st[(size_t)i * n + j] = std::sqrt(2.0 / N) * std::sin(pi * (((i + 1) * (j + 1)) % (2 * N)) / N);
+        const double q = std::sin(0.5 * pi * (i + 1) / N);
+        st[(size_t)n * n + i] = 4.0 * q * q;
+    }
+    return st;
+}
+
+// tiles of every kind of launch on a grid, chosen once per size
+void grid_plan(const GridOps &o, LevelDev &D, bool mixed) {
+    static std::mutex mu;
+    static std::map<std::tuple<int, int, int, int, int>, GridTiles> known;
+    std::lock_guard<std::mutex> lock(mu);
+    auto get = [&](int ns, int start, int tail, int word) {
+        const auto key = std::make_tuple(D.N, ns, start, tail, word);
+        auto it = known.find(key);
+        if (it == known.end()) it = known.emplace(key, o.tiles(D.N, ns, start, tail, word)).first;
+        return it->second;
+    };
+    const int w = mixed ? 4 : 8;
+    for (int tail : {kGridPlain, kGridRestrict}) {
+        for (int ns = 1; ns <= 2; ns++) D.tl[ns - 1][kGridFromZero][tail] = get(ns, kGridFromZero, tail, w);
+        D.tl[0][kGridFromU][tail] = get(1, kGridFromU, tail, w);
+    }
+    D.tl[0][kGridProlong][kGridPlain] = get(1, kGridProlong, kGridPlain, w);
+    for (int start : {kGridFromU, kGridProlong}) D.tl[0][start][kGridNorm] = get(1, start, kGridNorm, 8);
+    D.tl_res = get(0, kGridFromU, kGridResidual, 8);
+}
+
 void step_fp64(hhgr_ctx &c, const HView<double> &V, hipStream_t s, int slot) {
     cycle_and_norm(c, V, s, c.dnorm + slot);
 }
@@ -1164,9 +1418,10 @@ int read_norm(hhgr_ctx &c, int slot, double *out) {
 }
 
 void invalidate_graph(hhgr_ctx &c) {
-    if (c.gexec) hipGraphExecDestroy(c.gexec);
-    c.gexec = nullptr;
-    c.graph_ok = false;
+    for (auto &x : c.gexec) {
+        if (x) hipGraphExecDestroy(x);
+        x = nullptr;
+    }
     if (c.lgexec) hipGraphExecDestroy(c.lgexec);
     c.lgexec = nullptr;
     c.lg_tet = c.lg_n = -1;
@@ -1176,7 +1431,9 @@ void invalidate_graph(hhgr_ctx &c) {
 // the residual norm in dnorm[0] copied to hnorm[0]
 void enqueue_step(hhgr_ctx &c, hipStream_t s) {
     HView<double> V64 = global_view<double>(c, false, 0);
-    if (c.mixed) {
+    if (c.go) {
+        grid_step(c, false, true, s, c.dnorm);
+    } else if (c.mixed) {
         HView<float> V32 = global_view<float>(c, false, 0);
         step_mixed(c, V64, V32, s, 0);
     } else {
@@ -1185,19 +1442,30 @@ void enqueue_step(hhgr_ctx &c, hipStream_t s) {
     hipMemcpyAsync(c.hnorm, c.dnorm, sizeof(double), hipMemcpyDeviceToHost, s);
 }
 
+// whether a step ends in the other buffer of the finest u than it starts from
+int step_swaps(const hhgr_ctx &c) {
+    return !c.go ? 0 : c.mixed ? 1 : (c.d.nu_pre + std::max(c.d.nu_post, 1)) & 1;
+}
+
 int run_step(hhgr_ctx &c) {
     if (c.use_graph && !c.timing) {
-        if (!c.graph_ok) {
+        hipGraphExec_t &x = c.gexec[c.cur];
+        if (!x) {
+            const int cur = c.cur;
             hipGraph_t g = nullptr;
             HIPCHK(hipStreamBeginCapture(c.cap, hipStreamCaptureModeRelaxed));
             enqueue_step(c, c.cap);
+            c.cur = cur;  // nothing has run yet
             HIPCHK(hipStreamEndCapture(c.cap, &g));
-            hipError_t e = hipGraphInstantiate(&c.gexec, g, nullptr, nullptr, 0);
+            hipError_t e = hipGraphInstantiate(&x, g, nullptr, nullptr, 0);
             hipGraphDestroy(g);
-            if (e != hipSuccess) return fail(HHGR_EHIP, std::string("hipGraphInstantiate: ") + hipGetErrorString(e));
-            c.graph_ok = true;
+            if (e != hipSuccess) {
+                x = nullptr;
+                return fail(HHGR_EHIP, std::string("hipGraphInstantiate: ") + hipGetErrorString(e));
+            }
         }
-        HIPCHK(hipGraphLaunch(c.gexec, c.stream));
+        HIPCHK(hipGraphLaunch(x, c.stream));
+        c.cur ^= step_swaps(c);
     } else {
         enqueue_step(c, c.stream);
         CHKLAUNCH();
@@ -1207,6 +1475,10 @@ int run_step(hhgr_ctx &c) {
 
 // in mixed mode the residual (and b32) of the current u must be ready before a step
 void prime_mixed(hhgr_ctx &c, hipStream_t s) {
+    if (c.go) {
+        grid_residual(c, false, nullptr, c.lev[c.L].gb32, s, c.dnorm);
+        return;
+    }
     HView<double> V64 = global_view<double>(c, false, 0);
     finest_residual<float>(c, V64, c.lev[c.L].b32, s, c.dnorm);
 }
@@ -1264,12 +1536,48 @@ int dd_check(const hhgr_ctx &c, const int *tets, int n_tets, int n_intact, int n
     return HHGR_OK;
 }
 
+// host tables that copies queued on the stream read: freed once it is idle
+struct RecoveryTables {
+    hipStream_t stream;
+    std::vector<unsigned char> isf, cf;
+    std::vector<std::vector<VolDesc>> vds;
+    explicit RecoveryTables(hipStream_t s) : stream(s) {}
+    ~RecoveryTables() { hipStreamSynchronize(stream); }
+};
+
 // masks of the intact volumes and of the frozen interface nodes on every
 // level, the local hierarchy of the faulty tetrahedra, their ghost copies
-// restored and interiors zeroed, coarse corrections zeroed; synchronises
-int dd_setup(hhgr_ctx &c, const std::vector<int> &ft) {
+// restored and interiors zeroed, coarse corrections zeroed; synchronises,
+// except on the grid, where the caller keeps the tables until it does
+int dd_setup(hhgr_ctx &c, const std::vector<int> &ft, RecoveryTables &keep) {
     std::vector<char> isf(c.n_tets, 0);
     for (int t : ft) isf[t] = 1;
+    if (c.go) {
+        // the frozen closures as one byte per grid node; the coarsest unknowns
+        // by their index
+        const CoarseSystem &cs = c.topo->coarse;
+        const TopoLevel &T = c.topo->lev[c.Lc];
+        std::vector<unsigned char> fi(T.n_ifc, 0), &cf = keep.cf;
+        cf.assign(cs.n, 0);
+        for (int t : ft)
+            for (int q = T.tg_ptr[t]; q < T.tg_ptr[t + 1]; q++) {
+                const long long sl = T.tg_src[q] - T.ifc_base;
+                if (sl >= 0 && sl < T.n_ifc) fi[sl] = 1;
+            }
+        for (int q = 0; q < cs.n; q++) cf[q] = cs.is_vol[q] ? (unsigned char)isf[cs.tet[q]] : fi[cs.ifc[q]];
+        const int rc = upload(c, c.cfrozen, cf.data(), cf.size());
+        set_loc(c, ft);
+        const GridTets g = grid_tets(c, ft);
+        for (int l = c.Lc + 1; l <= c.L; l++) c.go->freeze_tets(c.stream, c.lev[l].N, c.lev[l].m, g, c.lev[l].gfrz);
+        c.go->zero_tets(c.stream, c.lev[c.L].N, c.lev[c.L].m, g, c.lev[c.L].gu[c.cur]);
+        grid_to_local(c, c.stream);
+        // the frozen unknowns of the coarsest level are not written: zero
+        const LevelDev &Dc = c.lev[c.Lc];
+        launch_fill<double>(c.stream, Dc.gu[0], grid_len(Dc.N), 0.0);
+        if (c.mixed) launch_fill<float>(c.stream, Dc.gu32[0], grid_len(Dc.N), 0.0f);
+        CHKLAUNCH();
+        return rc;
+    }
     std::vector<std::vector<VolDesc>> vds(c.L + 1);
     std::vector<std::vector<unsigned char>> frz(c.L + 1);
     int rc = HHGR_OK;
@@ -1341,6 +1649,11 @@ int dd_setup(hhgr_ctx &c, const std::vector<int> &ft) {
 // refinement step); with norm (or in mixed mode) the squared norm of the
 // intact residual goes to dnorm[slot]
 void dd_intact_step(hhgr_ctx &c, hipStream_t s, bool first, bool norm, int slot) {
+    if (c.go) {
+        if (c.mixed && first) grid_residual(c, true, nullptr, c.lev[c.L].gb32, s, c.dnorm + slot);
+        grid_step(c, true, norm, s, c.dnorm + slot);
+        return;
+    }
     HView<double> V64 = global_view<double>(c, true, 0);
     if (c.mixed) {
         HView<float> V32 = global_view<float>(c, true, 0);
@@ -1363,6 +1676,8 @@ void dd_local(hhgr_ctx &c, int n_local, hipStream_t s) {
 void dd_final_norm(hhgr_ctx &c, hipStream_t s) {
     if (c.mixed) {
         prime_mixed(c, s);
+    } else if (c.go) {
+        grid_residual(c, false, nullptr, nullptr, s, c.dnorm);
     } else {
         HView<double> V = global_view<double>(c, false, 0);
         finest_residual<double>(c, V, (double *)nullptr, s, c.dnorm);
@@ -1376,11 +1691,23 @@ void dd_final_norm(hhgr_ctx &c, hipStream_t s) {
 // interface); the faulty side runs local Dirichlet cycles whose boundary
 // values are refreshed from the interface at the start of every round
 // ----------------------------------------------------------------------------
-int dn_setup(hhgr_ctx &c, const std::vector<int> &ft) {
-    std::vector<unsigned char> isf(c.n_tets, 0);
+// the caller keeps the tables until the stream is synchronised
+int dn_setup(hhgr_ctx &c, const std::vector<int> &ft, RecoveryTables &keep) {
+    std::vector<unsigned char> &isf = keep.isf;
+    isf.assign(c.n_tets, 0);
     for (int t : ft) isf[t] = 1;
+    if (c.go) {
+        // the intact side's interface stencils are per master: this recovery
+        // runs in slot space (its right-hand side goes to aux_b)
+        LevelDev &D = c.lev[c.L];
+        c.go->to_closures(c.stream, grid_closures(c, D.vd_all, c.n_tets, true), false, D.gu[c.cur], D.u);
+        c.go->to_masters(c.stream, D.n_ifc, D.ifc_xyz, D.N, D.gu[c.cur], D.u + D.ifc_base);
+        c.go->to_closures(c.stream, grid_closures(c, D.vd_all, c.n_tets, false), false, D.gb, c.aux_b);
+        c.go->to_masters(c.stream, D.n_ifc, D.ifc_xyz, D.N, D.gb, c.aux_b + D.ifc_base);
+    }
     int rc = upload(c, c.dn_faulty, isf.data(), isf.size());
-    std::vector<std::vector<VolDesc>> vds(c.L + 1);
+    std::vector<std::vector<VolDesc>> &vds = keep.vds;
+    vds.assign(c.L + 1, {});
     for (int l = c.Lc; l <= c.L; l++) {
         LevelDev &D = c.lev[l];
         for (int t = 0; t < c.n_tets; t++)
@@ -1388,10 +1715,7 @@ int dn_setup(hhgr_ctx &c, const std::vector<int> &ft) {
         D.n_masked = (int)vds[l].size();
         rc = rc ? rc : upload(c, D.vd_masked, vds[l].data(), vds[l].size() * sizeof(VolDesc));
     }
-    if (rc) {
-        hipStreamSynchronize(c.stream);  // queued copies read vds
-        return rc;
-    }
+    if (rc) return rc;
     // an interface node lies in the closures of the tetrahedra holding its
     // ghost copies: frozen if all of them are faulty, on the interface Gamma
     // if some are; ghost copies in faulty closures are not written
@@ -1409,13 +1733,11 @@ int dn_setup(hhgr_ctx &c, const std::vector<int> &ft) {
         frc[f] = ni == 0;
     }
     const CoarseSystem &cs = c.topo->coarse;
-    std::vector<unsigned char> cf(cs.n, 0);
+    std::vector<unsigned char> &cf = keep.cf;
+    cf.assign(cs.n, 0);
     for (int q = 0; q < cs.n; q++) cf[q] = cs.is_vol[q] ? isf[cs.tet[q]] : frc[cs.ifc[q]];
     rc = upload(c, c.cfrozen, cf.data(), cf.size());
-    if (rc) {
-        hipStreamSynchronize(c.stream);  // queued copies read vds and cf
-        return rc;
-    }
+    if (rc) return rc;
     // intact-side operators on every level
     if (c.mesh) {
         // master rows over the elements of intact tetrahedra (host), and the
@@ -1484,12 +1806,14 @@ int dn_setup(hhgr_ctx &c, const std::vector<int> &ft) {
                                   c.dn_faulty, c.cval_dn);
     }
     CHKLAUNCH();
-    HIPCHK(hipStreamSynchronize(c.stream));
     set_loc(c, ft);
     LevelDev &F = c.lev[c.L];
     // static Neumann data from the data at the time of the fault (u_F plays
     // no part: its edges have zero intact-side weight)
-    HIPCHK(hipMemcpyAsync(c.aux_b, F.b, F.n_slots * sizeof(double), hipMemcpyDeviceToDevice, c.stream));
+    if (c.go)
+        c.go->to_closures(c.stream, grid_closures(c, F.vd_loc, F.n_loc, true), false, F.gb, F.b);
+    else
+        HIPCHK(hipMemcpyAsync(c.aux_b, F.b, F.n_slots * sizeof(double), hipMemcpyDeviceToDevice, c.stream));
     if (c.mesh)
         launch_neumann_rhs_w(c.stream, F.n_ifc, F.ifc_base, F.nb15, F.wi15_dn, F.nbw, F.gamma, F.u, c.aux_b);
     else if (c.gen)
@@ -1500,12 +1824,12 @@ int dn_setup(hhgr_ctx &c, const std::vector<int> &ft) {
     for (int l = c.Lc; l <= c.L; l++) {
         LevelDev &D = c.lev[l];
         if (l < c.L) launch_fill<double>(c.stream, D.u, D.n_slots, 0.0);
-        // the intact side never writes residuals inside faulty closures; its
-        // restriction reads them there as zero
-        launch_fill<double>(c.stream, D.r, D.n_slots, 0.0);
+        // the intact side never writes residuals inside faulty closures or at
+        // frozen masters; its restriction reads them there as zero
+        for (int t : ft) launch_fill<double>(c.stream, D.r + (long long)t * D.C_pad, D.C_pad, 0.0);
+        launch_fill<double>(c.stream, D.r + D.ifc_base, D.n_slots - D.ifc_base, 0.0);
     }
     CHKLAUNCH();
-    HIPCHK(hipStreamSynchronize(c.stream));
     return HHGR_OK;
 }
 
@@ -1569,6 +1893,13 @@ int gen_weights(hhgr_ctx &c) {
 }  // namespace
 }  // namespace hhgr
 
+namespace hhgr {
+namespace {
+// the structured-grid launchers of a context on the cube with k = 1, else null
+const GridOps *grid_path(const hhgr_ctx &c) { return !c.gen && !c.vk && grid_ops ? grid_ops() : nullptr; }
+}  // namespace
+}  // namespace hhgr
+
 // ============================================================================
 // C ABI
 // ============================================================================
@@ -1604,6 +1935,7 @@ int hhgr_workspace_bytes(const hhgr_desc *desc, size_t *bytes) {
     c.vk = desc->variable_coeff != 0;
     c.mixed = desc->precision == HHGR_MIXED;
     c.gen = desc->general_geometry != 0;
+    c.go = grid_path(c);
     std::string te = get_topology(desc->n_sub, c.L, c.Lc, c.topo_hold);
     if (!te.empty()) return fail(HHGR_EINVAL, te);
     c.topo = c.topo_hold.get();
@@ -1643,6 +1975,7 @@ int create_ctx(const hhgr_desc *desc, std::shared_ptr<const Topology> mesh_topo,
     c->vk = desc->variable_coeff != 0;
     c->mixed = desc->precision == HHGR_MIXED;
     c->gen = desc->general_geometry != 0;
+    c->go = mesh_topo ? nullptr : grid_path(*c);
     c->stream = (hipStream_t)hip_stream;
     if (mesh_topo) {
         c->topo_hold = mesh_topo;
@@ -1776,6 +2109,19 @@ int create_ctx(const hhgr_desc *desc, std::shared_ptr<const Topology> mesh_topo,
             launch_fill<double>(c->stream, D.lb, n, 0.0);
             launch_fill<double>(c->stream, D.lr, n, 0.0);
         }
+        if (c->go) {
+            if (l > c->Lc) {
+                grid_plan(*c->go, D, c->mixed);
+                if (!rc && (size_t)std::max({D.tl_res.blocks(), D.tl[0][kGridFromU][kGridNorm].blocks(),
+                                             D.tl[0][kGridProlong][kGridNorm].blocks()}) > gpartial_len(D.N))
+                    rc = fail(HHGR_EINVAL, "more tiles than partial sums");
+            }
+            for (double *p : {D.gu[0], D.gu[1], D.gb})
+                if (p) launch_fill<double>(c->stream, p, grid_len(D.N), 0.0);
+            for (float *p : {D.gu32[0], D.gu32[1], D.gb32})
+                if (p) launch_fill<float>(c->stream, p, grid_len(D.N), 0.0f);
+            if (D.gfrz) launch_fill<unsigned char>(c->stream, D.gfrz, grid_len(D.N), 0);
+        }
         launch_fill<unsigned char>(c->stream, D.frozen, T.n_ifc, 0);
         if (c->vk && c->gen) {
             launch_fill<double>(c->stream, D.wv, 8 * T.n_slots, 0.0);
@@ -1828,6 +2174,22 @@ int create_ctx(const hhgr_desc *desc, std::shared_ptr<const Topology> mesh_topo,
     if (c->gen) {
         rc = rc ? rc : upload(*c, c->ccol15, cs.col15.data(), cs.col15.size() * sizeof(int));
         launch_fill<double>(c->stream, c->cval15, 15LL * cs.n, 0.0);
+    }
+    std::vector<double> gst;
+    std::vector<long long> gslot(cs.n);
+    std::vector<int> gptr(cs.n + 1), gidx(cs.n);
+    if (c->go) {
+        const int Nc = tp.lev[c->Lc].N;
+        gst = sine_table(Nc);
+        for (int q = 0; q < cs.n; q++) {
+            gslot[q] = cs.pos[q][0] + grid_pitch(Nc) * (cs.pos[q][1] + (long long)Nc * cs.pos[q][2]);
+            gidx[q] = (int)gslot[q];
+            gptr[q + 1] = q + 1;
+        }
+        rc = rc ? rc : upload(*c, c->gst, gst.data(), gst.size() * sizeof(double));
+        rc = rc ? rc : upload(*c, c->gslot, gslot.data(), gslot.size() * sizeof(long long));
+        rc = rc ? rc : upload(*c, c->gcptr, gptr.data(), gptr.size() * sizeof(int));
+        rc = rc ? rc : upload(*c, c->gcidx, gidx.data(), gidx.size() * sizeof(int));
     }
     launch_fill<unsigned char>(c->stream, c->cfrozen, cs.n, 0);
     // the scratch vectors' zero slot and Dirichlet ghosts must read zero
@@ -1975,7 +2337,8 @@ void hhgr_destroy(hhgr_ctx *c) {
     if (c->ev_fork) hipEventDestroy(c->ev_fork);
     if (c->ev_join) hipEventDestroy(c->ev_join);
     for (hipEvent_t e : c->tev) hipEventDestroy(e);
-    if (c->gexec) hipGraphExecDestroy(c->gexec);
+    for (hipGraphExec_t x : c->gexec)
+        if (x) hipGraphExecDestroy(x);
     if (c->lgexec) hipGraphExecDestroy(c->lgexec);
     if (c->hnorm && c->hnorm != c->hnorm_local) hipHostFree(c->hnorm);
     delete c;
@@ -2002,8 +2365,19 @@ int hhgr_set_rhs(hhgr_ctx *c, const double *dev_vec, int kind) {
     const VolGeom vint = vgeom(D, D.vd_all, c->n_tets, false);
     const IfcGeom ig = igeom(D, 0, D.n_ifc, nullptr, false);
     bool aux_used = false;  // aux_u held the load in vector order
+    int gb = 0;             // workgroups that left sums of b^2 in gpartial
 
-    if (kind == HHGR_RHS_DIRICHLET && c->mesh) {
+    if (c->go) {
+        if (kind == HHGR_RHS_LOAD) {
+            gb = c->go->from_user(c->stream, D.N, dev_vec, D.gb, c->gpartial);
+        } else if (kind == HHGR_RHS_NODAL_F) {
+            gb = c->go->mass_load(c->stream, D.N, D.h, dev_vec, D.gb, c->gpartial);
+        } else {
+            launch_dirichlet_load(c->stream, D.N, D.h, nullptr, dev_vec, c->aux_u);
+            gb = c->go->from_user(c->stream, D.N, c->aux_u, D.gb, c->gpartial);
+            aux_used = true;
+        }
+    } else if (kind == HHGR_RHS_DIRICHLET && c->mesh) {
         // g at the boundary nodes (hhgr_mesh_boundary order): b = -A_IB g
         launch_fill<double>(c->stream, D.b, D.n_slots, 0.0);
         launch_dirichlet_rows(c->stream, c->n_dir_rows, c->dir_rows, c->dir_ptr, c->dir_col, c->dir_val, dev_vec, D.b);
@@ -2030,8 +2404,10 @@ int hhgr_set_rhs(hhgr_ctx *c, const double *dev_vec, int kind) {
     // aux_u is a scratch slot vector again (zero slot and boundary ghosts zero)
     if (aux_used) launch_fill<double>(c->stream, c->aux_u, D.n_slots, 0.0);
     // ||b|| over every interior node once
-    const int nb = launch_norm2(c->stream, vint, ig, D.b, c->partial[0]);
-    if (nb > 0)
+    const int nb = c->go ? 0 : launch_norm2(c->stream, vint, ig, D.b, c->partial[0]);
+    if (c->go)
+        launch_reduce(c->stream, c->gpartial, gb, c->dnorm + 1);
+    else if (nb > 0)
         launch_reduce(c->stream, c->partial[0], nb, c->dnorm + 1);
     else
         launch_fill<double>(c->stream, c->dnorm + 1, 1, 0.0);
@@ -2140,6 +2516,14 @@ int hhgr_set_geometry(hhgr_ctx *c, const double *host_xyz) {
 int hhgr_set_solution(hhgr_ctx *c, const double *dev_u) {
     if (!c) return fail(HHGR_EINVAL, "null context");
     LevelDev &D = c->lev[c->L];
+    if (c->go) {
+        if (dev_u)
+            c->go->from_user(c->stream, D.N, dev_u, D.gu[c->cur], nullptr);
+        else
+            launch_fill<double>(c->stream, D.gu[c->cur], grid_len(D.N), 0.0);
+        CHKLAUNCH();
+        return HHGR_OK;
+    }
     if (!dev_u) {
         // u = 0 in every slot (ghost copies and the zero slot included)
         launch_fill<double>(c->stream, D.u, D.n_slots, 0.0);
@@ -2155,7 +2539,10 @@ int hhgr_get_solution(const hhgr_ctx *cc, double *dev_u) {
     hhgr_ctx *c = const_cast<hhgr_ctx *>(cc);
     if (!c || !dev_u) return fail(HHGR_EINVAL, "null argument");
     LevelDev &D = c->lev[c->L];
-    to_user(*c, D, D.u, dev_u, c->stream);
+    if (c->go)
+        c->go->to_user(c->stream, D.N, D.gu[c->cur], dev_u);
+    else
+        to_user(*c, D, D.u, dev_u, c->stream);
     CHKLAUNCH();
     return HHGR_OK;
 }
@@ -2183,7 +2570,9 @@ int hhgr_vcycle(hhgr_ctx *c, int n, double *rel_res_out) {
     if (rel_res_out) {
         double rn;
         if (n == 0 || c->timing || !c->use_graph) {
-            if (n == 0) {
+            if (n == 0 && c->go) {
+                grid_residual(*c, false, nullptr, nullptr, c->stream, c->dnorm);
+            } else if (n == 0) {
                 HView<double> V = global_view<double>(*c, false, 0);
                 finest_residual<double>(*c, V, (double *)nullptr, c->stream, c->dnorm);
             }
@@ -2205,6 +2594,8 @@ int hhgr_solve(hhgr_ctx *c, double rel_tol, int max_cycles, hhgr_report *rep) {
     HView<double> V = global_view<double>(*c, false, 0);
     if (c->mixed)
         prime_mixed(*c, c->stream);
+    else if (c->go)
+        grid_residual(*c, false, nullptr, nullptr, c->stream, c->dnorm);
     else
         finest_residual<double>(*c, V, (double *)nullptr, c->stream, c->dnorm);
     CHKLAUNCH();
@@ -2235,8 +2626,12 @@ int hhgr_inject_fault(hhgr_ctx *c, int tet) {
     if (!c) return fail(HHGR_EINVAL, "null context");
     if (tet < 0 || tet >= c->n_tets) return fail(HHGR_EINVAL, "tet id out of range");
     // the closure is lost; its ghost copies come back from the surviving
-    // masters (eq. (4)) before any cycle reads them
-    restore_tet(*c, tet, c->stream);
+    // masters (eq. (4)) before any cycle reads them (the grid holds each
+    // interface value once: the interior alone is lost)
+    if (c->go)
+        c->go->zero_tets(c->stream, c->lev[c->L].N, c->lev[c->L].m, grid_tets(*c, {tet}), c->lev[c->L].gu[c->cur]);
+    else
+        restore_tet(*c, tet, c->stream);
     CHKLAUNCH();
     return HHGR_OK;
 }
@@ -2251,15 +2646,19 @@ int hhgr_recover_local(hhgr_ctx *c, int tet, int n_cycles, double *local_rel) {
     set_loc(*c, {tet});
     // restored ghosts, the local residual before and after the cycles
     auto enqueue = [&](hipStream_t s) {
-        restore_tet(*c, tet, s);
+        if (c->go)
+            grid_to_local(*c, s);
+        else
+            restore_tet(*c, tet, s);
         HView<double> V = local_view(*c, 0);
         finest_residual<double>(*c, V, (double *)nullptr, s, c->dnorm + 2);
         for (int q = 0; q < n_cycles; q++) vcycle<double>(*c, V, c->L, false, s);
         finest_residual<double>(*c, V, (double *)nullptr, s, c->dnorm + 3);
+        if (c->go) grid_from_local(*c, s);
     };
     if (!c->cap) {
         enqueue(c->stream);  // a context without a capture stream
-    } else if (!(c->lgexec && c->lg_tet == tet && c->lg_n == n_cycles)) {
+    } else if (!(c->lgexec && c->lg_tet == tet && c->lg_n == n_cycles && c->lg_cur == c->cur)) {
         if (c->lgexec) hipGraphExecDestroy(c->lgexec);
         c->lgexec = nullptr;
         c->lg_tet = c->lg_n = -1;
@@ -2275,6 +2674,7 @@ int hhgr_recover_local(hhgr_ctx *c, int tet, int n_cycles, double *local_rel) {
         }
         c->lg_tet = tet;
         c->lg_n = n_cycles;
+        c->lg_cur = c->cur;
     }
     if (c->lgexec) HIPCHK(hipGraphLaunch(c->lgexec, c->stream));
     CHKLAUNCH();
@@ -2294,7 +2694,8 @@ int hhgr_recover_dd(hhgr_ctx *c, const int *tets, int n_tets, int n_intact, int 
     rc = dd_check(*c, tets, n_tets, n_intact, n_local, ft);
     if (rc) return rc;
     invalidate_graph(*c);
-    rc = dd_setup(*c, ft);
+    RecoveryTables keep(c->stream);
+    rc = dd_setup(*c, ft, keep);
     if (rc) return rc;
     HIPCHK(hipEventRecord(c->ev_fork, c->stream));
     HIPCHK(hipStreamWaitEvent(c->stream2, c->ev_fork, 0));
@@ -2303,6 +2704,7 @@ int hhgr_recover_dd(hhgr_ctx *c, const int *tets, int n_tets, int n_intact, int 
     dd_local(*c, n_local, c->stream2);
     HIPCHK(hipEventRecord(c->ev_join, c->stream2));
     HIPCHK(hipStreamWaitEvent(c->stream, c->ev_join, 0));
+    if (c->go) grid_from_local(*c, c->stream);
     CHKLAUNCH();
     HIPCHK(hipStreamSynchronize(c->stream));
     dd_end(*c);
@@ -2316,7 +2718,8 @@ int hhgr_recover_dn(hhgr_ctx *c, const int *tets, int n_tets, int n_intact, int 
     rc = dd_check(*c, tets, n_tets, n_intact, eta, ft);
     if (rc) return rc;
     invalidate_graph(*c);
-    rc = dn_setup(*c, ft);
+    RecoveryTables keep(c->stream);
+    rc = dn_setup(*c, ft, keep);
     if (rc) return rc;
     HView<double> VI = dn_view(*c);
     HView<double> VL = local_view(*c, 1, c->aux_u);
@@ -2333,6 +2736,11 @@ int hhgr_recover_dn(hhgr_ctx *c, const int *tets, int n_tets, int n_intact, int 
         HIPCHK(hipStreamWaitEvent(c->stream, c->ev_join, 0));
     }
     refresh_faulty_ghosts(*c, ft, c->stream);
+    if (c->go) {
+        LevelDev &D = c->lev[c->L];
+        c->go->from_closures(c->stream, grid_closures(*c, D.vd_all, c->n_tets, false), D.u, D.gu[c->cur]);
+        c->go->from_masters(c->stream, D.n_ifc, D.ifc_xyz, D.N, D.u + D.ifc_base, D.gu[c->cur]);
+    }
     CHKLAUNCH();
     HIPCHK(hipStreamSynchronize(c->stream));
     dd_end(*c);
@@ -2343,15 +2751,56 @@ int hhgr_mass_apply(hhgr_ctx *c, const double *dev_x, double *dev_y) {
     if (!c || !dev_x || !dev_y) return fail(HHGR_EINVAL, "null argument");
     if (c->gen && !c->geom_set) return fail(HHGR_ESTATE, "no geometry set");
     LevelDev &D = c->lev[c->L];
+    if (!c->gen) {
+        // one grid stencil whatever k is: no trip through slot space
+        launch_mass_grid(c->stream, D.N, D.h, dev_x, dev_y);
+        CHKLAUNCH();
+        return HHGR_OK;
+    }
     const IfcGeom ig = igeom(D, 0, D.n_ifc, nullptr, false);
     to_slots(*c, D, dev_x, c->aux_b, c->stream);
-    if (c->gen)
-        launch_apply15(c->stream, vgeom(D, D.vd_all, c->n_tets, false), ig, gen15mass(D), c->aux_b, c->aux_u);
-    else
-        launch_mass(c->stream, vgeom(D, D.vd_all, c->n_tets, false), ig, D.nb15, c->aux_b, c->aux_u, D.h);
+    launch_apply15(c->stream, vgeom(D, D.vd_all, c->n_tets, false), ig, gen15mass(D), c->aux_b, c->aux_u);
     to_user(*c, D, c->aux_u, dev_y, c->stream);
     CHKLAUNCH();
     return HHGR_OK;
+}
+
+// hhgr_adjoint_grad on the grid (k = 1: dJ/df only)
+static int grid_adjoint(hhgr_ctx &c, const double *dev_g, double rel_tol, int max_cycles, double *dev_dJdf) {
+    LevelDev &D = c.lev[c.L];
+    const size_t bytes = (size_t)grid_len(D.N) * sizeof(double);
+    HIPCHK(hipMemcpyAsync(c.aux_u, D.gu[c.cur], bytes, hipMemcpyDeviceToDevice, c.stream));
+    HIPCHK(hipMemcpyAsync(c.aux_b, D.gb, bytes, hipMemcpyDeviceToDevice, c.stream));
+    const double bnorm_saved = c.bnorm;
+    const bool mixed_saved = c.mixed;
+    c.mixed = false;
+    invalidate_graph(c);
+    const int nb = c.go->from_user(c.stream, D.N, dev_g, D.gb, c.gpartial);
+    launch_reduce(c.stream, c.gpartial, nb, c.dnorm + 1);
+    launch_fill<double>(c.stream, D.gu[c.cur], grid_len(D.N), 0.0);
+    CHKLAUNCH();
+    if (mixed_saved)  // the FP64 cycle's launches (a mixed context plans the FP32 ones)
+        for (int l = c.Lc + 1; l <= c.L; l++) grid_plan(*c.go, c.lev[l], false);
+    double gn;
+    const int rc = read_norm(c, 1, &gn);
+    int result = HHGR_OK;
+    if (!rc) {
+        c.bnorm = gn;
+        hhgr_report rep{0, 0.0, nullptr, 0};
+        result = gn > 0 ? hhgr_solve(&c, rel_tol, max_cycles, &rep) : HHGR_OK;
+        if (dev_dJdf) c.go->mass_user(c.stream, D.N, D.h, D.gu[c.cur], dev_dJdf);
+    }
+    // restore the forward state
+    hipMemcpyAsync(D.gu[c.cur], c.aux_u, bytes, hipMemcpyDeviceToDevice, c.stream);
+    hipMemcpyAsync(D.gb, c.aux_b, bytes, hipMemcpyDeviceToDevice, c.stream);
+    c.bnorm = bnorm_saved;
+    c.mixed = mixed_saved;
+    if (mixed_saved)
+        for (int l = c.Lc + 1; l <= c.L; l++) grid_plan(*c.go, c.lev[l], true);
+    invalidate_graph(c);
+    CHKLAUNCH();
+    HIPCHK(hipStreamSynchronize(c.stream));
+    return rc ? rc : result;
 }
 
 int hhgr_adjoint_grad(hhgr_ctx *c, const double *dev_g, double rel_tol, int max_cycles, double *dev_dJdf,
@@ -2361,9 +2810,10 @@ int hhgr_adjoint_grad(hhgr_ctx *c, const double *dev_g, double rel_tol, int max_
     if (!dev_g) return fail(HHGR_EINVAL, "null g");
     if (dev_dJdk && !c->vk && !c->mesh) return fail(HHGR_ESTATE, "dJ/dk needs variable_coeff = 1");
     LevelDev &D = c->lev[c->L];
+    if (c->go) return grid_adjoint(*c, dev_g, rel_tol, max_cycles, dev_dJdf);
     const long long ns = D.n_slots;
     const IfcGeom ig = igeom(D, 0, D.n_ifc, nullptr, false);
-    const VolGeom vfull = vgeom(D, D.vd_all, c->n_tets, true), vint = vgeom(D, D.vd_all, c->n_tets, false);
+    const VolGeom vint = vgeom(D, D.vd_all, c->n_tets, false);
     // save u and b, solve A lambda = g from zero in FP64
     HIPCHK(hipMemcpyAsync(c->aux_u, D.u, ns * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
     HIPCHK(hipMemcpyAsync(c->aux_b, D.b, ns * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
@@ -2390,12 +2840,15 @@ int hhgr_adjoint_grad(hhgr_ctx *c, const double *dev_g, double rel_tol, int max_
         c->bnorm = gn;
         hhgr_report rep{0, 0.0, nullptr, 0};
         result = gn > 0 ? hhgr_solve(c, rel_tol, max_cycles, &rep) : HHGR_OK;
-        if (dev_dJdf) {
-            if (c->gen)
-                launch_apply15(c->stream, vint, ig, gen15mass(D), D.u, D.r);
-            else
-                launch_mass(c->stream, vint, ig, D.nb15, D.u, D.r, D.h);
+        double *lam = nullptr;  // lambda in vector order
+        if (dev_dJdf && c->gen) {
+            launch_apply15(c->stream, vint, ig, gen15mass(D), D.u, D.r);
             to_user(*c, D, D.r, dev_dJdf, c->stream);
+        } else if (dev_dJdf) {
+            // M lambda in vector order
+            lam = c->user_l ? c->user_l : D.r;
+            to_user(*c, D, D.u, lam, c->stream);
+            launch_mass_grid(c->stream, D.N, D.h, lam, dev_dJdf);
         }
         if (dev_dJdk && c->mesh) {
             // per macro tetrahedron from the saved u and lambda in slot space
@@ -2403,7 +2856,7 @@ int hhgr_adjoint_grad(hhgr_ctx *c, const double *dev_g, double rel_tol, int max_
             launch_mesh_grad_tet(c->stream, c->n_tets, D.m, D.M, D.rowC, D.C_pad, c->mesh_kel, c->aux_u, D.u, D.r,
                                  dev_dJdk);
         } else if (dev_dJdk) {
-            launch_slots_to_user<double>(c->stream, vint, c->tetinfo, D.m, D.N, ig, D.ifc_dof, D.u, c->user_l);
+            if (!lam) launch_slots_to_user<double>(c->stream, vint, c->tetinfo, D.m, D.N, ig, D.ifc_dof, D.u, c->user_l);
             if (c->gen)
                 launch_grad_k15(c->stream, D.N, D.m, c->d.n_sub, c->kel, c->user_u, c->user_l, dev_dJdk);
             else
@@ -2500,7 +2953,11 @@ int hhgr_kernel_stats(hhgr_ctx *c, long long *launches, double *mean_ms, double 
     // (3/4 word per unknown) and 3 words per node of its class (1/4)
     const double w = c->mixed ? 4.0 : 8.0;
     const LevelDev &F = c->lev[c->L];
-    if (F.fz_on && (c->mixed ? F.u32alt != nullptr : F.ualt != nullptr)) {
+    if (c->go) {
+        // a grid sweep reads u and b once and writes u once; the FP32 ones
+        // start from zero and do not read u
+        if (alg_bytes) *alg_bytes = (c->mixed ? 2.0 : 3.0) * w * (double)c->n_dofs;
+    } else if (F.fz_on && (c->mixed ? F.u32alt != nullptr : F.ualt != nullptr)) {
         // the fused sweep's volume kernel: u (both colours) and b read once,
         // u written once, over the volume-interior nodes
         const double mm = F.m;
@@ -2888,7 +3345,8 @@ int hhgr_batch_create(hhgr_ctx **ctxs, int n, void *hip_stream, hhgr_batch **out
 void hhgr_batch_destroy(hhgr_batch *b) {
     if (!b) return;
     if (b->stream) hipStreamSynchronize(b->stream);
-    if (b->gexec) hipGraphExecDestroy(b->gexec);
+    for (auto &st : b->step)
+        if (st.x) hipGraphExecDestroy(st.x);
     for (auto *ss : {&b->branch, &b->branch2})
         for (auto s : *ss)
             if (s) hipStreamDestroy(s);
@@ -2931,7 +3389,9 @@ int hhgr_batch_run(hhgr_batch *b, double rel_tol, int max_cycles, hhgr_report *r
     for (int q = 0; q < n; q++)
         if (b->dd[q].armed) {
             invalidate_graph(*b->ctx[q]);
-            int rc = dd_setup(*b->ctx[q], b->dd[q].tets);
+            // (synchronised at the end of the block: the steps run on other streams)
+            RecoveryTables keep(b->ctx[q]->stream);
+            int rc = dd_setup(*b->ctx[q], b->dd[q].tets, keep);
             if (rc) return rc;
             b->dd[q].step = 0;
         }
@@ -2941,6 +3401,8 @@ int hhgr_batch_run(hhgr_batch *b, double rel_tol, int max_cycles, hhgr_report *r
         HView<double> V = global_view<double>(*c, false, 0);
         if (c->mixed)
             prime_mixed(*c, b->stream);
+        else if (c->go)
+            grid_residual(*c, false, nullptr, nullptr, b->stream, c->dnorm);
         else
             finest_residual<double>(*c, V, (double *)nullptr, b->stream, c->dnorm);
         HIPCHK(hipMemcpyAsync(b->hnorm + q, c->dnorm, sizeof(double), hipMemcpyDeviceToHost, b->stream));
@@ -2966,26 +3428,35 @@ int hhgr_batch_run(hhgr_batch *b, double rel_tol, int max_cycles, hhgr_report *r
             }
             sig.push_back(q);
             sig.push_back(mode);
+            sig.push_back(b->ctx[q]->cur);
         }
         // the step graph holds every member's cycle (and a recovering member's
         // intact-side cycle); local recovery cycles run beside the graph launch
         // on the member's second stream, forked and joined by events
         auto in_graph = [](int mode) { return mode == 0 || (mode & kModeMasked) || !(mode & kModeLocal); };
-        if (sig != b->sig_in_graph || !b->gexec) {
-            if (b->gexec) hipGraphExecDestroy(b->gexec);
-            b->gexec = nullptr;
+        auto moves = [&](int mode) { return mode == 0 || (mode & kModeMasked); };  // runs a step of the member
+        hhgr_batch::Step *st = nullptr;
+        for (auto &k : b->step)
+            if (k.x && k.sig == sig) st = &k;
+        if (!st) {
+            st = &b->step[b->step_next];
+            b->step_next ^= 1;
+            if (st->x) hipGraphExecDestroy(st->x);
+            st->x = nullptr;
             hipGraph_t g = nullptr;
             HIPCHK(hipStreamBeginCapture(b->cap, hipStreamCaptureModeRelaxed));
             HIPCHK(hipEventRecord(b->ev[0], b->cap));
             for (size_t a = 0; a < active.size(); a++) {
-                const int q = sig[2 * a], mode = sig[2 * a + 1];
+                const int q = sig[3 * a], mode = sig[3 * a + 1];
                 if (!in_graph(mode)) continue;
                 hhgr_ctx *c = b->ctx[q];
                 hipStream_t s = b->branch[q];
                 hipStreamWaitEvent(s, b->ev[0], 0);
                 if (mode == 0) {
                     HView<double> V64 = global_view<double>(*c, false, 0);
-                    if (c->mixed) {
+                    if (c->go) {
+                        grid_step(*c, false, true, s, c->dnorm);
+                    } else if (c->mixed) {
                         HView<float> V32 = global_view<float>(*c, false, 0);
                         step_mixed(*c, V64, V32, s, 0);
                     } else {
@@ -2996,36 +3467,43 @@ int hhgr_batch_run(hhgr_batch *b, double rel_tol, int max_cycles, hhgr_report *r
                     if ((mode & kModeFinal) && !(mode & kModeLocal)) dd_final_norm(*c, s);
                 }
                 hipMemcpyAsync(b->hnorm + q, c->dnorm, sizeof(double), hipMemcpyDeviceToHost, s);
+                c->cur = sig[3 * a + 2];  // nothing has run yet
                 hipEventRecord(b->ev[1 + q], s);
                 hipStreamWaitEvent(b->cap, b->ev[1 + q], 0);
             }
             hipError_t ce = hipStreamEndCapture(b->cap, &g);
             if (ce != hipSuccess) return fail(HHGR_EHIP, std::string("batch capture: ") + hipGetErrorString(ce));
-            ce = hipGraphInstantiate(&b->gexec, g, nullptr, nullptr, 0);
+            ce = hipGraphInstantiate(&st->x, g, nullptr, nullptr, 0);
             hipGraphDestroy(g);
-            if (ce != hipSuccess) return fail(HHGR_EHIP, std::string("batch instantiate: ") + hipGetErrorString(ce));
-            b->sig_in_graph = sig;
+            if (ce != hipSuccess) {
+                st->x = nullptr;
+                return fail(HHGR_EHIP, std::string("batch instantiate: ") + hipGetErrorString(ce));
+            }
+            st->sig = sig;
         }
         // local cycles of recoveries starting now, concurrent with the graph:
         // forked before the graph launch, launched after it (the host then
         // launches the many small local kernels while the graph runs)
         for (size_t a = 0; a < active.size(); a++) {
-            const int q = sig[2 * a], mode = sig[2 * a + 1];
+            const int q = sig[3 * a], mode = sig[3 * a + 1];
             if (!(mode & kModeLocal)) continue;
             HIPCHK(hipEventRecord(b->evl[2 * q], b->stream));
             HIPCHK(hipStreamWaitEvent(b->branch2[q], b->evl[2 * q], 0));
         }
-        HIPCHK(hipGraphLaunch(b->gexec, b->stream));
+        HIPCHK(hipGraphLaunch(st->x, b->stream));
+        for (size_t a = 0; a < active.size(); a++)
+            if (moves(sig[3 * a + 1])) b->ctx[sig[3 * a]]->cur ^= step_swaps(*b->ctx[sig[3 * a]]);
         for (size_t a = 0; a < active.size(); a++) {
-            const int q = sig[2 * a], mode = sig[2 * a + 1];
+            const int q = sig[3 * a], mode = sig[3 * a + 1];
             if (!(mode & kModeLocal)) continue;
             dd_local(*b->ctx[q], b->dd[q].n_local, b->branch2[q]);
             HIPCHK(hipEventRecord(b->evl[2 * q + 1], b->branch2[q]));
         }
         for (size_t a = 0; a < active.size(); a++) {
-            const int q = sig[2 * a], mode = sig[2 * a + 1];
+            const int q = sig[3 * a], mode = sig[3 * a + 1];
             if (!(mode & kModeLocal)) continue;
             HIPCHK(hipStreamWaitEvent(b->stream, b->evl[2 * q + 1], 0));
+            if (b->ctx[q]->go) grid_from_local(*b->ctx[q], b->stream);
             if (mode & kModeFinal) {
                 hhgr_ctx *c = b->ctx[q];
                 dd_final_norm(*c, b->stream);
@@ -3036,7 +3514,7 @@ int hhgr_batch_run(hhgr_batch *b, double rel_tol, int max_cycles, hhgr_report *r
         HIPCHK(hipStreamSynchronize(b->stream));
         std::vector<int> next;
         for (size_t a = 0; a < active.size(); a++) {
-            const int q = sig[2 * a], mode = sig[2 * a + 1];
+            const int q = sig[3 * a], mode = sig[3 * a + 1];
             // during a recovery the norm is that of the intact part's residual;
             // a step without an intact cycle (local recovery only) is not a cycle
             rel[q] = b->ctx[q]->bnorm > 0 ? std::sqrt(std::max(b->hnorm[q], 0.0)) / b->ctx[q]->bnorm : 0.0;

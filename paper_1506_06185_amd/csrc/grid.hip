@@ -1,0 +1,845 @@
+// HIP kernels (gfx950) of the structured-grid path (grid.hpp).
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cstdlib>
+#include <type_traits>
+
+#include "grid.hpp"
+#include "kernels.hpp"
+
+namespace hhgr {
+
+extern __shared__ __align__(16) unsigned char grid_lds[];
+
+namespace {
+
+template <typename T>
+struct alignas(2 * sizeof(T)) Pair {
+    T lo, hi;
+};
+
+__device__ __forceinline__ unsigned grid_xcd(unsigned f, unsigned total) {
+    const unsigned per = total >> 3, rem = total & 7u, x = f & 7u, loc = f >> 3;
+    return x < rem ? x * (per + 1) + loc : rem * (per + 1) + (x - rem) * per + loc;
+}
+
+// halo of a launch of K = 2 ns colour passes: nodes below and above a tile
+// along each axis
+constexpr int halo_lo(int K, int tail) { return tail == kGridResidual ? 1 : tail == kGridRestrict ? K + 2 : tail == kGridNorm ? K + 1 : K; }
+constexpr int halo_hi(int K, int tail) { return tail == kGridResidual ? 1 : tail == kGridPlain ? K : K + 1; }
+
+// sum over the workgroup to partial[blockIdx.x], in a fixed order (the LDS is free)
+__device__ __forceinline__ void block_partial(double sum, double *partial) {
+    double *red = (double *)grid_lds;
+    const int tid = (int)threadIdx.x;
+    red[tid] = sum;
+    for (int n = (int)blockDim.x; n > 1;) {
+        const int hf = (n + 1) >> 1;
+        __syncthreads();
+        if (tid + hf < n) red[tid] += red[tid + hf];
+        n = hf;
+    }
+    if (tid == 0) partial[blockIdx.x] = red[0];
+}
+
+// ---------------------------------------------------------------------------
+// ns red-black sweeps in one launch
+// ---------------------------------------------------------------------------
+// A workgroup marches through the planes of its tile.  A thread owns a pair
+// of columns (2p, 2p + 1) of row y: column A has x + y even (red on even
+// planes), column B has x + y odd.  At step z the active column X (A on even
+// z, B on odd z) runs pass k = 1 .. K (red, black, red, ...) at its node of
+// plane z - k + 1: that node has pass k's colour on every such plane, and
+//   - its own old value is the column's pass k - 2 result of step z - 2,
+//   - its neighbours along z are the column's pass k - 1 results of this step
+//     and of step z - 2,
+//   - its neighbours in the plane are pass k - 1 results of step z - 1 of
+//     columns of the other kind: the pair's other column (in registers) and
+//     three of neighbouring threads (in LDS).
+// So every pass of a step reads what earlier steps published: one barrier per
+// step, whatever the number of passes.  Passes at a tile's edge read nodes
+// that the tile does not hold; the wrong values travel one node per pass and
+// stay in the halo.
+template <typename T, int NS, int START, int TAIL, bool MASK>
+__global__ void __launch_bounds__(1024) k_grid_sweep(GridSweep<T> g, GridTiles t, T h, T om, T omr) {
+    constexpr int K = 2 * NS;
+    constexpr bool RES = TAIL != kGridPlain;
+    constexpr int NL = K + (RES ? 1 : 0);  // published results: pass 0 (the input) .. NL - 1
+    constexpr int J0 = START == kGridFromZero ? 1 : 0;
+    const int N = g.N, P = N + 16;
+    const long long S = (long long)P * N;
+    const unsigned f = grid_xcd(blockIdx.x, gridDim.x);
+    const int ix = (int)(f % t.ntx), iy = (int)((f / t.ntx) % t.nty), iz = (int)(f / (t.ntx * t.nty));
+    constexpr int HL = halo_lo(K, TAIL), HH = halo_hi(K, TAIL);
+    // own ranges: pairs [P0, P1), rows [Y0, Y1), planes [Z0, Z1); loaded: + halo
+    const int np = N / 2;
+    const int P0 = ix * t.vp, P1 = min(np, P0 + t.vp);
+    const int Y0 = iy * t.vy, Y1 = min(N, Y0 + t.vy);
+    const int Z0 = iz * t.vz, Z1 = min(N, Z0 + t.vz);
+    const int p0 = max(0, P0 - (HL + 1) / 2), p1 = min(np + 1, P1 + (HH + 1) / 2);
+    const int y0 = max(0, Y0 - HL), y1 = min(N + 1, Y1 + HH);
+    const int tid = (int)threadIdx.x;
+    const int lr = tid / t.tp, lp = tid - lr * t.tp;
+    const int p = p0 + lp, y = y0 + lr;
+    const bool act = p < p1 && y < y1;
+    const int yo = y & 1;
+    // interior columns of A and B (x = 2p + yo and 2p + 1 - yo)
+    const bool rowin = act && y >= 1 && y < N;
+    bool in[2];
+    in[0] = rowin && 2 * p + yo >= 1 && 2 * p + yo < N;
+    in[1] = rowin && 2 * p + 1 - yo >= 1 && 2 * p + 1 - yo < N;
+    const bool own = act && p >= P0 && p < P1 && y >= Y0 && y < Y1;
+    // element offset of the pair in a plane (threads outside the tile read its first pair)
+    const unsigned off = act ? (unsigned)(y * P + 2 * p) : (unsigned)(y0 * P + 2 * p0);
+
+    const int rows = ((int)blockDim.x + t.tp - 1) / t.tp + 2;
+    const int LS = rows * t.tp + 2;  // one published plane, a row of padding on each side
+    T *const lds = (T *)grid_lds;
+    const int li = (lr + 1) * t.tp + lp + 1;
+    // neighbour of the other kind along x that is not the pair's own
+    const int dxA = yo ? 1 : -1;
+    // residual planes (ring of 3) for the restriction: [row][2 tp]
+    const int RS = rows * 2 * t.tp + 2;
+    T *const rs = lds + (NL - J0) * 2 * LS;
+    const int ri = (lr + 1) * 2 * t.tp + 2 * lp + 1;
+
+    // coarse grid of the interpolation and of the restriction
+    const int Nc = N / 2, Pc = Nc + 16;
+    const long long Sc = (long long)Pc * Nc;
+    const int yc = act ? y : y0, pc = act ? p : p0;
+    const unsigned cl = (unsigned)((yc >> 1) * Pc + pc), ch = (unsigned)(((yc + 1) >> 1) * Pc + pc);
+
+    struct Load {
+        Pair<T> u, b;
+        T e0, e1, e2;
+        unsigned short m;
+    };
+    auto plane = [&](int z) { return min(max(z, 0), N); };
+    // input of plane z and right-hand side of plane z - 1
+    auto issue = [&](int z, Load &L) {
+        const long long zu = plane(z), zb = plane(z - 1);
+        if (START != kGridFromZero) L.u = *(const Pair<T> *)(g.u + zu * S + off);
+        L.b = *(const Pair<T> *)(g.b + zb * S + off);
+        if (START == kGridProlong) {
+            const T *el = g.ec + (zu >> 1) * Sc, *eh = g.ec + ((zu + 1) >> 1) * Sc;
+            L.e0 = el[cl];
+            L.e1 = eh[ch];
+            L.e2 = eh[ch + 1];
+        }
+        if (MASK) L.m = *(const unsigned short *)(g.frz + zb * S + off);
+    };
+
+    // published results of the two columns' last steps: pv[c][k], k = 0 .. K
+    T pv[2][K + 1], uc[2], bh[2][NL + 1];
+    unsigned fz[2] = {0u, 0u};  // frozen flags, bit k - 1: the node of pass k
+#pragma unroll
+    for (int c = 0; c < 2; c++) {
+#pragma unroll
+        for (int k = 0; k <= K; k++) pv[c][k] = T(0);
+#pragma unroll
+        for (int k = 0; k <= NL; k++) bh[c][k] = T(0);
+        uc[c] = T(0);
+    }
+    double sum = 0.0;
+    T acc = T(0);
+    const int zs = (max(0, Z0 - HL) - 1) & ~1, ze = Z1 + (TAIL == kGridPlain ? K - 2 : TAIL == kGridNorm ? K - 1 : K);
+    Load ld[2];
+    issue(zs + 1, ld[1]);
+    issue(zs + 2, ld[0]);
+    for (int q = tid; q < (NL - J0) * 2 * LS; q += (int)blockDim.x) lds[q] = T(0);
+    __syncthreads();
+
+    auto step = [&](auto par, int z) {
+        constexpr int X = decltype(par)::value, Y = 1 - X;
+        // input of plane z + 1 (both columns), right-hand side of plane z
+        Load &L = ld[X ^ 1];
+        T in0[2], b0[2];
+        {
+            T ul = START == kGridFromZero ? T(0) : L.u.lo, uh = START == kGridFromZero ? T(0) : L.u.hi;
+            if (START == kGridProlong) {
+                // a coarse node's own value (twice the half) at even (x, y, z)
+                ul += T(0.5) * (L.e0 + L.e1);
+                uh += T(0.5) * (L.e0 + L.e2);
+            }
+            in0[0] = yo ? uh : ul;
+            in0[1] = yo ? ul : uh;
+            b0[0] = yo ? L.b.hi : L.b.lo;
+            b0[1] = yo ? L.b.lo : L.b.hi;
+        }
+        if (MASK) {
+            const unsigned ml = (L.m & 0xffu) ? 1u : 0u, mh = (L.m >> 8) ? 1u : 0u;
+            fz[0] = (fz[0] << 1) | (yo ? mh : ml);
+            fz[1] = (fz[1] << 1) | (yo ? ml : mh);
+        }
+        issue(z + 3, L);
+#pragma unroll
+        for (int c = 0; c < 2; c++) {
+#pragma unroll
+            for (int k = NL; k > 0; k--) bh[c][k] = bh[c][k - 1];
+            bh[c][0] = b0[c];
+        }
+        const int dx = X == 0 ? dxA : -dxA;
+        // neighbours in the plane: results of step z - 1
+        T nx[NL], ny[NL], nw[NL];
+#pragma unroll
+        for (int k = J0; k < NL; k++) {
+            const T *l = lds + ((k - J0) * 2 + Y) * LS + li;
+            nx[k] = l[dx];
+            ny[k] = l[-t.tp];
+            nw[k] = l[t.tp];
+        }
+        T res[K + 1];
+        res[0] = in0[X];
+        T rlast = T(0), rred = T(0);
+#pragma unroll
+        for (int k = 1; k <= NL; k++) {
+            const int zp = z - k + 1;
+            const bool up = in[X] && zp >= 1 && zp < N && (!MASK || !((fz[X] >> (k - 1)) & 1u));
+            T ctr, rr;
+            if (START == kGridFromZero && k == 1) {
+                ctr = T(0);
+                rr = bh[X][0];
+            } else {
+                ctr = k == 1 ? uc[X] : pv[X][k - 2];
+                const T a = ((nx[k - 1] + pv[Y][k - 1]) + (ny[k - 1] + nw[k - 1])) + (res[k - 1] + pv[X][k - 1]);
+                rr = bh[X][k - 1] - h * (T(6) * ctr - a);
+            }
+            if (k <= K) {
+                res[k] = up ? ctr + om * rr : ctr;
+                if (k == K) rlast = up ? omr * rr : T(0);
+            } else {
+                rred = up ? rr : T(0);
+            }
+        }
+        // the pair of plane z - K + 1 is final: X black now, Y red in step z - 1
+        const int zo = z - K + 1;
+        if (own && zo >= Z0 && zo < Z1) {
+            const T x0 = X == 0 ? res[K] : pv[0][K - 1], x1 = X == 0 ? pv[1][K - 1] : res[K];
+            Pair<T> o;
+            o.lo = yo ? x1 : x0;
+            o.hi = yo ? x0 : x1;
+            *(Pair<T> *)(g.v + zo * S + off) = o;
+        }
+        if (TAIL == kGridNorm) {
+            // residual of the black node of plane z - K + 1, of the red node of plane z - K
+            if (own && zo >= Z0 && zo < Z1) sum += (double)rlast * (double)rlast;
+            if (own && zo - 1 >= Z0 && zo - 1 < Z1) sum += (double)rred * (double)rred;
+        }
+        // publish; the input of plane z + 1 belongs to column X
+#pragma unroll
+        for (int k = J0; k < NL; k++) lds[((k - J0) * 2 + X) * LS + li] = res[k];
+        if (TAIL == kGridRestrict) {
+            const int zr = z - K;
+            const int q0 = (zr + 3 * 1024) % 3, q1 = q0 == 2 ? 0 : q0 + 1, q2 = q1 == 2 ? 0 : q1 + 1;
+            const int xl = X == 0 ? yo : 1 - yo;
+            rs[q0 * RS + ri + xl] = rred;
+            rs[q1 * RS + ri + xl] = rlast;
+            // plane z - K - 1 is complete since the last barrier
+            if (!yo) {
+                const T *r = rs + q2 * RS + ri;
+                const int zc = zr - 1, R2 = 2 * t.tp;
+                const T c0 = r[0], xp = r[1], xm = r[-1], yp = r[R2], ym = r[-R2], pp = r[R2 + 1], mm = r[-R2 - 1];
+                if (zc & 1) {
+                    const T o = acc + T(0.5) * ((c0 + xp) + (yp + pp));
+                    const int Zc = (zc - 1) >> 1;
+                    if (own && p >= 1 && y >= 2 && Zc >= 1 && 2 * Zc >= Z0 && 2 * Zc < Z1)
+                        g.bc[(long long)Zc * Sc + (unsigned)((y >> 1) * Pc + p)] = o;
+                    acc = T(0.5) * ((c0 + xm) + (ym + mm));
+                } else {
+                    acc += c0 + T(0.5) * (((xp + xm) + (yp + ym)) + (pp + mm));
+                }
+            }
+        }
+#pragma unroll
+        for (int k = 0; k <= K; k++) pv[X][k] = res[k];
+        uc[Y] = in0[Y];
+        __syncthreads();
+    };
+    for (int z = zs; z <= ze; z += 2) {
+        step(std::integral_constant<int, 0>(), z);
+        step(std::integral_constant<int, 1>(), z + 1);
+    }
+    if (TAIL == kGridNorm) block_partial(sum, g.partial);
+}
+
+// ---------------------------------------------------------------------------
+// residual, with an FP32 correction added first
+// ---------------------------------------------------------------------------
+// The same march with no pass: step z publishes the pair of plane z + 1 and
+// evaluates plane z from the plane published in step z - 1.
+template <bool ADD, bool MASK>
+__global__ void __launch_bounds__(1024) k_grid_residual(GridResidual g, GridTiles t) {
+    const int N = g.N, P = N + 16;
+    const long long S = (long long)P * N;
+    const unsigned f = grid_xcd(blockIdx.x, gridDim.x);
+    const int ix = (int)(f % t.ntx), iy = (int)((f / t.ntx) % t.nty), iz = (int)(f / (t.ntx * t.nty));
+    const int np = N / 2;
+    const int P0 = ix * t.vp, P1 = min(np, P0 + t.vp), Y0 = iy * t.vy, Y1 = min(N, Y0 + t.vy);
+    const int Z0 = iz * t.vz, Z1 = min(N, Z0 + t.vz);
+    const int p0 = max(0, P0 - 1), p1 = min(np + 1, P1 + 1), y0 = max(0, Y0 - 1), y1 = min(N + 1, Y1 + 1);
+    const int tid = (int)threadIdx.x, lr = tid / t.tp, lp = tid - lr * t.tp;
+    const int p = p0 + lp, y = y0 + lr;
+    const bool act = p < p1 && y < y1;
+    const bool own = act && p >= P0 && p < P1 && y >= Y0 && y < Y1;
+    const bool inlo = own && y >= 1 && p >= 1, inhi = own && y >= 1;
+    const unsigned off = act ? (unsigned)(y * P + 2 * p) : (unsigned)(y0 * P + 2 * p0);
+    const int rows = ((int)blockDim.x + t.tp - 1) / t.tp + 2;
+    const int LS = rows * t.tp + 2, li = (lr + 1) * t.tp + lp + 1;
+    Pair<double> *const lds = (Pair<double> *)grid_lds;
+    const double h = g.h;
+    struct Load {
+        Pair<double> u, b;
+        Pair<float> e;
+    };
+    // u (and e) of plane z, b of plane z - 1
+    auto issue = [&](int z, Load &L) {
+        const long long zu = min(max(z, 0), N), zb = min(max(z - 1, 0), N);
+        L.u = *(const Pair<double> *)(g.u + zu * S + off);
+        if (ADD) L.e = *(const Pair<float> *)(g.e + zu * S + off);
+        L.b = *(const Pair<double> *)(g.b + zb * S + off);
+    };
+    Load ld[2];
+    Pair<double> um = {0.0, 0.0}, uc = {0.0, 0.0};
+    double sum = 0.0;
+    const int zs = (max(0, Z0 - 1) - 1) & ~1, ze = Z1 - 1;
+    issue(zs + 1, ld[1]);
+    issue(zs + 2, ld[0]);
+    auto step = [&](auto par, int z) {
+        constexpr int X = decltype(par)::value;
+        Load &L = ld[X ^ 1];
+        Pair<double> up = L.u;
+        if (ADD) {
+            up.lo += (double)L.e.lo;
+            up.hi += (double)L.e.hi;
+        }
+        const Pair<double> bb = L.b;
+        issue(z + 3, L);
+        lds[X * LS + li] = up;  // plane z + 1
+        if (own && z >= Z0 && z < Z1) {
+            const Pair<double> *l = lds + (X ^ 1) * LS + li;
+            const Pair<double> ym = l[-t.tp], yp = l[t.tp];
+            const double xm = l[-1].hi, xp = l[1].lo;
+            const bool zin = z >= 1;
+            bool a0 = inlo && zin, a1 = inhi && zin;
+            if (MASK) {
+                const unsigned short m = *(const unsigned short *)(g.frz + z * S + off);
+                a0 = a0 && !(m & 0xffu);
+                a1 = a1 && !(m >> 8);
+            }
+            const double r0 = bb.lo - h * (6.0 * uc.lo - (((xm + uc.hi) + (ym.lo + yp.lo)) + (um.lo + up.lo)));
+            const double r1 = bb.hi - h * (6.0 * uc.hi - (((uc.lo + xp) + (ym.hi + yp.hi)) + (um.hi + up.hi)));
+            Pair<double> r = {a0 ? r0 : 0.0, a1 ? r1 : 0.0};
+            sum += r.lo * r.lo + r.hi * r.hi;
+            if (ADD) *(Pair<double> *)(g.v + z * S + off) = uc;
+            if (g.r64) *(Pair<double> *)(g.r64 + z * S + off) = r;
+            if (g.r32) *(Pair<float> *)(g.r32 + z * S + off) = Pair<float>{(float)r.lo, (float)r.hi};
+        }
+        um = uc;
+        uc = up;
+        __syncthreads();
+    };
+    for (int z = zs; z <= ze; z += 2) {
+        step(std::integral_constant<int, 0>(), z);
+        step(std::integral_constant<int, 1>(), z + 1);
+    }
+    if (g.partial) block_partial(sum, g.partial);
+}
+
+// ---------------------------------------------------------------------------
+// plain forms of the cycle's parts (sweep counts of zero): one node per thread
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ bool grid_node(int N, int &x, int &y, int &z) {
+    x = (int)(blockIdx.x * 64 + (threadIdx.x & 63)) + 1;
+    y = (int)(blockIdx.y * 4 + (threadIdx.x >> 6)) + 1;
+    z = (int)blockIdx.z + 1;
+    return x < N && y < N;
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256) k_grid_plain_residual(int N, T h, const T *u, const T *b, T *r) {
+    int x, y, z;
+    if (!grid_node(N, x, y, z)) return;
+    const int P = N + 16;
+    const long long S = (long long)P * N, i = x + (long long)P * y + S * z;
+    r[i] = b[i] - h * (T(6) * u[i] - (((u[i - 1] + u[i + 1]) + (u[i - P] + u[i + P])) + (u[i - S] + u[i + S])));
+}
+
+// bc at coarse node (x, y, z) of the grid of N / 2 cells
+template <typename T>
+__global__ void __launch_bounds__(256) k_grid_plain_restrict(int N, const T *r, T *bc) {
+    int x, y, z;
+    if (!grid_node(N / 2, x, y, z)) return;
+    const long long P = N + 16, S = P * N, i = 2 * (x + P * y + S * z);
+    auto two = [&](long long d) { return r[i + d] + r[i - d]; };
+    const T s = ((two(1) + two(P)) + (two(S) + two(1 + P))) + ((two(P + S) + two(1 + S)) + two(1 + P + S));
+    const long long Pc = N / 2 + 16;
+    bc[x + Pc * (y + (long long)(N / 2) * z)] = r[i] + T(0.5) * s;
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256) k_grid_plain_prolong(int N, const T *u, const T *ec, T *v) {
+    int x, y, z;
+    if (!grid_node(N, x, y, z)) return;
+    const long long P = N + 16, i = x + P * (y + (long long)N * z), Pc = N / 2 + 16, Nc = N / 2;
+    const T e0 = ec[(x >> 1) + Pc * ((y >> 1) + Nc * (z >> 1))];
+    const T e1 = ec[((x + 1) >> 1) + Pc * (((y + 1) >> 1) + Nc * ((z + 1) >> 1))];
+    v[i] = u[i] + T(0.5) * (e0 + e1);
+}
+
+// ---------------------------------------------------------------------------
+// coarsest level: u = A^{-1} b by sine transforms along x, y and z
+// ---------------------------------------------------------------------------
+// One workgroup, everything in LDS: six products with the (N - 1)^2 sine
+// matrix and a division by the eigenvalues.  Exact to rounding, whatever the
+// right-hand side; the data (343 or 1331 unknowns) is far below one CU's
+// LDS, so the time is the launch and six short barriers.
+constexpr int kSineMax = 11;
+__device__ __forceinline__ void sine_axis(int n, int stride, int q, int c, const double *st, const double *in, double *out) {
+    // out at element q, coordinate c along the axis of that stride
+    const double *a = in + q - c * stride;
+    double s = 0.0;
+    for (int j = 0; j < n; j++) s += st[c * n + j] * a[j * stride];
+    out[q] = s;
+}
+
+template <typename T>
+__global__ void __launch_bounds__(512) k_grid_coarse(int N, const double *st, const T *b, T *u) {
+    double *const A = (double *)grid_lds, *const B = A + kSineMax * kSineMax * kSineMax;
+    double *const S = B + kSineMax * kSineMax * kSineMax;
+    const int n = N - 1, n2 = n * n, n3 = n2 * n, tid = (int)threadIdx.x, nt = (int)blockDim.x;
+    const long long P = N + 16;
+    for (int q = tid; q < n2 + n; q += nt) S[q] = st[q];
+    for (int q = tid; q < n3; q += nt) A[q] = (double)b[(q % n + 1) + P * ((q / n) % n + 1 + (long long)N * (q / n2 + 1))];
+    __syncthreads();
+    for (int q = tid; q < n3; q += nt) sine_axis(n, 1, q, q % n, S, A, B);
+    __syncthreads();
+    for (int q = tid; q < n3; q += nt) sine_axis(n, n, q, (q / n) % n, S, B, A);
+    __syncthreads();
+    for (int q = tid; q < n3; q += nt) {
+        sine_axis(n, n2, q, q / n2, S, A, B);
+        B[q] *= (double)N / ((S[n2 + q % n] + S[n2 + (q / n) % n]) + S[n2 + q / n2]);
+    }
+    __syncthreads();
+    for (int q = tid; q < n3; q += nt) sine_axis(n, 1, q, q % n, S, B, A);
+    __syncthreads();
+    for (int q = tid; q < n3; q += nt) sine_axis(n, n, q, (q / n) % n, S, A, B);
+    __syncthreads();
+    for (int q = tid; q < n3; q += nt) {
+        sine_axis(n, n2, q, q / n2, S, B, A);
+        u[(q % n + 1) + P * ((q / n) % n + 1 + (long long)N * (q / n2 + 1))] = (T)A[q];
+    }
+}
+
+// ---------------------------------------------------------------------------
+// vector order <-> grid: a wavefront per row
+// ---------------------------------------------------------------------------
+__global__ void __launch_bounds__(256) k_grid_from_user(int N, const double *user, double *grid, double *partial) {
+    const int n = N - 1, w = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
+    const long long row = (long long)blockIdx.x * 4 + w;
+    double sum = 0.0;
+    if (row < (long long)n * n) {
+        const int y = (int)(row % n), z = (int)(row / n);
+        const double *s = user + row * n;
+        double *d = grid + (long long)(N + 16) * (y + 1 + (long long)N * (z + 1)) + 1;
+        for (int x = lane; x < n; x += 64) {
+            const double v = s[x];
+            d[x] = v;
+            sum += v * v;
+        }
+    }
+    if (partial) block_partial(sum, partial);
+}
+
+__global__ void __launch_bounds__(256) k_grid_to_user(int N, const double *grid, double *user) {
+    const int n = N - 1, w = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
+    const long long row = (long long)blockIdx.x * 4 + w;
+    if (row >= (long long)n * n) return;
+    const int y = (int)(row % n), z = (int)(row / n);
+    const double *s = grid + (long long)(N + 16) * (y + 1 + (long long)N * (z + 1)) + 1;
+    double *d = user + row * n;
+    for (int x = lane; x < n; x += 64) d[x] = s[x];
+}
+
+// ---------------------------------------------------------------------------
+// y = M x with the unit cube's consistent P1 mass matrix: 0.4 h^3 on the
+// diagonal, h^3/20 to the 6 axis neighbours and to +-(1,1,1), h^3/30 to
+// +-(1,1,0), +-(0,1,1), +-(1,0,1)
+// ---------------------------------------------------------------------------
+// A workgroup marches through the planes of a tile of 64 x 16 nodes (62 x 14
+// of them its own), each thread with one column; a plane's 7 values around a
+// node serve the node itself and the nodes above and below it, so a plane is
+// read once and published once.  IG, OG: input, output on the grid instead
+// of in vector order.
+constexpr int kMassX = 64, kMassY = 16, kMassZ = 32;
+template <bool IG, bool OG>
+__global__ void __launch_bounds__(1024) k_grid_mass(int N, double h3, const double *in, double *out, double *partial) {
+    double *const lds = (double *)grid_lds;  // [2][(kMassY + 2) kMassX + 2]
+    constexpr int LS = (kMassY + 2) * kMassX + 2;
+    const int ntx = (N - 1 + kMassX - 3) / (kMassX - 2), nty = (N - 1 + kMassY - 3) / (kMassY - 2);
+    const unsigned f = grid_xcd(blockIdx.x, gridDim.x);
+    const int ix = (int)(f % ntx), iy = (int)((f / ntx) % nty), iz = (int)(f / (ntx * nty));
+    const int lx = (int)(threadIdx.x & (kMassX - 1)), ly = (int)(threadIdx.x / kMassX);
+    const int x = ix * (kMassX - 2) + lx, y = iy * (kMassY - 2) + ly;  // grid coordinates
+    const int Z0 = 1 + iz * kMassZ, Z1 = min(N, Z0 + kMassZ);
+    const bool in_xy = x >= 1 && x < N && y >= 1 && y < N;
+    const bool own = in_xy && lx >= 1 && lx < kMassX - 1 && ly >= 1 && ly < kMassY - 1;
+    const int n = N - 1;
+    const long long SI = IG ? (long long)(N + 16) * N : (long long)n * n, SO = OG ? (long long)(N + 16) * N : (long long)n * n;
+    const long long oi = !in_xy ? 0 : IG ? x + (long long)(N + 16) * y : (x - 1) + (long long)n * (y - 1);
+    const long long oo = !in_xy ? 0 : OG ? x + (long long)(N + 16) * y : (x - 1) + (long long)n * (y - 1);
+    const int li = (ly + 1) * kMassX + lx + 1;
+    const double wc = 0.4 * h3, wax = h3 / 20.0, wfd = h3 / 30.0;
+    auto load = [&](int z) -> double {
+        const bool ok = in_xy && z >= 1 && z < N;
+        const double v = in[(ok ? oi : 0) + (ok ? (long long)(IG ? z : z - 1) * SI : 0)];
+        return ok ? v : 0.0;
+    };
+    double v0 = load(Z0 - 1), v1 = load(Z0), below = 0.0, acc = 0.0, sum = 0.0;
+    for (int z = Z0 - 1; z <= Z1; z++) {
+        const double v = v0;
+        v0 = v1;
+        v1 = load(z + 2);
+        double *l = lds + (z & 1) * LS + li;
+        l[0] = v;
+        __syncthreads();
+        const double xp = l[1], xm = l[-1], yp = l[kMassX], ym = l[-kMassX], pp = l[kMassX + 1], mm = l[-kMassX - 1];
+        if (own && z > Z0) {
+            const double o = acc + (wax * (v + pp) + wfd * (xp + yp));
+            out[oo + (long long)(OG ? z - 1 : z - 2) * SO] = o;
+            sum += o * o;
+        }
+        acc = below + (wc * v + wax * ((xp + xm) + (yp + ym)) + wfd * (pp + mm));
+        below = wax * (v + mm) + wfd * (xm + ym);
+    }
+    if (partial) {
+        __syncthreads();
+        block_partial(sum, partial);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// slot space <-> grid, and the nodes of single tetrahedra
+// ---------------------------------------------------------------------------
+// tetinfo: subcube corner V (3), first two axes a, b; closure node (i, j, k)
+// at m V + i e_a + j (e_a + e_b) + k (1, 1, 1)
+struct GNode {
+    long long g, s;  // grid index, slot
+    bool interior;
+};
+__device__ __forceinline__ bool closure_node(const GridClosures &c, GNode &o) {
+    const unsigned per = ((unsigned)c.nlist + 255u) >> 8;
+    const unsigned f = grid_xcd(blockIdx.x, gridDim.x);
+    const int v = (int)(f / per), e = (int)((f % per) * 256 + threadIdx.x);
+    if (e >= c.nlist) return false;
+    const unsigned w = c.list[e];
+    const int i = (int)(w & 1023u), j = (int)((w >> 10) & 1023u), k = (int)(w >> 20);
+    const VolDesc d = c.vd[v];
+    const int *ti = c.tetinfo + 6 * d.tet;
+    const int m = c.M - 1;
+    int X[3] = {m * ti[0] + k, m * ti[1] + k, m * ti[2] + k};
+    const int a = ti[3], b = ti[4];
+#pragma unroll
+    for (int q = 0; q < 3; q++) X[q] += (q == a ? i + j : 0) + (q == b ? j : 0);
+    o.g = X[0] + (long long)(c.N + 16) * (X[1] + (long long)c.N * X[2]);
+    const int2 r = c.rowC[k * c.M - ((k * (k - 1)) >> 1) + j];
+    o.s = d.vec + ((((i + k) & 1) ? r.y : r.x) + (i >> 1));
+    o.interior = i > 0 && j > 0 && k > 0 && i + j + k < m;
+    // the plane after the last holds x = N and y = N of the last row: zeros
+    return true;
+}
+
+__global__ void __launch_bounds__(256) k_grid_to_closures(GridClosures c, bool zero_interior, const double *grid, double *vec) {
+    GNode o;
+    if (!closure_node(c, o)) return;
+    vec[o.s] = zero_interior && o.interior ? 0.0 : grid[o.g];
+}
+__global__ void __launch_bounds__(256) k_grid_from_closures(GridClosures c, const double *vec, double *grid) {
+    GNode o;
+    if (closure_node(c, o)) grid[o.g] = vec[o.s];
+}
+__global__ void __launch_bounds__(256) k_grid_to_masters(int n, const int *xyz, int N, const double *grid, double *masters) {
+    const int q = (int)(blockIdx.x * 256 + threadIdx.x);
+    if (q < n) masters[q] = grid[xyz[3 * q] + (long long)(N + 16) * (xyz[3 * q + 1] + (long long)N * xyz[3 * q + 2])];
+}
+__global__ void __launch_bounds__(256) k_grid_from_masters(int n, const int *xyz, int N, const double *masters, double *grid) {
+    const int q = (int)(blockIdx.x * 256 + threadIdx.x);
+    if (q < n) grid[xyz[3 * q] + (long long)(N + 16) * (xyz[3 * q + 1] + (long long)N * xyz[3 * q + 2])] = masters[q];
+}
+
+// every node of the subcubes that hold the listed tetrahedra
+template <bool FREEZE>
+__global__ void __launch_bounds__(256) k_grid_tets(int N, int m, GridTets t, double *grid, unsigned char *frz) {
+    const int w = m + 1, per = (w * w * w + 255) / 256;
+    const int q = (int)(blockIdx.x / per), e = (int)(blockIdx.x % per) * 256 + (int)threadIdx.x;
+    if (e >= w * w * w) return;
+    const int d[3] = {e % w, (e / w) % w, e / (w * w)};
+    int V[3] = {0, 0, 0}, a = 0, b = 0;
+#pragma unroll
+    for (int r = 0; r < 8; r++)
+        if (r == q) {
+            V[0] = t.info[r][0];
+            V[1] = t.info[r][1];
+            V[2] = t.info[r][2];
+            a = t.info[r][3];
+            b = t.info[r][4];
+        }
+    const int c = 3 - a - b;
+    const int da = a == 0 ? d[0] : a == 1 ? d[1] : d[2], db = b == 0 ? d[0] : b == 1 ? d[1] : d[2];
+    const int dc = c == 0 ? d[0] : c == 1 ? d[1] : d[2];
+    const int X = m * V[0] + d[0], Y = m * V[1] + d[1], Z = m * V[2] + d[2];
+    const long long i = X + (long long)(N + 16) * (Y + (long long)N * Z);
+    if (FREEZE) {
+        // closure; the boundary nodes x = N and y = N have no byte of their own
+        if (da >= db && db >= dc && X < N && Y < N) frz[i] = 1;
+    } else if (m > da && da > db && db > dc && dc > 0) {
+        grid[i] = 0.0;
+    }
+}
+__global__ void __launch_bounds__(256) k_grid_zero32(unsigned *p, long long n) {
+    for (long long q = blockIdx.x * 256LL + threadIdx.x; q < n; q += 256LL * gridDim.x) p[q] = 0u;
+}
+
+size_t sweep_lds(const GridTiles &t, int ns, int start, int tail, int word) {
+    const int threads = grid_threads(t);
+    const size_t rows = (size_t)(threads + t.tp - 1) / t.tp + 2;
+    if (tail == kGridResidual)
+        return std::max(2 * (rows * t.tp + 2) * 2 * sizeof(double), threads * sizeof(double));
+    const int K = 2 * ns, NL = K + (tail != kGridPlain) - (start == kGridFromZero);
+    size_t n = (size_t)NL * 2 * (rows * t.tp + 2);
+    if (tail == kGridRestrict) n += 3 * (rows * 2 * t.tp + 2);
+    size_t by = n * word;
+    if (tail == kGridNorm) by = std::max(by, (size_t)threads * sizeof(double));
+    return by;
+}
+
+int cdiv(int a, int b) { return (a + b - 1) / b; }
+
+}  // namespace
+
+GridTiles grid_tiles_of(int N, int ns, int tail, int vp, int vy, int vz) {
+    const int np = N / 2, hl = halo_lo(2 * ns, tail), hh = halo_hi(2 * ns, tail);
+    GridTiles t;
+    t.vp = std::min(vp, np);
+    t.vy = std::min((vy + 1) & ~1, N);
+    t.vz = std::min((vz + 1) & ~1, N);
+    t.ntx = cdiv(np, t.vp);
+    t.nty = cdiv(N, t.vy);
+    t.ntz = cdiv(N, t.vz);
+    // the halo ends at the boundary nodes x = 0 and x = N (pair np)
+    for (int i = 0; i < t.ntx; i++) {
+        const int a = std::max(0, i * t.vp - (hl + 1) / 2);
+        const int b = std::min(np + 1, std::min(np, (i + 1) * t.vp) + (hh + 1) / 2);
+        t.tp = std::max(t.tp, b - a);
+    }
+    for (int i = 0; i < t.nty; i++) {
+        const int a = std::max(0, i * t.vy - hl), b = std::min(N + 1, std::min(N, (i + 1) * t.vy) + hh);
+        t.ty = std::max(t.ty, b - a);
+    }
+    return t;
+}
+
+namespace {
+
+template <typename T, int NS, int START, int TAIL>
+void sweep_mask(hipStream_t s, const GridTiles &t, const GridSweep<T> &g) {
+    const size_t lds = sweep_lds(t, NS, START, TAIL, (int)sizeof(T));
+    const T h = (T)g.h, om = (T)(g.omega / (6.0 * g.h)), omr = (T)(1.0 - g.omega);
+    const dim3 grid((unsigned)t.blocks()), block((unsigned)grid_threads(t));
+    if (g.frz)
+        hipLaunchKernelGGL((k_grid_sweep<T, NS, START, TAIL, true>), grid, block, lds, s, g, t, h, om, omr);
+    else
+        hipLaunchKernelGGL((k_grid_sweep<T, NS, START, TAIL, false>), grid, block, lds, s, g, t, h, om, omr);
+}
+
+template <typename T>
+void sweep_any(hipStream_t s, int ns, int start, int tail, const GridTiles &t, const GridSweep<T> &g) {
+    const bool rt = tail == kGridRestrict;
+    if (start == kGridFromZero && ns == 2)
+        rt ? sweep_mask<T, 2, kGridFromZero, kGridRestrict>(s, t, g) : sweep_mask<T, 2, kGridFromZero, kGridPlain>(s, t, g);
+    else if (start == kGridFromZero)
+        rt ? sweep_mask<T, 1, kGridFromZero, kGridRestrict>(s, t, g) : sweep_mask<T, 1, kGridFromZero, kGridPlain>(s, t, g);
+    else if constexpr (sizeof(T) == 8) {
+        if (start == kGridProlong)
+            tail == kGridNorm ? sweep_mask<T, 1, kGridProlong, kGridNorm>(s, t, g) : sweep_mask<T, 1, kGridProlong, kGridPlain>(s, t, g);
+        else if (tail == kGridNorm)
+            sweep_mask<T, 1, kGridFromU, kGridNorm>(s, t, g);
+        else
+            rt ? sweep_mask<T, 1, kGridFromU, kGridRestrict>(s, t, g) : sweep_mask<T, 1, kGridFromU, kGridPlain>(s, t, g);
+    } else {
+        if (start == kGridProlong)
+            sweep_mask<T, 1, kGridProlong, kGridPlain>(s, t, g);
+        else
+            rt ? sweep_mask<T, 1, kGridFromU, kGridRestrict>(s, t, g) : sweep_mask<T, 1, kGridFromU, kGridPlain>(s, t, g);
+    }
+}
+
+void residual_any(hipStream_t s, const GridTiles &t, const GridResidual &g) {
+    const size_t lds = sweep_lds(t, 0, kGridFromU, kGridResidual, 8);
+    const dim3 grid((unsigned)t.blocks()), block((unsigned)grid_threads(t));
+    if (g.e && g.frz)
+        hipLaunchKernelGGL((k_grid_residual<true, true>), grid, block, lds, s, g, t);
+    else if (g.e)
+        hipLaunchKernelGGL((k_grid_residual<true, false>), grid, block, lds, s, g, t);
+    else if (g.frz)
+        hipLaunchKernelGGL((k_grid_residual<false, true>), grid, block, lds, s, g, t);
+    else
+        hipLaunchKernelGGL((k_grid_residual<false, false>), grid, block, lds, s, g, t);
+}
+
+dim3 node_blocks(int N) { return dim3((unsigned)cdiv(N - 1, 64), (unsigned)cdiv(N - 1, 4), (unsigned)(N - 1)); }
+
+template <typename T>
+void plain_residual(hipStream_t s, int N, double h, const T *u, const T *b, T *r) {
+    hipLaunchKernelGGL((k_grid_plain_residual<T>), node_blocks(N), dim3(256), 0, s, N, (T)h, u, b, r);
+}
+template <typename T>
+void plain_restrict(hipStream_t s, int N, const T *r, T *bc) {
+    hipLaunchKernelGGL((k_grid_plain_restrict<T>), node_blocks(N / 2), dim3(256), 0, s, N, r, bc);
+}
+template <typename T>
+void plain_prolong(hipStream_t s, int N, const T *u, const T *ec, T *v) {
+    hipLaunchKernelGGL((k_grid_plain_prolong<T>), node_blocks(N), dim3(256), 0, s, N, u, ec, v);
+}
+template <typename T>
+void coarse(hipStream_t s, int N, const double *st, const T *b, T *u) {
+    const size_t lds = (2 * kSineMax * kSineMax * kSineMax + kSineMax * (kSineMax + 1)) * sizeof(double);
+    hipLaunchKernelGGL((k_grid_coarse<T>), dim3(1), dim3(512), lds, s, N, st, b, u);
+}
+int row_blocks(int N) { return (int)(((long long)(N - 1) * (N - 1) + 3) / 4); }
+int from_user(hipStream_t s, int N, const double *user, double *grid, double *partial) {
+    hipLaunchKernelGGL(k_grid_from_user, dim3((unsigned)row_blocks(N)), dim3(256), 256 * sizeof(double), s, N, user, grid,
+                       partial);
+    return row_blocks(N);
+}
+void to_user(hipStream_t s, int N, const double *grid, double *user) {
+    hipLaunchKernelGGL(k_grid_to_user, dim3((unsigned)row_blocks(N)), dim3(256), 0, s, N, grid, user);
+}
+template <bool IG, bool OG>
+int mass(hipStream_t s, int N, double h, const double *in, double *out, double *partial) {
+    const int nb = cdiv(N - 1, kMassX - 2) * cdiv(N - 1, kMassY - 2) * cdiv(N - 1, kMassZ);
+    const size_t lds = 2 * ((kMassY + 2) * kMassX + 2) * sizeof(double);
+    hipLaunchKernelGGL((k_grid_mass<IG, OG>), dim3((unsigned)nb), dim3(kMassX * kMassY), lds, s, N, h * h * h, in, out,
+                       partial);
+    return nb;
+}
+int mass_load(hipStream_t s, int N, double h, const double *f, double *grid, double *partial) {
+    return mass<false, true>(s, N, h, f, grid, partial);
+}
+void mass_user(hipStream_t s, int N, double h, const double *grid, double *user) {
+    mass<true, false>(s, N, h, grid, user, nullptr);
+}
+unsigned closure_blocks(const GridClosures &c) { return (unsigned)(((c.nlist + 255) / 256) * c.nvol); }
+void to_closures(hipStream_t s, const GridClosures &c, bool zero_interior, const double *grid, double *vec) {
+    if (closure_blocks(c))
+        hipLaunchKernelGGL(k_grid_to_closures, dim3(closure_blocks(c)), dim3(256), 0, s, c, zero_interior, grid, vec);
+}
+void from_closures(hipStream_t s, const GridClosures &c, const double *vec, double *grid) {
+    if (closure_blocks(c)) hipLaunchKernelGGL(k_grid_from_closures, dim3(closure_blocks(c)), dim3(256), 0, s, c, vec, grid);
+}
+void to_masters(hipStream_t s, int n, const int *xyz, int N, const double *grid, double *masters) {
+    if (n > 0) hipLaunchKernelGGL(k_grid_to_masters, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, s, n, xyz, N, grid, masters);
+}
+void from_masters(hipStream_t s, int n, const int *xyz, int N, const double *masters, double *grid) {
+    if (n > 0)
+        hipLaunchKernelGGL(k_grid_from_masters, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, s, n, xyz, N, masters, grid);
+}
+void zero_tets(hipStream_t s, int N, int m, const GridTets &t, double *grid) {
+    const unsigned per = (unsigned)(((long long)(m + 1) * (m + 1) * (m + 1) + 255) / 256);
+    if (t.n > 0) hipLaunchKernelGGL((k_grid_tets<false>), dim3(per * t.n), dim3(256), 0, s, N, m, t, grid, (unsigned char *)nullptr);
+}
+void freeze_tets(hipStream_t s, int N, int m, const GridTets &t, unsigned char *frz) {
+    const unsigned per = (unsigned)(((long long)(m + 1) * (m + 1) * (m + 1) + 255) / 256);
+    hipLaunchKernelGGL(k_grid_zero32, dim3(1024), dim3(256), 0, s, (unsigned *)frz, (grid_len(N) + 3) / 4);
+    if (t.n > 0) hipLaunchKernelGGL((k_grid_tets<true>), dim3(per * t.n), dim3(256), 0, s, N, m, t, (double *)nullptr, frz);
+}
+
+// Tile choice.  Measured times (N = 64 .. 512) follow two bounds:
+//   memory: what the tiles read (halo included) at 6.2 TB/s and the own nodes
+//     written at 4 TB/s, once about 768 threads per CU are resident (N = 256,
+//     one plain sweep: 105 us, 98 by this; N = 512: 730 us);
+//   latency: each step of the march costs about 0.4 us (barrier, LDS reads,
+//     a chain of passes), so small grids take thin tiles on many CUs.
+GridTiles tiles(int N, int ns, int start, int tail, int word) {
+    const int K = tail == kGridResidual ? 0 : 2 * ns, np = N / 2;
+    const int hz = halo_lo(K, tail) + K + 2;
+    const double nodes = (double)N * N * N;
+    const double wr = nodes * word / 4.0e6;
+    // registers: 128 at two sweeps or with a tail, fewer otherwise
+    const int cap = ns >= 2 || tail == kGridRestrict || tail == kGridNorm ? 1024 : 1536;
+    GridTiles best;
+    double bc = 1e300;
+    for (int ntx = 1, vp0 = 0; ntx <= np; ntx++) {
+        const int vp = cdiv(np, ntx);
+        if (vp == vp0) continue;
+        vp0 = vp;
+        if (vp < 4 && ntx > 1) break;
+        for (int nty = 1, vy0 = 0; nty <= N / 2; nty++) {
+            const int vy = (cdiv(N, nty) + 1) & ~1;
+            if (vy == vy0) continue;
+            vy0 = vy;
+            GridTiles t = grid_tiles_of(N, ns, tail, vp, cdiv(N, nty), N);
+            const int th = grid_threads(t);
+            if (th > 1024) continue;
+            const size_t lds = sweep_lds(t, ns, start, tail, word);
+            if (lds > (size_t)160 * 1024) continue;
+            const int bpc = std::max(1, std::min({cap / th, (int)((size_t)160 * 1024 / lds), 8}));
+            for (int ntz = 1, vz0 = 0; ntz <= N / 2; ntz++) {
+                const int vz = (cdiv(N, ntz) + 1) & ~1;
+                if (vz == vz0) continue;
+                vz0 = vz;
+                t.vz = vz;
+                t.ntz = cdiv(N, vz);
+                const int blocks = t.blocks(), rounds = cdiv(blocks, 256 * bpc), res = std::min(bpc, cdiv(blocks, 256));
+                const double steps = vz + hz;
+                const double lat = rounds * steps * (0.32 + 0.0003 * th * res);
+                // threads resident on average
+                const double active = (double)blocks * th / (256.0 * rounds);
+                const double rd = (double)blocks * (vz + halo_lo(K, tail) + halo_hi(K, tail)) * t.tp * t.ty * 4 * word / 6.2e6;
+                const double bw = (wr + rd) * std::max(1.0, 768.0 / active);
+                const double cost = std::max(lat, bw) + 0.15 * std::min(lat, bw);
+                if (cost < bc) {
+                    bc = cost;
+                    best = t;
+                }
+            }
+        }
+    }
+    return best;
+}
+
+const GridOps kOps = {tiles,
+                      sweep_any<double>,
+                      sweep_any<float>,
+                      residual_any,
+                      plain_residual<double>,
+                      plain_residual<float>,
+                      plain_restrict<double>,
+                      plain_restrict<float>,
+                      plain_prolong<double>,
+                      plain_prolong<float>,
+                      coarse<double>,
+                      coarse<float>,
+                      from_user,
+                      to_user,
+                      mass_load,
+                      mass_user,
+                      to_closures,
+                      from_closures,
+                      to_masters,
+                      from_masters,
+                      zero_tets,
+                      freeze_tets};
+
+}  // namespace
+
+int grid_threads(const GridTiles &t) { return (t.tp * t.ty + 63) & ~63; }
+
+const GridOps *grid_ops() { return &kOps; }
+
+// b = M f, both in vector order
+void launch_mass_grid(hipStream_t s, int N, double h, const double *f, double *b) {
+    mass<false, false>(s, N, h, f, b, nullptr);
+}
+
+}  // namespace hhgr

@@ -1,0 +1,141 @@
+// Structured-grid path of the cube with k = 1: descriptors and launchers.
+//
+// The Kuhn tetrahedra tile the N^3 grid and the k = 1 operator couples a node
+// to its 6 axis neighbours with one stencil everywhere, so the unmasked and
+// the Dirichlet-Dirichlet cycles of such a context keep u and b of every
+// level as one grid, x fastest: node (x, y, z) at x + P (y + N z), 0 <= x,
+// y < N, 0 <= z <= N, with the Dirichlet nodes stored as zeros.  The row
+// pitch P exceeds N, and row y = N of a plane is row y = 0 of the next one,
+// so every neighbour of an interior node is a plain offset and a row's node
+// pairs (2p, 2p + 1) are aligned.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+namespace hhgr {
+
+struct VolDesc;
+
+// row pitch: 128 bytes (FP64) beyond the power of two that N often is, so
+// that a column of rows does not fall on one memory channel
+inline int grid_pitch(int N) { return N + 16; }
+inline long long grid_plane(int N) { return (long long)grid_pitch(N) * N; }
+// one plane of zeros above, and two rows beyond it
+inline long long grid_len(int N) { return grid_plane(N) * (N + 1) + 2 * grid_pitch(N); }
+
+constexpr int kGridFromU = 0, kGridFromZero = 1, kGridProlong = 2;
+constexpr int kGridPlain = 0, kGridRestrict = 1, kGridNorm = 2, kGridResidual = 3;
+
+// Tiles of one marching launch: a workgroup owns vp pairs x vy rows x vz
+// planes and loads tp pairs x ty rows (its own and the halo that the launch's
+// passes need).
+struct GridTiles {
+    int vp = 0, vy = 0, vz = 0;
+    int tp = 0, ty = 0;
+    int ntx = 0, nty = 0, ntz = 0;
+    int blocks() const { return ntx * nty * ntz; }
+};
+
+// ns red-black SOR sweeps of one level in one launch, u -> v (different
+// buffers): from u, from zero (u is not read) or from u + P ec (linear
+// interpolation of the coarse grid ec).  tail kGridRestrict also writes
+// bc = P^T (b - A v) at the interior coarse nodes, kGridNorm leaves
+// per-workgroup sums of (b - A v)^2 in partial.  frz (optional): one byte per
+// node of the grid; nonzero nodes keep their values and do not count.
+// Built: ns = 1 from u (any tail), from zero (plain, restrict) and
+// interpolating (plain, norm); ns = 2 from zero (plain, restrict); norms in
+// FP64 only.
+template <typename T>
+struct GridSweep {
+    int N = 0;
+    double h = 0, omega = 1;
+    const T *u = nullptr;
+    T *v = nullptr;
+    const T *b = nullptr;
+    const T *ec = nullptr;
+    T *bc = nullptr;
+    const unsigned char *frz = nullptr;
+    double *partial = nullptr;
+};
+
+// r = b - A (u + e): e (optional) is added first and u + e written to v; r
+// (optional) in its own type; per-workgroup sums of r^2 to partial (optional)
+struct GridResidual {
+    int N = 0;
+    double h = 0;
+    const double *u = nullptr, *b = nullptr;
+    const float *e = nullptr;
+    double *v = nullptr;
+    double *r64 = nullptr;
+    float *r32 = nullptr;
+    const unsigned char *frz = nullptr;
+    double *partial = nullptr;
+};
+
+// node list of volume containers in slot space (see VolGeom) and where their
+// nodes lie on the grid (tetinfo: subcube corner and axis order per tet)
+struct GridClosures {
+    const VolDesc *vd = nullptr;
+    int nvol = 0;
+    const unsigned *list = nullptr;
+    int nlist = 0;
+    const int2 *rowC = nullptr;
+    const int *tetinfo = nullptr;
+    int M = 0, N = 0;
+};
+
+// faulty tetrahedra (subcube corner, axis order), passed by value
+struct GridTets {
+    int n = 0;
+    int info[8][6];
+};
+
+// tiles of vp x vy x vz own pairs, rows and planes (rows and planes rounded up
+// to even numbers) for ns sweeps, or for a residual with tail kGridResidual;
+// the tiles chosen for a launch of that kind; and their workgroup size, at
+// most 1024
+GridTiles grid_tiles_of(int N, int ns, int tail, int vp, int vy, int vz);
+int grid_threads(const GridTiles &t);
+
+// The launchers.  The engine reaches them through this table, so that its
+// host logic also links without device code (it then keeps the cube's
+// vectors in slot space throughout).
+struct GridOps {
+    GridTiles (*tiles)(int N, int ns, int start, int tail, int word);
+    void (*sweep64)(hipStream_t, int ns, int start, int tail, const GridTiles &, const GridSweep<double> &);
+    void (*sweep32)(hipStream_t, int ns, int start, int tail, const GridTiles &, const GridSweep<float> &);
+    void (*residual)(hipStream_t, const GridTiles &, const GridResidual &);
+    // r = b - A u, bc = P^T r and v = u + P ec in plain form (sweep counts of zero)
+    void (*plain_residual64)(hipStream_t, int N, double h, const double *u, const double *b, double *r);
+    void (*plain_residual32)(hipStream_t, int N, double h, const float *u, const float *b, float *r);
+    void (*plain_restrict64)(hipStream_t, int N, const double *r, double *bc);
+    void (*plain_restrict32)(hipStream_t, int N, const float *r, float *bc);
+    void (*plain_prolong64)(hipStream_t, int N, const double *u, const double *ec, double *v);
+    void (*plain_prolong32)(hipStream_t, int N, const float *u, const float *ec, float *v);
+    // coarsest level (N <= 12) by sine transforms: u = A^{-1} b; st holds the
+    // [(N-1)^2] orthonormal sine transform matrix and the [N-1] values
+    // 2 - 2 cos(pi q / N)
+    void (*coarse64)(hipStream_t, int N, const double *st, const double *b, double *u);
+    void (*coarse32)(hipStream_t, int N, const double *st, const float *b, float *u);
+    // vector order ((N-1)^3 interior nodes) <-> grid; per-workgroup sums of
+    // squares to partial (optional); returns the number of workgroups
+    int (*from_user)(hipStream_t, int N, const double *user, double *grid, double *partial);
+    void (*to_user)(hipStream_t, int N, const double *grid, double *user);
+    // grid = M f with f in vector order, sums of squares as above; and
+    // y = M x from the grid to vector order
+    int (*mass_load)(hipStream_t, int N, double h, const double *f, double *grid, double *partial);
+    void (*mass_user)(hipStream_t, int N, double h, const double *grid, double *user);
+    // grid -> closures (list: every node; interior nodes get zero if
+    // zero_interior), closures -> grid (list: interior nodes)
+    void (*to_closures)(hipStream_t, const GridClosures &, bool zero_interior, const double *grid, double *vec);
+    void (*from_closures)(hipStream_t, const GridClosures &, const double *vec, double *grid);
+    void (*to_masters)(hipStream_t, int n, const int *xyz, int N, const double *grid, double *masters);
+    void (*from_masters)(hipStream_t, int n, const int *xyz, int N, const double *masters, double *grid);
+    // grid = 0 strictly inside the tetrahedra; frz = 1 on their closures, else 0
+    void (*zero_tets)(hipStream_t, int N, int m, const GridTets &, double *grid);
+    void (*freeze_tets)(hipStream_t, int N, int m, const GridTets &, unsigned char *frz);
+};
+const GridOps *grid_ops() __attribute__((weak));
+
+
+}  // namespace hhgr

@@ -1064,73 +1064,6 @@ __global__ void __launch_bounds__(512) k_mesh_slots_to_user(VolGeom vg, long lon
     user[dof] = (double)(vec + d.vec)[lslot(vg.rowC, vg.M, n.i, n.j, n.k)];
 }
 
-// consistent P1 mass matrix on the Kuhn meshes: diagonal 24 h^3/60, axis
-// edges h^3/20 (6 tetrahedra), face diagonals h^3/30 (4), body diagonal h^3/20 (6)
-template <int CPB>
-__global__ void __launch_bounds__(512) k_mass(VolGeom vg, IfcGeom ig, int nib, const int *__restrict__ nb15,
-                                              const double *__restrict__ x, double *__restrict__ y, double h3) {
-    const double wc = 0.4 * h3, wax = h3 / 20.0, wfd = h3 / 30.0, wbd = h3 / 20.0;
-    const unsigned f = blockIdx.x;
-    if (f < (unsigned)nib) {
-        const int t = ig.i0 + (int)(f * blockDim.x + threadIdx.x);
-        if (t >= ig.i1) return;
-        const long long st = ig.stride;
-        double ax = 0.0, fd = 0.0, bd = 0.0;
-        for (int e = 1; e < 7; e++) ax += x[nb15[e * st + t]];
-        for (int e = 7; e < 13; e++) fd += x[nb15[e * st + t]];
-        for (int e = 13; e < 15; e++) bd += x[nb15[e * st + t]];
-        y[ig.base + t] = wc * x[nb15[t]] + wax * ax + wfd * fd + wbd * bd;
-        return;
-    }
-    const unsigned per_vol = list_blocks_per_vol<CPB>(vg);
-    const unsigned blk = block_order(f - nib, gridDim.x - nib, vg.remap);
-    const int M = vg.M;
-#pragma unroll
-    for (int q = 0; q < CPB; q++) {
-        LNode n;
-        if (!list_node<CPB>(vg, blk, per_vol, q, n)) continue;
-        const VolDesc d = vg.vd[n.v];
-        const double *xv = x + d.vec;
-        const int i = n.i, j = n.j, k = n.k;
-        auto X = [&](int di, int dj, int dk) { return xv[lslot(vg.rowC, M, i + di, j + dj, k + dk)]; };
-        // axis (a, b, c), face diagonals (a+b, b+c, a+c), body diagonal (a+b+c)
-        const double ax =
-            ((X(1, 0, 0) + X(-1, 0, 0)) + (X(-1, 1, 0) + X(1, -1, 0))) + (X(0, -1, 1) + X(0, 1, -1));
-        const double fd =
-            ((X(0, 1, 0) + X(0, -1, 0)) + (X(-1, 0, 1) + X(1, 0, -1))) + (X(1, -1, 1) + X(-1, 1, -1));
-        const double bd = X(0, 0, 1) + X(0, 0, -1);
-        (y + d.vec)[lslot(vg.rowC, M, i, j, k)] = wc * X(0, 0, 0) + wax * ax + wfd * fd + wbd * bd;
-    }
-}
-
-// b = M f on the unit cube's Kuhn mesh in vector order (interior node
-// (x, y, z) at (x-1) + (N-1)((y-1) + (N-1)(z-1)); f = 0 on the boundary).
-// The consistent P1 mass matrix does not depend on k: 0.4 h^3 on the
-// diagonal, h^3/20 to the 6 axis neighbours (6 elements share such an edge),
-// h^3/30 to the face diagonals (1,1,0), (0,1,1), (1,0,1) (4 elements) and
-// h^3/20 to the body diagonal (1,1,1) (6 elements), each in both signs.
-__global__ void __launch_bounds__(256) k_mass_grid(int N, double h3, const double *__restrict__ f,
-                                                   double *__restrict__ b) {
-    const int n = N - 1;
-    const long long sz = (long long)n * n;
-    const long long q = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (q >= sz * n) return;
-    const int x = (int)(q % n), y = (int)((q / n) % n), z = (int)(q / sz);
-    // a neighbour outside the interior reads the node itself (a valid
-    // address) and contributes zero
-    auto F = [&](int dx, int dy, int dz) -> double {
-        const bool in = (unsigned)(x + dx) < (unsigned)n && (unsigned)(y + dy) < (unsigned)n &&
-                        (unsigned)(z + dz) < (unsigned)n;
-        const double v = f[in ? q + dx + (long long)dy * n + (long long)dz * sz : q];
-        return in ? v : 0.0;
-    };
-    const double wc = 0.4 * h3, wax = h3 / 20.0, wfd = h3 / 30.0, wbd = h3 / 20.0;
-    const double ax = ((F(1, 0, 0) + F(-1, 0, 0)) + (F(0, 1, 0) + F(0, -1, 0))) + (F(0, 0, 1) + F(0, 0, -1));
-    const double fd = ((F(1, 1, 0) + F(-1, -1, 0)) + (F(0, 1, 1) + F(0, -1, -1))) + (F(1, 0, 1) + F(-1, 0, -1));
-    const double bd = F(1, 1, 1) + F(-1, -1, -1);
-    b[q] = wc * F(0, 0, 0) + wax * ax + wfd * fd + wbd * bd;
-}
-
 // per-block partial sums of v^2 over the volume nodes of vg's list and the
 // interface masters of ig (every interior node once); CPB volume nodes per
 // thread, whose load chains (list entry, row table, value) are independent
@@ -1981,23 +1914,6 @@ template void launch_mesh_user_to_slots<double>(hipStream_t, const VolGeom &, lo
                                                 const int *, const double *, double *);
 template void launch_mesh_slots_to_user<double>(hipStream_t, const VolGeom &, long long, long long, const IfcGeom &,
                                                 const int *, const double *, double *);
-
-void launch_mass(hipStream_t s, const VolGeom &vint, const IfcGeom &ig, const int *nb15, const double *x, double *y,
-                 double h) {
-    const int nib = ifc_blocks(ig, vint.bs);
-    const long long grid = nib + list_blocks(vint);
-    if (grid == 0) return;
-    if (vint.cpb == 1)
-        hipLaunchKernelGGL(k_mass<1>, dim3((unsigned)grid), dim3(vint.bs), 0, s, vint, ig, nib, nb15, x, y, h * h * h);
-    else
-        hipLaunchKernelGGL(k_mass<4>, dim3((unsigned)grid), dim3(vint.bs), 0, s, vint, ig, nib, nb15, x, y, h * h * h);
-}
-
-void launch_mass_grid(hipStream_t s, int N, double h, const double *f, double *b) {
-    const long long n = (long long)(N - 1) * (N - 1) * (N - 1);
-    if (n <= 0) return;
-    hipLaunchKernelGGL(k_mass_grid, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, N, h * h * h, f, b);
-}
 
 int launch_norm2(hipStream_t s, const VolGeom &vg, const IfcGeom &ig, const double *v, double *partial) {
     VolGeom g = vg;

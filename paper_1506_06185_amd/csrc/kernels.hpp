@@ -200,7 +200,7 @@ void launch_coarse_dense(hipStream_t s, int n, const long long *slot, const doub
                          const int *cptr, const int *cidx);
 
 // b = M f with the unit cube's k-independent P1 mass matrix, both in vector
-// order ((N-1)^3 interior nodes, x fastest)
+// order ((N-1)^3 interior nodes, x fastest; grid.hip)
 void launch_mass_grid(hipStream_t s, int N, double h, const double *f, double *b);
 
 // per-block partial sums of v^2 over every interior node once (the volume
@@ -263,10 +263,6 @@ void launch_user_to_slots(hipStream_t s, const VolGeom &vfull, const int *tetinf
 template <typename T>
 void launch_slots_to_user(hipStream_t s, const VolGeom &vint, const int *tetinfo, int m, int N, const IfcGeom &ig,
                           const int *ifc_dof, const T *vec, double *user);
-
-// y = M x (consistent P1 mass matrix) at volume-interior and interface slots
-void launch_mass(hipStream_t s, const VolGeom &vint, const IfcGeom &ig, const int *nb15, const double *x, double *y,
-                 double h);
 
 // u64 += e32 over the closure slots [0, span) of the listed volumes and the
 // interface slots

@@ -1,0 +1,248 @@
+// CPU check of the structured-grid marching kernels (grid.hip) compiled for
+// the host against the device-code emulation in mockgrid/: for several grid
+// sizes and tile shapes, every built start and tail, FP64 and FP32, with and
+// without frozen nodes, one sweep launch against plain sweeps,
+// interpolation, residual and restriction written here node by node; the
+// residual, mass and coarsest-level kernels likewise.  Buffers are exact-size
+// vectors under AddressSanitizer, and LDS starts as NaN.
+#include <cmath>
+#include <cstdio>
+#include <random>
+#include <vector>
+
+#include "../../paper_1506_06185_amd/csrc/grid.hpp"
+
+namespace hhgr {
+alignas(16) unsigned char grid_lds[kMockLds];
+}
+using namespace hhgr;
+
+static int fails = 0, cases = 0;
+
+struct Ref {
+    int N, P;
+    long long S;
+    explicit Ref(int n) : N(n), P(grid_pitch(n)), S(grid_plane(n)) {}
+    long long at(int x, int y, int z) const { return x + (long long)P * y + S * z; }
+};
+
+template <typename T>
+static std::vector<T> random_grid(int N, std::mt19937 &g) {
+    Ref r(N);
+    std::uniform_real_distribution<double> d(-1.0, 1.0);
+    std::vector<T> v(grid_len(N), T(0));
+    for (int z = 1; z < N; z++)
+        for (int y = 1; y < N; y++)
+            for (int x = 1; x < N; x++) v[r.at(x, y, z)] = (T)d(g);
+    return v;
+}
+
+template <typename T>
+static void run_case(int N, int ns, int start, int tail, bool mask, int vp, int vy, int vz, unsigned seed) {
+    std::mt19937 g(seed);
+    const Ref r(N), rc(N / 2);
+    const std::vector<T> u = random_grid<T>(N, g), b = random_grid<T>(N, g);
+    std::vector<T> e = random_grid<T>(N / 2, g);
+    std::vector<unsigned char> fz(grid_len(N), 0);
+    if (mask)
+        for (int z = 1; z < N; z++)
+            for (int y = 1; y < N; y++)
+                for (int x = 1; x < N; x++) fz[r.at(x, y, z)] = x >= y && y >= z && x <= N / 2;
+    if (mask && start == kGridProlong)
+        for (int z = 0; z <= N / 2; z++)
+            for (int y = 0; y < N / 2; y++)
+                for (int x = 0; x < N / 2; x++)
+                    if (x >= y && y >= z && x <= N / 4) e[rc.at(x, y, z)] = T(0);
+    const double h = 1.0 / N, omega = 1.25;
+    // reference
+    std::vector<double> w(u.begin(), u.end());
+    auto frozen = [&](long long i) { return mask && fz[i]; };
+    if (start == kGridFromZero)
+        for (auto &x : w) x = 0.0;
+    if (mask && start == kGridFromZero)
+        for (auto &x : w) x = 0.0;
+    if (start == kGridProlong)
+        for (int z = 1; z < N; z++)
+            for (int y = 1; y < N; y++)
+                for (int x = 1; x < N; x++)
+                    w[r.at(x, y, z)] += 0.5 * ((double)e[rc.at(x / 2, y / 2, z / 2)] +
+                                               (double)e[rc.at((x + 1) / 2, (y + 1) / 2, (z + 1) / 2)]);
+    auto rr = [&](long long i) {
+        return (double)b[i] - h * (6.0 * w[i] - (w[i - 1] + w[i + 1] + w[i - r.P] + w[i + r.P] + w[i - r.S] + w[i + r.S]));
+    };
+    for (int q = 0; q < 2 * ns; q++)
+        for (int z = 1; z < N; z++)
+            for (int y = 1; y < N; y++)
+                for (int x = 1; x < N; x++)
+                    if (((x + y + z) & 1) == (q & 1) && !frozen(r.at(x, y, z))) w[r.at(x, y, z)] += omega / (6.0 * h) * rr(r.at(x, y, z));
+    std::vector<double> res(w.size(), 0.0);
+    double norm = 0.0;
+    for (int z = 1; z < N; z++)
+        for (int y = 1; y < N; y++)
+            for (int x = 1; x < N; x++)
+                if (!frozen(r.at(x, y, z))) {
+                    const double v = rr(r.at(x, y, z));
+                    res[r.at(x, y, z)] = v;
+                    norm += v * v;
+                }
+    // launch
+    GridTiles t = grid_tiles_of(N, ns, tail, vp, vy, vz);
+    std::vector<T> v(grid_len(N), T(0)), bc(grid_len(N / 2), T(0));
+    std::vector<double> part(t.blocks(), -1.0);
+    GridSweep<T> gs;
+    gs.N = N;
+    gs.h = h;
+    gs.omega = omega;
+    gs.u = u.data();
+    gs.v = v.data();
+    gs.b = b.data();
+    gs.ec = e.data();
+    gs.bc = bc.data();
+    gs.frz = mask ? fz.data() : nullptr;
+    gs.partial = part.data();
+    if constexpr (sizeof(T) == 8)
+        grid_ops()->sweep64(nullptr, ns, start, tail, t, gs);
+    else
+        grid_ops()->sweep32(nullptr, ns, start, tail, t, gs);
+    const double tol = sizeof(T) == 8 ? 1e-13 : 3e-5;
+    double err = 0.0;
+    for (size_t i = 0; i < w.size(); i++) err = std::max(err, std::fabs(w[i] - (double)v[i]) / (std::isfinite((double)v[i]) ? 1.0 : 0.0));
+    bool ok = err < tol * 4.0;
+    double erc = 0.0, ern = 0.0;
+    if (tail == kGridRestrict) {
+        static const int d[7][3] = {{1, 0, 0}, {0, 1, 0}, {0, 0, 1}, {1, 1, 0}, {0, 1, 1}, {1, 0, 1}, {1, 1, 1}};
+        for (int z = 0; z <= N / 2; z++)
+            for (int y = 0; y < N / 2; y++)
+                for (int x = 0; x < N / 2; x++) {
+                    double s = 0.0;
+                    const bool in = x > 0 && y > 0 && z > 0 && z < N / 2;
+                    const long long i = r.at(2 * x, 2 * y, 2 * z);
+                    if (in && frozen(i)) continue;  // a frozen coarse node is never read
+                    if (in) {
+                        s = res[i];
+                        for (auto &o : d) {
+                            const long long q = o[0] + (long long)r.P * o[1] + r.S * o[2];
+                            s += 0.5 * (res[i + q] + res[i - q]);
+                        }
+                    }
+                    erc = std::max(erc, std::fabs(s - (double)bc[rc.at(x, y, z)]));
+                }
+        ok = ok && erc < tol * 20.0;
+    }
+    if (tail == kGridNorm) {
+        double s = 0.0;
+        for (double x : part) s += x;
+        ern = std::fabs(s - norm) / norm;
+        ok = ok && ern < tol * 10.0;
+    }
+    cases++;
+    if (!ok) {
+        std::printf("FAIL N=%d ns=%d start=%d tail=%d mask=%d tile %d %d %d word %zu: u %.2e bc %.2e norm %.2e\n", N, ns, start,
+                    tail, mask, vp, vy, vz, sizeof(T), err, erc, ern);
+        fails++;
+    }
+}
+
+static void check(bool ok, const char *what, int N, double err) {
+    cases++;
+    if (!ok) {
+        std::printf("FAIL %s N=%d: %.2e\n", what, N, err);
+        fails++;
+    }
+}
+
+static void run_residual(int N, bool add, bool mask, int vp, int vy, int vz, unsigned seed) {
+    std::mt19937 g(seed);
+    const Ref r(N);
+    const std::vector<double> u = random_grid<double>(N, g), b = random_grid<double>(N, g);
+    const std::vector<float> e = random_grid<float>(N, g);
+    std::vector<unsigned char> fz(grid_len(N), 0);
+    if (mask)
+        for (int z = 1; z < N; z++)
+            for (int y = 1; y < N; y++)
+                for (int x = 1; x < N; x++) fz[r.at(x, y, z)] = x >= y && y >= z;
+    GridResidual q;
+    const GridTiles t = grid_tiles_of(N, 0, kGridResidual, vp, vy, vz);
+    std::vector<double> v(grid_len(N), 0.0), r64(grid_len(N), 0.0), part(t.blocks(), -1.0);
+    std::vector<float> r32(grid_len(N), 0.0f);
+    q.N = N;
+    q.h = 1.0 / N;
+    q.u = u.data();
+    q.b = b.data();
+    q.e = add ? e.data() : nullptr;
+    q.v = v.data();
+    q.r64 = r64.data();
+    q.r32 = r32.data();
+    q.frz = mask ? fz.data() : nullptr;
+    q.partial = part.data();
+    grid_ops()->residual(nullptr, t, q);
+    std::vector<double> w(u);
+    if (add)
+        for (size_t i = 0; i < w.size(); i++) w[i] += (double)e[i];
+    double err = 0.0, norm = 0.0, sum = 0.0;
+    for (int z = 0; z < N; z++)
+        for (int y = 0; y < N; y++)
+            for (int x = 0; x < N; x++) {
+                const long long i = r.at(x, y, z);
+                double s = 0.0;
+                if (x && y && z && !fz[i])
+                    s = b[i] - (6.0 * w[i] - (w[i - 1] + w[i + 1] + w[i - r.P] + w[i + r.P] + w[i - r.S] + w[i + r.S])) / N;
+                norm += s * s;
+                err = std::max({err, std::fabs(s - r64[i]), std::fabs((float)s - r32[i]) * 1e-7, add ? std::fabs(w[i] - v[i]) : 0.0});
+            }
+    for (double x : part) sum += x;
+    check(err < 1e-13 && std::fabs(sum - norm) < 1e-12 * norm, "residual", N, err);
+}
+
+static void run_mass(int N, unsigned seed) {
+    std::mt19937 g(seed);
+    const Ref r(N);
+    const std::vector<double> f = random_grid<double>(N, g);
+    const int n = N - 1;
+    std::vector<double> user((size_t)n * n * n), out(user.size()), back(grid_len(N), 0.0), part(1 << 16, 0.0);
+    grid_ops()->to_user(nullptr, N, f.data(), user.data());
+    const int nb = grid_ops()->mass_load(nullptr, N, 1.0 / N, user.data(), back.data(), part.data());
+    grid_ops()->mass_user(nullptr, N, 1.0 / N, f.data(), out.data());
+    double err = 0.0, norm = 0.0, sum = 0.0, big = 0.0;
+    for (int q = 0; q < nb; q++) sum += part[q];
+    const double h3 = 1.0 / ((double)N * N * N);
+    for (int z = 1; z < N; z++)
+        for (int y = 1; y < N; y++)
+            for (int x = 1; x < N; x++) {
+                const long long i = r.at(x, y, z);
+                auto two = [&](long long d) { return f[i + d] + f[i - d]; };
+                const double s = h3 * (0.4 * f[i] + (two(1) + two(r.P) + two(r.S) + two(1 + r.P + r.S)) / 20.0 +
+                                       (two(1 + r.P) + two(r.P + r.S) + two(1 + r.S)) / 30.0);
+                const long long k = (x - 1) + (long long)n * ((y - 1) + (long long)n * (z - 1));
+                norm += s * s;
+                big = std::max(big, std::fabs(s));
+                err = std::max({err, std::fabs(s - back[i]), std::fabs(s - out[k]), std::fabs(user[k] - f[i])});
+            }
+    check(err < 1e-14 * big && std::fabs(sum - norm) < 1e-12 * norm, "mass", N, err);
+}
+
+int main() {
+    const int shapes[][4] = {{16, 8, 16, 16}, {16, 3, 6, 4}, {24, 5, 8, 10}, {8, 4, 8, 8}, {8, 2, 2, 2}};
+    const int kinds[][3] = {{1, 0, 0}, {1, 0, 1}, {1, 0, 2}, {1, 1, 0}, {1, 1, 1}, {1, 2, 0}, {1, 2, 2}, {2, 1, 0}, {2, 1, 1}};
+    unsigned seed = 1;
+    for (auto &sh : shapes) {
+        for (auto &k : kinds) {
+            run_case<double>(sh[0], k[0], k[1], k[2], false, sh[1], sh[2], sh[3], seed++);
+            run_case<double>(sh[0], k[0], k[1], k[2], true, sh[1], sh[2], sh[3], seed++);
+            if (k[2] != kGridNorm) run_case<float>(sh[0], k[0], k[1], k[2], (seed & 1) != 0, sh[1], sh[2], sh[3], seed++);
+        }
+        for (int q = 0; q < 4; q++) run_residual(sh[0], q & 1, q >> 1, sh[1], sh[2], sh[3], seed++);
+    }
+    run_mass(8, seed++);
+    run_mass(24, seed++);
+    // every chosen tiling fits a workgroup, from the smallest grid to the largest of one GPU
+    for (int N : {8, 12, 16, 24, 48, 64, 96, 128, 192, 256, 384, 512, 768})
+        for (auto &k : kinds) {
+            const GridTiles t = grid_ops()->tiles(N, k[0], k[1], k[2], 8);
+            const bool ok = grid_threads(t) <= 1024 && t.ntx * t.vp >= N / 2 && t.nty * t.vy >= N && t.ntz * t.vz >= N &&
+                            t.blocks() <= std::max(N * N / 4, 65536);
+            check(ok, "tiles", N, t.blocks());
+        }
+    std::printf("grid_check: %s (%d cases, %d failures)\n", fails ? "FAILED" : "ok", cases, fails);
+    return fails ? 1 : 0;
+}
