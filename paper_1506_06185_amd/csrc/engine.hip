@@ -231,6 +231,7 @@ struct hhgr_ctx {
     // cur of its two
     const GridOps *go = nullptr;
     int cur = 0;
+    size_t grid_off = 0, grid_bytes = 0;  // the grid vectors of every level in the workspace
     double *gpartial = nullptr;
     double *gst = nullptr;  // sine transform of the coarsest level
     long long *gslot = nullptr;  // grid index of every coarsest unknown
@@ -521,8 +522,16 @@ void carve(hhgr_ctx &c, Carver &cv) {
             D.lb = cv.take<double>((size_t)nf * T.C_pad);
             D.lr = cv.take<double>((size_t)nf * T.C_pad);
         }
-        if (c.go) {
-            const size_t n = (size_t)grid_len(T.N);
+        D.wi_dn = cv.take<double>(6 * (size_t)T.n_ifc);
+        D.gidx_dn = cv.take<int>(T.gidx.size());
+        if (l == c.L) D.gamma = cv.take<unsigned char>(T.n_ifc);
+    }
+    if (c.go) {
+        // one stretch, cleared by one fill
+        c.grid_off = (cv.off + 255) & ~size_t(255);
+        for (int l = c.Lc; l <= c.L; l++) {
+            LevelDev &D = c.lev[l];
+            const size_t n = (size_t)grid_len(D.N);
             D.gu[0] = cv.take<double>(n);
             D.gb = cv.take<double>(n);
             if (l > c.Lc) D.gu[1] = cv.take<double>(n);
@@ -533,9 +542,8 @@ void carve(hhgr_ctx &c, Carver &cv) {
             }
             if (c.d.max_faults > 0 && l > c.Lc) D.gfrz = cv.take<unsigned char>(n);
         }
-        D.wi_dn = cv.take<double>(6 * (size_t)T.n_ifc);
-        D.gidx_dn = cv.take<int>(T.gidx.size());
-        if (l == c.L) D.gamma = cv.take<unsigned char>(T.n_ifc);
+        c.grid_bytes = ((cv.off + 7) & ~size_t(7)) - c.grid_off;
+        cv.off = c.grid_off + c.grid_bytes;
     }
     c.partial_cap = max_blocks;
     c.partial[0] = cv.take<double>(max_blocks);
@@ -580,9 +588,10 @@ void carve(hhgr_ctx &c, Carver &cv) {
         c.gpartial = cv.take<double>(gpartial_len(TL.N));
         const int n = tp.lev[c.Lc].N - 1;
         c.gst = cv.take<double>((size_t)n * n + n);
-        c.gslot = cv.take<long long>(c.cn);
-        c.gcptr = cv.take<int>(c.cn + 1);
-        c.gcidx = cv.take<int>(c.cn);
+        // grid index of every coarsest unknown, and the PCG's lists of its copies
+        c.gslot = cv.take<long long>(2 * (size_t)c.cn + 1);
+        c.gcptr = c.gslot ? reinterpret_cast<int *>(c.gslot + c.cn) : nullptr;
+        c.gcidx = c.gcptr ? c.gcptr + c.cn + 1 : nullptr;
     }
     if (c.vk) {
         c.user_u = cv.take<double>(c.n_dofs);
@@ -1235,6 +1244,13 @@ int grid_cycle(hhgr_ctx &c, int l, bool zero, int q, bool masked, bool norm, hip
             o.coarse32(s, D.N, c.gst, b, u[0]);
         return 0;
     }
+    if (!masked && zero && o.tail_fits(D.N, c.lev[c.Lc].N)) {
+        if constexpr (std::is_same<T, double>::value)
+            o.tail64(s, D.N, c.lev[c.Lc].N, c.d.nu_pre, c.d.nu_post, D.h, c.d.omega, c.gst, b, u[0], nullptr);
+        else
+            o.tail32(s, D.N, c.lev[c.Lc].N, c.d.nu_pre, c.d.nu_post, D.h, c.d.omega, c.gst, b, u[0], nullptr);
+        return 0;
+    }
     const LevelDev &Dc = c.lev[l - 1];
     GridSweep<T> g;
     g.N = D.N;
@@ -1306,6 +1322,10 @@ void grid_residual(hhgr_ctx &c, bool masked, const float *e, float *r32, hipStre
     launch_reduce(s, c.gpartial, D.tl_res.blocks(), dst);
 }
 
+// the finest level itself is among the last levels that one workgroup cycles
+// (in place, in the buffer cur)
+bool grid_in_tail(const hhgr_ctx &c) { return !c.mixed && c.go->tail_fits(c.lev[c.L].N, c.lev[c.Lc].N); }
+
 // one FP64 cycle or mixed refinement step, with the squared residual norm
 // to *dst (FP64: only if norm)
 void grid_step(hhgr_ctx &c, bool masked, bool norm, hipStream_t s, double *dst) {
@@ -1313,6 +1333,10 @@ void grid_step(hhgr_ctx &c, bool masked, bool norm, hipStream_t s, double *dst) 
     if (c.mixed) {
         const int q = grid_cycle<float>(c, c.L, true, 0, masked, false, s);
         grid_residual(c, masked, D.gu32[q], D.gb32, s, dst);
+        return;
+    }
+    if (!masked && grid_in_tail(c)) {
+        c.go->tail64(s, D.N, c.lev[c.Lc].N, c.d.nu_pre, c.d.nu_post, D.h, c.d.omega, c.gst, D.gb, D.gu[c.cur], dst);
         return;
     }
     const bool tail = norm && c.d.nu_post > 0;
@@ -1443,8 +1467,10 @@ void enqueue_step(hhgr_ctx &c, hipStream_t s) {
 }
 
 // whether a step ends in the other buffer of the finest u than it starts from
-int step_swaps(const hhgr_ctx &c) {
-    return !c.go ? 0 : c.mixed ? 1 : (c.d.nu_pre + std::max(c.d.nu_post, 1)) & 1;
+int step_swaps(const hhgr_ctx &c, bool masked = false) {
+    if (!c.go) return 0;
+    if (c.mixed) return 1;
+    return !masked && grid_in_tail(c) ? 0 : (c.d.nu_pre + std::max(c.d.nu_post, 1)) & 1;
 }
 
 int run_step(hhgr_ctx &c) {
@@ -1950,6 +1976,20 @@ int hhgr_workspace_bytes(const hhgr_desc *desc, size_t *bytes) {
 namespace hhgr {
 namespace {
 
+// a grid context's tiles on every level, and its vectors zero (Dirichlet nodes
+// and row padding included)
+int grid_vectors(hhgr_ctx &c) {
+    for (int l = c.Lc + 1; l <= c.L; l++) {
+        LevelDev &D = c.lev[l];
+        grid_plan(*c.go, D, c.mixed);
+        if ((size_t)std::max({D.tl_res.blocks(), D.tl[0][kGridFromU][kGridNorm].blocks(),
+                              D.tl[0][kGridProlong][kGridNorm].blocks()}) > gpartial_len(D.N))
+            return fail(HHGR_EINVAL, "more tiles than partial sums");
+    }
+    launch_fill<double>(c.stream, reinterpret_cast<double *>((char *)c.ws + c.grid_off), (long long)(c.grid_bytes / 8), 0.0);
+    return HHGR_OK;
+}
+
 // hhgr_create and the context of hhgr_solve_static.  own_objects: create the
 // second stream, the capture stream, the fork/join events and the pinned
 // read-back buffer; without them (a context that allocates nothing) the
@@ -2024,7 +2064,12 @@ int create_ctx(const hhgr_desc *desc, std::shared_ptr<const Topology> mesh_topo,
     std::vector<std::vector<VolDesc>> vd_store;
     std::vector<std::vector<int4>> rown_store;
     int rc = HHGR_OK;
-    for (int l = c->Lc; l <= c->L && rc == HHGR_OK; l++) {
+    // a context on the grid that runs no recoveries and no single operators
+    // (hhgr_solve_static) reads no slot table and no slot vector: it is set up
+    // on every call, and those tables are about a hundred copies
+    const bool slots = own_objects || !c->go;
+    if (c->go) rc = grid_vectors(*c);
+    for (int l = c->Lc; slots && l <= c->L && rc == HHGR_OK; l++) {
         const TopoLevel &T = tp.lev[l];
         LevelDev &D = c->lev[l];
         rc = rc ? rc : upload(*c, D.nbr, T.nbr.data(), T.nbr.size() * sizeof(int));
@@ -2109,19 +2154,6 @@ int create_ctx(const hhgr_desc *desc, std::shared_ptr<const Topology> mesh_topo,
             launch_fill<double>(c->stream, D.lb, n, 0.0);
             launch_fill<double>(c->stream, D.lr, n, 0.0);
         }
-        if (c->go) {
-            if (l > c->Lc) {
-                grid_plan(*c->go, D, c->mixed);
-                if (!rc && (size_t)std::max({D.tl_res.blocks(), D.tl[0][kGridFromU][kGridNorm].blocks(),
-                                             D.tl[0][kGridProlong][kGridNorm].blocks()}) > gpartial_len(D.N))
-                    rc = fail(HHGR_EINVAL, "more tiles than partial sums");
-            }
-            for (double *p : {D.gu[0], D.gu[1], D.gb})
-                if (p) launch_fill<double>(c->stream, p, grid_len(D.N), 0.0);
-            for (float *p : {D.gu32[0], D.gu32[1], D.gb32})
-                if (p) launch_fill<float>(c->stream, p, grid_len(D.N), 0.0f);
-            if (D.gfrz) launch_fill<unsigned char>(c->stream, D.gfrz, grid_len(D.N), 0);
-        }
         launch_fill<unsigned char>(c->stream, D.frozen, T.n_ifc, 0);
         if (c->vk && c->gen) {
             launch_fill<double>(c->stream, D.wv, 8 * T.n_slots, 0.0);
@@ -2138,17 +2170,21 @@ int create_ctx(const hhgr_desc *desc, std::shared_ptr<const Topology> mesh_topo,
             tinfo[6 * t + a] = tp.V0[t][a];
             tinfo[6 * t + 3 + a] = tp.perm[t][a];
         }
-    rc = rc ? rc : upload(*c, c->tetinfo, tinfo.data(), tinfo.size() * sizeof(int));
+    if (slots) rc = rc ? rc : upload(*c, c->tetinfo, tinfo.data(), tinfo.size() * sizeof(int));
     const CoarseSystem &cs = tp.coarse;
     std::vector<int> cpos(3 * (size_t)cs.n);
     for (int q = 0; q < cs.n; q++)
         for (int a = 0; a < 3; a++) cpos[3 * q + a] = cs.pos[q][a];
     c->cval_host = cs.val;
-    rc = rc ? rc : upload(*c, c->cslot, cs.slot.data(), cs.slot.size() * sizeof(long long));
-    rc = rc ? rc : upload(*c, c->ccol, cs.col.data(), cs.col.size() * sizeof(int));
-    rc = rc ? rc : upload(*c, c->cval, c->cval_host.data(), c->cval_host.size() * sizeof(double));
+    if (slots) {
+        rc = rc ? rc : upload(*c, c->cslot, cs.slot.data(), cs.slot.size() * sizeof(long long));
+        rc = rc ? rc : upload(*c, c->ccol, cs.col.data(), cs.col.size() * sizeof(int));
+        rc = rc ? rc : upload(*c, c->cval, c->cval_host.data(), c->cval_host.size() * sizeof(double));
+    }
     std::vector<double> cinv_host;
-    if (!c->gen && c->cinv && coarse_inverse(cs.n, 7, cs.col, cs.val, cinv_host)) {
+    // (the grid cycles solve the coarsest level by sine transforms: there the
+    // inverse serves hhgr_debug_op alone, which computes it when first asked)
+    if (!c->gen && !c->go && c->cinv && coarse_inverse(cs.n, 7, cs.col, cs.val, cinv_host)) {
         rc = rc ? rc : upload(*c, c->cinv, cinv_host.data(), cinv_host.size() * sizeof(double));
         c->dense_coarse = true;
     }
@@ -2168,33 +2204,36 @@ int create_ctx(const hhgr_desc *desc, std::shared_ptr<const Topology> mesh_topo,
         c->dense_coarse = true;
         c->geom_set = true;
     }
-    rc = rc ? rc : upload(*c, c->cptr, cs.cptr.data(), cs.cptr.size() * sizeof(int));
-    rc = rc ? rc : upload(*c, c->cidx, cs.cidx.data(), cs.cidx.size() * sizeof(int));
-    rc = rc ? rc : upload(*c, c->cpos, cpos.data(), cpos.size() * sizeof(int));
+    if (slots) {
+        rc = rc ? rc : upload(*c, c->cptr, cs.cptr.data(), cs.cptr.size() * sizeof(int));
+        rc = rc ? rc : upload(*c, c->cidx, cs.cidx.data(), cs.cidx.size() * sizeof(int));
+        rc = rc ? rc : upload(*c, c->cpos, cpos.data(), cpos.size() * sizeof(int));
+    }
     if (c->gen) {
         rc = rc ? rc : upload(*c, c->ccol15, cs.col15.data(), cs.col15.size() * sizeof(int));
         launch_fill<double>(c->stream, c->cval15, 15LL * cs.n, 0.0);
     }
     std::vector<double> gst;
-    std::vector<long long> gslot(cs.n);
-    std::vector<int> gptr(cs.n + 1), gidx(cs.n);
+    std::vector<long long> gslot(2 * (size_t)cs.n + 1);
     if (c->go) {
         const int Nc = tp.lev[c->Lc].N;
         gst = sine_table(Nc);
+        std::vector<int> lists(2 * (size_t)cs.n + 2, 0);  // gcptr, gcidx: one copy each
         for (int q = 0; q < cs.n; q++) {
             gslot[q] = cs.pos[q][0] + grid_pitch(Nc) * (cs.pos[q][1] + (long long)Nc * cs.pos[q][2]);
-            gidx[q] = (int)gslot[q];
-            gptr[q + 1] = q + 1;
+            lists[q + 1] = q + 1;
+            lists[cs.n + 1 + q] = (int)gslot[q];
         }
+        std::memcpy(gslot.data() + cs.n, lists.data(), (size_t)(cs.n + 1) * sizeof(long long));
         rc = rc ? rc : upload(*c, c->gst, gst.data(), gst.size() * sizeof(double));
-        rc = rc ? rc : upload(*c, c->gslot, gslot.data(), gslot.size() * sizeof(long long));
-        rc = rc ? rc : upload(*c, c->gcptr, gptr.data(), gptr.size() * sizeof(int));
-        rc = rc ? rc : upload(*c, c->gcidx, gidx.data(), gidx.size() * sizeof(int));
+        if (slots) rc = rc ? rc : upload(*c, c->gslot, gslot.data(), gslot.size() * sizeof(long long));
     }
     launch_fill<unsigned char>(c->stream, c->cfrozen, cs.n, 0);
     // the scratch vectors' zero slot and Dirichlet ghosts must read zero
-    launch_fill<double>(c->stream, c->aux_u, tp.lev[c->L].n_slots, 0.0);
-    launch_fill<double>(c->stream, c->aux_b, tp.lev[c->L].n_slots, 0.0);
+    if (slots) {
+        launch_fill<double>(c->stream, c->aux_u, tp.lev[c->L].n_slots, 0.0);
+        launch_fill<double>(c->stream, c->aux_b, tp.lev[c->L].n_slots, 0.0);
+    }
     launch_fill<double>(c->stream, c->dnorm, 8, 0.0);
     launch_fill<unsigned int>(c->stream, c->counter, 64, 0u);
     if (rc != HHGR_OK) return bail(rc);
@@ -3199,6 +3238,16 @@ int hhgr_debug_op(hhgr_ctx *c, int op, int l, const double *in0, const double *i
     if ((op <= 3 || op == 5 || class_op || fused_op) && !in1) return fail(HHGR_EINVAL, "null second input");
     if (c->vk && !c->coeff_set) return fail(HHGR_ESTATE, "no coefficient set");
     if (c->gen && !c->geom_set && op != 4 && op != 5) return fail(HHGR_ESTATE, "no geometry set");
+    if (op == 7 && c->go && c->cinv && !c->dense_coarse) {
+        const CoarseSystem &cs = c->topo->coarse;
+        std::vector<double> inv;
+        if (coarse_inverse(cs.n, 7, cs.col, cs.val, inv)) {
+            const int rc = upload(*c, c->cinv, inv.data(), inv.size() * sizeof(double));
+            HIPCHK(hipStreamSynchronize(c->stream));  // the copy reads inv
+            if (rc) return rc;
+            c->dense_coarse = true;
+        }
+    }
     if (op == 7 && !c->dense_coarse) return fail(HHGR_EINVAL, "no dense coarsest-level inverse in this context");
     if (op == 6 && c->mesh) return fail(HHGR_EINVAL, "an unstructured macro mesh solves its coarsest level densely (op 7)");
     invalidate_graph(*c);
@@ -3492,7 +3541,8 @@ int hhgr_batch_run(hhgr_batch *b, double rel_tol, int max_cycles, hhgr_report *r
         }
         HIPCHK(hipGraphLaunch(st->x, b->stream));
         for (size_t a = 0; a < active.size(); a++)
-            if (moves(sig[3 * a + 1])) b->ctx[sig[3 * a]]->cur ^= step_swaps(*b->ctx[sig[3 * a]]);
+            if (moves(sig[3 * a + 1]))
+                b->ctx[sig[3 * a]]->cur ^= step_swaps(*b->ctx[sig[3 * a]], (sig[3 * a + 1] & kModeMasked) != 0);
         for (size_t a = 0; a < active.size(); a++) {
             const int q = sig[3 * a], mode = sig[3 * a + 1];
             if (!(mode & kModeLocal)) continue;

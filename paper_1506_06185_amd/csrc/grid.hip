@@ -432,6 +432,216 @@ __global__ void __launch_bounds__(512) k_grid_coarse(int N, const double *st, co
 }
 
 // ---------------------------------------------------------------------------
+// the last levels (N <= 16) of a cycle in one workgroup
+// ---------------------------------------------------------------------------
+// At 15^3 nodes and fewer a launch costs more than its work (9 + 5 us for the
+// two sweep launches of N = 16, 4 us for the coarsest level), so one
+// workgroup runs every pass of these levels in LDS: u of a level lives there
+// with its zero boundary, b and (while the level's residual takes its place)
+// u in the registers of the threads that own the nodes.  A thread owns pairs
+// of nodes (2p, 2p + 1), one of each colour.
+constexpr int kTailN = 16, kTailThreads = 1024;
+constexpr int kTailLen = (kTailN + 2) * (kTailN + 1) * (kTailN + 1);
+constexpr __host__ __device__ int tail_len(int N) { return (N + 2) * (N + 1) * (N + 1); }
+
+struct TailLds {
+    double *A, *B, *S;  // sine transforms of the coarsest level
+    double *red;
+};
+
+// NP: pairs per thread; lv: this level's u, then the coarser levels'; bl: the
+// restricted right-hand side of the next coarser level
+template <typename T, int NP>
+__device__ __forceinline__ void tail_level(int N, int Nc, const T (&b)[NP][2], T (&u)[NP][2], bool zero, T h, T om, int nu_pre,
+                                           int nu_post, T *lv, T *bl, const TailLds &q) {
+    const int tid = (int)threadIdx.x, nt = (int)blockDim.x;
+    const int Pl = N + 2, Sl = Pl * (N + 1), np = N / 2, npairs = np * (N - 1) * (N - 1);
+    int idx[NP], par[NP];
+    bool act[NP], lo[NP];
+#pragma unroll
+    for (int s = 0; s < NP; s++) {
+        const int k = tid + s * nt;
+        act[s] = k < npairs;
+        const int p = k % np, y = (k / np) % (N - 1) + 1, z = k / (np * (N - 1)) + 1;
+        idx[s] = act[s] ? 2 * p + Pl * y + Sl * z : 0;
+        par[s] = (y + z) & 1;
+        lo[s] = act[s] && p > 0;
+    }
+    for (int k = tid; k < tail_len(N); k += nt) lv[k] = T(0);
+    __syncthreads();
+    auto put = [&](const T(&v)[NP][2]) {
+#pragma unroll
+        for (int s = 0; s < NP; s++) {
+            if (lo[s]) lv[idx[s]] = v[s][0];
+            if (act[s]) lv[idx[s] + 1] = v[s][1];
+        }
+        __syncthreads();
+    };
+    auto around = [&](int i) { return ((lv[i - 1] + lv[i + 1]) + (lv[i - Pl] + lv[i + Pl])) + (lv[i - Sl] + lv[i + Sl]); };
+    auto sweep = [&]() {
+        for (int c = 0; c < 2; c++) {
+#pragma unroll
+            for (int s = 0; s < NP; s++) {
+                const int o = par[s] ^ c;  // the pair's node of colour c
+                const bool on = o ? act[s] : lo[s];
+                const int i = on ? idx[s] + o : Sl + Pl + 1;
+                const T ctr = o ? u[s][1] : u[s][0], bb = o ? b[s][1] : b[s][0];
+                const T n = ctr + om * (bb - h * (T(6) * ctr - around(i)));
+                if (on) lv[i] = n;
+                u[s][0] = on && !o ? n : u[s][0];
+                u[s][1] = on && o ? n : u[s][1];
+            }
+            __syncthreads();
+        }
+    };
+    if (zero) {
+#pragma unroll
+        for (int s = 0; s < NP; s++) u[s][0] = u[s][1] = T(0);
+    } else {
+        put(u);
+    }
+    for (int k = 0; k < nu_pre; k++) sweep();
+    T r[NP][2];
+#pragma unroll
+    for (int s = 0; s < NP; s++)
+#pragma unroll
+        for (int o = 0; o < 2; o++) {
+            const int i = (o ? act[s] : lo[s]) ? idx[s] + o : Sl + Pl + 1;
+            r[s][o] = b[s][o] - h * (T(6) * u[s][o] - around(i));
+        }
+    __syncthreads();
+    put(r);
+    // restriction to the coarser level, in its layout
+    const int M = N / 2, Pm = M + 2, Sm = Pm * (M + 1), nm = M - 1;
+    T *const lc = lv + tail_len(N);
+    for (int k = tid; k < nm * nm * nm; k += nt) {
+        const int x = k % nm + 1, y = (k / nm) % nm + 1, z = k / (nm * nm) + 1;
+        const T *c = lv + 2 * (x + Pl * y + Sl * z);
+        auto two = [&](int d) { return c[d] + c[-d]; };
+        const T v = c[0] + T(0.5) * (((two(1) + two(Pl)) + (two(Sl) + two(1 + Pl))) +
+                                     ((two(Pl + Sl) + two(1 + Sl)) + two(1 + Pl + Sl)));
+        bl[x + Pm * y + Sm * z] = v;
+    }
+    __syncthreads();
+    put(u);
+    if (M == Nc) {
+        for (int k = tid; k < tail_len(M); k += nt) lc[k] = T(0);
+        const int n2 = nm * nm, n3 = n2 * nm;
+        auto each = [&](auto f) {
+            __syncthreads();
+            for (int k = tid; k < n3; k += nt) f(k, k % nm, (k / nm) % nm, k / n2);
+        };
+        each([&](int k, int x, int y, int z) { q.A[k] = (double)bl[(x + 1) + Pm * (y + 1) + Sm * (z + 1)]; });
+        each([&](int k, int x, int, int) { sine_axis(nm, 1, k, x, q.S, q.A, q.B); });
+        each([&](int k, int, int y, int) { sine_axis(nm, nm, k, y, q.S, q.B, q.A); });
+        each([&](int k, int x, int y, int z) {
+            sine_axis(nm, n2, k, z, q.S, q.A, q.B);
+            q.B[k] *= (double)M / ((q.S[n2 + x] + q.S[n2 + y]) + q.S[n2 + z]);
+        });
+        each([&](int k, int x, int, int) { sine_axis(nm, 1, k, x, q.S, q.B, q.A); });
+        each([&](int k, int, int y, int) { sine_axis(nm, nm, k, y, q.S, q.A, q.B); });
+        each([&](int k, int x, int y, int z) {
+            sine_axis(nm, n2, k, z, q.S, q.B, q.A);
+            lc[(x + 1) + Pm * (y + 1) + Sm * (z + 1)] = (T)q.A[k];
+        });
+        __syncthreads();
+    } else if constexpr (NP > 1) {
+        // one pair per thread below N = 16
+        T bm[1][2], um[1][2];
+        const int k = tid, mp = M / 2;
+        const bool on = k < mp * nm * nm;
+        const int i = 2 * (k % mp) + Pm * ((k / mp) % nm + 1) + Sm * (k / (mp * nm) + 1);
+        bm[0][0] = on && k % mp > 0 ? bl[i] : T(0);
+        bm[0][1] = on ? bl[i + 1] : T(0);
+        um[0][0] = um[0][1] = T(0);
+        __syncthreads();
+        tail_level<T, 1>(M, Nc, bm, um, true, T(2) * h, T(0.5) * om, nu_pre, nu_post, lc, bl, q);
+    }
+    // interpolation from lc
+#pragma unroll
+    for (int s = 0; s < NP; s++) {
+        const int i = idx[s], z = i / Sl, y = (i - z * Sl) / Pl, x = i - z * Sl - y * Pl;
+        const T e0 = lc[(x >> 1) + Pm * (y >> 1) + Sm * (z >> 1)];
+        const T *eh = lc + (x >> 1) + Pm * ((y + 1) >> 1) + Sm * ((z + 1) >> 1);
+        if (act[s]) {
+            u[s][0] += T(0.5) * (e0 + eh[0]);
+            u[s][1] += T(0.5) * (e0 + eh[1]);
+        }
+    }
+    __syncthreads();
+    put(u);
+    for (int k = 0; k < nu_post; k++) sweep();
+}
+
+// FINEST: u is read and the squared residual norm of the result goes to norm;
+// else the cycle starts from zero
+template <typename T, int NP, bool FINEST>
+__global__ void __launch_bounds__(kTailThreads) k_grid_tail(int N, int Nc, int nu_pre, int nu_post, T h, T om, const double *st,
+                                                            const T *gb, T *gu, double *norm) {
+    const int tid = (int)threadIdx.x, nt = (int)blockDim.x;
+    const long long P = N + 16;
+    TailLds q;
+    q.A = (double *)grid_lds;
+    q.B = q.A + 343;
+    q.S = q.B + 343;
+    q.red = q.S + 56;
+    T *const bl = (T *)(q.red + kTailThreads), *const lv = bl + tail_len(kTailN / 2);
+    const int nc = Nc - 1;
+    for (int k = tid; k < nc * nc + nc; k += nt) q.S[k] = st[k];
+    T b[NP][2], u[NP][2];
+    const int np = N / 2, npairs = np * (N - 1) * (N - 1);
+#pragma unroll
+    for (int s = 0; s < NP; s++) {
+        const int k = tid + s * nt;
+        const bool on = k < npairs;
+        const long long i = on ? 2 * (k % np) + P * ((k / np) % (N - 1) + 1 + (long long)N * (k / (np * (N - 1)) + 1)) : 0;
+        // the boundary node x = 0 holds zeros
+        const Pair<T> bb = *(const Pair<T> *)(gb + i);
+        b[s][0] = on ? bb.lo : T(0);
+        b[s][1] = on ? bb.hi : T(0);
+        u[s][0] = u[s][1] = T(0);
+        if (FINEST) {
+            const Pair<T> uu = *(const Pair<T> *)(gu + i);
+            u[s][0] = on ? uu.lo : T(0);
+            u[s][1] = on ? uu.hi : T(0);
+        }
+    }
+    tail_level<T, NP>(N, Nc, b, u, !FINEST, h, om, nu_pre, nu_post, lv, bl, q);
+    const int Pl = N + 2, Sl = Pl * (N + 1);
+    double sum = 0.0;
+#pragma unroll
+    for (int s = 0; s < NP; s++) {
+        const int k = tid + s * nt;
+        if (k >= npairs) continue;
+        const int p = k % np, y = (k / np) % (N - 1) + 1, z = k / (np * (N - 1)) + 1;
+        Pair<T> o;
+        o.lo = u[s][0];
+        o.hi = u[s][1];
+        *(Pair<T> *)(gu + 2 * p + P * (y + (long long)N * z)) = o;
+        if (FINEST) {
+            const T *c = lv + 2 * p + Pl * y + Sl * z;
+#pragma unroll
+            for (int e = 0; e < 2; e++) {
+                if (e == 0 && p == 0) continue;
+                const T *v = c + e;
+                const double r = (double)(b[s][e] - h * (T(6) * u[s][e] - (((v[-1] + v[1]) + (v[-Pl] + v[Pl])) + (v[-Sl] + v[Sl]))));
+                sum += r * r;
+            }
+        }
+    }
+    if (FINEST) {
+        q.red[tid] = sum;
+        for (int n = nt; n > 1;) {
+            const int hf = (n + 1) >> 1;
+            __syncthreads();
+            if (tid + hf < n) q.red[tid] += q.red[tid + hf];
+            n = hf;
+        }
+        if (tid == 0) *norm = q.red[0];
+    }
+}
+
+// ---------------------------------------------------------------------------
 // vector order <-> grid: a wavefront per row
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) k_grid_from_user(int N, const double *user, double *grid, double *partial) {
@@ -706,6 +916,25 @@ void coarse(hipStream_t s, int N, const double *st, const T *b, T *u) {
     const size_t lds = (2 * kSineMax * kSineMax * kSineMax + kSineMax * (kSineMax + 1)) * sizeof(double);
     hipLaunchKernelGGL((k_grid_coarse<T>), dim3(1), dim3(512), lds, s, N, st, b, u);
 }
+template <typename T, int NP, bool FINEST>
+void tail_run(hipStream_t s, int N, int Nc, int nu_pre, int nu_post, double h, double omega, const double *st, const T *b, T *u,
+              double *norm) {
+    const size_t lds = (2 * 343 + 56 + kTailThreads) * sizeof(double) +
+                       (tail_len(kTailN / 2) + tail_len(N) + tail_len(N / 2) + tail_len(N / 4)) * sizeof(T);
+    hipLaunchKernelGGL((k_grid_tail<T, NP, FINEST>), dim3(1), dim3(kTailThreads), lds, s, N, Nc, nu_pre, nu_post, (T)h,
+                       (T)(omega / (6.0 * h)), st, b, u, norm);
+}
+bool tail_fits(int N, int Nc) { return N <= kTailN && Nc <= 8 && N > Nc && (N / 2 == Nc || (N == kTailN && N / 4 == Nc)); }
+template <typename T>
+void tail_cycle(hipStream_t s, int N, int Nc, int nu_pre, int nu_post, double h, double omega, const double *st, const T *b, T *u,
+                double *norm) {
+    if (N > 8)
+        norm ? tail_run<T, 2, true>(s, N, Nc, nu_pre, nu_post, h, omega, st, b, u, norm)
+             : tail_run<T, 2, false>(s, N, Nc, nu_pre, nu_post, h, omega, st, b, u, norm);
+    else
+        norm ? tail_run<T, 1, true>(s, N, Nc, nu_pre, nu_post, h, omega, st, b, u, norm)
+             : tail_run<T, 1, false>(s, N, Nc, nu_pre, nu_post, h, omega, st, b, u, norm);
+}
 int row_blocks(int N) { return (int)(((long long)(N - 1) * (N - 1) + 3) / 4); }
 int from_user(hipStream_t s, int N, const double *user, double *grid, double *partial) {
     hipLaunchKernelGGL(k_grid_from_user, dim3((unsigned)row_blocks(N)), dim3(256), 256 * sizeof(double), s, N, user, grid,
@@ -820,6 +1049,9 @@ const GridOps kOps = {tiles,
                       plain_prolong<float>,
                       coarse<double>,
                       coarse<float>,
+                      tail_fits,
+                      tail_cycle<double>,
+                      tail_cycle<float>,
                       from_user,
                       to_user,
                       mass_load,

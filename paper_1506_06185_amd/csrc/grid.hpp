@@ -117,6 +117,14 @@ struct GridOps {
     // 2 - 2 cos(pi q / N)
     void (*coarse64)(hipStream_t, int N, const double *st, const double *b, double *u);
     void (*coarse32)(hipStream_t, int N, const double *st, const float *b, float *u);
+    // a whole cycle on a grid of N <= 16 cells, its coarsest level of Nc cells
+    // included, in one workgroup (tail_fits): u = cycle from zero, or (norm
+    // not null) from u, with the squared residual norm of the result to *norm
+    bool (*tail_fits)(int N, int Nc);
+    void (*tail64)(hipStream_t, int N, int Nc, int nu_pre, int nu_post, double h, double omega, const double *st,
+                   const double *b, double *u, double *norm);
+    void (*tail32)(hipStream_t, int N, int Nc, int nu_pre, int nu_post, double h, double omega, const double *st,
+                   const float *b, float *u, double *norm);
     // vector order ((N-1)^3 interior nodes) <-> grid; per-workgroup sums of
     // squares to partial (optional); returns the number of workgroups
     int (*from_user)(hipStream_t, int N, const double *user, double *grid, double *partial);

@@ -5,6 +5,7 @@
 // interpolation, residual and restriction written here node by node; the
 // residual, mass and coarsest-level kernels likewise.  Buffers are exact-size
 // vectors under AddressSanitizer, and LDS starts as NaN.
+#define _USE_MATH_DEFINES
 #include <cmath>
 #include <cstdio>
 #include <random>
@@ -221,6 +222,54 @@ static void run_mass(int N, unsigned seed) {
     check(err < 1e-14 * big && std::fabs(sum - norm) < 1e-12 * norm, "mass", N, err);
 }
 
+// the one-workgroup cycle against the same cycle of separate launches
+static std::vector<double> launches(int N, int Nc, int pre, int post, const std::vector<double> &b, std::vector<double> u,
+                                    const std::vector<double> &st) {
+    const GridOps &o = *grid_ops();
+    if (N == Nc) {
+        o.coarse64(nullptr, N, st.data(), b.data(), u.data());
+        return u;
+    }
+    std::vector<double> v(u.size(), 0.0), bc(grid_len(N / 2), 0.0), r(u.size(), 0.0);
+    GridSweep<double> g;
+    g.N = N;
+    g.h = 1.0 / N;
+    g.omega = 1.25;
+    g.b = b.data();
+    auto sweep = [&](int start) {
+        g.u = u.data();
+        g.v = v.data();
+        o.sweep64(nullptr, 1, start, kGridPlain, grid_tiles_of(N, 1, kGridPlain, 4, 8, 8), g);
+        u.swap(v);
+    };
+    for (int k = 0; k < pre; k++) sweep(kGridFromU);
+    o.plain_residual64(nullptr, N, 1.0 / N, u.data(), b.data(), r.data());
+    o.plain_restrict64(nullptr, N, r.data(), bc.data());
+    const std::vector<double> e = launches(N / 2, Nc, pre, post, bc, std::vector<double>(bc.size(), 0.0), st);
+    o.plain_prolong64(nullptr, N, u.data(), e.data(), v.data());
+    u.swap(v);
+    for (int k = 0; k < post; k++) sweep(kGridFromU);
+    return u;
+}
+
+static void run_tail(int N, int Nc, int pre, int post, bool finest, unsigned seed) {
+    std::mt19937 g(seed);
+    const std::vector<double> b = random_grid<double>(N, g);
+    std::vector<double> u = random_grid<double>(N, g), st((Nc - 1) * Nc);
+    for (int i = 0; i < Nc - 1; i++) {
+        for (int j = 0; j < Nc - 1; j++) st[i * (Nc - 1) + j] = std::sqrt(2.0 / Nc) * std::sin(M_PI * (i + 1) * (j + 1) / Nc);
+        st[(Nc - 1) * (Nc - 1) + i] = 2.0 - 2.0 * std::cos(M_PI * (i + 1) / Nc);
+    }
+    const std::vector<double> w = launches(N, Nc, pre, post, b, finest ? u : std::vector<double>(u.size(), 0.0), st);
+    std::vector<double> r(u.size(), 0.0);
+    grid_ops()->plain_residual64(nullptr, N, 1.0 / N, w.data(), b.data(), r.data());
+    double norm = -1.0, ref = 0.0, err = 0.0;
+    for (double x : r) ref += x * x;
+    grid_ops()->tail64(nullptr, N, Nc, pre, post, 1.0 / N, 1.25, st.data(), b.data(), u.data(), finest ? &norm : nullptr);
+    for (size_t i = 0; i < u.size(); i++) err = std::max(err, std::isfinite(u[i]) ? std::fabs(u[i] - w[i]) : 1.0);
+    check(err < 1e-11 && (!finest || std::fabs(norm - ref) < 1e-10 * ref), "tail", N, err);
+}
+
 int main() {
     const int shapes[][4] = {{16, 8, 16, 16}, {16, 3, 6, 4}, {24, 5, 8, 10}, {8, 4, 8, 8}, {8, 2, 2, 2}};
     const int kinds[][3] = {{1, 0, 0}, {1, 0, 1}, {1, 0, 2}, {1, 1, 0}, {1, 1, 1}, {1, 2, 0}, {1, 2, 2}, {2, 1, 0}, {2, 1, 1}};
@@ -233,6 +282,10 @@ int main() {
         }
         for (int q = 0; q < 4; q++) run_residual(sh[0], q & 1, q >> 1, sh[1], sh[2], sh[3], seed++);
     }
+    run_tail(16, 8, 2, 1, false, seed++);
+    run_tail(16, 4, 2, 1, true, seed++);
+    run_tail(8, 4, 1, 2, true, seed++);
+    run_tail(8, 4, 0, 1, false, seed++);
     run_mass(8, seed++);
     run_mass(24, seed++);
     // every chosen tiling fits a workgroup, from the smallest grid to the largest of one GPU

@@ -62,8 +62,10 @@ void mockgrid_launch(K kernel, dim3 grid, dim3 block, size_t lds, A... args) {
     for (unsigned tx = 0; tx < block.x; tx++)
         th.emplace_back([&, tx]() {
             threadIdx.x = tx;
-            for (unsigned bx = 0; bx < grid.x; bx++) {
-                blockIdx.x = bx;
+            for (unsigned q = 0; q < grid.x * grid.y * grid.z; q++) {
+                blockIdx.x = q % grid.x;
+                blockIdx.y = (q / grid.x) % grid.y;
+                blockIdx.z = q / (grid.x * grid.y);
                 kernel(args...);
                 bar.arrive_and_wait();
             }
