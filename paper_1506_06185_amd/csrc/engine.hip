@@ -143,6 +143,8 @@ struct LevelDev {
     double *gu[2] = {}, *gb = nullptr;
     float *gu32[2] = {}, *gb32 = nullptr;
     unsigned char *gfrz = nullptr;
+    double *gw = nullptr;   // per-element k: edge weights along x, y and z
+    float *gw32 = nullptr;
     GridTiles tl[2][3][3];  // [ns - 1][start][tail]
     GridTiles tl_res;
 };
@@ -541,6 +543,10 @@ void carve(hhgr_ctx &c, Carver &cv) {
                 if (l > c.Lc) D.gu32[1] = cv.take<float>(n);
             }
             if (c.d.max_faults > 0 && l > c.Lc) D.gfrz = cv.take<unsigned char>(n);
+            if (c.vk && l > c.Lc) {
+                D.gw = cv.take<double>(3 * n);
+                if (c.mixed) D.gw32 = cv.take<float>(3 * n);
+            }
         }
         c.grid_bytes = ((cv.off + 7) & ~size_t(7)) - c.grid_off;
         cv.off = c.grid_off + c.grid_bytes;
@@ -1215,6 +1221,16 @@ template <>
 float *gvec<float>(const LevelDev &D, int q) {
     return q < 2 ? D.gu32[q] : D.gb32;
 }
+template <typename T>
+const T *gweights(const LevelDev &D);
+template <>
+const double *gweights<double>(const LevelDev &D) {
+    return D.gw;
+}
+template <>
+const float *gweights<float>(const LevelDev &D) {
+    return D.gw32;
+}
 
 void grid_ops_sweep(const GridOps &o, hipStream_t s, int ns, int start, int tail, const GridTiles &t,
                     const GridSweep<double> &g) {
@@ -1235,8 +1251,8 @@ int grid_cycle(hhgr_ctx &c, int l, bool zero, int q, bool masked, bool norm, hip
     LevelDev &D = c.lev[l];
     T *const u[2] = {gvec<T>(D, 0), gvec<T>(D, 1)}, *const b = gvec<T>(D, 2);
     if (l == c.Lc) {
-        if (masked)
-            launch_coarse_pcg<T>(s, c.cn, c.gslot, c.ccol, c.cval, c.cfrozen, b, u[0], c.gcptr, c.gcidx, kCoarseRtol,
+        if (masked || c.vk)
+            launch_coarse_pcg<T>(s, c.cn, c.gslot, c.ccol, c.cval, masked ? c.cfrozen : nullptr, b, u[0], c.gcptr, c.gcidx, kCoarseRtol,
                                  kCoarseMaxit, c.citers);
         else if constexpr (std::is_same<T, double>::value)
             o.coarse64(s, D.N, c.gst, b, u[0]);
@@ -1244,7 +1260,7 @@ int grid_cycle(hhgr_ctx &c, int l, bool zero, int q, bool masked, bool norm, hip
             o.coarse32(s, D.N, c.gst, b, u[0]);
         return 0;
     }
-    if (!masked && zero && o.tail_fits(D.N, c.lev[c.Lc].N)) {
+    if (!masked && !c.vk && zero && o.tail_fits(D.N, c.lev[c.Lc].N)) {
         if constexpr (std::is_same<T, double>::value)
             o.tail64(s, D.N, c.lev[c.Lc].N, c.d.nu_pre, c.d.nu_post, D.h, c.d.omega, c.gst, b, u[0], nullptr);
         else
@@ -1260,6 +1276,8 @@ int grid_cycle(hhgr_ctx &c, int l, bool zero, int q, bool masked, bool norm, hip
     g.bc = gvec<T>(Dc, 2);
     g.frz = masked ? D.gfrz : nullptr;
     g.partial = c.gpartial;
+    g.w = gweights<T>(D);
+    g.wstride = grid_len(D.N);
     auto sweep = [&](int ns, int start, int tail) {
         g.u = u[q];
         q = start == kGridFromZero ? 0 : 1 - q;
@@ -1273,7 +1291,8 @@ int grid_cycle(hhgr_ctx &c, int l, bool zero, int q, bool masked, bool norm, hip
         // two sweeps in one launch only from zero: there the first pass reads
         // b alone (N = 256: 105 us against 67 + 110; from u 275 against 105 + 110)
         const int start = zero && k == 0 ? kGridFromZero : kGridFromU;
-        const int ns = start == kGridFromZero && c.d.nu_pre >= 2 ? 2 : 1;
+        // (with edge weights the second sweep's registers do not fit)
+        const int ns = start == kGridFromZero && c.d.nu_pre >= 2 && !c.vk ? 2 : 1;
         k += ns;
         sweep(ns, start, k == c.d.nu_pre ? kGridRestrict : kGridPlain);
     }
@@ -1283,10 +1302,10 @@ int grid_cycle(hhgr_ctx &c, int l, bool zero, int q, bool masked, bool norm, hip
             launch_fill<T>(s, u[0], grid_len(D.N), T(0));
         }
         if constexpr (std::is_same<T, double>::value) {
-            o.plain_residual64(s, D.N, D.h, u[q], b, u[1 - q]);
+            o.plain_residual64(s, D.N, D.h, u[q], b, g.w, g.wstride, u[1 - q]);
             o.plain_restrict64(s, D.N, u[1 - q], g.bc);
         } else {
-            o.plain_residual32(s, D.N, D.h, u[q], b, u[1 - q]);
+            o.plain_residual32(s, D.N, D.h, u[q], b, g.w, g.wstride, u[1 - q]);
             o.plain_restrict32(s, D.N, u[1 - q], g.bc);
         }
     }
@@ -1317,6 +1336,8 @@ void grid_residual(hhgr_ctx &c, bool masked, const float *e, float *r32, hipStre
     g.r32 = r32;
     g.frz = masked ? D.gfrz : nullptr;
     g.partial = c.gpartial;
+    g.w = D.gw;
+    g.wstride = grid_len(D.N);
     c.go->residual(s, D.tl_res, g);
     if (e) c.cur = 1 - c.cur;
     launch_reduce(s, c.gpartial, D.tl_res.blocks(), dst);
@@ -1324,7 +1345,7 @@ void grid_residual(hhgr_ctx &c, bool masked, const float *e, float *r32, hipStre
 
 // the finest level itself is among the last levels that one workgroup cycles
 // (in place, in the buffer cur)
-bool grid_in_tail(const hhgr_ctx &c) { return !c.mixed && c.go->tail_fits(c.lev[c.L].N, c.lev[c.Lc].N); }
+bool grid_in_tail(const hhgr_ctx &c) { return !c.mixed && !c.vk && c.go->tail_fits(c.lev[c.L].N, c.lev[c.Lc].N); }
 
 // one FP64 cycle or mixed refinement step, with the squared residual norm
 // to *dst (FP64: only if norm)
@@ -1402,14 +1423,14 @@ std::vector<double> sine_table(int N) {
 }
 
 // tiles of every kind of launch on a grid, chosen once per size
-void grid_plan(const GridOps &o, LevelDev &D, bool mixed) {
+void grid_plan(const GridOps &o, LevelDev &D, bool mixed, bool vk) {
     static std::mutex mu;
-    static std::map<std::tuple<int, int, int, int, int>, GridTiles> known;
+    static std::map<std::tuple<int, int, int, int, int, bool>, GridTiles> known;
     std::lock_guard<std::mutex> lock(mu);
     auto get = [&](int ns, int start, int tail, int word) {
-        const auto key = std::make_tuple(D.N, ns, start, tail, word);
+        const auto key = std::make_tuple(D.N, ns, start, tail, word, vk);
         auto it = known.find(key);
-        if (it == known.end()) it = known.emplace(key, o.tiles(D.N, ns, start, tail, word)).first;
+        if (it == known.end()) it = known.emplace(key, o.tiles(D.N, ns, start, tail, word, vk)).first;
         return it->second;
     };
     const int w = mixed ? 4 : 8;
@@ -1921,8 +1942,8 @@ int gen_weights(hhgr_ctx &c) {
 
 namespace hhgr {
 namespace {
-// the structured-grid launchers of a context on the cube with k = 1, else null
-const GridOps *grid_path(const hhgr_ctx &c) { return !c.gen && !c.vk && grid_ops ? grid_ops() : nullptr; }
+// the structured-grid launchers of a context on the cube, else null
+const GridOps *grid_path(const hhgr_ctx &c) { return !c.gen && grid_ops ? grid_ops() : nullptr; }
 }  // namespace
 }  // namespace hhgr
 
@@ -1981,7 +2002,7 @@ namespace {
 int grid_vectors(hhgr_ctx &c) {
     for (int l = c.Lc + 1; l <= c.L; l++) {
         LevelDev &D = c.lev[l];
-        grid_plan(*c.go, D, c.mixed);
+        grid_plan(*c.go, D, c.mixed, c.vk);
         if ((size_t)std::max({D.tl_res.blocks(), D.tl[0][kGridFromU][kGridNorm].blocks(),
                               D.tl[0][kGridProlong][kGridNorm].blocks()}) > gpartial_len(D.N))
             return fail(HHGR_EINVAL, "more tiles than partial sums");
@@ -2412,7 +2433,7 @@ int hhgr_set_rhs(hhgr_ctx *c, const double *dev_vec, int kind) {
         } else if (kind == HHGR_RHS_NODAL_F) {
             gb = c->go->mass_load(c->stream, D.N, D.h, dev_vec, D.gb, c->gpartial);
         } else {
-            launch_dirichlet_load(c->stream, D.N, D.h, nullptr, dev_vec, c->aux_u);
+            launch_dirichlet_load(c->stream, D.N, D.h, c->vk ? D.kc : nullptr, dev_vec, c->aux_u);
             gb = c->go->from_user(c->stream, D.N, c->aux_u, D.gb, c->gpartial);
             aux_used = true;
         }
@@ -2482,6 +2503,7 @@ int hhgr_set_coeff(hhgr_ctx *c, const double *dev_k) {
             for (int s = 0; s < 3; s++) launch_cast<double, float>(c->stream, D.w[s], D.w32[s], D.n_slots);
             launch_cast<double, float>(c->stream, D.wi, D.wi32, 6LL * D.n_ifc);
         }
+        if (D.gw) c->go->weights(c->stream, D.N, D.h, D.kc, D.gw, D.gw32, grid_len(D.N));
     }
     const LevelDev &Dc = c->lev[c->Lc];
     launch_coarse_vals(c->stream, c->cn, c->cpos, c->ccol, Dc.N, Dc.h, Dc.kc, c->cval);
@@ -2804,8 +2826,9 @@ int hhgr_mass_apply(hhgr_ctx *c, const double *dev_x, double *dev_y) {
     return HHGR_OK;
 }
 
-// hhgr_adjoint_grad on the grid (k = 1: dJ/df only)
-static int grid_adjoint(hhgr_ctx &c, const double *dev_g, double rel_tol, int max_cycles, double *dev_dJdf) {
+// hhgr_adjoint_grad on the grid
+static int grid_adjoint(hhgr_ctx &c, const double *dev_g, double rel_tol, int max_cycles, double *dev_dJdf,
+                        double *dev_dJdk) {
     LevelDev &D = c.lev[c.L];
     const size_t bytes = (size_t)grid_len(D.N) * sizeof(double);
     HIPCHK(hipMemcpyAsync(c.aux_u, D.gu[c.cur], bytes, hipMemcpyDeviceToDevice, c.stream));
@@ -2819,7 +2842,7 @@ static int grid_adjoint(hhgr_ctx &c, const double *dev_g, double rel_tol, int ma
     launch_fill<double>(c.stream, D.gu[c.cur], grid_len(D.N), 0.0);
     CHKLAUNCH();
     if (mixed_saved)  // the FP64 cycle's launches (a mixed context plans the FP32 ones)
-        for (int l = c.Lc + 1; l <= c.L; l++) grid_plan(*c.go, c.lev[l], false);
+        for (int l = c.Lc + 1; l <= c.L; l++) grid_plan(*c.go, c.lev[l], false, c.vk);
     double gn;
     const int rc = read_norm(c, 1, &gn);
     int result = HHGR_OK;
@@ -2828,6 +2851,11 @@ static int grid_adjoint(hhgr_ctx &c, const double *dev_g, double rel_tol, int ma
         hhgr_report rep{0, 0.0, nullptr, 0};
         result = gn > 0 ? hhgr_solve(&c, rel_tol, max_cycles, &rep) : HHGR_OK;
         if (dev_dJdf) c.go->mass_user(c.stream, D.N, D.h, D.gu[c.cur], dev_dJdf);
+        if (dev_dJdk) {
+            c.go->to_user(c.stream, D.N, c.aux_u, c.user_u);
+            c.go->to_user(c.stream, D.N, D.gu[c.cur], c.user_l);
+            launch_grad_k(c.stream, c.user_u, c.user_l, D.N, D.h, dev_dJdk);
+        }
     }
     // restore the forward state
     hipMemcpyAsync(D.gu[c.cur], c.aux_u, bytes, hipMemcpyDeviceToDevice, c.stream);
@@ -2835,7 +2863,7 @@ static int grid_adjoint(hhgr_ctx &c, const double *dev_g, double rel_tol, int ma
     c.bnorm = bnorm_saved;
     c.mixed = mixed_saved;
     if (mixed_saved)
-        for (int l = c.Lc + 1; l <= c.L; l++) grid_plan(*c.go, c.lev[l], true);
+        for (int l = c.Lc + 1; l <= c.L; l++) grid_plan(*c.go, c.lev[l], true, c.vk);
     invalidate_graph(c);
     CHKLAUNCH();
     HIPCHK(hipStreamSynchronize(c.stream));
@@ -2849,7 +2877,7 @@ int hhgr_adjoint_grad(hhgr_ctx *c, const double *dev_g, double rel_tol, int max_
     if (!dev_g) return fail(HHGR_EINVAL, "null g");
     if (dev_dJdk && !c->vk && !c->mesh) return fail(HHGR_ESTATE, "dJ/dk needs variable_coeff = 1");
     LevelDev &D = c->lev[c->L];
-    if (c->go) return grid_adjoint(*c, dev_g, rel_tol, max_cycles, dev_dJdf);
+    if (c->go) return grid_adjoint(*c, dev_g, rel_tol, max_cycles, dev_dJdf, dev_dJdk);
     const long long ns = D.n_slots;
     const IfcGeom ig = igeom(D, 0, D.n_ifc, nullptr, false);
     const VolGeom vint = vgeom(D, D.vd_all, c->n_tets, false);

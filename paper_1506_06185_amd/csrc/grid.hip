@@ -24,6 +24,10 @@ __device__ __forceinline__ unsigned grid_xcd(unsigned f, unsigned total) {
     return x < rem ? x * (per + 1) + loc : rem * (per + 1) + (x - rem) * per + loc;
 }
 
+// workgroups of the variants with edge weights: their registers allow 3
+// wavefronts per SIMD
+constexpr int kVkThreads = 512;
+
 // halo of a launch of K = 2 ns colour passes: nodes below and above a tile
 // along each axis
 constexpr int halo_lo(int K, int tail) { return tail == kGridResidual ? 1 : tail == kGridRestrict ? K + 2 : tail == kGridNorm ? K + 1 : K; }
@@ -61,8 +65,16 @@ __device__ __forceinline__ void block_partial(double sum, double *partial) {
 // step, whatever the number of passes.  Passes at a tile's edge read nodes
 // that the tile does not hold; the wrong values travel one node per pass and
 // stay in the halo.
-template <typename T, int NS, int START, int TAIL, bool MASK>
-__global__ void __launch_bounds__(1024) k_grid_sweep(GridSweep<T> g, GridTiles t, T h, T om, T omr) {
+// VK (per-element k): a pass needs the 6 edge weights of its node, which it
+// loads one step ahead; the residual of a red node reuses those of its red
+// pass two steps before.  The weights are stored split by colour (grid.hpp),
+// so the nodes of one pass read whole lines.  N = 128: 37, 61 and 55 us for a
+// plain sweep, one with restriction, one with interpolation and norm (39, 71
+// and 64 in node order with every pass's weights loaded; loading two steps
+// ahead 43, 62 and 56); bound by the instructions of the passes, of which the
+// halo repeats as many again.
+template <typename T, int NS, int START, int TAIL, bool MASK, bool VK>
+__global__ void __launch_bounds__(VK ? kVkThreads : 1024) k_grid_sweep(GridSweep<T> g, GridTiles t, T h, T om, T omr) {
     constexpr int K = 2 * NS;
     constexpr bool RES = TAIL != kGridPlain;
     constexpr int NL = K + (RES ? 1 : 0);  // published results: pass 0 (the input) .. NL - 1
@@ -147,11 +159,43 @@ __global__ void __launch_bounds__(1024) k_grid_sweep(GridSweep<T> g, GridTiles t
     Load ld[2];
     issue(zs + 1, ld[1]);
     issue(zs + 2, ld[0]);
+    // edge weights of a step's passes: along x to the neighbouring thread's
+    // column and to the pair's other column, y - 1, y + 1, z - 1, z + 1
+    struct Edges {
+        T x, o, ym, yp, zm, zp;
+    };
+    Edges ew[VK ? NL : 1] = {}, keep[2] = {};
+    auto edges = [&](auto par, int z) {
+        if constexpr (VK) {
+            constexpr int X = decltype(par)::value;
+            const int xl = X == 0 ? yo : 1 - yo;
+            const bool right = (X == 0 ? dxA : -dxA) > 0;
+            const unsigned PH = (unsigned)P >> 1;
+            // (threads outside the tile and boundary nodes: any address of the grid)
+            const unsigned o = (off >> 1) + (in[X] ? 0u : 1u + PH);
+            const long long half = g.wstride >> 1;
+#pragma unroll
+            for (int k = 0; k < (NL > 2 ? 2 : NL); k++) {
+                const long long zp = (min(max(z - k, 1), N - 1)) * (S >> 1);
+                // the pass's own colour k & 1, and the other one
+                const T *wo = g.w + (k & 1 ? half : 0) + zp, *wn = g.w + (k & 1 ? 0 : half) + zp;
+                const T wr = wo[o], wl = wn[o + (unsigned)xl - 1u];
+                ew[k].x = right ? wr : wl;
+                ew[k].o = right ? wl : wr;
+                ew[k].yp = wo[g.wstride + o];
+                ew[k].ym = wn[g.wstride + o - PH];
+                ew[k].zp = wo[2 * g.wstride + o];
+                ew[k].zm = wn[2 * g.wstride + o - (S >> 1)];
+            }
+        }
+    };
+    edges(std::integral_constant<int, 0>(), zs);
     for (int q = tid; q < (NL - J0) * 2 * LS; q += (int)blockDim.x) lds[q] = T(0);
     __syncthreads();
 
     auto step = [&](auto par, int z) {
         constexpr int X = decltype(par)::value, Y = 1 - X;
+        if (VK && NL > 2) ew[VK && NL > 2 ? 2 : 0] = keep[X];
         // input of plane z + 1 (both columns), right-hand side of plane z
         Load &L = ld[X ^ 1];
         T in0[2], b0[2];
@@ -202,16 +246,30 @@ __global__ void __launch_bounds__(1024) k_grid_sweep(GridSweep<T> g, GridTiles t
                 rr = bh[X][0];
             } else {
                 ctr = k == 1 ? uc[X] : pv[X][k - 2];
-                const T a = ((nx[k - 1] + pv[Y][k - 1]) + (ny[k - 1] + nw[k - 1])) + (res[k - 1] + pv[X][k - 1]);
-                rr = bh[X][k - 1] - h * (T(6) * ctr - a);
+                if constexpr (VK) {
+                    const Edges &e = ew[k - 1];
+                    const T a = ((e.x * nx[k - 1] + e.o * pv[Y][k - 1]) + (e.ym * ny[k - 1] + e.yp * nw[k - 1])) +
+                                (e.zp * res[k - 1] + e.zm * pv[X][k - 1]);
+                    rr = bh[X][k - 1] - ((((e.x + e.o) + (e.ym + e.yp)) + (e.zm + e.zp)) * ctr - a);
+                } else {
+                    const T a = ((nx[k - 1] + pv[Y][k - 1]) + (ny[k - 1] + nw[k - 1])) + (res[k - 1] + pv[X][k - 1]);
+                    rr = bh[X][k - 1] - h * (T(6) * ctr - a);
+                }
             }
             if (k <= K) {
-                res[k] = up ? ctr + om * rr : ctr;
+                T scale = om;
+                if constexpr (VK) {
+                    const Edges &e = ew[k - 1];
+                    scale = om / (((e.x + e.o) + (e.ym + e.yp)) + (e.zm + e.zp));
+                }
+                res[k] = up ? ctr + scale * rr : ctr;
                 if (k == K) rlast = up ? omr * rr : T(0);
             } else {
                 rred = up ? rr : T(0);
             }
         }
+        if (VK) keep[X] = ew[0];
+        edges(std::integral_constant<int, Y>(), z + 1);
         // the pair of plane z - K + 1 is final: X black now, Y red in step z - 1
         const int zo = z - K + 1;
         if (own && zo >= Z0 && zo < Z1) {
@@ -268,8 +326,8 @@ __global__ void __launch_bounds__(1024) k_grid_sweep(GridSweep<T> g, GridTiles t
 // ---------------------------------------------------------------------------
 // The same march with no pass: step z publishes the pair of plane z + 1 and
 // evaluates plane z from the plane published in step z - 1.
-template <bool ADD, bool MASK>
-__global__ void __launch_bounds__(1024) k_grid_residual(GridResidual g, GridTiles t) {
+template <bool ADD, bool MASK, bool VK>
+__global__ void __launch_bounds__(VK ? kVkThreads : 1024) k_grid_residual(GridResidual g, GridTiles t) {
     const int N = g.N, P = N + 16;
     const long long S = (long long)P * N;
     const unsigned f = grid_xcd(blockIdx.x, gridDim.x);
@@ -327,8 +385,27 @@ __global__ void __launch_bounds__(1024) k_grid_residual(GridResidual g, GridTile
                 a0 = a0 && !(m & 0xffu);
                 a1 = a1 && !(m >> 8);
             }
-            const double r0 = bb.lo - h * (6.0 * uc.lo - (((xm + uc.hi) + (ym.lo + yp.lo)) + (um.lo + up.lo)));
-            const double r1 = bb.hi - h * (6.0 * uc.hi - (((uc.lo + xp) + (ym.hi + yp.hi)) + (um.hi + up.hi)));
+            double r0, r1;
+            if constexpr (VK) {
+                // colour-split weights: the pair's even node has the colour of y + z
+                // (a boundary row or plane reads the weights of a node inside)
+                const long long half = g.wstride >> 1, i = max(z, 1) * (S >> 1) + (off >> 1) + (y >= 1 ? 0 : P >> 1);
+                const int cl = (y + z) & 1;
+                const double *we = g.w + (cl ? half : 0) + i, *wo = g.w + (cl ? 0 : half) + i;
+                const double *wye = we + g.wstride, *wyo = wo + g.wstride, *wze = wye + g.wstride, *wzo = wyo + g.wstride;
+                const Pair<double> wx = {we[0], wo[0]}, wyp = {wye[0], wyo[0]}, wym = {wyo[-(P >> 1)], wye[-(P >> 1)]};
+                const Pair<double> wzp = {wze[0], wzo[0]}, wzm = {wzo[-(S >> 1)], wze[-(S >> 1)]};
+                const double wxm = wo[-1];
+                const double d0 = ((wxm + wx.lo) + (wym.lo + wyp.lo)) + (wzm.lo + wzp.lo);
+                const double d1 = ((wx.lo + wx.hi) + (wym.hi + wyp.hi)) + (wzm.hi + wzp.hi);
+                r0 = bb.lo - (d0 * uc.lo - (((wxm * xm + wx.lo * uc.hi) + (wym.lo * ym.lo + wyp.lo * yp.lo)) +
+                                            (wzm.lo * um.lo + wzp.lo * up.lo)));
+                r1 = bb.hi - (d1 * uc.hi - (((wx.lo * uc.lo + wx.hi * xp) + (wym.hi * ym.hi + wyp.hi * yp.hi)) +
+                                            (wzm.hi * um.hi + wzp.hi * up.hi)));
+            } else {
+                r0 = bb.lo - h * (6.0 * uc.lo - (((xm + uc.hi) + (ym.lo + yp.lo)) + (um.lo + up.lo)));
+                r1 = bb.hi - h * (6.0 * uc.hi - (((uc.lo + xp) + (ym.hi + yp.hi)) + (um.hi + up.hi)));
+            }
             Pair<double> r = {a0 ? r0 : 0.0, a1 ? r1 : 0.0};
             sum += r.lo * r.lo + r.hi * r.hi;
             if (ADD) *(Pair<double> *)(g.v + z * S + off) = uc;
@@ -356,12 +433,25 @@ __device__ __forceinline__ bool grid_node(int N, int &x, int &y, int &z) {
     return x < N && y < N;
 }
 
+// index of the weight of the edge from node (x, y, z) in its array
+__device__ __forceinline__ long long grid_weight(int N, long long ws, int x, int y, int z) {
+    return (((x + y + z) & 1) ? ws >> 1 : 0) + (x >> 1) + (long long)((N + 16) >> 1) * (y + (long long)N * z);
+}
+
 template <typename T>
-__global__ void __launch_bounds__(256) k_grid_plain_residual(int N, T h, const T *u, const T *b, T *r) {
+__global__ void __launch_bounds__(256) k_grid_plain_residual(int N, T h, const T *u, const T *b, const T *w, long long ws, T *r) {
     int x, y, z;
     if (!grid_node(N, x, y, z)) return;
     const int P = N + 16;
     const long long S = (long long)P * N, i = x + (long long)P * y + S * z;
+    if (w) {
+        const long long o = grid_weight(N, ws, x, y, z);
+        const T a = w[grid_weight(N, ws, x - 1, y, z)], c = w[o], d = w[ws + grid_weight(N, ws, x, y - 1, z)], e = w[ws + o];
+        const T f = w[2 * ws + grid_weight(N, ws, x, y, z - 1)], g = w[2 * ws + o];
+        r[i] = b[i] - ((((a + c) + (d + e)) + (f + g)) * u[i] -
+                       (((a * u[i - 1] + c * u[i + 1]) + (d * u[i - P] + e * u[i + P])) + (f * u[i - S] + g * u[i + S])));
+        return;
+    }
     r[i] = b[i] - h * (T(6) * u[i] - (((u[i - 1] + u[i + 1]) + (u[i - P] + u[i + P])) + (u[i - S] + u[i + S])));
 }
 
@@ -729,6 +819,43 @@ __global__ void __launch_bounds__(1024) k_grid_mass(int N, double h3, const doub
 }
 
 // ---------------------------------------------------------------------------
+// edge weights: (h/6) times the sum of k over the 6 elements whose axis path
+// holds the edge; zero at edges with an end outside the interior's
+// neighbourhood (never read)
+// ---------------------------------------------------------------------------
+template <int A>
+__device__ __forceinline__ double edge_sum(const double *k, int N, int x, int y, int z) {
+    constexpr int kP[6][3] = {{0, 1, 2}, {0, 2, 1}, {1, 0, 2}, {1, 2, 0}, {2, 0, 1}, {2, 1, 0}};
+    double s = 0.0;
+#pragma unroll
+    for (int d = 0; d < 8; d++) {
+        const int dl[3] = {d & 1, (d >> 1) & 1, (d >> 2) & 1};
+        if (dl[A]) continue;
+        const int ns = dl[0] + dl[1] + dl[2];
+        const long long cell = (x - dl[0]) + (long long)N * ((y - dl[1]) + (long long)N * (z - dl[2]));
+#pragma unroll
+        for (int q = 0; q < 6; q++) {
+            if (kP[q][ns] != A || (ns > 0 && !dl[kP[q][0]]) || (ns > 1 && !dl[kP[q][1]])) continue;
+            s += k[6 * cell + q];
+        }
+    }
+    return s;
+}
+__global__ void __launch_bounds__(256) k_grid_weights(int N, double h, const double *k, double *w, float *w32, long long ws) {
+    const int x = (int)(blockIdx.x * 64 + (threadIdx.x & 63)), y = (int)(blockIdx.y * 4 + (threadIdx.x >> 6)), z = (int)blockIdx.z;
+    if (x >= N || y >= N) return;
+    const long long i = grid_weight(N, ws, x, y, z);
+    const bool xi = x >= 1, yi = y >= 1, zi = z >= 1;
+    const double v[3] = {yi && zi ? edge_sum<0>(k, N, x, y, z) * h / 6.0 : 0.0, xi && zi ? edge_sum<1>(k, N, x, y, z) * h / 6.0 : 0.0,
+                         xi && yi ? edge_sum<2>(k, N, x, y, z) * h / 6.0 : 0.0};
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        w[a * ws + i] = v[a];
+        if (w32) w32[a * ws + i] = (float)v[a];
+    }
+}
+
+// ---------------------------------------------------------------------------
 // slot space <-> grid, and the nodes of single tetrahedra
 // ---------------------------------------------------------------------------
 // tetinfo: subcube corner V (3), first two axes a, b; closure node (i, j, k)
@@ -856,10 +983,19 @@ void sweep_mask(hipStream_t s, const GridTiles &t, const GridSweep<T> &g) {
     const size_t lds = sweep_lds(t, NS, START, TAIL, (int)sizeof(T));
     const T h = (T)g.h, om = (T)(g.omega / (6.0 * g.h)), omr = (T)(1.0 - g.omega);
     const dim3 grid((unsigned)t.blocks()), block((unsigned)grid_threads(t));
+    if constexpr (NS == 1) {
+        if (g.w) {
+            if (g.frz)
+                hipLaunchKernelGGL((k_grid_sweep<T, 1, START, TAIL, true, true>), grid, block, lds, s, g, t, h, (T)g.omega, omr);
+            else
+                hipLaunchKernelGGL((k_grid_sweep<T, 1, START, TAIL, false, true>), grid, block, lds, s, g, t, h, (T)g.omega, omr);
+            return;
+        }
+    }
     if (g.frz)
-        hipLaunchKernelGGL((k_grid_sweep<T, NS, START, TAIL, true>), grid, block, lds, s, g, t, h, om, omr);
+        hipLaunchKernelGGL((k_grid_sweep<T, NS, START, TAIL, true, false>), grid, block, lds, s, g, t, h, om, omr);
     else
-        hipLaunchKernelGGL((k_grid_sweep<T, NS, START, TAIL, false>), grid, block, lds, s, g, t, h, om, omr);
+        hipLaunchKernelGGL((k_grid_sweep<T, NS, START, TAIL, false, false>), grid, block, lds, s, g, t, h, om, omr);
 }
 
 template <typename T>
@@ -887,21 +1023,28 @@ void sweep_any(hipStream_t s, int ns, int start, int tail, const GridTiles &t, c
 void residual_any(hipStream_t s, const GridTiles &t, const GridResidual &g) {
     const size_t lds = sweep_lds(t, 0, kGridFromU, kGridResidual, 8);
     const dim3 grid((unsigned)t.blocks()), block((unsigned)grid_threads(t));
-    if (g.e && g.frz)
-        hipLaunchKernelGGL((k_grid_residual<true, true>), grid, block, lds, s, g, t);
-    else if (g.e)
-        hipLaunchKernelGGL((k_grid_residual<true, false>), grid, block, lds, s, g, t);
-    else if (g.frz)
-        hipLaunchKernelGGL((k_grid_residual<false, true>), grid, block, lds, s, g, t);
-    else
-        hipLaunchKernelGGL((k_grid_residual<false, false>), grid, block, lds, s, g, t);
+    auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, lds, s, g, t); };
+    if (g.w) {
+        if (g.e)
+            g.frz ? run(k_grid_residual<true, true, true>) : run(k_grid_residual<true, false, true>);
+        else
+            g.frz ? run(k_grid_residual<false, true, true>) : run(k_grid_residual<false, false, true>);
+    } else if (g.e) {
+        g.frz ? run(k_grid_residual<true, true, false>) : run(k_grid_residual<true, false, false>);
+    } else {
+        g.frz ? run(k_grid_residual<false, true, false>) : run(k_grid_residual<false, false, false>);
+    }
 }
 
 dim3 node_blocks(int N) { return dim3((unsigned)cdiv(N - 1, 64), (unsigned)cdiv(N - 1, 4), (unsigned)(N - 1)); }
 
 template <typename T>
-void plain_residual(hipStream_t s, int N, double h, const T *u, const T *b, T *r) {
-    hipLaunchKernelGGL((k_grid_plain_residual<T>), node_blocks(N), dim3(256), 0, s, N, (T)h, u, b, r);
+void plain_residual(hipStream_t s, int N, double h, const T *u, const T *b, const T *w, long long ws, T *r) {
+    hipLaunchKernelGGL((k_grid_plain_residual<T>), node_blocks(N), dim3(256), 0, s, N, (T)h, u, b, w, ws, r);
+}
+void weights(hipStream_t s, int N, double h, const double *k, double *w, float *w32, long long ws) {
+    hipLaunchKernelGGL(k_grid_weights, dim3((unsigned)cdiv(N, 64), (unsigned)cdiv(N, 4), (unsigned)N), dim3(256), 0, s, N, h, k, w,
+                       w32, ws);
 }
 template <typename T>
 void plain_restrict(hipStream_t s, int N, const T *r, T *bc) {
@@ -989,13 +1132,14 @@ void freeze_tets(hipStream_t s, int N, int m, const GridTets &t, unsigned char *
 //     one plain sweep: 105 us, 98 by this; N = 512: 730 us);
 //   latency: each step of the march costs about 0.4 us (barrier, LDS reads,
 //     a chain of passes), so small grids take thin tiles on many CUs.
-GridTiles tiles(int N, int ns, int start, int tail, int word) {
+GridTiles tiles(int N, int ns, int start, int tail, int word, bool vk) {
     const int K = tail == kGridResidual ? 0 : 2 * ns, np = N / 2;
     const int hz = halo_lo(K, tail) + K + 2;
     const double nodes = (double)N * N * N;
     const double wr = nodes * word / 4.0e6;
     // registers: 128 at two sweeps or with a tail, fewer otherwise
-    const int cap = ns >= 2 || tail == kGridRestrict || tail == kGridNorm ? 1024 : 1536;
+    const int cap = vk ? 768 : ns >= 2 || tail == kGridRestrict || tail == kGridNorm ? 1024 : 1536;
+    const int most = vk ? kVkThreads : 1024;
     GridTiles best;
     double bc = 1e300;
     for (int ntx = 1, vp0 = 0; ntx <= np; ntx++) {
@@ -1009,7 +1153,7 @@ GridTiles tiles(int N, int ns, int start, int tail, int word) {
             vy0 = vy;
             GridTiles t = grid_tiles_of(N, ns, tail, vp, cdiv(N, nty), N);
             const int th = grid_threads(t);
-            if (th > 1024) continue;
+            if (th > most) continue;
             const size_t lds = sweep_lds(t, ns, start, tail, word);
             if (lds > (size_t)160 * 1024) continue;
             const int bpc = std::max(1, std::min({cap / th, (int)((size_t)160 * 1024 / lds), 8}));
@@ -1024,7 +1168,7 @@ GridTiles tiles(int N, int ns, int start, int tail, int word) {
                 const double lat = rounds * steps * (0.32 + 0.0003 * th * res);
                 // threads resident on average
                 const double active = (double)blocks * th / (256.0 * rounds);
-                const double rd = (double)blocks * (vz + halo_lo(K, tail) + halo_hi(K, tail)) * t.tp * t.ty * 4 * word / 6.2e6;
+                const double rd = (double)blocks * (vz + halo_lo(K, tail) + halo_hi(K, tail)) * t.tp * t.ty * (vk ? 12 : 4) * word / 6.2e6;
                 const double bw = (wr + rd) * std::max(1.0, 768.0 / active);
                 const double cost = std::max(lat, bw) + 0.15 * std::min(lat, bw);
                 if (cost < bc) {
@@ -1056,6 +1200,7 @@ const GridOps kOps = {tiles,
                       to_user,
                       mass_load,
                       mass_user,
+                      weights,
                       to_closures,
                       from_closures,
                       to_masters,

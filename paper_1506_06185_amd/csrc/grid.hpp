@@ -1,13 +1,13 @@
-// Structured-grid path of the cube with k = 1: descriptors and launchers.
+// Structured-grid path of the cube: descriptors and launchers.
 //
-// The Kuhn tetrahedra tile the N^3 grid and the k = 1 operator couples a node
-// to its 6 axis neighbours with one stencil everywhere, so the unmasked and
-// the Dirichlet-Dirichlet cycles of such a context keep u and b of every
-// level as one grid, x fastest: node (x, y, z) at x + P (y + N z), 0 <= x,
-// y < N, 0 <= z <= N, with the Dirichlet nodes stored as zeros.  The row
-// pitch P exceeds N, and row y = N of a plane is row y = 0 of the next one,
-// so every neighbour of an interior node is a plain offset and a row's node
-// pairs (2p, 2p + 1) are aligned.
+// The Kuhn tetrahedra tile the N^3 grid and the operator couples a node to
+// its 6 axis neighbours (k = 1: one stencil everywhere; per-element k: a
+// weight per edge), so the unmasked and the Dirichlet-Dirichlet cycles keep u
+// and b of every level as one grid, x fastest: node (x, y, z) at
+// x + P (y + N z), 0 <= x, y < N, 0 <= z <= N, with the Dirichlet nodes stored
+// as zeros.  The row pitch P exceeds N, and row y = N of a plane is row y = 0
+// of the next one, so every neighbour of an interior node is a plain offset
+// and a row's node pairs (2p, 2p + 1) are aligned.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -42,9 +42,13 @@ struct GridTiles {
 // bc = P^T (b - A v) at the interior coarse nodes, kGridNorm leaves
 // per-workgroup sums of (b - A v)^2 in partial.  frz (optional): one byte per
 // node of the grid; nonzero nodes keep their values and do not count.
+// w (optional): per-element k, the weight of the edge from each node along
+// +x, then (w + wstride) +y, then +z; else k = 1.  Each of the three arrays
+// holds the nodes of even x + y + z, then (wstride / 2 on) the odd ones, node
+// (x, y, z) at (x >> 1) + (P / 2) (y + N z).
 // Built: ns = 1 from u (any tail), from zero (plain, restrict) and
-// interpolating (plain, norm); ns = 2 from zero (plain, restrict); norms in
-// FP64 only.
+// interpolating (plain, norm); ns = 2 from zero with k = 1 (plain, restrict);
+// norms in FP64 only.
 template <typename T>
 struct GridSweep {
     int N = 0;
@@ -56,6 +60,8 @@ struct GridSweep {
     T *bc = nullptr;
     const unsigned char *frz = nullptr;
     double *partial = nullptr;
+    const T *w = nullptr;
+    long long wstride = 0;
 };
 
 // r = b - A (u + e): e (optional) is added first and u + e written to v; r
@@ -70,6 +76,8 @@ struct GridResidual {
     float *r32 = nullptr;
     const unsigned char *frz = nullptr;
     double *partial = nullptr;
+    const double *w = nullptr;
+    long long wstride = 0;
 };
 
 // node list of volume containers in slot space (see VolGeom) and where their
@@ -101,13 +109,16 @@ int grid_threads(const GridTiles &t);
 // host logic also links without device code (it then keeps the cube's
 // vectors in slot space throughout).
 struct GridOps {
-    GridTiles (*tiles)(int N, int ns, int start, int tail, int word);
+    // vk: for launches with edge weights
+    GridTiles (*tiles)(int N, int ns, int start, int tail, int word, bool vk);
     void (*sweep64)(hipStream_t, int ns, int start, int tail, const GridTiles &, const GridSweep<double> &);
     void (*sweep32)(hipStream_t, int ns, int start, int tail, const GridTiles &, const GridSweep<float> &);
     void (*residual)(hipStream_t, const GridTiles &, const GridResidual &);
     // r = b - A u, bc = P^T r and v = u + P ec in plain form (sweep counts of zero)
-    void (*plain_residual64)(hipStream_t, int N, double h, const double *u, const double *b, double *r);
-    void (*plain_residual32)(hipStream_t, int N, double h, const float *u, const float *b, float *r);
+    void (*plain_residual64)(hipStream_t, int N, double h, const double *u, const double *b, const double *w,
+                             long long wstride, double *r);
+    void (*plain_residual32)(hipStream_t, int N, double h, const float *u, const float *b, const float *w,
+                             long long wstride, float *r);
     void (*plain_restrict64)(hipStream_t, int N, const double *r, double *bc);
     void (*plain_restrict32)(hipStream_t, int N, const float *r, float *bc);
     void (*plain_prolong64)(hipStream_t, int N, const double *u, const double *ec, double *v);
@@ -133,6 +144,9 @@ struct GridOps {
     // y = M x from the grid to vector order
     int (*mass_load)(hipStream_t, int N, double h, const double *f, double *grid, double *partial);
     void (*mass_user)(hipStream_t, int N, double h, const double *grid, double *user);
+    // edge weights of a level from its k per element (w, and rounded to w32 if
+    // not null)
+    void (*weights)(hipStream_t, int N, double h, const double *k, double *w, float *w32, long long wstride);
     // grid -> closures (list: every node; interior nodes get zero if
     // zero_interior), closures -> grid (list: interior nodes)
     void (*to_closures)(hipStream_t, const GridClosures &, bool zero_interior, const double *grid, double *vec);

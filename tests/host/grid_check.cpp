@@ -38,8 +38,22 @@ static std::vector<T> random_grid(int N, std::mt19937 &g) {
     return v;
 }
 
+// edge weights in node order -> split by colour
 template <typename T>
-static void run_case(int N, int ns, int start, int tail, bool mask, int vp, int vy, int vz, unsigned seed) {
+static std::vector<T> split(const Ref &r, const std::vector<T> &w) {
+    const long long L = grid_len(r.N);
+    std::vector<T> o(3 * L, T(0));
+    for (int a = 0; a < 3; a++)
+        for (int z = 0; z < r.N; z++)
+            for (int y = 0; y < r.N; y++)
+                for (int x = 0; x < r.N; x++)
+                    o[a * L + (((x + y + z) & 1) ? L / 2 : 0) + (x >> 1) + (long long)(r.P / 2) * (y + (long long)r.N * z)] =
+                        w[a * L + r.at(x, y, z)];
+    return o;
+}
+
+template <typename T>
+static void run_case(int N, int ns, int start, int tail, bool mask, int vp, int vy, int vz, unsigned seed, bool vk = false) {
     std::mt19937 g(seed);
     const Ref r(N), rc(N / 2);
     const std::vector<T> u = random_grid<T>(N, g), b = random_grid<T>(N, g);
@@ -68,14 +82,27 @@ static void run_case(int N, int ns, int start, int tail, bool mask, int vp, int 
                 for (int x = 1; x < N; x++)
                     w[r.at(x, y, z)] += 0.5 * ((double)e[rc.at(x / 2, y / 2, z / 2)] +
                                                (double)e[rc.at((x + 1) / 2, (y + 1) / 2, (z + 1) / 2)]);
+    // edge weights: random around h, or h
+    std::vector<T> ew(3 * grid_len(N), T(0));
+    std::uniform_real_distribution<double> wd(0.2, 3.0);
+    if (vk)
+        for (auto &x : ew) x = (T)(h * wd(g));
+    const long long L = grid_len(N);
+    auto diag = [&](long long i) {
+        return vk ? (double)ew[i] + ew[i - 1] + ew[L + i] + ew[L + i - r.P] + ew[2 * L + i] + ew[2 * L + i - r.S] : 6.0 * h;
+    };
     auto rr = [&](long long i) {
+        if (vk)
+            return (double)b[i] - (diag(i) * w[i] - (ew[i] * w[i + 1] + ew[i - 1] * w[i - 1] + ew[L + i] * w[i + r.P] +
+                                                     ew[L + i - r.P] * w[i - r.P] + ew[2 * L + i] * w[i + r.S] +
+                                                     ew[2 * L + i - r.S] * w[i - r.S]));
         return (double)b[i] - h * (6.0 * w[i] - (w[i - 1] + w[i + 1] + w[i - r.P] + w[i + r.P] + w[i - r.S] + w[i + r.S]));
     };
     for (int q = 0; q < 2 * ns; q++)
         for (int z = 1; z < N; z++)
             for (int y = 1; y < N; y++)
                 for (int x = 1; x < N; x++)
-                    if (((x + y + z) & 1) == (q & 1) && !frozen(r.at(x, y, z))) w[r.at(x, y, z)] += omega / (6.0 * h) * rr(r.at(x, y, z));
+                    if (((x + y + z) & 1) == (q & 1) && !frozen(r.at(x, y, z))) w[r.at(x, y, z)] += omega / diag(r.at(x, y, z)) * rr(r.at(x, y, z));
     std::vector<double> res(w.size(), 0.0);
     double norm = 0.0;
     for (int z = 1; z < N; z++)
@@ -101,6 +128,9 @@ static void run_case(int N, int ns, int start, int tail, bool mask, int vp, int 
     gs.bc = bc.data();
     gs.frz = mask ? fz.data() : nullptr;
     gs.partial = part.data();
+    const std::vector<T> es = split(r, ew);
+    gs.w = vk ? es.data() : nullptr;
+    gs.wstride = L;
     if constexpr (sizeof(T) == 8)
         grid_ops()->sweep64(nullptr, ns, start, tail, t, gs);
     else
@@ -138,7 +168,7 @@ static void run_case(int N, int ns, int start, int tail, bool mask, int vp, int 
     }
     cases++;
     if (!ok) {
-        std::printf("FAIL N=%d ns=%d start=%d tail=%d mask=%d tile %d %d %d word %zu: u %.2e bc %.2e norm %.2e\n", N, ns, start,
+        std::printf("FAIL vk=%d N=%d ns=%d start=%d tail=%d mask=%d tile %d %d %d word %zu: u %.2e bc %.2e norm %.2e\n", vk, N, ns, start,
                     tail, mask, vp, vy, vz, sizeof(T), err, erc, ern);
         fails++;
     }
@@ -152,7 +182,7 @@ static void check(bool ok, const char *what, int N, double err) {
     }
 }
 
-static void run_residual(int N, bool add, bool mask, int vp, int vy, int vz, unsigned seed) {
+static void run_residual(int N, bool add, bool mask, bool vk, int vp, int vy, int vz, unsigned seed) {
     std::mt19937 g(seed);
     const Ref r(N);
     const std::vector<double> u = random_grid<double>(N, g), b = random_grid<double>(N, g);
@@ -176,6 +206,13 @@ static void run_residual(int N, bool add, bool mask, int vp, int vy, int vz, uns
     q.r32 = r32.data();
     q.frz = mask ? fz.data() : nullptr;
     q.partial = part.data();
+    const long long L = grid_len(N);
+    std::vector<double> ew(3 * L, 0.0);
+    std::uniform_real_distribution<double> wd(0.2, 3.0);
+    for (auto &x : ew) x = vk ? wd(g) / N : 1.0 / N;
+    const std::vector<double> es = split(r, ew);
+    q.w = vk ? es.data() : nullptr;
+    q.wstride = L;
     grid_ops()->residual(nullptr, t, q);
     std::vector<double> w(u);
     if (add)
@@ -187,7 +224,8 @@ static void run_residual(int N, bool add, bool mask, int vp, int vy, int vz, uns
                 const long long i = r.at(x, y, z);
                 double s = 0.0;
                 if (x && y && z && !fz[i])
-                    s = b[i] - (6.0 * w[i] - (w[i - 1] + w[i + 1] + w[i - r.P] + w[i + r.P] + w[i - r.S] + w[i + r.S])) / N;
+                    s = b[i] + ew[i - 1] * (w[i - 1] - w[i]) + ew[i] * (w[i + 1] - w[i]) + ew[L + i - r.P] * (w[i - r.P] - w[i]) +
+                        ew[L + i] * (w[i + r.P] - w[i]) + ew[2 * L + i - r.S] * (w[i - r.S] - w[i]) + ew[2 * L + i] * (w[i + r.S] - w[i]);
                 norm += s * s;
                 err = std::max({err, std::fabs(s - r64[i]), std::fabs((float)s - r32[i]) * 1e-7, add ? std::fabs(w[i] - v[i]) : 0.0});
             }
@@ -243,7 +281,7 @@ static std::vector<double> launches(int N, int Nc, int pre, int post, const std:
         u.swap(v);
     };
     for (int k = 0; k < pre; k++) sweep(kGridFromU);
-    o.plain_residual64(nullptr, N, 1.0 / N, u.data(), b.data(), r.data());
+    o.plain_residual64(nullptr, N, 1.0 / N, u.data(), b.data(), nullptr, 0, r.data());
     o.plain_restrict64(nullptr, N, r.data(), bc.data());
     const std::vector<double> e = launches(N / 2, Nc, pre, post, bc, std::vector<double>(bc.size(), 0.0), st);
     o.plain_prolong64(nullptr, N, u.data(), e.data(), v.data());
@@ -262,7 +300,7 @@ static void run_tail(int N, int Nc, int pre, int post, bool finest, unsigned see
     }
     const std::vector<double> w = launches(N, Nc, pre, post, b, finest ? u : std::vector<double>(u.size(), 0.0), st);
     std::vector<double> r(u.size(), 0.0);
-    grid_ops()->plain_residual64(nullptr, N, 1.0 / N, w.data(), b.data(), r.data());
+    grid_ops()->plain_residual64(nullptr, N, 1.0 / N, w.data(), b.data(), nullptr, 0, r.data());
     double norm = -1.0, ref = 0.0, err = 0.0;
     for (double x : r) ref += x * x;
     grid_ops()->tail64(nullptr, N, Nc, pre, post, 1.0 / N, 1.25, st.data(), b.data(), u.data(), finest ? &norm : nullptr);
@@ -278,9 +316,10 @@ int main() {
         for (auto &k : kinds) {
             run_case<double>(sh[0], k[0], k[1], k[2], false, sh[1], sh[2], sh[3], seed++);
             run_case<double>(sh[0], k[0], k[1], k[2], true, sh[1], sh[2], sh[3], seed++);
+            if (k[0] == 1) run_case<double>(sh[0], 1, k[1], k[2], (seed & 1) != 0, sh[1], sh[2], sh[3], seed, true), seed++;
             if (k[2] != kGridNorm) run_case<float>(sh[0], k[0], k[1], k[2], (seed & 1) != 0, sh[1], sh[2], sh[3], seed++);
         }
-        for (int q = 0; q < 4; q++) run_residual(sh[0], q & 1, q >> 1, sh[1], sh[2], sh[3], seed++);
+        for (int q = 0; q < 8; q++) run_residual(sh[0], q & 1, (q >> 1) & 1, q >> 2, sh[1], sh[2], sh[3], seed++);
     }
     run_tail(16, 8, 2, 1, false, seed++);
     run_tail(16, 4, 2, 1, true, seed++);
@@ -291,7 +330,7 @@ int main() {
     // every chosen tiling fits a workgroup, from the smallest grid to the largest of one GPU
     for (int N : {8, 12, 16, 24, 48, 64, 96, 128, 192, 256, 384, 512, 768})
         for (auto &k : kinds) {
-            const GridTiles t = grid_ops()->tiles(N, k[0], k[1], k[2], 8);
+            const GridTiles t = grid_ops()->tiles(N, k[0], k[1], k[2], 8, false);
             const bool ok = grid_threads(t) <= 1024 && t.ntx * t.vp >= N / 2 && t.nty * t.vy >= N && t.ntz * t.vz >= N &&
                             t.blocks() <= std::max(N * N / 4, 65536);
             check(ok, "tiles", N, t.blocks());
