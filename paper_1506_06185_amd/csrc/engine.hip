@@ -193,7 +193,10 @@ struct hhgr_ctx {
     unsigned int *counter = nullptr;  // [2] last-block detection of the norm reductions
     int partial_cap = 0;
     double *dnorm = nullptr;
-    double *hnorm = nullptr;  // pinned, or hnorm_local in a context without HIP objects of its own
+    // squared norms read by the host: pinned memory that the kernels write
+    // themselves (dnorm is the same memory then), or hnorm_local, copied from
+    // dnorm, in a context without HIP objects of its own
+    double *hnorm = nullptr;
     double hnorm_local[8] = {};
     int *tetinfo = nullptr;
     // coarsest level
@@ -285,7 +288,6 @@ struct hhgr_batch {
     };
     Step step[2];
     int step_next = 0;
-    double *hnorm = nullptr;        // pinned, one per member
 };
 
 namespace hhgr {
@@ -1456,7 +1458,8 @@ void step_mixed(hhgr_ctx &c, const HView<double> &V64, const HView<float> &V32, 
 }
 
 int read_norm(hhgr_ctx &c, int slot, double *out) {
-    HIPCHK(hipMemcpyAsync(c.hnorm + slot, c.dnorm + slot, sizeof(double), hipMemcpyDeviceToHost, c.stream));
+    if (c.hnorm != c.dnorm)
+        HIPCHK(hipMemcpyAsync(c.hnorm + slot, c.dnorm + slot, sizeof(double), hipMemcpyDeviceToHost, c.stream));
     HIPCHK(hipStreamSynchronize(c.stream));
     *out = std::sqrt(std::max(c.hnorm[slot], 0.0));
     return HHGR_OK;
@@ -1473,7 +1476,7 @@ void invalidate_graph(hhgr_ctx &c) {
 }
 
 // enqueue one global step (FP64 cycle or mixed refinement step) ending with
-// the residual norm in dnorm[0] copied to hnorm[0]
+// the squared residual norm in dnorm[0] and hnorm[0]
 void enqueue_step(hhgr_ctx &c, hipStream_t s) {
     HView<double> V64 = global_view<double>(c, false, 0);
     if (c.go) {
@@ -1484,7 +1487,7 @@ void enqueue_step(hhgr_ctx &c, hipStream_t s) {
     } else {
         step_fp64(c, V64, s, 0);
     }
-    hipMemcpyAsync(c.hnorm, c.dnorm, sizeof(double), hipMemcpyDeviceToHost, s);
+    if (c.hnorm != c.dnorm) hipMemcpyAsync(c.hnorm, c.dnorm, sizeof(double), hipMemcpyDeviceToHost, s);
 }
 
 // whether a step ends in the other buffer of the finest u than it starts from
@@ -2076,6 +2079,7 @@ int create_ctx(const hhgr_desc *desc, std::shared_ptr<const Topology> mesh_topo,
             return bail(fail(HHGR_EHIP, "event create"));
         if (hipHostMalloc((void **)&c->hnorm, 8 * sizeof(double), hipHostMallocDefault) != hipSuccess)
             return bail(fail(HHGR_EHIP, "pinned host allocation"));
+        c->dnorm = c->hnorm;
     } else {
         c->hnorm = c->hnorm_local;
     }
@@ -3413,8 +3417,6 @@ int hhgr_batch_create(hhgr_ctx **ctxs, int n, void *hip_stream, hhgr_batch **out
     for (auto *evs : {&b->ev, &b->evl})
         for (auto &e : *evs)
             if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) return bail("event create");
-    if (hipHostMalloc((void **)&b->hnorm, sizeof(double) * n, hipHostMallocDefault) != hipSuccess)
-        return bail("pinned host allocation");
     *out = b;
     return HHGR_OK;
 }
@@ -3431,7 +3433,6 @@ void hhgr_batch_destroy(hhgr_batch *b) {
     for (auto *evs : {&b->ev, &b->evl})
         for (auto e : *evs)
             if (e) hipEventDestroy(e);
-    if (b->hnorm) hipHostFree(b->hnorm);
     delete b;
 }
 
@@ -3482,13 +3483,12 @@ int hhgr_batch_run(hhgr_batch *b, double rel_tol, int max_cycles, hhgr_report *r
             grid_residual(*c, false, nullptr, nullptr, b->stream, c->dnorm);
         else
             finest_residual<double>(*c, V, (double *)nullptr, b->stream, c->dnorm);
-        HIPCHK(hipMemcpyAsync(b->hnorm + q, c->dnorm, sizeof(double), hipMemcpyDeviceToHost, b->stream));
     }
     CHKLAUNCH();
     HIPCHK(hipStreamSynchronize(b->stream));
     auto in_dd = [&](int q) { return b->dd[q].armed && b->dd[q].step < std::max(b->dd[q].n_intact, 1); };
     for (int q = 0; q < n; q++) {
-        rel[q] = b->ctx[q]->bnorm > 0 ? std::sqrt(std::max(b->hnorm[q], 0.0)) / b->ctx[q]->bnorm : 0.0;
+        rel[q] = b->ctx[q]->bnorm > 0 ? std::sqrt(std::max(b->ctx[q]->hnorm[0], 0.0)) / b->ctx[q]->bnorm : 0.0;
         if (reps && reps[q].history && reps[q].history_cap > 0) reps[q].history[0] = rel[q];
         if ((rel[q] > rel_tol || in_dd(q)) && max_cycles > 0) active.push_back(q);
     }
@@ -3543,7 +3543,6 @@ int hhgr_batch_run(hhgr_batch *b, double rel_tol, int max_cycles, hhgr_report *r
                     if (mode & kModeMasked) dd_intact_step(*c, s, b->dd[q].step == 0, true, 0);
                     if ((mode & kModeFinal) && !(mode & kModeLocal)) dd_final_norm(*c, s);
                 }
-                hipMemcpyAsync(b->hnorm + q, c->dnorm, sizeof(double), hipMemcpyDeviceToHost, s);
                 c->cur = sig[3 * a + 2];  // nothing has run yet
                 hipEventRecord(b->ev[1 + q], s);
                 hipStreamWaitEvent(b->cap, b->ev[1 + q], 0);
@@ -3585,7 +3584,6 @@ int hhgr_batch_run(hhgr_batch *b, double rel_tol, int max_cycles, hhgr_report *r
             if (mode & kModeFinal) {
                 hhgr_ctx *c = b->ctx[q];
                 dd_final_norm(*c, b->stream);
-                HIPCHK(hipMemcpyAsync(b->hnorm + q, c->dnorm, sizeof(double), hipMemcpyDeviceToHost, b->stream));
             }
         }
         CHKLAUNCH();
@@ -3595,7 +3593,7 @@ int hhgr_batch_run(hhgr_batch *b, double rel_tol, int max_cycles, hhgr_report *r
             const int q = sig[3 * a], mode = sig[3 * a + 1];
             // during a recovery the norm is that of the intact part's residual;
             // a step without an intact cycle (local recovery only) is not a cycle
-            rel[q] = b->ctx[q]->bnorm > 0 ? std::sqrt(std::max(b->hnorm[q], 0.0)) / b->ctx[q]->bnorm : 0.0;
+            rel[q] = b->ctx[q]->bnorm > 0 ? std::sqrt(std::max(b->ctx[q]->hnorm[0], 0.0)) / b->ctx[q]->bnorm : 0.0;
             if (mode == 0 || (mode & kModeMasked)) {
                 cyc[q]++;
                 if (reps && reps[q].history && cyc[q] < reps[q].history_cap) reps[q].history[cyc[q]] = rel[q];

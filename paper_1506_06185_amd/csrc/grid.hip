@@ -529,23 +529,41 @@ __global__ void __launch_bounds__(512) k_grid_coarse(int N, const double *st, co
 // workgroup runs every pass of these levels in LDS: u of a level lives there
 // with its zero boundary, b and (while the level's residual takes its place)
 // u in the registers of the threads that own the nodes.  A thread owns pairs
-// of nodes (2p, 2p + 1), one of each colour.
+// of nodes (2p, 2p + 1), one of each colour; the LDS holds the colours apart,
+// node (x, y, z) of colour c at c H + (x >> 1) + (N / 2 + 1) (y + (N + 1) z),
+// so a pass reads and writes consecutive words.  16 us from zero at N = 16, bound
+// by about 25 barriers and the latency between them (with the nodes in grid
+// order in LDS, half of its banks idle, 17 us).
 constexpr int kTailN = 16, kTailThreads = 1024;
-constexpr int kTailLen = (kTailN + 2) * (kTailN + 1) * (kTailN + 1);
-constexpr __host__ __device__ int tail_len(int N) { return (N + 2) * (N + 1) * (N + 1); }
+constexpr __host__ __device__ int tail_half(int N) { return (N / 2 + 1) * (N + 1) * (N + 1); }
+constexpr __host__ __device__ int tail_len(int N) { return 2 * tail_half(N); }
 
 struct TailLds {
     double *A, *B, *S;  // sine transforms of the coarsest level
     double *red;
 };
 
+// index of node (x, y, z) in the colour-split layout of a level
+__device__ __forceinline__ int tail_at(int N, int x, int y, int z) {
+    return ((x + y + z) & 1) * tail_half(N) + (x >> 1) + (N / 2 + 1) * (y + (N + 1) * z);
+}
+// sum of the 6 neighbours of the pair's node o (0: 2p, 1: 2p + 1) of colour
+// c; i: the pair's index, mate: the pair's other node
+template <typename T>
+__device__ __forceinline__ T tail_around(const T *lv, int N, int i, int c, int o, T mate) {
+    const int PH = N / 2 + 1, SH = PH * (N + 1);
+    const T *v = lv + (c ? 0 : tail_half(N)) + i;
+    return ((mate + v[o ? 1 : -1]) + (v[-PH] + v[PH])) + (v[-SH] + v[SH]);
+}
+
 // NP: pairs per thread; lv: this level's u, then the coarser levels'; bl: the
-// restricted right-hand side of the next coarser level
+// restricted right-hand side of the next coarser level, in grid order
 template <typename T, int NP>
 __device__ __forceinline__ void tail_level(int N, int Nc, const T (&b)[NP][2], T (&u)[NP][2], bool zero, T h, T om, int nu_pre,
                                            int nu_post, T *lv, T *bl, const TailLds &q) {
     const int tid = (int)threadIdx.x, nt = (int)blockDim.x;
-    const int Pl = N + 2, Sl = Pl * (N + 1), np = N / 2, npairs = np * (N - 1) * (N - 1);
+    const int PH = N / 2 + 1, H = tail_half(N), np = N / 2, npairs = np * (N - 1) * (N - 1);
+    const int safe = PH * (N + 2) + 1;  // an interior pair
     int idx[NP], par[NP];
     bool act[NP], lo[NP];
 #pragma unroll
@@ -553,7 +571,7 @@ __device__ __forceinline__ void tail_level(int N, int Nc, const T (&b)[NP][2], T
         const int k = tid + s * nt;
         act[s] = k < npairs;
         const int p = k % np, y = (k / np) % (N - 1) + 1, z = k / (np * (N - 1)) + 1;
-        idx[s] = act[s] ? 2 * p + Pl * y + Sl * z : 0;
+        idx[s] = act[s] ? p + PH * (y + (N + 1) * z) : safe;
         par[s] = (y + z) & 1;
         lo[s] = act[s] && p > 0;
     }
@@ -562,22 +580,21 @@ __device__ __forceinline__ void tail_level(int N, int Nc, const T (&b)[NP][2], T
     auto put = [&](const T(&v)[NP][2]) {
 #pragma unroll
         for (int s = 0; s < NP; s++) {
-            if (lo[s]) lv[idx[s]] = v[s][0];
-            if (act[s]) lv[idx[s] + 1] = v[s][1];
+            if (lo[s]) lv[par[s] * H + idx[s]] = v[s][0];
+            if (act[s]) lv[(1 - par[s]) * H + idx[s]] = v[s][1];
         }
         __syncthreads();
     };
-    auto around = [&](int i) { return ((lv[i - 1] + lv[i + 1]) + (lv[i - Pl] + lv[i + Pl])) + (lv[i - Sl] + lv[i + Sl]); };
     auto sweep = [&]() {
         for (int c = 0; c < 2; c++) {
 #pragma unroll
             for (int s = 0; s < NP; s++) {
                 const int o = par[s] ^ c;  // the pair's node of colour c
                 const bool on = o ? act[s] : lo[s];
-                const int i = on ? idx[s] + o : Sl + Pl + 1;
-                const T ctr = o ? u[s][1] : u[s][0], bb = o ? b[s][1] : b[s][0];
-                const T n = ctr + om * (bb - h * (T(6) * ctr - around(i)));
-                if (on) lv[i] = n;
+                const int i = on ? idx[s] : safe;
+                const T ctr = o ? u[s][1] : u[s][0], mate = o ? u[s][0] : u[s][1], bb = o ? b[s][1] : b[s][0];
+                const T n = ctr + om * (bb - h * (T(6) * ctr - tail_around(lv, N, i, c, o, mate)));
+                if (on) lv[c * H + i] = n;
                 u[s][0] = on && !o ? n : u[s][0];
                 u[s][1] = on && o ? n : u[s][1];
             }
@@ -596,20 +613,23 @@ __device__ __forceinline__ void tail_level(int N, int Nc, const T (&b)[NP][2], T
     for (int s = 0; s < NP; s++)
 #pragma unroll
         for (int o = 0; o < 2; o++) {
-            const int i = (o ? act[s] : lo[s]) ? idx[s] + o : Sl + Pl + 1;
-            r[s][o] = b[s][o] - h * (T(6) * u[s][o] - around(i));
+            const int i = (o ? act[s] : lo[s]) ? idx[s] : safe;
+            r[s][o] = b[s][o] - h * (T(6) * u[s][o] - tail_around(lv, N, i, par[s] ^ o, o, u[s][1 - o]));
         }
     __syncthreads();
     put(r);
-    // restriction to the coarser level, in its layout
+    // restriction to the coarser level
     const int M = N / 2, Pm = M + 2, Sm = Pm * (M + 1), nm = M - 1;
     T *const lc = lv + tail_len(N);
     for (int k = tid; k < nm * nm * nm; k += nt) {
         const int x = k % nm + 1, y = (k / nm) % nm + 1, z = k / (nm * nm) + 1;
-        const T *c = lv + 2 * (x + Pl * y + Sl * z);
-        auto two = [&](int d) { return c[d] + c[-d]; };
-        const T v = c[0] + T(0.5) * (((two(1) + two(Pl)) + (two(Sl) + two(1 + Pl))) +
-                                     ((two(Pl + Sl) + two(1 + Sl)) + two(1 + Pl + Sl)));
+        // fine node (2x, 2y, 2z), colour 0; an offset of odd sum is colour 1,
+        // an odd step down in x is the pair before
+        const T *e = lv + x + PH * (2 * y + 2 * (N + 1) * z), *o = e + H;
+        const int Y = PH, Z = PH * (N + 1);
+        const T s1 = ((o[0] + o[-1]) + (o[Y] + o[-Y])) + (o[Z] + o[-Z]);
+        const T s2 = ((e[Y] + e[-1 - Y]) + (e[Y + Z] + e[-Y - Z])) + (e[Z] + e[-1 - Z]);
+        const T v = e[0] + T(0.5) * ((s1 + s2) + (o[Y + Z] + o[-1 - Y - Z]));
         bl[x + Pm * y + Sm * z] = v;
     }
     __syncthreads();
@@ -632,7 +652,7 @@ __device__ __forceinline__ void tail_level(int N, int Nc, const T (&b)[NP][2], T
         each([&](int k, int, int y, int) { sine_axis(nm, nm, k, y, q.S, q.A, q.B); });
         each([&](int k, int x, int y, int z) {
             sine_axis(nm, n2, k, z, q.S, q.B, q.A);
-            lc[(x + 1) + Pm * (y + 1) + Sm * (z + 1)] = (T)q.A[k];
+            lc[tail_at(M, x + 1, y + 1, z + 1)] = (T)q.A[k];
         });
         __syncthreads();
     } else if constexpr (NP > 1) {
@@ -640,7 +660,7 @@ __device__ __forceinline__ void tail_level(int N, int Nc, const T (&b)[NP][2], T
         T bm[1][2], um[1][2];
         const int k = tid, mp = M / 2;
         const bool on = k < mp * nm * nm;
-        const int i = 2 * (k % mp) + Pm * ((k / mp) % nm + 1) + Sm * (k / (mp * nm) + 1);
+        const int i = on ? 2 * (k % mp) + Pm * ((k / mp) % nm + 1) + Sm * (k / (mp * nm) + 1) : 0;
         bm[0][0] = on && k % mp > 0 ? bl[i] : T(0);
         bm[0][1] = on ? bl[i + 1] : T(0);
         um[0][0] = um[0][1] = T(0);
@@ -650,13 +670,12 @@ __device__ __forceinline__ void tail_level(int N, int Nc, const T (&b)[NP][2], T
     // interpolation from lc
 #pragma unroll
     for (int s = 0; s < NP; s++) {
-        const int i = idx[s], z = i / Sl, y = (i - z * Sl) / Pl, x = i - z * Sl - y * Pl;
-        const T e0 = lc[(x >> 1) + Pm * (y >> 1) + Sm * (z >> 1)];
-        const T *eh = lc + (x >> 1) + Pm * ((y + 1) >> 1) + Sm * ((z + 1) >> 1);
-        if (act[s]) {
-            u[s][0] += T(0.5) * (e0 + eh[0]);
-            u[s][1] += T(0.5) * (e0 + eh[1]);
-        }
+        const int k = act[s] ? tid + s * nt : 0;
+        const int x = 2 * (k % np), y = (k / np) % (N - 1) + 1, z = k / (np * (N - 1)) + 1;
+        const T e0 = lc[tail_at(M, x >> 1, y >> 1, z >> 1)];
+        const T e1 = lc[tail_at(M, x >> 1, (y + 1) >> 1, (z + 1) >> 1)], e2 = lc[tail_at(M, (x >> 1) + 1, (y + 1) >> 1, (z + 1) >> 1)];
+        if (lo[s]) u[s][0] += T(0.5) * (e0 + e1);
+        if (act[s]) u[s][1] += T(0.5) * (e0 + e2);
     }
     __syncthreads();
     put(u);
@@ -697,7 +716,6 @@ __global__ void __launch_bounds__(kTailThreads) k_grid_tail(int N, int Nc, int n
         }
     }
     tail_level<T, NP>(N, Nc, b, u, !FINEST, h, om, nu_pre, nu_post, lv, bl, q);
-    const int Pl = N + 2, Sl = Pl * (N + 1);
     double sum = 0.0;
 #pragma unroll
     for (int s = 0; s < NP; s++) {
@@ -709,12 +727,11 @@ __global__ void __launch_bounds__(kTailThreads) k_grid_tail(int N, int Nc, int n
         o.hi = u[s][1];
         *(Pair<T> *)(gu + 2 * p + P * (y + (long long)N * z)) = o;
         if (FINEST) {
-            const T *c = lv + 2 * p + Pl * y + Sl * z;
+            const int i = p + (N / 2 + 1) * (y + (N + 1) * z);
 #pragma unroll
             for (int e = 0; e < 2; e++) {
                 if (e == 0 && p == 0) continue;
-                const T *v = c + e;
-                const double r = (double)(b[s][e] - h * (T(6) * u[s][e] - (((v[-1] + v[1]) + (v[-Pl] + v[Pl])) + (v[-Sl] + v[Sl]))));
+                const double r = (double)(b[s][e] - h * (T(6) * u[s][e] - tail_around(lv, N, i, ((y + z) & 1) ^ e, e, u[s][1 - e])));
                 sum += r * r;
             }
         }
