@@ -154,6 +154,30 @@ __device__ __forceinline__ void block_sum2_dpp(double &a, double &b, double *sh)
     }
 }
 
+// ghost copies of a master: the list's bounds and its first four entries are
+// loaded as soon as the master is known, beside its stencil, so that the
+// stores do not wait for two more dependent loads after the update
+struct Copies {
+    int g0 = 0, g1 = 0, to[4] = {0, 0, 0, 0};
+};
+__device__ __forceinline__ Copies load_copies(const IfcGeom &ig, int t) {
+    Copies c;
+    if (ig.gptr) {
+        c.g0 = ig.gptr[t];
+        c.g1 = ig.gptr[t + 1];
+#pragma unroll
+        for (int e = 0; e < 4; e++) c.to[e] = c.g0 < c.g1 ? ig.gidx[c.g0 + e < c.g1 ? c.g0 + e : c.g1 - 1] : 0;
+    }
+    return c;
+}
+template <typename T>
+__device__ __forceinline__ void set_copies(const IfcGeom &ig, const Copies &c, T *__restrict__ u, T v) {
+#pragma unroll
+    for (int e = 0; e < 4; e++)
+        if (c.g0 + e < c.g1) u[c.to[e]] = v;
+    for (int g = c.g0 + 4; g < c.g1; g++) u[ig.gidx[g]] = v;
+}
+
 inline int ifc_blocks(const IfcGeom &ig, int bs) {
     const int n = ig.i1 - ig.i0;
     if (n <= 0) return 0;
@@ -575,13 +599,13 @@ __global__ void __launch_bounds__(512) k_colour15(VolGeom vg, IfcGeom ig, Gen15 
             const int t = g.ifcq[q];
             if (!(ig.frozen && ig.frozen[t])) {
                 const long long sl = ig.base + t;
+                const Copies cp = load_copies(ig, t);
                 const T uo = u[sl];
                 T diag;
                 const T rr = b[sl] - master_Au<T, VKI>(ig, g, u, t, uo, diag);
                 const T un = uo + omega * rr / diag;
                 u[sl] = un;
-                if (ig.gptr)
-                    for (int gq = ig.gptr[t]; gq < ig.gptr[t + 1]; gq++) u[ig.gidx[gq]] = un;
+                set_copies(ig, cp, u, un);
                 if (TAIL == kTailNorm) {
                     const double e = (1.0 - (double)omega) * (double)rr;
                     r2 = e * e;
