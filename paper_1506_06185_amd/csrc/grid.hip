@@ -1143,20 +1143,26 @@ void freeze_tets(hipStream_t s, int N, int m, const GridTets &t, unsigned char *
     if (t.n > 0) hipLaunchKernelGGL((k_grid_tets<true>), dim3(per * t.n), dim3(256), 0, s, N, m, t, (double *)nullptr, frz);
 }
 
-// Tile choice.  Measured times (N = 64 .. 512) follow two bounds:
-//   memory: what the tiles read (halo included) at 6.2 TB/s and the own nodes
-//     written at 4 TB/s, once about 768 threads per CU are resident (N = 256,
-//     one plain sweep: 105 us, 98 by this; N = 512: 730 us);
-//   latency: each step of the march costs about 0.4 us (barrier, LDS reads,
-//     a chain of passes), so small grids take thin tiles on many CUs.
+// Tile choice.  The time of a launch is modelled as the larger of two bounds
+// plus a part of the smaller; the constants are a fit to 400 measured launches
+// (N = 16 .. 512, every kind, FP64), whose fastest tiles the model misses by
+// 1 % on average:
+//   memory: what the tiles read, halo and partial lines at row ends included,
+//     at 8.8 TB/s (halo reads hit in L2 in part) and the own nodes written at
+//     4 TB/s; large grids need about 860 threads resident per CU for that;
+//   latency: a step of the march costs 0.2 to 0.6 us (barrier, LDS reads, the
+//     chain of passes), more with more threads on the CU, so small grids take
+//     thin tiles on many CUs.
+// At N = 256 a plain sweep takes 100 us (98 by the bounds), at N = 512 730.
 GridTiles tiles(int N, int ns, int start, int tail, int word, bool vk) {
     const int K = tail == kGridResidual ? 0 : 2 * ns, np = N / 2;
-    const int hz = halo_lo(K, tail) + K + 2;
-    const double nodes = (double)N * N * N;
-    const double wr = nodes * word / 4.0e6;
+    const int hl = halo_lo(K, tail), hh = halo_hi(K, tail);
+    const double wr = (double)N * N * N * word / 4.0e6;
     // registers: 128 at two sweeps or with a tail, fewer otherwise
     const int cap = vk ? 768 : ns >= 2 || tail == kGridRestrict || tail == kGridNorm ? 1024 : 1536;
     const int most = vk ? kVkThreads : 1024;
+    // words read per pair: u and b (from zero: b), and three edge weights
+    const double words = (start == kGridFromZero ? 2 : 4) + (vk ? 6 : 0);
     GridTiles best;
     double bc = 1e300;
     for (int ntx = 1, vp0 = 0; ntx <= np; ntx++) {
@@ -1168,7 +1174,7 @@ GridTiles tiles(int N, int ns, int start, int tail, int word, bool vk) {
             const int vy = (cdiv(N, nty) + 1) & ~1;
             if (vy == vy0) continue;
             vy0 = vy;
-            GridTiles t = grid_tiles_of(N, ns, tail, vp, cdiv(N, nty), N);
+            GridTiles t = grid_tiles_of(N, ns, tail, vp, vy, N);
             const int th = grid_threads(t);
             if (th > most) continue;
             const size_t lds = sweep_lds(t, ns, start, tail, word);
@@ -1181,13 +1187,12 @@ GridTiles tiles(int N, int ns, int start, int tail, int word, bool vk) {
                 t.vz = vz;
                 t.ntz = cdiv(N, vz);
                 const int blocks = t.blocks(), rounds = cdiv(blocks, 256 * bpc), res = std::min(bpc, cdiv(blocks, 256));
-                const double steps = vz + hz;
-                const double lat = rounds * steps * (0.32 + 0.0003 * th * res);
-                // threads resident on average
-                const double active = (double)blocks * th / (256.0 * rounds);
-                const double rd = (double)blocks * (vz + halo_lo(K, tail) + halo_hi(K, tail)) * t.tp * t.ty * (vk ? 12 : 4) * word / 6.2e6;
-                const double bw = (wr + rd) * std::max(1.0, 768.0 / active);
-                const double cost = std::max(lat, bw) + 0.15 * std::min(lat, bw);
+                const double step = 0.11 + 0.115 * K + (0.12 + 0.19 * K) * 1e-3 * th * res;
+                const double lat = rounds * (vz + hl + K + 3) * step * (vk ? 1.6 : 1.0);
+                double bw = wr + (double)blocks * (vz + hl + hh) * t.tp * t.ty * words * word * (1.0 + 60.0 / (2 * word * t.tp)) / 8.8e6;
+                const double active = (double)blocks * th / (256.0 * rounds);  // threads resident per CU on average
+                if (bw > 30.0) bw *= std::max(1.0, 860.0 / active);
+                const double cost = std::max(lat, bw) + 0.18 * std::min(lat, bw);
                 if (cost < bc) {
                     bc = cost;
                     best = t;
