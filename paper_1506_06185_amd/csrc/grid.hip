@@ -1215,6 +1215,8 @@ const GridOps kOps = {tiles,
                       plain_prolong<float>,
                       coarse<double>,
                       coarse<float>,
+                      launch_coarse_pcg_sine<double>,
+                      launch_coarse_pcg_sine<float>,
                       tail_fits,
                       tail_cycle<double>,
                       tail_cycle<float>,

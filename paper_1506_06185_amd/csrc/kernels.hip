@@ -21,6 +21,7 @@
 
 #include <cstdint>
 
+#include "grid.hpp"
 #include "kernels.hpp"
 
 namespace hhgr {
@@ -917,6 +918,136 @@ __global__ void __launch_bounds__(64) k_coarse_pcg_wave(int n, const long long *
         for (int c = cptr[q]; c < cptr[q + 1]; c++) u[cidx[c]] = xv;
     }
     if (tid == 0 && iters) *iters = it;
+}
+
+// PCG of the coarsest level of a cube on the grid (grid.hpp), preconditioned
+// with the k = 1 operator between the square roots of the diagonals: its
+// inverse is sine transforms along x, y and z.  The coarsest k is a mean over
+// many elements, so few iterations are left (Jacobi: 35 and more), each with
+// six short products in LDS.  ord: unknown of every interior grid node (x
+// fastest).  Latency binds it: about 12 barriers per iteration.  343 unknowns,
+// log-normal k: 25.5 us, with the Jacobi PCG above 45; with the closures of two
+// tetrahedra frozen, which the transforms know nothing of, 55 against 47
+template <typename T, int NPT>
+__global__ void __launch_bounds__(512) k_coarse_pcg_sine(int N, const int *__restrict__ ord, const double *__restrict__ val,
+                                                         const int *__restrict__ col,
+                                                         const unsigned char *__restrict__ frozen,
+                                                         const double *__restrict__ st, const T *__restrict__ b,
+                                                         T *__restrict__ u, double rtol, int maxit) {
+    constexpr int kMax = 512 * NPT;
+    __shared__ double P[kMax], A[kMax], B[kMax], S[11 * 12], red[2][16];
+    const int tid = threadIdx.x, nm = N - 1, n2 = nm * nm, n = n2 * nm;
+    const long long pitch = N + 16;
+    double x[NPT], r[NPT], p[NPT], dsi[NPT], dg[NPT], av[NPT][6], lam[NPT];
+    int cx[NPT], cy[NPT], cz[NPT];
+    long long at[NPT];
+    bool act[NPT];
+    for (int q = tid; q < n2 + nm; q += 512) S[q] = st[q];
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < NPT; s++) {
+        const int m = tid + 512 * s;
+        const bool in = m < n;
+        cx[s] = in ? m % nm : 0;
+        cy[s] = in ? (m / nm) % nm : 0;
+        cz[s] = in ? m / n2 : 0;
+        at[s] = (cx[s] + 1) + pitch * ((cy[s] + 1) + (long long)N * (cz[s] + 1));
+        const int q = in ? ord[m] : 0;
+        act[s] = in && !(frozen && frozen[q]);
+        dg[s] = act[s] ? val[7 * q] : 0.0;
+        dsi[s] = act[s] ? 1.0 / sqrt(dg[s]) : 0.0;
+        r[s] = act[s] ? (double)b[at[s]] : 0.0;
+        x[s] = 0.0;
+#pragma unroll
+        for (int e = 0; e < 6; e++) av[s][e] = act[s] && col[7 * q + 1 + e] >= 0 ? val[7 * q + 1 + e] : 0.0;
+        lam[s] = 6.0 / ((S[n2 + cx[s]] + S[n2 + cy[s]]) + S[n2 + cz[s]]);
+    }
+    // z = M^-1 r through A and B; every thread keeps its own entries
+    auto axis = [&](const double *in, int s, int stride, int c) {
+        const int m = tid + 512 * s;
+        double v = 0.0;
+        if (m < n) {
+            const double *a = in + m - c * stride;
+            for (int j = 0; j < nm; j++) v += S[c * nm + j] * a[j * stride];
+        }
+        return v;
+    };
+    double z[NPT];
+    auto precond = [&]() {
+        auto pass = [&](const double *in, double *out, int stride, int which, bool scale) {
+            __syncthreads();
+#pragma unroll
+            for (int s = 0; s < NPT; s++) {
+                const double v = axis(in, s, stride, which == 0 ? cx[s] : which == 1 ? cy[s] : cz[s]);
+                if (tid + 512 * s < n) out[tid + 512 * s] = scale ? v * lam[s] : v;
+            }
+        };
+#pragma unroll
+        for (int s = 0; s < NPT; s++)
+            if (tid + 512 * s < n) A[tid + 512 * s] = dsi[s] * r[s];
+        pass(A, B, 1, 0, false);
+        pass(B, A, nm, 1, false);
+        pass(A, B, n2, 2, true);
+        pass(B, A, 1, 0, false);
+        pass(A, B, nm, 1, false);
+        __syncthreads();
+#pragma unroll
+        for (int s = 0; s < NPT; s++) z[s] = dsi[s] * axis(B, s, n2, cz[s]);
+    };
+    precond();
+    double rz = 0.0, rr0 = 0.0;
+#pragma unroll
+    for (int s = 0; s < NPT; s++) {
+        rz += r[s] * z[s];
+        rr0 += r[s] * r[s];
+        p[s] = z[s];
+        if (tid + 512 * s < n) P[tid + 512 * s] = p[s];
+    }
+    block_sum2_dpp<8>(rz, rr0, red[1]);
+    if (rr0 > 0.0) {
+        const double stop = rtol * rtol * rr0;
+        for (int it = 1; it <= maxit; it++) {
+            __syncthreads();
+            double qv[NPT], pq = 0.0, dummy = 0.0;
+#pragma unroll
+            for (int s = 0; s < NPT; s++) {
+                const int m = tid + 512 * s;
+                // (a missing neighbour has weight zero and reads the node itself)
+                auto at1 = [&](bool has, int d) { return P[has ? m + d : (m < n ? m : 0)]; };
+                const bool in = m < n;
+                double a = dg[s] * p[s];
+                a += av[s][0] * at1(in && cx[s] + 1 < nm, 1) + av[s][1] * at1(in && cx[s] > 0, -1);
+                a += av[s][2] * at1(in && cy[s] + 1 < nm, nm) + av[s][3] * at1(in && cy[s] > 0, -nm);
+                a += av[s][4] * at1(in && cz[s] + 1 < nm, n2) + av[s][5] * at1(in && cz[s] > 0, -n2);
+                qv[s] = act[s] ? a : 0.0;
+                pq += p[s] * qv[s];
+            }
+            block_sum2_dpp<8>(pq, dummy, red[0]);
+            const double alpha = rz / pq;
+            double rr = 0.0, rz1 = 0.0;
+#pragma unroll
+            for (int s = 0; s < NPT; s++) {
+                x[s] += alpha * p[s];
+                r[s] -= alpha * qv[s];
+                rr += r[s] * r[s];
+            }
+            precond();
+#pragma unroll
+            for (int s = 0; s < NPT; s++) rz1 += r[s] * z[s];
+            block_sum2_dpp<8>(rr, rz1, red[1]);
+            if (rr <= stop) break;
+            const double beta = rz1 / rz;
+            rz = rz1;
+#pragma unroll
+            for (int s = 0; s < NPT; s++) {
+                p[s] = z[s] + beta * p[s];
+                if (tid + 512 * s < n) P[tid + 512 * s] = p[s];
+            }
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < NPT; s++)
+        if (act[s]) u[at[s]] = (T)x[s];
 }
 
 // coarsest level with a precomputed dense inverse (row-major n x n): one
@@ -1869,6 +2000,21 @@ void launch_coarse_pcg(hipStream_t s, int n, const long long *slot, const int *c
     else
         run(k_coarse_pcg<T, 8, 4>, 512);
 }
+
+template <typename T>
+void launch_coarse_pcg_sine(hipStream_t s, int N, const int *ord, const double *val, const int *col,
+                            const unsigned char *frozen, const double *st, const T *b, T *u, double rtol, int maxit) {
+    if (N <= 8)
+        hipLaunchKernelGGL((k_coarse_pcg_sine<T, 1>), dim3(1), dim3(512), 0, s, N, ord, val, col, frozen, st, b, u, rtol,
+                           maxit);
+    else
+        hipLaunchKernelGGL((k_coarse_pcg_sine<T, 3>), dim3(1), dim3(512), 0, s, N, ord, val, col, frozen, st, b, u, rtol,
+                           maxit);
+}
+template void launch_coarse_pcg_sine<double>(hipStream_t, int, const int *, const double *, const int *,
+                                             const unsigned char *, const double *, const double *, double *, double, int);
+template void launch_coarse_pcg_sine<float>(hipStream_t, int, const int *, const double *, const int *,
+                                            const unsigned char *, const double *, const float *, float *, double, int);
 
 template <typename T>
 void launch_coarse_dense(hipStream_t s, int n, const long long *slot, const double *inv, const T *b, T *u,
