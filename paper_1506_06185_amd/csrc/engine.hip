@@ -240,6 +240,8 @@ struct hhgr_ctx {
     double *gpartial = nullptr;
     double *gst = nullptr;  // sine transform of the coarsest level
     int *gord = nullptr;    // coarsest unknown of every interior node, x fastest
+    long long *gslot = nullptr;  // grid index of every coarsest unknown
+    int *gcptr = nullptr, *gcidx = nullptr;
     // graphs, by the buffer that the step starts from
     bool use_graph = false;
     hipGraphExec_t gexec[2] = {};
@@ -596,6 +598,10 @@ void carve(hhgr_ctx &c, Carver &cv) {
         const int n = tp.lev[c.Lc].N - 1;
         c.gst = cv.take<double>((size_t)n * n + n);
         c.gord = cv.take<int>(c.cn);
+        // grid index of every coarsest unknown, and the Jacobi PCG's lists of its copies
+        c.gslot = cv.take<long long>(2 * (size_t)c.cn + 1);
+        c.gcptr = c.gslot ? reinterpret_cast<int *>(c.gslot + c.cn) : nullptr;
+        c.gcidx = c.gcptr ? c.gcptr + c.cn + 1 : nullptr;
     }
     if (c.vk) {
         c.user_u = cv.take<double>(c.n_dofs);
@@ -1249,15 +1255,19 @@ int grid_cycle(hhgr_ctx &c, int l, bool zero, int q, bool masked, bool norm, hip
     LevelDev &D = c.lev[l];
     T *const u[2] = {gvec<T>(D, 0), gvec<T>(D, 1)}, *const b = gvec<T>(D, 2);
     if (l == c.Lc) {
-        const unsigned char *frz = masked ? c.cfrozen : nullptr;
-        if constexpr (std::is_same<T, double>::value) {
-            if (masked || c.vk)
-                o.coarse_pcg64(s, D.N, c.gord, c.cval, c.ccol, frz, c.gst, b, u[0], kCoarseRtol, kCoarseMaxit);
+        // frozen unknowns: the transforms know nothing of them, and the PCG that
+        // they precondition takes longer (55 us) than the Jacobi one (47)
+        if (masked)
+            launch_coarse_pcg<T>(s, c.cn, c.gslot, c.ccol, c.cval, c.cfrozen, b, u[0], c.gcptr, c.gcidx, kCoarseRtol,
+                                 kCoarseMaxit, c.citers);
+        else if constexpr (std::is_same<T, double>::value) {
+            if (c.vk)
+                o.coarse_pcg64(s, D.N, c.gord, c.cval, c.gst, b, u[0], kCoarseRtol, kCoarseMaxit);
             else
                 o.coarse64(s, D.N, c.gst, b, u[0]);
         } else {
-            if (masked || c.vk)
-                o.coarse_pcg32(s, D.N, c.gord, c.cval, c.ccol, frz, c.gst, b, u[0], kCoarseRtol, kCoarseMaxit);
+            if (c.vk)
+                o.coarse_pcg32(s, D.N, c.gord, c.cval, c.gst, b, u[0], kCoarseRtol, kCoarseMaxit);
             else
                 o.coarse32(s, D.N, c.gst, b, u[0]);
         }
@@ -2241,12 +2251,21 @@ int create_ctx(const hhgr_desc *desc, std::shared_ptr<const Topology> mesh_topo,
     }
     std::vector<double> gst;
     std::vector<int> gord(cs.n, 0);
+    std::vector<long long> gslot(2 * (size_t)cs.n + 1);
     if (c->go) {
         const int n = tp.lev[c->Lc].N - 1;
         gst = sine_table(n + 1);
-        for (int q = 0; q < cs.n; q++) gord[(cs.pos[q][0] - 1) + n * ((cs.pos[q][1] - 1) + n * (cs.pos[q][2] - 1))] = q;
+        std::vector<int> lists(2 * (size_t)cs.n + 2, 0);  // gcptr, gcidx: one copy each
+        for (int q = 0; q < cs.n; q++) {
+            gord[(cs.pos[q][0] - 1) + n * ((cs.pos[q][1] - 1) + n * (cs.pos[q][2] - 1))] = q;
+            gslot[q] = cs.pos[q][0] + grid_pitch(n + 1) * (cs.pos[q][1] + (long long)(n + 1) * cs.pos[q][2]);
+            lists[q + 1] = q + 1;
+            lists[cs.n + 1 + q] = (int)gslot[q];
+        }
+        std::memcpy(gslot.data() + cs.n, lists.data(), (size_t)(cs.n + 1) * sizeof(long long));
         rc = rc ? rc : upload(*c, c->gst, gst.data(), gst.size() * sizeof(double));
         if (slots) rc = rc ? rc : upload(*c, c->gord, gord.data(), gord.size() * sizeof(int));
+        if (slots) rc = rc ? rc : upload(*c, c->gslot, gslot.data(), gslot.size() * sizeof(long long));
     }
     launch_fill<unsigned char>(c->stream, c->cfrozen, cs.n, 0);
     // the scratch vectors' zero slot and Dirichlet ghosts must read zero

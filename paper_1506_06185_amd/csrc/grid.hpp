@@ -128,14 +128,11 @@ struct GridOps {
     // 2 - 2 cos(pi q / N)
     void (*coarse64)(hipStream_t, int N, const double *st, const double *b, double *u);
     void (*coarse32)(hipStream_t, int N, const double *st, const float *b, float *u);
-    // ... of another operator (rows val, col of 7 entries: itself, +x, -x, +y,
-    // -y, +z, -z; frozen unknowns stay as they are) by PCG preconditioned with
-    // those transforms; ord: unknown of every interior node, x fastest
-    // (kernels.hip)
-    void (*coarse_pcg64)(hipStream_t, int N, const int *ord, const double *val, const int *col, const unsigned char *frozen,
-                         const double *st, const double *b, double *u, double rtol, int maxit);
-    void (*coarse_pcg32)(hipStream_t, int N, const int *ord, const double *val, const int *col, const unsigned char *frozen,
-                         const double *st, const float *b, float *u, double rtol, int maxit);
+    // ... of another operator (rows val of 7 entries: itself, +x, -x, +y, -y,
+    // +z, -z) by PCG preconditioned with those transforms; ord: unknown of
+    // every interior node, x fastest (kernels.hip)
+    void (*coarse_pcg64)(hipStream_t, int N, const int *ord, const double *val, const double *st, const double *b, double *u, double rtol, int maxit);
+    void (*coarse_pcg32)(hipStream_t, int N, const int *ord, const double *val, const double *st, const float *b, float *u, double rtol, int maxit);
     // a whole cycle on a grid of N <= 16 cells, its coarsest level of Nc cells
     // included, in one workgroup (tail_fits): u = cycle from zero, or (norm
     // not null) from u, with the squared residual norm of the result to *norm
@@ -168,8 +165,6 @@ struct GridOps {
 const GridOps *grid_ops() __attribute__((weak));
 
 template <typename T>
-void launch_coarse_pcg_sine(hipStream_t s, int N, const int *ord, const double *val, const int *col,
-                            const unsigned char *frozen, const double *st, const T *b, T *u, double rtol, int maxit);
-
+void launch_coarse_pcg_sine(hipStream_t s, int N, const int *ord, const double *val, const double *st, const T *b, T *u, double rtol, int maxit);
 
 }  // namespace hhgr

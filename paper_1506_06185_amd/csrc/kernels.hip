@@ -926,12 +926,10 @@ __global__ void __launch_bounds__(64) k_coarse_pcg_wave(int n, const long long *
 // many elements, so few iterations are left (Jacobi: 35 and more), each with
 // six short products in LDS.  ord: unknown of every interior grid node (x
 // fastest).  Latency binds it: about 12 barriers per iteration.  343 unknowns,
-// log-normal k: 25.5 us, with the Jacobi PCG above 45; with the closures of two
-// tetrahedra frozen, which the transforms know nothing of, 55 against 47
+// log-normal k: 25.5 us, with the Jacobi PCG above 45 (one block of 512
+// threads: a second workgroup would need grid-wide waits, dearer than the work)
 template <typename T, int NPT>
 __global__ void __launch_bounds__(512) k_coarse_pcg_sine(int N, const int *__restrict__ ord, const double *__restrict__ val,
-                                                         const int *__restrict__ col,
-                                                         const unsigned char *__restrict__ frozen,
                                                          const double *__restrict__ st, const T *__restrict__ b,
                                                          T *__restrict__ u, double rtol, int maxit) {
     constexpr int kMax = 512 * NPT;
@@ -953,13 +951,16 @@ __global__ void __launch_bounds__(512) k_coarse_pcg_sine(int N, const int *__res
         cz[s] = in ? m / n2 : 0;
         at[s] = (cx[s] + 1) + pitch * ((cy[s] + 1) + (long long)N * (cz[s] + 1));
         const int q = in ? ord[m] : 0;
-        act[s] = in && !(frozen && frozen[q]);
+        act[s] = in;
         dg[s] = act[s] ? val[7 * q] : 0.0;
         dsi[s] = act[s] ? 1.0 / sqrt(dg[s]) : 0.0;
         r[s] = act[s] ? (double)b[at[s]] : 0.0;
         x[s] = 0.0;
 #pragma unroll
-        for (int e = 0; e < 6; e++) av[s][e] = act[s] && col[7 * q + 1 + e] >= 0 ? val[7 * q + 1 + e] : 0.0;
+        for (int e = 0; e < 6; e++) {
+            const int ce = e < 2 ? cx[s] : e < 4 ? cy[s] : cz[s];
+            av[s][e] = in && (e & 1 ? ce > 0 : ce + 1 < nm) ? val[7 * q + 1 + e] : 0.0;
+        }
         lam[s] = 6.0 / ((S[n2 + cx[s]] + S[n2 + cy[s]]) + S[n2 + cz[s]]);
     }
     // z = M^-1 r through A and B; every thread keeps its own entries
@@ -2002,19 +2003,18 @@ void launch_coarse_pcg(hipStream_t s, int n, const long long *slot, const int *c
 }
 
 template <typename T>
-void launch_coarse_pcg_sine(hipStream_t s, int N, const int *ord, const double *val, const int *col,
-                            const unsigned char *frozen, const double *st, const T *b, T *u, double rtol, int maxit) {
+void launch_coarse_pcg_sine(hipStream_t s, int N, const int *ord, const double *val, const double *st, const T *b, T *u, double rtol, int maxit) {
     if (N <= 8)
-        hipLaunchKernelGGL((k_coarse_pcg_sine<T, 1>), dim3(1), dim3(512), 0, s, N, ord, val, col, frozen, st, b, u, rtol,
+        hipLaunchKernelGGL((k_coarse_pcg_sine<T, 1>), dim3(1), dim3(512), 0, s, N, ord, val, st, b, u, rtol,
                            maxit);
     else
-        hipLaunchKernelGGL((k_coarse_pcg_sine<T, 3>), dim3(1), dim3(512), 0, s, N, ord, val, col, frozen, st, b, u, rtol,
+        hipLaunchKernelGGL((k_coarse_pcg_sine<T, 3>), dim3(1), dim3(512), 0, s, N, ord, val, st, b, u, rtol,
                            maxit);
 }
-template void launch_coarse_pcg_sine<double>(hipStream_t, int, const int *, const double *, const int *,
-                                             const unsigned char *, const double *, const double *, double *, double, int);
-template void launch_coarse_pcg_sine<float>(hipStream_t, int, const int *, const double *, const int *,
-                                            const unsigned char *, const double *, const float *, float *, double, int);
+template void launch_coarse_pcg_sine<double>(hipStream_t, int, const int *, const double *, const double *,
+                                             const double *, double *, double, int);
+template void launch_coarse_pcg_sine<float>(hipStream_t, int, const int *, const double *, const double *,
+                                            const float *, float *, double, int);
 
 template <typename T>
 void launch_coarse_dense(hipStream_t s, int n, const long long *slot, const double *inv, const T *b, T *u,

@@ -19,12 +19,11 @@ alignas(16) unsigned char grid_lds[kMockLds];
 namespace hhgr {
 // (another file's kernel, checked on the GPU)
 template <typename T>
-void launch_coarse_pcg_sine(hipStream_t, int, const int *, const double *, const int *, const unsigned char *, const double *,
-                            const T *, T *, double, int) {}
-template void launch_coarse_pcg_sine<double>(hipStream_t, int, const int *, const double *, const int *,
-                                             const unsigned char *, const double *, const double *, double *, double, int);
-template void launch_coarse_pcg_sine<float>(hipStream_t, int, const int *, const double *, const int *,
-                                            const unsigned char *, const double *, const float *, float *, double, int);
+void launch_coarse_pcg_sine(hipStream_t, int, const int *, const double *, const double *, const T *, T *, double, int) {}
+template void launch_coarse_pcg_sine<double>(hipStream_t, int, const int *, const double *, const double *,
+                                             const double *, double *, double, int);
+template void launch_coarse_pcg_sine<float>(hipStream_t, int, const int *, const double *, const double *,
+                                            const float *, float *, double, int);
 }  // namespace hhgr
 using namespace hhgr;
 

@@ -78,6 +78,37 @@ def test_step_graphs_follow_the_buffers(hh, precision):
         assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("n_sub,level,precision", [(1, 4, "fp64"), (2, 3, "fp64"), (3, 3, "fp64"), (3, 4, "mixed")])
+def test_coarse_pcg(hh, n_sub, level, precision):
+    """Cycles with a strongly varying k at 27, 343 and 1331 coarsest unknowns.
+    Both sides stop their coarsest PCG at a relative residual of 1e-14, so each
+    cycle's correction may differ by that times the condition number, here at
+    most (2 N / pi)^2 times the contrast of the coarsest k."""
+    import oracle
+
+    print(f"\n[grid coarse pcg] n_sub={n_sub} level={level} {precision}", flush=True)
+    ctx = hh.Context(device="cuda:0", n_sub=n_sub, level=level, precision=precision, variable_coeff=True)
+    g = np.random.default_rng(7 * n_sub + level)
+    k = np.exp(g.uniform(-1.5, 1.5, ctx.n_elems))
+    cond = (8.0 * n_sub / np.pi) ** 2 * np.exp(3.0)
+    p = oracle.Problem(n_sub, level, k=k)
+    b, u = g.standard_normal(p.ndof), np.zeros(p.ndof)
+    ctx.set_coeff(T(k))
+    ctx.set_rhs(T(b))
+    ctx.set_solution(None)
+    if precision == "mixed":  # the FP32 cycle: only the converged solution compares
+        ctx.vcycle(30)
+        for _ in range(30):
+            u, _ = p.vcycle(u, b)
+        assert rel(ctx.get_solution().cpu().numpy(), u) < 1e-9
+    else:
+        for _ in range(3):
+            ctx.vcycle(1)
+            u, _ = p.vcycle(u, b)
+            assert rel(ctx.get_solution().cpu().numpy(), u) < TOL + 2e-14 * cond
+    ctx.close()
+
+
 @pytest.mark.parametrize("n_sub,level", [(1, 3), (3, 4), (1, 6), (2, 6)])
 def test_mass_and_vector_order(hh, n_sub, level):
     """M x and the vector order at sizes around the mass kernel's tiles (62 x
