@@ -10,11 +10,9 @@ stored faces/edges/vertex, then global V-cycles continue to ||r|| <= 1e-8 ||b||.
 value = unknowns x global V-cycles / step wall time (MDoF/s), so the fault
 and the recovery count against it; ms_per_step is the time to 1e-8.
 roofline: the finest-level FP64 smoother kernel, timed with HIP events on
-the stream it runs on during the timed steps: the red-black colour pass
-(12 B per unknown: a sweep reads u and b once and writes u once, 24 B per
-unknown, in two passes; the pass's own count, 16 B, is reported beside it),
-or the fused sweep kernel where the autotuner chose it (24 B per
-volume-interior unknown).  cpu_baseline: the CPU oracle on
+the stream it runs on during the timed steps: the pre-smoothing sweeps of the
+grid (24 B per unknown: a sweep reads u and b once and writes u once).
+cpu_baseline: the CPU oracle on
 the same job (time to 1e-8 on every host thread, a one-thread sample, and the
 gradient workload's forward and adjoint solves).
 
@@ -55,8 +53,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "fused_sweep_fp64_l7_48tets_traffic.json")
-TRAFFIC_FILE_COLOUR = os.path.join(ROOT, "profiles", "colour_pass_fp64_l7_48tets_traffic.json")
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "grid_sweep_fp64_l7_48tets_traffic.json")
 TRAFFIC_FILE_GENERAL = os.path.join(ROOT, "profiles", "class_pass15_fp64_l7_48tets_traffic.json")
 
 
@@ -69,7 +66,7 @@ def kernel_source_hash(name: str = "kernels.hip") -> str:
         return hashlib.sha256(f.read()).hexdigest()[:16]
 
 
-def measured_traffic(n_sub: int, level: int, path: str = TRAFFIC_FILE, source: str = "fused.hip"):
+def measured_traffic(n_sub: int, level: int, path: str = TRAFFIC_FILE, source: str = "grid.hip"):
     """HBM bytes per launch of the finest-level dominant kernel from the committed
     rocprofv3 counter summary, or None when the summary is not for this workload
     or not for the current kernel source.  The figure is the L2-to-memory read
@@ -629,7 +626,7 @@ def main():
     ap.add_argument("--no-general", action="store_true", help="skip the general-macro-mesh leg")
     ap.add_argument("--no-mesh", action="store_true", help="skip the unstructured-macro-mesh leg")
     ap.add_argument("--fused-sweeps", choices=("auto", "on", "off"), default="auto",
-                    help="finest-level smoother of the headline job: fused red-black sweep pairs or two colour "
+                    help="slot-space smoother: fused red-black sweep pairs or two colour "
                          "passes per sweep (default: the autotuner's choice)")
     ap.add_argument("--graph", action="store_true", help="replay captured graphs (disables kernel timing)")
     ap.add_argument("--tune-cache", default=None,
@@ -684,7 +681,7 @@ def main():
     total_cycles = 0
     rel = None
     for s in range(args.steps):
-        # HIP events bracket the finest-level colour passes of the last timed
+        # HIP events bracket the finest-level pre-smoothing sweeps of the last timed
         # step (the roofline's launches); the other steps run without them
         if s == args.steps - 1 and not args.graph:
             ctx.kernel_timing(True)
@@ -716,36 +713,20 @@ def main():
     roofline = None
     if launches > 0:
         t = mean_ms * 1e-3
-        pass_bytes = 2.0 * 8.0 * ctx.n_dofs  # a colour pass's own count: u all, b and u of its colour
-        if abs(alg_bytes - pass_bytes) > 1.0:
-            # the autotuner chose fused sweep pairs on the finest level
-            kernel = "k_sweep_fused<double> (finest-level fused red-black SOR sweep of the volume interiors, FP64, k=1)"
-            sweep_bytes, own = alg_bytes, None
-            traffic = measured_traffic(n_sub, level)
-        else:
-            # per red-black sweep u and b are read once and u is written once
-            # (24 B per unknown in FP64), i.e. 12 B per colour pass; the pass
-            # itself reads u of both colours, so its own count is 16 B
-            kernel = "k_colour<double> (finest-level red-black SOR colour pass, FP64, k=1)"
-            sweep_bytes = 12.0 * ctx.n_dofs
-            own = {"algorithmic_bytes_per_launch": pass_bytes, "achieved": round(pass_bytes / t / 1e9, 1),
-                   "frac": round(pass_bytes / t / 1e9 / HBM_PEAK_GBS, 4),
-                   "count": "16 B per unknown: u of both colours, b and u of the pass's colour"}
-            traffic = measured_traffic(n_sub, level, TRAFFIC_FILE_COLOUR, "kernels.hip")
+        sweep_bytes = alg_bytes
         achieved = sweep_bytes / t / 1e9
         roofline = {
             "bound": "hbm",
-            "kernel": kernel,
+            "kernel": "k_grid_sweep<double> (finest-level pre-smoothing red-black SOR sweep on the grid, FP64, k=1)",
             "achieved": round(achieved, 1),
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 4),
-            "traffic": traffic,
+            "traffic": measured_traffic(n_sub, level),
             "launches": launches,
             "mean_launch_ms": round(mean_ms, 5),
             "algorithmic_bytes_per_launch": sweep_bytes,
-            "count": "24 B per unknown per red-black sweep (u and b read once, u written once), 12 B per colour pass",
-            "pass_own_count": own,
+            "count": "24 B per unknown per red-black sweep (u and b read once, u written once)",
         }
     ctx.close()
 
@@ -810,7 +791,7 @@ def main():
             "workload": f"poisson-kuhn-cube n_sub={n_sub} ({6 * n_sub ** 3} macro tets) level={level}: "
                         f"fault after 5 V(2,1) cycles, 3 local recovery cycles, solve to 1e-8",
             "unknowns": int(f_dev.numel()),
-            "smoother": "red-black SOR omega=1.25, V(2,1), coarse level 2 solved with its dense inverse",
+            "smoother": "red-black SOR omega=1.25, V(2,1), coarse level 2 solved by sine transforms",
             "fault_tet": t_fault,
             "graph": bool(args.graph),
             "fused_sweeps": args.fused_sweeps,
