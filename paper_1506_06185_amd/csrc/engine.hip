@@ -1394,8 +1394,8 @@ GridTets grid_tets(const hhgr_ctx &c, const std::vector<int> &tets) {
 }
 
 // containers of the finest level (full: every node of the closures, else the
-// interior nodes), with or without the masters
-GridClosures grid_closures(const hhgr_ctx &c, const VolDesc *vd, int nvol, bool full, bool masters) {
+// interior nodes)
+GridClosures grid_closures(const hhgr_ctx &c, const VolDesc *vd, int nvol, bool full) {
     const LevelDev &D = c.lev[c.L];
     GridClosures g;
     g.vd = vd;
@@ -1406,9 +1406,6 @@ GridClosures grid_closures(const hhgr_ctx &c, const VolDesc *vd, int nvol, bool 
     g.tetinfo = c.tetinfo;
     g.M = D.M;
     g.N = D.N;
-    g.ifc_xyz = D.ifc_xyz;
-    g.n_ifc = masters ? D.n_ifc : 0;
-    g.ifc_base = D.ifc_base;
     return g;
 }
 
@@ -1416,11 +1413,13 @@ GridClosures grid_closures(const hhgr_ctx &c, const VolDesc *vd, int nvol, bool 
 // space for the local cycles; their interiors back to the grid
 void grid_to_local(hhgr_ctx &c, hipStream_t s) {
     LevelDev &D = c.lev[c.L];
-    c.go->to_slots(s, grid_closures(c, D.vd_loc, D.n_loc, true, false), true, D.gu[c.cur], D.u, D.gb, D.b);
+    const GridClosures g = grid_closures(c, D.vd_loc, D.n_loc, true);
+    c.go->to_closures(s, g, true, D.gu[c.cur], D.u);
+    c.go->to_closures(s, g, false, D.gb, D.b);
 }
 void grid_from_local(hhgr_ctx &c, hipStream_t s) {
     LevelDev &D = c.lev[c.L];
-    c.go->from_slots(s, grid_closures(c, D.vd_loc, D.n_loc, false, false), D.u, D.gu[c.cur]);
+    c.go->from_closures(s, grid_closures(c, D.vd_loc, D.n_loc, false), D.u, D.gu[c.cur]);
 }
 
 // transform matrix and eigenvalues of the coarsest level (see k_grid_coarse)
@@ -1762,7 +1761,10 @@ int dn_setup(hhgr_ctx &c, const std::vector<int> &ft, RecoveryTables &keep) {
         // the intact side's interface stencils are per master: this recovery
         // runs in slot space (its right-hand side goes to aux_b)
         LevelDev &D = c.lev[c.L];
-        c.go->to_slots(c.stream, grid_closures(c, D.vd_all, c.n_tets, true, true), false, D.gu[c.cur], D.u, D.gb, c.aux_b);
+        c.go->to_closures(c.stream, grid_closures(c, D.vd_all, c.n_tets, true), false, D.gu[c.cur], D.u);
+        c.go->to_masters(c.stream, D.n_ifc, D.ifc_xyz, D.N, D.gu[c.cur], D.u + D.ifc_base);
+        c.go->to_closures(c.stream, grid_closures(c, D.vd_all, c.n_tets, false), false, D.gb, c.aux_b);
+        c.go->to_masters(c.stream, D.n_ifc, D.ifc_xyz, D.N, D.gb, c.aux_b + D.ifc_base);
     }
     int rc = upload(c, c.dn_faulty, isf.data(), isf.size());
     std::vector<std::vector<VolDesc>> &vds = keep.vds;
@@ -1870,7 +1872,7 @@ int dn_setup(hhgr_ctx &c, const std::vector<int> &ft, RecoveryTables &keep) {
     // static Neumann data from the data at the time of the fault (u_F plays
     // no part: its edges have zero intact-side weight)
     if (c.go)
-        c.go->to_slots(c.stream, grid_closures(c, F.vd_loc, F.n_loc, true, false), true, nullptr, nullptr, F.gb, F.b);
+        c.go->to_closures(c.stream, grid_closures(c, F.vd_loc, F.n_loc, true), false, F.gb, F.b);
     else
         HIPCHK(hipMemcpyAsync(c.aux_b, F.b, F.n_slots * sizeof(double), hipMemcpyDeviceToDevice, c.stream));
     if (c.mesh)
@@ -2815,7 +2817,8 @@ int hhgr_recover_dn(hhgr_ctx *c, const int *tets, int n_tets, int n_intact, int 
     refresh_faulty_ghosts(*c, ft, c->stream);
     if (c->go) {
         LevelDev &D = c->lev[c->L];
-        c->go->from_slots(c->stream, grid_closures(*c, D.vd_all, c->n_tets, false, true), D.u, D.gu[c->cur]);
+        c->go->from_closures(c->stream, grid_closures(*c, D.vd_all, c->n_tets, false), D.u, D.gu[c->cur]);
+        c->go->from_masters(c->stream, D.n_ifc, D.ifc_xyz, D.N, D.u + D.ifc_base, D.gu[c->cur]);
     }
     CHKLAUNCH();
     HIPCHK(hipStreamSynchronize(c->stream));

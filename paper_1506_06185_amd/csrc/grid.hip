@@ -877,84 +877,48 @@ __global__ void __launch_bounds__(256) k_grid_weights(int N, double h, const dou
 // ---------------------------------------------------------------------------
 // tetinfo: subcube corner V (3), first two axes a, b; closure node (i, j, k)
 // at m V + i e_a + j (e_a + e_b) + k (1, 1, 1)
-// One launch moves the closures and, in its last blocks, the masters, of u and
-// b together, two nodes per thread.  Two thirds of the tetrahedra run along y
-// or z, which binds it (162 tetrahedra, 7.0 M unknowns, u and b: 88 us, 2.5
-// TB/s, as with a launch for each vector); a small level waits for launches
-// (a local recovery at level 5: 216 -> 207 us)
-constexpr int kSlotNodes = 2;
 struct GNode {
     long long g, s;  // grid index, slot
-    bool ok, interior;
+    bool interior;
 };
-__device__ __forceinline__ void closure_nodes(const GridClosures &c, unsigned nblocks, GNode (&o)[kSlotNodes]) {
-    const unsigned per = ((unsigned)c.nlist + 256u * kSlotNodes - 1) / (256u * kSlotNodes);
-    const unsigned f = grid_xcd(blockIdx.x, nblocks);
-    const int v = (int)(f / per);
+__device__ __forceinline__ bool closure_node(const GridClosures &c, GNode &o) {
+    const unsigned per = ((unsigned)c.nlist + 255u) >> 8;
+    const unsigned f = grid_xcd(blockIdx.x, gridDim.x);
+    const int v = (int)(f / per), e = (int)((f % per) * 256 + threadIdx.x);
+    if (e >= c.nlist) return false;
+    const unsigned w = c.list[e];
+    const int i = (int)(w & 1023u), j = (int)((w >> 10) & 1023u), k = (int)(w >> 20);
     const VolDesc d = c.vd[v];
     const int *ti = c.tetinfo + 6 * d.tet;
-    const int m = c.M - 1, a = ti[3], b = ti[4];
+    const int m = c.M - 1;
+    int X[3] = {m * ti[0] + k, m * ti[1] + k, m * ti[2] + k};
+    const int a = ti[3], b = ti[4];
 #pragma unroll
-    for (int q = 0; q < kSlotNodes; q++) {
-        const int e = (int)((f % per) * (256 * kSlotNodes) + 256 * q + threadIdx.x);
-        o[q].ok = e < c.nlist;
-        const unsigned w = c.list[o[q].ok ? e : 0];
-        const int i = (int)(w & 1023u), j = (int)((w >> 10) & 1023u), k = (int)(w >> 20);
-        int X[3] = {m * ti[0] + k, m * ti[1] + k, m * ti[2] + k};
-#pragma unroll
-        for (int t = 0; t < 3; t++) X[t] += (t == a ? i + j : 0) + (t == b ? j : 0);
-        // (the plane after the last holds x = N and y = N of the last row: zeros)
-        o[q].g = X[0] + (long long)(c.N + 16) * (X[1] + (long long)c.N * X[2]);
-        const int2 r = c.rowC[k * c.M - ((k * (k - 1)) >> 1) + j];
-        o[q].s = d.vec + ((((i + k) & 1) ? r.y : r.x) + (i >> 1));
-        o[q].interior = i > 0 && j > 0 && k > 0 && i + j + k < m;
-    }
-}
-__device__ __forceinline__ long long master_node(const GridClosures &c, int q) {
-    return c.ifc_xyz[3 * q] + (long long)(c.N + 16) * (c.ifc_xyz[3 * q + 1] + (long long)c.N * c.ifc_xyz[3 * q + 2]);
+    for (int q = 0; q < 3; q++) X[q] += (q == a ? i + j : 0) + (q == b ? j : 0);
+    o.g = X[0] + (long long)(c.N + 16) * (X[1] + (long long)c.N * X[2]);
+    const int2 r = c.rowC[k * c.M - ((k * (k - 1)) >> 1) + j];
+    o.s = d.vec + ((((i + k) & 1) ? r.y : r.x) + (i >> 1));
+    o.interior = i > 0 && j > 0 && k > 0 && i + j + k < m;
+    // the plane after the last holds x = N and y = N of the last row: zeros
+    return true;
 }
 
-// local: u = 0 strictly inside the closures, b on whole closures; else u as it
-// is and b at the interior nodes.  gu may be null.
-__global__ void __launch_bounds__(256) k_grid_to_slots(GridClosures c, unsigned nblocks, bool local, const double *gu, double *u,
-                                                       const double *gb, double *b) {
-    if (blockIdx.x >= nblocks) {
-        const int q = (int)((blockIdx.x - nblocks) * 256 + threadIdx.x);
-        if (q >= c.n_ifc) return;
-        const long long g = master_node(c, q);
-        if (gu) u[c.ifc_base + q] = gu[g];
-        b[c.ifc_base + q] = gb[g];
-        return;
-    }
-    GNode o[kSlotNodes];
-    closure_nodes(c, nblocks, o);
-    double vu[kSlotNodes], vb[kSlotNodes];
-#pragma unroll
-    for (int q = 0; q < kSlotNodes; q++) {
-        vu[q] = gu ? gu[o[q].g] : 0.0;
-        vb[q] = gb[o[q].g];
-    }
-#pragma unroll
-    for (int q = 0; q < kSlotNodes; q++) {
-        if (!o[q].ok) continue;
-        if (gu) u[o[q].s] = local && o[q].interior ? 0.0 : vu[q];
-        if (local || o[q].interior) b[o[q].s] = vb[q];
-    }
+__global__ void __launch_bounds__(256) k_grid_to_closures(GridClosures c, bool zero_interior, const double *grid, double *vec) {
+    GNode o;
+    if (!closure_node(c, o)) return;
+    vec[o.s] = zero_interior && o.interior ? 0.0 : grid[o.g];
 }
-__global__ void __launch_bounds__(256) k_grid_from_slots(GridClosures c, unsigned nblocks, const double *u, double *gu) {
-    if (blockIdx.x >= nblocks) {
-        const int q = (int)((blockIdx.x - nblocks) * 256 + threadIdx.x);
-        if (q < c.n_ifc) gu[master_node(c, q)] = u[c.ifc_base + q];
-        return;
-    }
-    GNode o[kSlotNodes];
-    closure_nodes(c, nblocks, o);
-    double v[kSlotNodes];
-#pragma unroll
-    for (int q = 0; q < kSlotNodes; q++) v[q] = u[o[q].s];
-#pragma unroll
-    for (int q = 0; q < kSlotNodes; q++)
-        if (o[q].ok) gu[o[q].g] = v[q];
+__global__ void __launch_bounds__(256) k_grid_from_closures(GridClosures c, const double *vec, double *grid) {
+    GNode o;
+    if (closure_node(c, o)) grid[o.g] = vec[o.s];
+}
+__global__ void __launch_bounds__(256) k_grid_to_masters(int n, const int *xyz, int N, const double *grid, double *masters) {
+    const int q = (int)(blockIdx.x * 256 + threadIdx.x);
+    if (q < n) masters[q] = grid[xyz[3 * q] + (long long)(N + 16) * (xyz[3 * q + 1] + (long long)N * xyz[3 * q + 2])];
+}
+__global__ void __launch_bounds__(256) k_grid_from_masters(int n, const int *xyz, int N, const double *masters, double *grid) {
+    const int q = (int)(blockIdx.x * 256 + threadIdx.x);
+    if (q < n) grid[xyz[3 * q] + (long long)(N + 16) * (xyz[3 * q + 1] + (long long)N * xyz[3 * q + 2])] = masters[q];
 }
 
 // every node of the subcubes that hold the listed tetrahedra
@@ -1154,16 +1118,20 @@ int mass_load(hipStream_t s, int N, double h, const double *f, double *grid, dou
 void mass_user(hipStream_t s, int N, double h, const double *grid, double *user) {
     mass<true, false>(s, N, h, grid, user, nullptr);
 }
-unsigned closure_blocks(const GridClosures &c) {
-    return (unsigned)(((c.nlist + 256 * kSlotNodes - 1) / (256 * kSlotNodes)) * c.nvol);
+unsigned closure_blocks(const GridClosures &c) { return (unsigned)(((c.nlist + 255) / 256) * c.nvol); }
+void to_closures(hipStream_t s, const GridClosures &c, bool zero_interior, const double *grid, double *vec) {
+    if (closure_blocks(c))
+        hipLaunchKernelGGL(k_grid_to_closures, dim3(closure_blocks(c)), dim3(256), 0, s, c, zero_interior, grid, vec);
 }
-void to_slots(hipStream_t s, const GridClosures &c, bool local, const double *gu, double *u, const double *gb, double *b) {
-    const unsigned nb = closure_blocks(c), grid = nb + (unsigned)cdiv(c.n_ifc, 256);
-    if (grid) hipLaunchKernelGGL(k_grid_to_slots, dim3(grid), dim3(256), 0, s, c, nb, local, gu, u, gb, b);
+void from_closures(hipStream_t s, const GridClosures &c, const double *vec, double *grid) {
+    if (closure_blocks(c)) hipLaunchKernelGGL(k_grid_from_closures, dim3(closure_blocks(c)), dim3(256), 0, s, c, vec, grid);
 }
-void from_slots(hipStream_t s, const GridClosures &c, const double *u, double *gu) {
-    const unsigned nb = closure_blocks(c), grid = nb + (unsigned)cdiv(c.n_ifc, 256);
-    if (grid) hipLaunchKernelGGL(k_grid_from_slots, dim3(grid), dim3(256), 0, s, c, nb, u, gu);
+void to_masters(hipStream_t s, int n, const int *xyz, int N, const double *grid, double *masters) {
+    if (n > 0) hipLaunchKernelGGL(k_grid_to_masters, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, s, n, xyz, N, grid, masters);
+}
+void from_masters(hipStream_t s, int n, const int *xyz, int N, const double *masters, double *grid) {
+    if (n > 0)
+        hipLaunchKernelGGL(k_grid_from_masters, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, s, n, xyz, N, masters, grid);
 }
 void zero_tets(hipStream_t s, int N, int m, const GridTets &t, double *grid) {
     const unsigned per = (unsigned)(((long long)(m + 1) * (m + 1) * (m + 1) + 255) / 256);
@@ -1257,8 +1225,10 @@ const GridOps kOps = {tiles,
                       mass_load,
                       mass_user,
                       weights,
-                      to_slots,
-                      from_slots,
+                      to_closures,
+                      from_closures,
+                      to_masters,
+                      from_masters,
                       zero_tets,
                       freeze_tets};
 

@@ -90,10 +90,6 @@ struct GridClosures {
     const int2 *rowC = nullptr;
     const int *tetinfo = nullptr;
     int M = 0, N = 0;
-    // interface masters (at ifc_base of a slot vector), or none
-    const int *ifc_xyz = nullptr;
-    int n_ifc = 0;
-    long long ifc_base = 0;
 };
 
 // faulty tetrahedra (subcube corner, axis order), passed by value
@@ -156,11 +152,12 @@ struct GridOps {
     // edge weights of a level from its k per element (w, and rounded to w32 if
     // not null)
     void (*weights)(hipStream_t, int N, double h, const double *k, double *w, float *w32, long long wstride);
-    // grid -> slots: u (gu may be null) and b, on the listed nodes and the
-    // masters; local: u = 0 strictly inside the closures and b on all of them,
-    // else b at interior nodes only.  Slots -> grid (list: interior nodes)
-    void (*to_slots)(hipStream_t, const GridClosures &, bool local, const double *gu, double *u, const double *gb, double *b);
-    void (*from_slots)(hipStream_t, const GridClosures &, const double *u, double *gu);
+    // grid -> closures (list: every node; interior nodes get zero if
+    // zero_interior), closures -> grid (list: interior nodes)
+    void (*to_closures)(hipStream_t, const GridClosures &, bool zero_interior, const double *grid, double *vec);
+    void (*from_closures)(hipStream_t, const GridClosures &, const double *vec, double *grid);
+    void (*to_masters)(hipStream_t, int n, const int *xyz, int N, const double *grid, double *masters);
+    void (*from_masters)(hipStream_t, int n, const int *xyz, int N, const double *masters, double *grid);
     // grid = 0 strictly inside the tetrahedra; frz = 1 on their closures, else 0
     void (*zero_tets)(hipStream_t, int N, int m, const GridTets &, double *grid);
     void (*freeze_tets)(hipStream_t, int N, int m, const GridTets &, unsigned char *frz);
