@@ -111,7 +111,7 @@ int hhgr_sizes(const hhgr_ctx *ctx, long long *n_dofs, int *n_tets, long long *n
  * (tetrahedron interior, face, edge, vertex) shares one 15-point stencil;
  * these are computed on the host and uploaded (with k = 1 and at most 512
  * coarsest unknowns, also the dense inverse of the coarsest-level matrix,
- * which the cycles then apply as on the cube).  With variable_coeff = 1 the
+ * which the cycles then apply).  With variable_coeff = 1 the
  * element coefficients of hhgr_set_coeff (element order above; coarse levels
  * take the mean of the 8 children) weight the element matrices, and the GPU
  * computes per-node stencils on every level and the coarsest-level matrix
@@ -235,10 +235,10 @@ int hhgr_get_solution(const hhgr_ctx *ctx, double *dev_u);
 
 /* n multigrid V-cycles of the correction scheme (Sec. 2.1): red-black SOR
  * smoothing, restriction by the transpose of linear interpolation, the
- * coarsest level solved to round-off (Jacobi-PCG to a relative residual of
- * 1e-14; with k = 1 on the cube and at most 512 coarsest unknowns, a dense
- * inverse factorised on the host at hhgr_create), linear interpolation of
- * the correction.
+ * coarsest level solved to round-off (k = 1 on the cube: exactly, by sine
+ * transforms; per-element k or frozen unknowns: PCG to a relative residual of
+ * 1e-14; meshes with k = 1: a dense inverse factorised on the host), linear
+ * interpolation of the correction.
  * With precision = HHGR_MIXED one cycle is one refinement step
  * u += V32(b - A u) with the residual and update in FP64.  rel_res_out
  * (optional) receives ||b - A u|| / ||b||.  ESTATE without a right-hand side. */
@@ -342,7 +342,9 @@ int hhgr_set_graph(hhgr_ctx *ctx, int use_graph);
  * (level, precision, coefficient mode) for all volume kernels of that level;
  * at that shape it then picks 1 or 4 nodes per thread separately for the
  * residual, the prolongation and the red post-smoothing pass that adds the
- * coarse-grid correction.  cache_path (optional) is a text file read before
+ * coarse-grid correction.  On the cube these launches are the recoveries'
+ * (Dirichlet-Neumann, single tetrahedra); global cycles there choose their
+ * tiles by a model, tuned or not.  cache_path (optional) is a text file read before
  * and written after tuning, keyed by device name.  Enqueues work and
  * synchronises. */
 int hhgr_autotune(hhgr_ctx *ctx, const char *cache_path);
@@ -358,7 +360,8 @@ int hhgr_tuning_info(const hhgr_ctx *ctx, int level, int *block_size, int *xcd_o
  * two consecutive sweeps of an unmasked cycle as a pair of single-launch
  * sweeps (red and black of each plane in one kernel, planes marched through
  * LDS), on = 0 as two colour passes per sweep.  The iterates are the same
- * bit for bit.  hhgr_autotune sets it where the pair is faster; this call
+ * bit for bit.  The cube's global cycles, whose sweeps are single launches on
+ * the grid anyway, do not depend on it.  hhgr_autotune sets it where the pair is faster; this call
  * overrides that (e.g. to time the kernel).  EINVAL where the fused kernel
  * cannot take the level (general or unstructured meshes, variable k, levels
  * with fewer than 8 segments per edge). */
@@ -371,8 +374,8 @@ int hhgr_set_fused_sweeps(hhgr_ctx *ctx, int level, int on);
 int hhgr_set_tuning(hhgr_ctx *ctx, int level, int block_size, int xcd_order, int nodes_per_thread);
 
 /* Kernel timing for roofline reports: when enabled, every launch of the
- * finest-level volume smoother kernel is bracketed by HIP events on the
- * context's stream; hhgr_kernel_stats returns the launch count and mean
+ * finest-level smoother kernel (the cube: pre-smoothing sweeps of the grid;
+ * meshes: class passes) is bracketed by HIP events on the context's stream; hhgr_kernel_stats returns the launch count and mean
  * duration in milliseconds since the last enable and the bytes the
  * algorithm moves per launch. */
 int hhgr_kernel_timing(hhgr_ctx *ctx, int enable);
@@ -388,7 +391,8 @@ int hhgr_kernel_stats(hhgr_ctx *ctx, long long *launches, double *mean_ms, doubl
  *   op 4: out (level-1) = P^T in0               (restriction)
  *   op 5: out = in1 + P in0, in0 on level-1     (interpolation and correction)
  *   op 6: out = coarsest-level PCG solution for right-hand side in0 (level = coarse_level)
- *   op 7: the same through the dense inverse (EINVAL where the context has none)
+ *   op 7: the same through the dense inverse (EINVAL where the context has none;
+ *         on the cube it is factorised by the first such call)
  * With general_geometry = 1, ops 1 and 2 are EINVAL, op 3 is one 4-class
  * sweep and op 8 + mask (mask 1..15) runs the passes of the classes whose
  * bits are set in mask, lowest class first.
