@@ -207,8 +207,9 @@ struct hhgr_ctx {
     int cn = 0;
     // dense inverse of the unmasked coarsest-level operator (k = 1, at most
     // kDenseCoarseMax unknowns): workspace room in cinv, valid once
-    // dense_coarse is set (at create on the cube, by hhgr_set_geometry on a
-    // general mesh); the other operators use PCG
+    // dense_coarse is set (by hhgr_set_geometry on a general mesh, at create on
+    // an unstructured one; on the cube by the debug call that reads it, as the
+    // grid cycles solve this level by sine transforms); the others use PCG
     bool dense_coarse = false;
     double *cinv = nullptr;
     // unstructured macro meshes: dense inverse of the coarsest operator with
