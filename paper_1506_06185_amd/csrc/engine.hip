@@ -283,7 +283,8 @@ struct hhgr_batch {
     std::vector<hipEvent_t> evl;               // [2q] local fork, [2q + 1] local join
     std::vector<BatchDD> dd;
     // step graphs by the (member, mode, start buffer) triples they were
-    // captured for; a step on the grid swaps its buffers, so two serve in turn
+    // captured for; a step on the grid swaps its buffers, so two serve in turn.
+    // Dropped when a member is armed
     struct Step {
         std::vector<int> sig;
         hipGraphExec_t x = nullptr;
@@ -3481,6 +3482,12 @@ int hhgr_batch_run(hhgr_batch *b, double rel_tol, int max_cycles, hhgr_report *r
     // armed recoveries: masks, local hierarchies, restored ghosts (eager, synchronous)
     for (int q = 0; q < n; q++)
         if (b->dd[q].armed) {
+            // a step captured for another faulty set holds that set's number of
+            // intact tetrahedra
+            for (auto &st : b->step) {
+                if (st.x) hipGraphExecDestroy(st.x);
+                st.x = nullptr;
+            }
             invalidate_graph(*b->ctx[q]);
             // (synchronised at the end of the block: the steps run on other streams)
             RecoveryTables keep(b->ctx[q]->stream);
