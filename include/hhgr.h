@@ -309,7 +309,8 @@ int hhgr_recover_dn(hhgr_ctx *ctx, const int *tets, int n_tets, int n_intact, in
 int hhgr_adjoint_grad(hhgr_ctx *ctx, const double *dev_g, double rel_tol, int max_cycles, double *dev_dJdf,
                       double *dev_dJdk);
 
-/* Apply the consistent P1 mass matrix M to a device vector (vector order). */
+/* Apply the consistent P1 mass matrix M to a device vector (vector order);
+ * dev_y may be dev_x or overlap it. */
 int hhgr_mass_apply(hhgr_ctx *ctx, const double *dev_x, double *dev_y);
 
 /* Batched solves: independent contexts (each with its own workspace and

@@ -2833,7 +2833,14 @@ int hhgr_mass_apply(hhgr_ctx *c, const double *dev_x, double *dev_y) {
     if (c->gen && !c->geom_set) return fail(HHGR_ESTATE, "no geometry set");
     LevelDev &D = c->lev[c->L];
     if (!c->gen) {
-        // one grid stencil whatever k is: no trip through slot space
+        // one grid stencil whatever k is: no trip through slot space, but x is
+        // read around every node, so a y that shares memory with it needs a copy
+        const size_t bytes = (size_t)c->n_dofs * sizeof(double);
+        const uintptr_t x0 = reinterpret_cast<uintptr_t>(dev_x), y0 = reinterpret_cast<uintptr_t>(dev_y);
+        if (x0 < y0 + bytes && y0 < x0 + bytes) {
+            HIPCHK(hipMemcpyAsync(c->aux_u, dev_x, bytes, hipMemcpyDeviceToDevice, c->stream));
+            dev_x = c->aux_u;
+        }
         launch_mass_grid(c->stream, D.N, D.h, dev_x, dev_y);
         CHKLAUNCH();
         return HHGR_OK;
