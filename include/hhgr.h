@@ -375,10 +375,12 @@ int hhgr_set_fused_sweeps(hhgr_ctx *ctx, int level, int on);
 int hhgr_set_tuning(hhgr_ctx *ctx, int level, int block_size, int xcd_order, int nodes_per_thread);
 
 /* Kernel timing for roofline reports: when enabled, every launch of the
- * finest-level smoother kernel (the cube: pre-smoothing sweeps of the grid;
- * meshes: class passes) is bracketed by HIP events on the context's stream; hhgr_kernel_stats returns the launch count and mean
- * duration in milliseconds since the last enable and the bytes the
- * algorithm moves per launch. */
+ * finest-level smoother kernel is bracketed by HIP events on the context's
+ * stream (the cube: launches of pre-smoothing sweeps on the grid, or the
+ * whole cycle where one launch runs it, at most 16 cells and k = 1;
+ * meshes: class passes).  hhgr_kernel_stats returns the launch count and mean
+ * duration in milliseconds since the last enable and the bytes that the
+ * algorithm moves per launch (on the cube the mean over these launches). */
 int hhgr_kernel_timing(hhgr_ctx *ctx, int enable);
 int hhgr_kernel_stats(hhgr_ctx *ctx, long long *launches, double *mean_ms, double *algorithmic_bytes);
 

@@ -262,6 +262,7 @@ struct hhgr_ctx {
     bool timing = false;
     std::vector<hipEvent_t> tev;
     size_t tev_used = 0;
+    double tev_bytes = 0.0;  // what the timed sweeps on the grid cannot do without
     void *ws = nullptr;
     size_t ws_bytes = 0;
 };
@@ -878,10 +879,11 @@ void timed_begin(hhgr_ctx &c, hipStream_t s) {
     }
     if (c.tev_used + 2 <= c.tev.size()) hipEventRecord(c.tev[c.tev_used], s);
 }
-void timed_end(hhgr_ctx &c, hipStream_t s) {
+void timed_end(hhgr_ctx &c, hipStream_t s, double bytes = 0.0) {
     if (c.tev_used + 2 <= c.tev.size()) {
         hipEventRecord(c.tev[c.tev_used + 1], s);
         c.tev_used += 2;
+        c.tev_bytes += bytes;
     }
 }
 
@@ -1276,10 +1278,13 @@ int grid_cycle(hhgr_ctx &c, int l, bool zero, int q, bool masked, bool norm, hip
         return 0;
     }
     if (!masked && !c.vk && zero && o.tail_fits(D.N, c.lev[c.Lc].N)) {
+        const bool timed = c.timing && l == c.L;  // (mixed: the whole FP32 cycle)
+        if (timed) timed_begin(c, s);
         if constexpr (std::is_same<T, double>::value)
             o.tail64(s, D.N, c.lev[c.Lc].N, c.d.nu_pre, c.d.nu_post, D.h, c.d.omega, c.gst, b, u[0], nullptr);
         else
             o.tail32(s, D.N, c.lev[c.Lc].N, c.d.nu_pre, c.d.nu_post, D.h, c.d.omega, c.gst, b, u[0], nullptr);
+        if (timed) timed_end(c, s, 2.0 * sizeof(T) * (double)c.n_dofs);
         return 0;
     }
     const LevelDev &Dc = c.lev[l - 1];
@@ -1293,14 +1298,16 @@ int grid_cycle(hhgr_ctx &c, int l, bool zero, int q, bool masked, bool norm, hip
     g.partial = c.gpartial;
     g.w = gweights<T>(D);
     g.wstride = grid_len(D.N);
-    auto sweep = [&](int ns, int start, int tail) {
+    auto sweep = [&](int ns, int start, int tail, bool pre) {
         g.u = u[q];
         q = start == kGridFromZero ? 0 : 1 - q;
         g.v = u[q];
-        const bool timed = c.timing && !masked && l == c.L && start != kGridProlong;
+        const bool timed = c.timing && pre && !masked && l == c.L;
         if (timed) timed_begin(c, s);
         grid_ops_sweep(o, s, ns, start, tail, D.tl[ns - 1][start][tail], g);
-        if (timed) timed_end(c, s);
+        // b read and u written, u read unless it starts from zero, three edge weights
+        if (timed)
+            timed_end(c, s, (double)c.n_dofs * sizeof(T) * (2 + (start != kGridFromZero ? 1 : 0) + (c.vk ? 3 : 0)));
     };
     for (int k = 0; k < c.d.nu_pre;) {
         // two sweeps in one launch only from zero: there the first pass reads
@@ -1309,7 +1316,7 @@ int grid_cycle(hhgr_ctx &c, int l, bool zero, int q, bool masked, bool norm, hip
         // (with edge weights the second sweep's registers do not fit)
         const int ns = start == kGridFromZero && c.d.nu_pre >= 2 && !c.vk ? 2 : 1;
         k += ns;
-        sweep(ns, start, k == c.d.nu_pre ? kGridRestrict : kGridPlain);
+        sweep(ns, start, k == c.d.nu_pre ? kGridRestrict : kGridPlain, true);
     }
     if (c.d.nu_pre == 0) {
         if (zero) {
@@ -1326,7 +1333,7 @@ int grid_cycle(hhgr_ctx &c, int l, bool zero, int q, bool masked, bool norm, hip
     }
     g.ec = gvec<T>(Dc, grid_cycle<T>(c, l - 1, true, 0, masked, false, s));
     for (int k = 0; k < c.d.nu_post; k++)
-        sweep(1, k == 0 ? kGridProlong : kGridFromU, norm && k == c.d.nu_post - 1 ? kGridNorm : kGridPlain);
+        sweep(1, k == 0 ? kGridProlong : kGridFromU, norm && k == c.d.nu_post - 1 ? kGridNorm : kGridPlain, false);
     if (c.d.nu_post == 0) {
         if constexpr (std::is_same<T, double>::value)
             o.plain_prolong64(s, D.N, u[q], g.ec, u[1 - q]);
@@ -1372,7 +1379,9 @@ void grid_step(hhgr_ctx &c, bool masked, bool norm, hipStream_t s, double *dst) 
         return;
     }
     if (!masked && grid_in_tail(c)) {
+        if (c.timing) timed_begin(c, s);
         c.go->tail64(s, D.N, c.lev[c.Lc].N, c.d.nu_pre, c.d.nu_post, D.h, c.d.omega, c.gst, D.gb, D.gu[c.cur], dst);
+        if (c.timing) timed_end(c, s, 3.0 * sizeof(double) * (double)c.n_dofs);
         return;
     }
     const bool tail = norm && c.d.nu_post > 0;
@@ -3024,6 +3033,7 @@ int hhgr_kernel_timing(hhgr_ctx *c, int enable) {
     HIPCHK(hipStreamSynchronize(c->stream));
     c->timing = enable != 0;
     c->tev_used = 0;
+    c->tev_bytes = 0.0;
     return HHGR_OK;
 }
 
@@ -3048,9 +3058,8 @@ int hhgr_kernel_stats(hhgr_ctx *c, long long *launches, double *mean_ms, double 
     const double w = c->mixed ? 4.0 : 8.0;
     const LevelDev &F = c->lev[c->L];
     if (c->go) {
-        // a grid sweep reads u and b once and writes u once; the FP32 ones
-        // start from zero and do not read u
-        if (alg_bytes) *alg_bytes = (c->mixed ? 2.0 : 3.0) * w * (double)c->n_dofs;
+        // counted launch by launch
+        if (alg_bytes) *alg_bytes = c->tev_used ? c->tev_bytes / (0.5 * (double)c->tev_used) : 0.0;
     } else if (F.fz_on && (c->mixed ? F.u32alt != nullptr : F.ualt != nullptr)) {
         // the fused sweep's volume kernel: u (both colours) and b read once,
         // u written once, over the volume-interior nodes
