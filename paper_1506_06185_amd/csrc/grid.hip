@@ -783,14 +783,15 @@ __global__ void __launch_bounds__(256) k_grid_to_user(int N, const double *grid,
 // diagonal, h^3/20 to the 6 axis neighbours and to +-(1,1,1), h^3/30 to
 // +-(1,1,0), +-(0,1,1), +-(1,0,1)
 // ---------------------------------------------------------------------------
-// A workgroup marches through the planes of a tile of 64 x 16 nodes (62 x 14
+// A workgroup marches through vz planes of a tile of 64 x 16 nodes (62 x 14
 // of them its own), each thread with one column; a plane's 7 values around a
 // node serve the node itself and the nodes above and below it, so a plane is
-// read once and published once.  IG, OG: input, output on the grid instead
-// of in vector order.
-constexpr int kMassX = 64, kMassY = 16, kMassZ = 32;
+// read once and published once.  The sums over the neighbours are carried
+// unweighted, so each weight multiplies once.  IG, OG: input, output on the
+// grid instead of in vector order.
+constexpr int kMassX = 64, kMassY = 16;
 template <bool IG, bool OG>
-__global__ void __launch_bounds__(1024) k_grid_mass(int N, double h3, const double *in, double *out, double *partial) {
+__global__ void __launch_bounds__(1024) k_grid_mass(int N, int vz, double h3, const double *in, double *out, double *partial) {
     double *const lds = (double *)grid_lds;  // [2][(kMassY + 2) kMassX + 2]
     constexpr int LS = (kMassY + 2) * kMassX + 2;
     const int ntx = (N - 1 + kMassX - 3) / (kMassX - 2), nty = (N - 1 + kMassY - 3) / (kMassY - 2);
@@ -798,7 +799,7 @@ __global__ void __launch_bounds__(1024) k_grid_mass(int N, double h3, const doub
     const int ix = (int)(f % ntx), iy = (int)((f / ntx) % nty), iz = (int)(f / (ntx * nty));
     const int lx = (int)(threadIdx.x & (kMassX - 1)), ly = (int)(threadIdx.x / kMassX);
     const int x = ix * (kMassX - 2) + lx, y = iy * (kMassY - 2) + ly;  // grid coordinates
-    const int Z0 = 1 + iz * kMassZ, Z1 = min(N, Z0 + kMassZ);
+    const int Z0 = 1 + iz * vz, Z1 = min(N, Z0 + vz);
     const bool in_xy = x >= 1 && x < N && y >= 1 && y < N;
     const bool own = in_xy && lx >= 1 && lx < kMassX - 1 && ly >= 1 && ly < kMassY - 1;
     const int n = N - 1;
@@ -812,22 +813,29 @@ __global__ void __launch_bounds__(1024) k_grid_mass(int N, double h3, const doub
         const double v = in[(ok ? oi : 0) + (ok ? (long long)(IG ? z : z - 1) * SI : 0)];
         return ok ? v : 0.0;
     };
-    double v0 = load(Z0 - 1), v1 = load(Z0), below = 0.0, acc = 0.0, sum = 0.0;
+    // node of plane z - 1: its value v1 and the sums so far of its axis and body
+    // diagonal neighbours (ax) and of its face diagonal ones (fd); of plane
+    // z - 1 itself, what the node above takes: v1, x - 1 and y - 1 (fm), mm1
+    double v1 = 0.0, ax = 0.0, fd = 0.0, fm = 0.0, mm1 = 0.0;
+    double a0 = load(Z0 - 1), a1 = load(Z0), sum = 0.0;
     for (int z = Z0 - 1; z <= Z1; z++) {
-        const double v = v0;
-        v0 = v1;
-        v1 = load(z + 2);
+        const double v = a0;
+        a0 = a1;
+        a1 = load(z + 2);
         double *l = lds + (z & 1) * LS + li;
         l[0] = v;
         __syncthreads();
         const double xp = l[1], xm = l[-1], yp = l[kMassX], ym = l[-kMassX], pp = l[kMassX + 1], mm = l[-kMassX - 1];
         if (own && z > Z0) {
-            const double o = acc + (wax * (v + pp) + wfd * (xp + yp));
+            const double o = wc * v1 + (wax * (ax + (v + pp)) + wfd * (fd + (xp + yp)));
             out[oo + (long long)(OG ? z - 1 : z - 2) * SO] = o;
             sum += o * o;
         }
-        acc = below + (wc * v + wax * ((xp + xm) + (yp + ym)) + wfd * (pp + mm));
-        below = wax * (v + mm) + wfd * (xm + ym);
+        ax = ((xp + xm) + (yp + ym)) + (v1 + mm1);
+        fd = (pp + mm) + fm;
+        fm = xm + ym;
+        mm1 = mm;
+        v1 = v;
     }
     if (partial) {
         __syncthreads();
@@ -1106,10 +1114,23 @@ void to_user(hipStream_t s, int N, const double *grid, double *user) {
 }
 template <bool IG, bool OG>
 int mass(hipStream_t s, int N, double h, const double *in, double *out, double *partial) {
-    const int nb = cdiv(N - 1, kMassX - 2) * cdiv(N - 1, kMassY - 2) * cdiv(N - 1, kMassZ);
+    const int cols = cdiv(N - 1, kMassX - 2) * cdiv(N - 1, kMassY - 2);
+    // planes per workgroup: rounds of 512 workgroups (two per CU) times the
+    // steps of a march, which two planes of halo and the pipeline lengthen
+    // (N = 32: 5.6 us with 4 planes, 18 with 32; N = 128: 13 with 8, 22 with 32)
+    int vz = 32;
+    double best = 1e300;
+    for (int v = 32; v >= 4; v /= 2) {
+        const double c = (double)cdiv(cols * cdiv(N - 1, v), 512) * (v + 3) * (v + 1) / v;
+        if (c < best) {
+            best = c;
+            vz = v;
+        }
+    }
+    const int nb = cols * cdiv(N - 1, vz);
     const size_t lds = 2 * ((kMassY + 2) * kMassX + 2) * sizeof(double);
-    hipLaunchKernelGGL((k_grid_mass<IG, OG>), dim3((unsigned)nb), dim3(kMassX * kMassY), lds, s, N, h * h * h, in, out,
-                       partial);
+    hipLaunchKernelGGL((k_grid_mass<IG, OG>), dim3((unsigned)nb), dim3(kMassX * kMassY), lds, s, N, vz, h * h * h, in,
+                       out, partial);
     return nb;
 }
 int mass_load(hipStream_t s, int N, double h, const double *f, double *grid, double *partial) {
