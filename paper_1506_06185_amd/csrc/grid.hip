@@ -1173,7 +1173,9 @@ void freeze_tets(hipStream_t s, int N, int m, const GridTets &t, unsigned char *
 //     4 TB/s; large grids need about 860 threads resident per CU for that;
 //   latency: a step of the march costs 0.2 to 0.6 us (barrier, LDS reads, the
 //     chain of passes), more with more threads on the CU, so small grids take
-//     thin tiles on many CUs.
+//     thin tiles on many CUs.  A residual with edge weights waits for them in
+//     every step, 0.7 to 0.9 us (N = 64, 96, 128: 5.5, 11 and 21 us, against
+//     9, 18 and 32 with the tiles of a plain residual's step).
 // At N = 256 a plain sweep takes 100 us (98 by the bounds), at N = 512 730.
 GridTiles tiles(int N, int ns, int start, int tail, int word, bool vk) {
     const int K = tail == kGridResidual ? 0 : 2 * ns, np = N / 2;
@@ -1208,7 +1210,7 @@ GridTiles tiles(int N, int ns, int start, int tail, int word, bool vk) {
                 t.vz = vz;
                 t.ntz = cdiv(N, vz);
                 const int blocks = t.blocks(), rounds = cdiv(blocks, 256 * bpc), res = std::min(bpc, cdiv(blocks, 256));
-                const double step = 0.11 + 0.115 * K + (0.12 + 0.19 * K) * 1e-3 * th * res;
+                const double step = (K == 0 && vk ? 0.42 : 0.11) + 0.115 * K + (0.12 + 0.19 * K) * 1e-3 * th * res;
                 const double lat = rounds * (vz + hl + K + 3) * step * (vk ? 1.6 : 1.0);
                 double bw = wr + (double)blocks * (vz + hl + hh) * t.tp * t.ty * words * word * (1.0 + 60.0 / (2 * word * t.tp)) / 8.8e6;
                 const double active = (double)blocks * th / (256.0 * rounds);  // threads resident per CU on average
