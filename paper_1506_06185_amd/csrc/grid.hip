@@ -929,13 +929,16 @@ __global__ void __launch_bounds__(256) k_grid_from_masters(int n, const int *xyz
     if (q < n) grid[xyz[3 * q] + (long long)(N + 16) * (xyz[3 * q + 1] + (long long)N * xyz[3 * q + 2])] = masters[q];
 }
 
-// every node of the subcubes that hold the listed tetrahedra
-template <bool FREEZE>
+// nodes of the listed tetrahedra: strictly inside them (zeroed) or their
+// closures (frozen).  A wavefront per grid row of the tetrahedron's
+// subcube walks the row's nodes of the tetrahedron, an interval along x.
+constexpr int kTetsZero = 0, kTetsFreeze = 1;
+template <int MODE>
 __global__ void __launch_bounds__(256) k_grid_tets(int N, int m, GridTets t, double *grid, unsigned char *frz) {
-    const int w = m + 1, per = (w * w * w + 255) / 256;
-    const int q = (int)(blockIdx.x / per), e = (int)(blockIdx.x % per) * 256 + (int)threadIdx.x;
-    if (e >= w * w * w) return;
-    const int d[3] = {e % w, (e / w) % w, e / (w * w)};
+    const int w = m + 1, per = (w * w + 3) / 4;
+    const int q = (int)(blockIdx.x / per), row = (int)(blockIdx.x % per) * 4 + (int)(threadIdx.x >> 6);
+    if (row >= w * w) return;
+    const int dy = row % w, dz = row / w;
     int V[3] = {0, 0, 0}, a = 0, b = 0;
 #pragma unroll
     for (int r = 0; r < 8; r++)
@@ -946,16 +949,35 @@ __global__ void __launch_bounds__(256) k_grid_tets(int N, int m, GridTets t, dou
             a = t.info[r][3];
             b = t.info[r][4];
         }
+    // d[a] >= d[b] >= d[c]; inside: all bounds strict by one
+    constexpr int e = MODE == kTetsFreeze ? 0 : 1;
     const int c = 3 - a - b;
-    const int da = a == 0 ? d[0] : a == 1 ? d[1] : d[2], db = b == 0 ? d[0] : b == 1 ? d[1] : d[2];
-    const int dc = c == 0 ? d[0] : c == 1 ? d[1] : d[2];
-    const int X = m * V[0] + d[0], Y = m * V[1] + d[1], Z = m * V[2] + d[2];
-    const long long i = X + (long long)(N + 16) * (Y + (long long)N * Z);
-    if (FREEZE) {
-        // closure; the boundary nodes x = N and y = N have no byte of their own
-        if (da >= db && db >= dc && X < N && Y < N) frz[i] = 1;
-    } else if (m > da && da > db && db > dc && dc > 0) {
-        grid[i] = 0.0;
+    const int db = b == 1 ? dy : dz, dc = c == 1 ? dy : dz, da = a == 1 ? dy : dz;
+    int lo, hi;
+    bool some;
+    if (a == 0) {
+        lo = db + e;
+        hi = m - e;
+        some = db >= dc + e && dc >= e;
+    } else if (b == 0) {
+        lo = dc + e;
+        hi = da - e;
+        some = da <= m - e && dc >= e;
+    } else {
+        lo = e;
+        hi = db - e;
+        some = da >= db + e && da <= m - e;
+    }
+    const int Y = m * V[1] + dy, Z = m * V[2] + dz, X0 = m * V[0];
+    // the boundary nodes x = N and y = N have no place of their own
+    if (!some || Y >= N) return;
+    const long long i = X0 + (long long)(N + 16) * (Y + (long long)N * Z);
+    for (int x = lo + (int)(threadIdx.x & 63); x <= hi; x += 64) {
+        if (X0 + x >= N) break;
+        if (MODE == kTetsZero)
+            grid[i + x] = 0.0;
+        else
+            frz[i + x] = 1;
     }
 }
 __global__ void __launch_bounds__(256) k_grid_zero32(unsigned *p, long long n) {
@@ -1154,14 +1176,17 @@ void from_masters(hipStream_t s, int n, const int *xyz, int N, const double *mas
     if (n > 0)
         hipLaunchKernelGGL(k_grid_from_masters, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, s, n, xyz, N, masters, grid);
 }
+template <int MODE>
+void tets(hipStream_t s, int N, int m, const GridTets &t, double *grid, unsigned char *frz) {
+    const unsigned per = (unsigned)(((m + 1) * (m + 1) + 3) / 4);
+    if (t.n > 0) hipLaunchKernelGGL((k_grid_tets<MODE>), dim3(per * t.n), dim3(256), 0, s, N, m, t, grid, frz);
+}
 void zero_tets(hipStream_t s, int N, int m, const GridTets &t, double *grid) {
-    const unsigned per = (unsigned)(((long long)(m + 1) * (m + 1) * (m + 1) + 255) / 256);
-    if (t.n > 0) hipLaunchKernelGGL((k_grid_tets<false>), dim3(per * t.n), dim3(256), 0, s, N, m, t, grid, (unsigned char *)nullptr);
+    tets<kTetsZero>(s, N, m, t, grid, nullptr);
 }
 void freeze_tets(hipStream_t s, int N, int m, const GridTets &t, unsigned char *frz) {
-    const unsigned per = (unsigned)(((long long)(m + 1) * (m + 1) * (m + 1) + 255) / 256);
     hipLaunchKernelGGL(k_grid_zero32, dim3(1024), dim3(256), 0, s, (unsigned *)frz, (grid_len(N) + 3) / 4);
-    if (t.n > 0) hipLaunchKernelGGL((k_grid_tets<true>), dim3(per * t.n), dim3(256), 0, s, N, m, t, (double *)nullptr, frz);
+    tets<kTetsFreeze>(s, N, m, t, nullptr, frz);
 }
 
 // Tile choice.  The time of a launch is modelled as the larger of two bounds
