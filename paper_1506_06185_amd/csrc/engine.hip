@@ -100,7 +100,7 @@ struct LevelDev {
     VolDesc *vd_all = nullptr, *vd_masked = nullptr, *vd_loc = nullptr;
     int n_masked = 0, n_loc = 0;
     unsigned char *frozen = nullptr;
-    double *lu = nullptr, *lb = nullptr, *lr = nullptr;  // local hierarchy (levels < L)
+    double *lu = nullptr, *lb = nullptr, *lr = nullptr;  // local hierarchy (levels < L; on the grid every level)
     // Dirichlet-Neumann recovery: intact-side interface weights, ghost copies
     // outside the faulty closures, interface nodes with static Neumann data
     double *wi_dn = nullptr;
@@ -137,16 +137,20 @@ struct LevelDev {
     int fz_TJ = 0, fz_TK = 0;
     long long fz_black0 = 0;
     bool fz_on = false;  // the cycles use fused pairs on this level (autotuner: where faster)
-    // the cube with k = 1: u (two buffers, a sweep goes from one to the
-    // other) and b on the grid (grid.hpp), the frozen nodes of a
-    // Dirichlet-Dirichlet recovery, and the tiles of each kind of launch
+    // the cube: u (two buffers, a sweep goes from one to the other) and b on
+    // the grid (grid.hpp), the frozen nodes of a recovery's intact side, and
+    // the tiles of each kind of launch.  Slot vectors are scratch memory that
+    // single operators borrow (SlotScratch).
     double *gu[2] = {}, *gb = nullptr;
     float *gu32[2] = {}, *gb32 = nullptr;
     unsigned char *gfrz = nullptr;
     double *gw = nullptr;   // per-element k: edge weights along x, y and z
     float *gw32 = nullptr;
+    double *gsave = nullptr;         // finest level: b at the masters that hold Neumann data
+    unsigned char *gcode = nullptr;  // k = 1: elements at the edges, of the Dirichlet-Neumann intact side
     GridTiles tl[2][3][3];  // [ns - 1][start][tail]
     GridTiles tl_res;
+    GridTiles tl_dn[3][3];  // FP64 sweeps with edge weights (Dirichlet-Neumann): [start][tail]
 };
 
 template <typename T>
@@ -233,8 +237,7 @@ struct hhgr_ctx {
     double bnorm = 0.0;
     bool rhs_set = false, coeff_set = false;
     bool vk = false, mixed = false;
-    // the cube with k = 1 keeps u and b on the grid: the finest u is buffer
-    // cur of its two
+    // the cube keeps u and b on the grid: the finest u is buffer cur of its two
     const GridOps *go = nullptr;
     int cur = 0;
     size_t grid_off = 0, grid_bytes = 0;  // the grid vectors of every level in the workspace
@@ -377,12 +380,15 @@ void to_user(const hhgr_ctx &c, const LevelDev &D, const double *vec, double *us
 // tiles of a marching launch (a few thousand)
 size_t gpartial_len(int N) { return std::max<size_t>((size_t)N * N / 4 + 1, 65536); }
 
+// closures of the local hierarchy
+int local_max(const hhgr_ctx &c) { return std::min(std::max(c.d.max_faults, 1), c.n_tets); }
+
 // ----------------------------------------------------------------------------
 // layout of the workspace (sizing and carving share this code)
 // ----------------------------------------------------------------------------
 void carve(hhgr_ctx &c, Carver &cv) {
     const Topology &tp = *c.topo;
-    const int nf = std::max(c.d.max_faults, 1);
+    const int nf = local_max(c);
     c.lev.assign(c.L + 1, LevelDev());
     int max_blocks = 0;
     for (int l = c.Lc; l <= c.L; l++) {
@@ -476,18 +482,21 @@ void carve(hhgr_ctx &c, Carver &cv) {
         D.tg_dst = cv.take<int>(T.tg_dst.size());
         D.tg_src = cv.take<int>(T.tg_src.size());
         D.tg_ptr = T.tg_ptr;
-        D.u = cv.take<double>(T.n_slots);
-        D.b = cv.take<double>(T.n_slots);
-        D.r = cv.take<double>(T.n_slots);
-        if (c.mixed) {
-            D.u32 = cv.take<float>(T.n_slots);
-            D.b32 = cv.take<float>(T.n_slots);
-            D.r32 = cv.take<float>(T.n_slots);
+        if (!c.go) {
+            D.u = cv.take<double>(T.n_slots);
+            D.b = cv.take<double>(T.n_slots);
+            D.r = cv.take<double>(T.n_slots);
+            if (c.mixed) {
+                D.u32 = cv.take<float>(T.n_slots);
+                D.b32 = cv.take<float>(T.n_slots);
+                D.r32 = cv.take<float>(T.n_slots);
+            }
         }
         if (!c.gen && !c.vk && l > c.Lc && T.m >= 8 && fused_tables(T, D)) {
             D.fz_ps = cv.take<int>(D.fz_ps_host.size());
             D.fz_tiles = cv.take<int4>(D.fz_tiles_host.size());
-            if (c.mixed)
+            if (c.go) {
+            } else if (c.mixed)
                 D.u32alt = cv.take<float>(T.n_slots);
             else
                 D.ualt = cv.take<double>(T.n_slots);
@@ -515,7 +524,7 @@ void carve(hhgr_ctx &c, Carver &cv) {
         } else if (c.vk) {
             for (int s = 0; s < 3; s++) D.w[s] = cv.take<double>(T.n_slots);
             D.wi = cv.take<double>(6 * (size_t)T.n_ifc);
-            if (c.mixed) {
+            if (c.mixed && !c.go) {
                 for (int s = 0; s < 3; s++) D.w32[s] = cv.take<float>(T.n_slots);
                 D.wi32 = cv.take<float>(6 * (size_t)T.n_ifc);
             }
@@ -528,11 +537,12 @@ void carve(hhgr_ctx &c, Carver &cv) {
         if (l < c.L) {
             D.lu = cv.take<double>((size_t)nf * T.C_pad);
             D.lb = cv.take<double>((size_t)nf * T.C_pad);
-            D.lr = cv.take<double>((size_t)nf * T.C_pad);
         }
-        D.wi_dn = cv.take<double>(6 * (size_t)T.n_ifc);
+        if (l < c.L || c.go) D.lr = cv.take<double>((size_t)nf * T.C_pad);
+        if (l == c.L || !c.go) D.wi_dn = cv.take<double>(6 * (size_t)T.n_ifc);
         D.gidx_dn = cv.take<int>(T.gidx.size());
         if (l == c.L) D.gamma = cv.take<unsigned char>(T.n_ifc);
+        if (l == c.L && c.go) D.gsave = cv.take<double>(T.n_ifc);
     }
     if (c.go) {
         // one stretch, cleared by one fill
@@ -540,9 +550,11 @@ void carve(hhgr_ctx &c, Carver &cv) {
         for (int l = c.Lc; l <= c.L; l++) {
             LevelDev &D = c.lev[l];
             const size_t n = (size_t)grid_len(D.N);
-            D.gu[0] = cv.take<double>(n);
+            // (the finest u's idle buffer also serves as a slot vector)
+            const size_t nu = l == c.L ? std::max(n, (size_t)D.n_slots) : n;
+            D.gu[0] = cv.take<double>(nu);
             D.gb = cv.take<double>(n);
-            if (l > c.Lc) D.gu[1] = cv.take<double>(n);
+            if (l > c.Lc) D.gu[1] = cv.take<double>(nu);
             if (c.mixed) {
                 D.gu32[0] = cv.take<float>(n);
                 D.gb32 = cv.take<float>(n);
@@ -556,6 +568,8 @@ void carve(hhgr_ctx &c, Carver &cv) {
         }
         c.grid_bytes = ((cv.off + 7) & ~size_t(7)) - c.grid_off;
         cv.off = c.grid_off + c.grid_bytes;
+        if (c.d.max_faults > 0 && !c.vk)
+            for (int l = c.Lc + 1; l <= c.L; l++) c.lev[l].gcode = cv.take<unsigned char>(3 * (size_t)grid_len(c.lev[l].N));
     }
     c.partial_cap = max_blocks;
     c.partial[0] = cv.take<double>(max_blocks);
@@ -595,6 +609,10 @@ void carve(hhgr_ctx &c, Carver &cv) {
     c.aux_u = cv.take<double>(n_aux);
     c.aux_b = cv.take<double>(n_aux);
     if (c.go) {
+        // the finest closures of the local hierarchy (nothing else uses the
+        // scratch vectors during a recovery)
+        c.lev[c.L].lu = c.aux_u;
+        c.lev[c.L].lb = c.aux_b;
         // a marching launch has at most a few thousand tiles, a row launch a
         // workgroup for 4 rows
         c.gpartial = cv.take<double>(gpartial_len(TL.N));
@@ -606,7 +624,7 @@ void carve(hhgr_ctx &c, Carver &cv) {
         c.gcptr = c.gslot ? reinterpret_cast<int *>(c.gslot + c.cn) : nullptr;
         c.gcidx = c.gcptr ? c.gcptr + c.cn + 1 : nullptr;
     }
-    if (c.vk) {
+    if (c.vk && !c.go) {
         c.user_u = cv.take<double>(c.n_dofs);
         c.user_l = cv.take<double>(c.n_dofs);
     }
@@ -850,7 +868,7 @@ HView<double> local_view(hhgr_ctx &c, int stream_idx, double *finest_r = nullptr
     for (int l = c.Lc; l <= c.L; l++) {
         LevelDev &D = c.lev[l];
         LevView<double> &v = V.lv[l];
-        if (l == c.L) {
+        if (l == c.L && !c.go) {
             v.u = D.u;
             v.b = D.b;
             v.r = finest_r ? finest_r : D.r;
@@ -892,7 +910,7 @@ void timed_end(hhgr_ctx &c, hipStream_t s, double bytes = 0.0) {
 template <typename T>
 long long view_len(const hhgr_ctx &c, const HView<T> &V, int l) {
     const LevelDev &D = c.lev[l];
-    return V.local && l < c.L ? (long long)std::max(c.d.max_faults, 1) * D.C_pad : D.n_slots;
+    return V.local && (l < c.L || c.go) ? (long long)local_max(c) * D.C_pad : D.n_slots;
 }
 
 // per-workgroup sums of the squared residual that the last black pass (or
@@ -1217,7 +1235,7 @@ void cycle_and_norm(hhgr_ctx &c, const HView<double> &V, hipStream_t s, double *
 }
 
 // ----------------------------------------------------------------------------
-// the cube with k = 1: cycles on the grid (grid.hpp)
+// the cube: cycles on the grid (grid.hpp)
 // ----------------------------------------------------------------------------
 template <typename T>
 T *gvec(const LevelDev &D, int q);
@@ -1240,6 +1258,12 @@ const float *gweights<float>(const LevelDev &D) {
     return D.gw32;
 }
 
+// sides of a cycle: everything; a Dirichlet-Dirichlet intact side (closures of
+// the faulty tetrahedra frozen); a Dirichlet-Neumann one (their interiors and
+// the interface nodes of faulty tetrahedra alone frozen, elements of faulty
+// tetrahedra left out; FP64)
+enum { kSideAll = 0, kSideDirichlet = 1, kSideNeumann = 2 };
+
 void grid_ops_sweep(const GridOps &o, hipStream_t s, int ns, int start, int tail, const GridTiles &t,
                     const GridSweep<double> &g) {
     o.sweep64(s, ns, start, tail, t, g);
@@ -1250,20 +1274,22 @@ void grid_ops_sweep(const GridOps &o, hipStream_t s, int ns, int start, int tail
 }
 
 // one V-cycle on level l: from zero, or from buffer q of the level's u;
-// returns the buffer that holds the result.  masked: the intact side of a
-// Dirichlet-Dirichlet recovery.  norm: the last launch leaves the squared
-// residual in gpartial (finest level, at least one post-smoothing sweep).
+// returns the buffer that holds the result.  side: the whole problem or the
+// intact side of a recovery.  norm: the last launch leaves the squared
+// residual in gpartial (finest level, at least one post-smoothing sweep; not
+// for kSideNeumann).
 template <typename T>
-int grid_cycle(hhgr_ctx &c, int l, bool zero, int q, bool masked, bool norm, hipStream_t s) {
+int grid_cycle(hhgr_ctx &c, int l, bool zero, int q, int side, bool norm, hipStream_t s) {
     const GridOps &o = *c.go;
+    const bool masked = side != kSideAll, dn = side == kSideNeumann;
     LevelDev &D = c.lev[l];
     T *const u[2] = {gvec<T>(D, 0), gvec<T>(D, 1)}, *const b = gvec<T>(D, 2);
     if (l == c.Lc) {
         // frozen unknowns: the transforms know nothing of them, and the PCG that
         // they precondition takes longer (55 us) than the Jacobi one (47)
         if (masked)
-            launch_coarse_pcg<T>(s, c.cn, c.gslot, c.ccol, c.cval, c.cfrozen, b, u[0], c.gcptr, c.gcidx, kCoarseRtol,
-                                 kCoarseMaxit, c.citers);
+            launch_coarse_pcg<T>(s, c.cn, c.gslot, c.ccol, dn ? c.cval_dn : c.cval, c.cfrozen, b, u[0], c.gcptr, c.gcidx,
+                                 kCoarseRtol, kCoarseMaxit, c.citers);
         else if constexpr (std::is_same<T, double>::value) {
             if (c.vk)
                 o.coarse_pcg64(s, D.N, c.gord, c.cval, c.gst, b, u[0], kCoarseRtol, kCoarseMaxit);
@@ -1297,6 +1323,7 @@ int grid_cycle(hhgr_ctx &c, int l, bool zero, int q, bool masked, bool norm, hip
     g.frz = masked ? D.gfrz : nullptr;
     g.partial = c.gpartial;
     g.w = gweights<T>(D);
+    g.code = dn ? D.gcode : nullptr;
     g.wstride = grid_len(D.N);
     auto sweep = [&](int ns, int start, int tail, bool pre) {
         g.u = u[q];
@@ -1304,7 +1331,7 @@ int grid_cycle(hhgr_ctx &c, int l, bool zero, int q, bool masked, bool norm, hip
         g.v = u[q];
         const bool timed = c.timing && pre && !masked && l == c.L;
         if (timed) timed_begin(c, s);
-        grid_ops_sweep(o, s, ns, start, tail, D.tl[ns - 1][start][tail], g);
+        grid_ops_sweep(o, s, ns, start, tail, dn ? D.tl_dn[start][tail] : D.tl[ns - 1][start][tail], g);
         // b read and u written, u read unless it starts from zero, three edge weights
         if (timed)
             timed_end(c, s, (double)c.n_dofs * sizeof(T) * (2 + (start != kGridFromZero ? 1 : 0) + (c.vk ? 3 : 0)));
@@ -1314,7 +1341,7 @@ int grid_cycle(hhgr_ctx &c, int l, bool zero, int q, bool masked, bool norm, hip
         // b alone (N = 256: 105 us against 67 + 110; from u 275 against 105 + 110)
         const int start = zero && k == 0 ? kGridFromZero : kGridFromU;
         // (with edge weights the second sweep's registers do not fit)
-        const int ns = start == kGridFromZero && c.d.nu_pre >= 2 && !c.vk ? 2 : 1;
+        const int ns = start == kGridFromZero && c.d.nu_pre >= 2 && !c.vk && !dn ? 2 : 1;
         k += ns;
         sweep(ns, start, k == c.d.nu_pre ? kGridRestrict : kGridPlain, true);
     }
@@ -1324,19 +1351,22 @@ int grid_cycle(hhgr_ctx &c, int l, bool zero, int q, bool masked, bool norm, hip
             launch_fill<T>(s, u[0], grid_len(D.N), T(0));
         }
         if constexpr (std::is_same<T, double>::value) {
-            o.plain_residual64(s, D.N, D.h, u[q], b, g.w, g.wstride, u[1 - q]);
+            if (dn)
+                o.plain_residual_intact(s, D.N, D.h, u[q], b, g.w, g.code, g.wstride, g.frz, u[1 - q]);
+            else
+                o.plain_residual64(s, D.N, D.h, u[q], b, g.w, g.wstride, u[1 - q]);
             o.plain_restrict64(s, D.N, u[1 - q], g.bc);
         } else {
             o.plain_residual32(s, D.N, D.h, u[q], b, g.w, g.wstride, u[1 - q]);
             o.plain_restrict32(s, D.N, u[1 - q], g.bc);
         }
     }
-    g.ec = gvec<T>(Dc, grid_cycle<T>(c, l - 1, true, 0, masked, false, s));
+    g.ec = gvec<T>(Dc, grid_cycle<T>(c, l - 1, true, 0, side, false, s));
     for (int k = 0; k < c.d.nu_post; k++)
         sweep(1, k == 0 ? kGridProlong : kGridFromU, norm && k == c.d.nu_post - 1 ? kGridNorm : kGridPlain, false);
     if (c.d.nu_post == 0) {
         if constexpr (std::is_same<T, double>::value)
-            o.plain_prolong64(s, D.N, u[q], g.ec, u[1 - q]);
+            dn ? o.plain_prolong_intact(s, D.N, u[q], g.ec, g.frz, u[1 - q]) : o.plain_prolong64(s, D.N, u[q], g.ec, u[1 - q]);
         else
             o.plain_prolong32(s, D.N, u[q], g.ec, u[1 - q]);
         q = 1 - q;
@@ -1374,7 +1404,7 @@ bool grid_in_tail(const hhgr_ctx &c) { return !c.mixed && !c.vk && c.go->tail_fi
 void grid_step(hhgr_ctx &c, bool masked, bool norm, hipStream_t s, double *dst) {
     LevelDev &D = c.lev[c.L];
     if (c.mixed) {
-        const int q = grid_cycle<float>(c, c.L, true, 0, masked, false, s);
+        const int q = grid_cycle<float>(c, c.L, true, 0, masked ? kSideDirichlet : kSideAll, false, s);
         grid_residual(c, masked, D.gu32[q], D.gb32, s, dst);
         return;
     }
@@ -1385,7 +1415,7 @@ void grid_step(hhgr_ctx &c, bool masked, bool norm, hipStream_t s, double *dst) 
         return;
     }
     const bool tail = norm && c.d.nu_post > 0;
-    c.cur = grid_cycle<double>(c, c.L, false, c.cur, masked, tail, s);
+    c.cur = grid_cycle<double>(c, c.L, false, c.cur, masked ? kSideDirichlet : kSideAll, tail, s);
     if (tail)
         launch_reduce(s, c.gpartial,
                       D.tl[0][c.d.nu_post > 1 ? kGridFromU : kGridProlong][kGridNorm].blocks(), dst);
@@ -1404,15 +1434,13 @@ GridTets grid_tets(const hhgr_ctx &c, const std::vector<int> &tets) {
     return g;
 }
 
-// containers of the finest level (full: every node of the closures, else the
-// interior nodes)
-GridClosures grid_closures(const hhgr_ctx &c, const VolDesc *vd, int nvol, bool full) {
-    const LevelDev &D = c.lev[c.L];
+// containers of a level, every node of their closures
+GridClosures grid_closures(const hhgr_ctx &c, const LevelDev &D, const VolDesc *vd, int nvol) {
     GridClosures g;
     g.vd = vd;
     g.nvol = nvol;
-    g.list = full ? D.flist : D.ilist;
-    g.nlist = full ? D.nflist : D.nilist;
+    g.list = D.flist;
+    g.nlist = D.nflist;
     g.rowC = D.rowC;
     g.tetinfo = c.tetinfo;
     g.M = D.M;
@@ -1420,18 +1448,54 @@ GridClosures grid_closures(const hhgr_ctx &c, const VolDesc *vd, int nvol, bool 
     return g;
 }
 
-// the tetrahedra of vd_loc: closures of u (interiors zero) and b into slot
-// space for the local cycles; their interiors back to the grid
+// the finest containers of the local hierarchy
+GridLocal grid_local(const hhgr_ctx &c) {
+    const LevelDev &D = c.lev[c.L];
+    GridLocal g;
+    g.tets = grid_tets(c, c.loc_tets);
+    g.stride = D.C_pad;
+    g.rowC = D.rowC;
+    g.M = D.M;
+    g.N = D.N;
+    return g;
+}
+// the tetrahedra of vd_loc: closures of u (interiors zero) and b into the
+// local hierarchy; their interiors back to the grid
 void grid_to_local(hhgr_ctx &c, hipStream_t s) {
     LevelDev &D = c.lev[c.L];
-    const GridClosures g = grid_closures(c, D.vd_loc, D.n_loc, true);
-    c.go->to_closures(s, g, true, D.gu[c.cur], D.u);
-    c.go->to_closures(s, g, false, D.gb, D.b);
+    c.go->to_closures(s, grid_local(c), kInteriorZero, D.gu[c.cur], D.lu, D.gb, D.lb);
 }
 void grid_from_local(hhgr_ctx &c, hipStream_t s) {
     LevelDev &D = c.lev[c.L];
-    c.go->from_closures(s, grid_closures(c, D.vd_loc, D.n_loc, false), D.u, D.gu[c.cur]);
+    c.go->from_closures(s, grid_local(c), D.lu, D.gu[c.cur]);
 }
+
+// Slot vectors of a grid context's levels l and l - 1 for single operators:
+// u, b (or either of the coarser level) and r (or the fused sweeps' second u)
+// in the scratch vectors and the idle buffer of the finest u, which is zero
+// again at the end.
+struct SlotScratch {
+    hhgr_ctx &c;
+    int l;
+    SlotScratch(hhgr_ctx &c_, int l_) : c(c_), l(l_) {
+        if (!c.go) return;
+        LevelDev &D = c.lev[l], &F = c.lev[c.L];
+        double *idle = F.gu[1 - c.cur];
+        D.u = c.aux_u;
+        D.b = c.aux_b;
+        D.r = idle;
+        if (D.fz_ps && !c.mixed) D.ualt = idle;
+        if (l > c.Lc) c.lev[l - 1].u = c.lev[l - 1].b = c.aux_b;
+        for (double *v : {c.aux_u, c.aux_b, idle}) launch_fill<double>(c.stream, v, D.n_slots, 0.0);
+    }
+    ~SlotScratch() {
+        if (!c.go) return;
+        LevelDev &D = c.lev[l];
+        launch_fill<double>(c.stream, D.r, D.n_slots, 0.0);
+        D.u = D.b = D.r = D.ualt = nullptr;
+        if (l > c.Lc) c.lev[l - 1].u = c.lev[l - 1].b = nullptr;
+    }
+};
 
 // transform matrix and eigenvalues of the coarsest level (see k_grid_coarse)
 std::vector<double> sine_table(int N) {
@@ -1465,6 +1529,11 @@ void grid_plan(const GridOps &o, LevelDev &D, bool mixed, bool vk) {
     D.tl[0][kGridProlong][kGridPlain] = get(1, kGridProlong, kGridPlain, w);
     for (int start : {kGridFromU, kGridProlong}) D.tl[0][start][kGridNorm] = get(1, start, kGridNorm, 8);
     D.tl_res = get(0, kGridFromU, kGridResidual, 8);
+    // Dirichlet-Neumann sweeps: FP64 with edge weights
+    vk = true;
+    for (int start : {kGridFromZero, kGridFromU})
+        for (int tail : {kGridPlain, kGridRestrict}) D.tl_dn[start][tail] = get(1, start, tail, 8);
+    D.tl_dn[kGridProlong][kGridPlain] = get(1, kGridProlong, kGridPlain, 8);
 }
 
 void step_fp64(hhgr_ctx &c, const HView<double> &V, hipStream_t s, int slot) {
@@ -1562,7 +1631,7 @@ void set_loc(hhgr_ctx &c, const std::vector<int> &tets) {
         LevelDev &D = c.lev[l];
         h[l].resize(tets.size());
         for (size_t f = 0; f < tets.size(); f++) {
-            h[l][f].vec = (l == c.L ? (long long)tets[f] : (long long)f) * D.C_pad;
+            h[l][f].vec = (l == c.L && !c.go ? (long long)tets[f] : (long long)f) * D.C_pad;
             h[l][f].w = (long long)tets[f] * D.C_pad;
             h[l][f].tet = tets[f];
             h[l][f].pad = 0;
@@ -1763,24 +1832,60 @@ void dd_final_norm(hhgr_ctx &c, hipStream_t s) {
 // interface); the faulty side runs local Dirichlet cycles whose boundary
 // values are refreshed from the interface at the start of every round
 // ----------------------------------------------------------------------------
+
+// edge weights of the grid's levels over the elements of intact tetrahedra
+// (faulty: their flags; null: over all again), in the closures of vd_loc
+void grid_intact_weights(hhgr_ctx &c, const unsigned char *faulty) {
+    for (int l = c.Lc + 1; l <= c.L; l++) {
+        LevelDev &D = c.lev[l];
+        c.go->intact_weights(c.stream, grid_closures(c, D, D.vd_loc, D.n_loc), c.d.n_sub, D.h, D.kc, faulty, D.gw,
+                             D.gcode, grid_len(D.N));
+    }
+}
+
+// Dirichlet-Neumann recovery on the grid, after the masks of dn_setup: frozen
+// nodes, intact-side weights and coarsest operator, Neumann data at the
+// interface in b (the values there are kept in gsave until grid_dn_end),
+// interiors of the faulty tetrahedra zero, local hierarchy
+int grid_dn_setup(hhgr_ctx &c, const std::vector<int> &ft) {
+    LevelDev &F = c.lev[c.L];
+    const LevelDev &Dc = c.lev[c.Lc];
+    set_loc(c, ft);
+    const GridTets g = grid_tets(c, ft);
+    for (int l = c.Lc + 1; l <= c.L; l++) {
+        LevelDev &D = c.lev[l];
+        c.go->freeze_inside(c.stream, D.N, D.m, g, D.n_ifc, D.ifc_xyz, D.frozen, D.gfrz);
+    }
+    launch_ifc_weights_intact(c.stream, F.n_ifc, F.ifc_xyz, F.N, F.m, c.d.n_sub, F.h, c.vk ? F.kc : nullptr, c.dn_faulty,
+                              F.wi_dn);
+    launch_coarse_vals_intact(c.stream, c.cn, c.cpos, c.ccol, Dc.N, Dc.m, c.d.n_sub, Dc.h, c.vk ? Dc.kc : nullptr,
+                              c.dn_faulty, c.cval_dn);
+    grid_intact_weights(c, c.dn_faulty);
+    c.go->zero_tets(c.stream, F.N, F.m, g, F.gu[c.cur]);
+    c.go->neumann(c.stream, F.n_ifc, F.ifc_xyz, F.N, F.wi_dn, F.gamma, F.gu[c.cur], F.gb, F.gsave);
+    grid_to_local(c, c.stream);
+    // the frozen unknowns of the coarsest level are not written: zero
+    launch_fill<double>(c.stream, Dc.gu[0], grid_len(Dc.N), 0.0);
+    CHKLAUNCH();
+    return HHGR_OK;
+}
+// the recovered interiors back to the grid; b and the weights as before
+void grid_dn_end(hhgr_ctx &c) {
+    LevelDev &F = c.lev[c.L];
+    grid_from_local(c, c.stream);
+    c.go->neumann_end(c.stream, F.n_ifc, F.ifc_xyz, F.N, F.gamma, F.gsave, F.gb);
+    grid_intact_weights(c, nullptr);
+}
+
 // the caller keeps the tables until the stream is synchronised
 int dn_setup(hhgr_ctx &c, const std::vector<int> &ft, RecoveryTables &keep) {
     std::vector<unsigned char> &isf = keep.isf;
     isf.assign(c.n_tets, 0);
     for (int t : ft) isf[t] = 1;
-    if (c.go) {
-        // the intact side's interface stencils are per master: this recovery
-        // runs in slot space (its right-hand side goes to aux_b)
-        LevelDev &D = c.lev[c.L];
-        c.go->to_closures(c.stream, grid_closures(c, D.vd_all, c.n_tets, true), false, D.gu[c.cur], D.u);
-        c.go->to_masters(c.stream, D.n_ifc, D.ifc_xyz, D.N, D.gu[c.cur], D.u + D.ifc_base);
-        c.go->to_closures(c.stream, grid_closures(c, D.vd_all, c.n_tets, false), false, D.gb, c.aux_b);
-        c.go->to_masters(c.stream, D.n_ifc, D.ifc_xyz, D.N, D.gb, c.aux_b + D.ifc_base);
-    }
     int rc = upload(c, c.dn_faulty, isf.data(), isf.size());
     std::vector<std::vector<VolDesc>> &vds = keep.vds;
     vds.assign(c.L + 1, {});
-    for (int l = c.Lc; l <= c.L; l++) {
+    for (int l = c.Lc; l <= c.L && !c.go; l++) {  // (the grid has no lists of intact tetrahedra)
         LevelDev &D = c.lev[l];
         for (int t = 0; t < c.n_tets; t++)
             if (!isf[t]) vds[l].push_back(VolDesc{(long long)t * D.C_pad, (long long)t * D.C_pad, t, 0});
@@ -1810,6 +1915,7 @@ int dn_setup(hhgr_ctx &c, const std::vector<int> &ft, RecoveryTables &keep) {
     for (int q = 0; q < cs.n; q++) cf[q] = cs.is_vol[q] ? isf[cs.tet[q]] : frc[cs.ifc[q]];
     rc = upload(c, c.cfrozen, cf.data(), cf.size());
     if (rc) return rc;
+    if (c.go) return grid_dn_setup(c, ft);
     // intact-side operators on every level
     if (c.mesh) {
         // master rows over the elements of intact tetrahedra (host), and the
@@ -1882,10 +1988,7 @@ int dn_setup(hhgr_ctx &c, const std::vector<int> &ft, RecoveryTables &keep) {
     LevelDev &F = c.lev[c.L];
     // static Neumann data from the data at the time of the fault (u_F plays
     // no part: its edges have zero intact-side weight)
-    if (c.go)
-        c.go->to_closures(c.stream, grid_closures(c, F.vd_loc, F.n_loc, true), false, F.gb, F.b);
-    else
-        HIPCHK(hipMemcpyAsync(c.aux_b, F.b, F.n_slots * sizeof(double), hipMemcpyDeviceToDevice, c.stream));
+    HIPCHK(hipMemcpyAsync(c.aux_b, F.b, F.n_slots * sizeof(double), hipMemcpyDeviceToDevice, c.stream));
     if (c.mesh)
         launch_neumann_rhs_w(c.stream, F.n_ifc, F.ifc_base, F.nb15, F.wi15_dn, F.nbw, F.gamma, F.u, c.aux_b);
     else if (c.gen)
@@ -2187,27 +2290,26 @@ int create_ctx(const hhgr_desc *desc, std::shared_ptr<const Topology> mesh_topo,
         // zero every vector (also the Dirichlet ghosts and the zero slot)
         if (D.ualt) launch_fill<double>(c->stream, D.ualt, T.n_slots, 0.0);
         if (D.u32alt) launch_fill<float>(c->stream, D.u32alt, T.n_slots, 0.0f);
-        launch_fill<double>(c->stream, D.u, T.n_slots, 0.0);
-        launch_fill<double>(c->stream, D.b, T.n_slots, 0.0);
-        launch_fill<double>(c->stream, D.r, T.n_slots, 0.0);
-        if (c->mixed) {
+        if (!c->go) {
+            launch_fill<double>(c->stream, D.u, T.n_slots, 0.0);
+            launch_fill<double>(c->stream, D.b, T.n_slots, 0.0);
+            launch_fill<double>(c->stream, D.r, T.n_slots, 0.0);
+        }
+        if (c->mixed && !c->go) {
             launch_fill<float>(c->stream, D.u32, T.n_slots, 0.0f);
             launch_fill<float>(c->stream, D.b32, T.n_slots, 0.0f);
             launch_fill<float>(c->stream, D.r32, T.n_slots, 0.0f);
         }
-        if (D.lu) {
-            const long long n = (long long)std::max(c->d.max_faults, 1) * T.C_pad;
-            launch_fill<double>(c->stream, D.lu, n, 0.0);
-            launch_fill<double>(c->stream, D.lb, n, 0.0);
-            launch_fill<double>(c->stream, D.lr, n, 0.0);
-        }
+        for (double *v : {D.lu, D.lb, D.lr})
+            if (v) launch_fill<double>(c->stream, v, (long long)local_max(*c) * T.C_pad, 0.0);
+        if (D.gcode) launch_fill<unsigned char>(c->stream, D.gcode, 3 * grid_len(D.N), 6);
         launch_fill<unsigned char>(c->stream, D.frozen, T.n_ifc, 0);
         if (c->vk && c->gen) {
             launch_fill<double>(c->stream, D.wv, 8 * T.n_slots, 0.0);
             launch_fill<double>(c->stream, D.wi15, 15LL * T.n_ifc, 0.0);
         } else if (c->vk) {
             for (int s = 0; s < 3; s++) launch_fill<double>(c->stream, D.w[s], T.n_slots, 0.0);
-            if (c->mixed)
+            if (c->mixed && !c->go)
                 for (int s = 0; s < 3; s++) launch_fill<float>(c->stream, D.w32[s], T.n_slots, 0.0f);
         }
     }
@@ -2464,7 +2566,6 @@ int hhgr_set_rhs(hhgr_ctx *c, const double *dev_vec, int kind) {
         } else {
             launch_dirichlet_load(c->stream, D.N, D.h, c->vk ? D.kc : nullptr, dev_vec, c->aux_u);
             gb = c->go->from_user(c->stream, D.N, c->aux_u, D.gb, c->gpartial);
-            aux_used = true;
         }
     } else if (kind == HHGR_RHS_DIRICHLET && c->mesh) {
         // g at the boundary nodes (hhgr_mesh_boundary order): b = -A_IB g
@@ -2525,14 +2626,22 @@ int hhgr_set_coeff(hhgr_ctx *c, const double *dev_k) {
     }
     for (int l = c->Lc; l <= c->L; l++) {
         LevelDev &D = c->lev[l];
+        if (D.gw) {
+            // the grid's weights from k; those of slot space (local cycles,
+            // single operators) are the same numbers
+            c->go->weights(c->stream, D.N, D.h, D.kc, D.gw, D.gw32, grid_len(D.N));
+            c->go->closure_weights(c->stream, grid_closures(*c, D, D.vd_all, c->n_tets), D.gw, grid_len(D.N), D.w[0],
+                                   D.w[1], D.w[2]);
+            c->go->master_weights(c->stream, D.n_ifc, D.ifc_xyz, D.N, D.gw, grid_len(D.N), D.wi);
+            continue;
+        }
         launch_vol_weights(c->stream, vgeom(D, D.vd_all, c->n_tets, true), c->tetinfo, D.m, D.N, D.h, D.kc, D.w[0],
                            D.w[1], D.w[2]);
         launch_ifc_weights(c->stream, D.n_ifc, D.ifc_xyz, D.N, D.h, D.kc, D.wi);
-        if (c->mixed) {
+        if (c->mixed && !c->go) {
             for (int s = 0; s < 3; s++) launch_cast<double, float>(c->stream, D.w[s], D.w32[s], D.n_slots);
             launch_cast<double, float>(c->stream, D.wi, D.wi32, 6LL * D.n_ifc);
         }
-        if (D.gw) c->go->weights(c->stream, D.N, D.h, D.kc, D.gw, D.gw32, grid_len(D.N));
     }
     const LevelDev &Dc = c->lev[c->Lc];
     launch_coarse_vals(c->stream, c->cn, c->cpos, c->ccol, Dc.N, Dc.h, Dc.kc, c->cval);
@@ -2811,25 +2920,41 @@ int hhgr_recover_dn(hhgr_ctx *c, const int *tets, int n_tets, int n_intact, int 
     RecoveryTables keep(c->stream);
     rc = dn_setup(*c, ft, keep);
     if (rc) return rc;
-    HView<double> VI = dn_view(*c);
-    HView<double> VL = local_view(*c, 1, c->aux_u);
+    // (on the grid: whatever happens, b and the weights are the whole problem's again)
+    struct End {
+        hhgr_ctx *c;
+        ~End() {
+            if (!c) return;
+            grid_dn_end(*c);
+            hipStreamSynchronize(c->stream);
+        }
+    } end{c->go ? c : nullptr};
+    const HView<double> VI = c->go ? HView<double>() : dn_view(*c);
+    const HView<double> VL = local_view(*c, 1, c->aux_u);
+    LevelDev &F = c->lev[c->L];
     for (int q = 0; q < n_intact; q++) {
         // the faulty side reads the interface values of the start of the round
-        refresh_faulty_ghosts(*c, ft, c->stream);
+        if (c->go)
+            c->go->to_closures(c->stream, grid_local(*c), kInteriorKeep, F.gu[c->cur], F.lu, nullptr, nullptr);
+        else
+            refresh_faulty_ghosts(*c, ft, c->stream);
         HIPCHK(hipEventRecord(c->ev_fork, c->stream));
         HIPCHK(hipStreamWaitEvent(c->stream2, c->ev_fork, 0));
         // the intact cycle first: its launches then reach the GPU while the
         // host is still launching the many small local kernels
-        vcycle<double>(*c, VI, c->L, false, c->stream);
+        if (c->go)
+            c->cur = grid_cycle<double>(*c, c->L, false, c->cur, kSideNeumann, false, c->stream);
+        else
+            vcycle<double>(*c, VI, c->L, false, c->stream);
         for (int e = 0; e < eta; e++) vcycle<double>(*c, VL, c->L, false, c->stream2);
         HIPCHK(hipEventRecord(c->ev_join, c->stream2));
         HIPCHK(hipStreamWaitEvent(c->stream, c->ev_join, 0));
     }
-    refresh_faulty_ghosts(*c, ft, c->stream);
     if (c->go) {
-        LevelDev &D = c->lev[c->L];
-        c->go->from_closures(c->stream, grid_closures(*c, D.vd_all, c->n_tets, false), D.u, D.gu[c->cur]);
-        c->go->from_masters(c->stream, D.n_ifc, D.ifc_xyz, D.N, D.u + D.ifc_base, D.gu[c->cur]);
+        grid_dn_end(*c);
+        end.c = nullptr;
+    } else {
+        refresh_faulty_ghosts(*c, ft, c->stream);
     }
     CHKLAUNCH();
     HIPCHK(hipStreamSynchronize(c->stream));
@@ -2887,11 +3012,7 @@ static int grid_adjoint(hhgr_ctx &c, const double *dev_g, double rel_tol, int ma
         hhgr_report rep{0, 0.0, nullptr, 0};
         result = gn > 0 ? hhgr_solve(&c, rel_tol, max_cycles, &rep) : HHGR_OK;
         if (dev_dJdf) c.go->mass_user(c.stream, D.N, D.h, D.gu[c.cur], dev_dJdf);
-        if (dev_dJdk) {
-            c.go->to_user(c.stream, D.N, c.aux_u, c.user_u);
-            c.go->to_user(c.stream, D.N, D.gu[c.cur], c.user_l);
-            launch_grad_k(c.stream, c.user_u, c.user_l, D.N, D.h, dev_dJdk);
-        }
+        if (dev_dJdk) c.go->grad_k(c.stream, D.N, D.h, c.aux_u, D.gu[c.cur], dev_dJdk);
     }
     // restore the forward state
     hipMemcpyAsync(D.gu[c.cur], c.aux_u, bytes, hipMemcpyDeviceToDevice, c.stream);
@@ -3124,6 +3245,69 @@ int hhgr_autotune(hhgr_ctx *c, const char *cache_path) {
         };
         double best = 1e30;
         int bq = 1, br = 1, bc = 1;
+        if (c->go) {
+            // the launches of the local cycles, on one tetrahedron of the local
+            // hierarchy (global cycles run on the grid): workgroup size and
+            // block order of the red pass, then nodes per thread of the
+            // residual, the prolongation and the pass that adds the correction
+            const LevelDev &Dc = c->lev[l - 1];
+            for (double *v : {D.lu, D.lb, D.lr, Dc.lu}) launch_fill<double>(c->stream, v, v == Dc.lu ? Dc.C_pad : D.C_pad, 0.0);
+            const Weights<double> w = weights<double>(D);
+            auto shape = [&](int colour, int npt) {
+                VolGeom vg = vgeom(D, D.vd_all, 1, false, -1, colour);
+                vg.cpb = npt;
+                return vg;
+            };
+            for (int rq = 0; rq < 12; rq++) {
+                D.bs_sel = rq % 3;
+                D.remap = (rq / 3) % 2 == 0 ? 1 : 0;
+                const int npt = rq < 6 ? 1 : 4;
+                const float ms = time_it([&]() {
+                    launch_colour<double>(c->stream, shape(0, npt), ig_none(), D.lu, D.lb, w, c->vk, D.h, c->d.omega, false,
+                                          false);
+                }, 20);
+                if (ms < best) {
+                    best = ms;
+                    bq = D.bs_sel;
+                    br = D.remap;
+                    bc = npt;
+                }
+            }
+            D.bs_sel = bq;
+            D.remap = br;
+            D.cpb = bc;
+            float tr[2], tp[2], tf[2];
+            for (int qc = 0; qc < 2; qc++) {
+                const int npt = qc ? 4 : 1;
+                tr[qc] = time_it([&]() {
+                    launch_residual<double, double>(c->stream, shape(-1, npt), ig_none(), D.lu, D.lb, w, c->vk, D.h, D.lr,
+                                                    nullptr);
+                }, 20);
+                tp[qc] = time_it([&]() {
+                    launch_prolong<double>(c->stream, shape(1, npt), Dc.vd_all, Dc.rowC, Dc.M, ig_none(), D.prl, Dc.lu, D.lu);
+                }, 20);
+                Prol<double> pr;
+                pr.vdc = Dc.vd_all;
+                pr.cC = Dc.rowC;
+                pr.Mc = Dc.M;
+                pr.prl = D.prl;
+                pr.ec = Dc.lu;
+                tf[qc] = time_it([&]() {
+                    launch_colour_prol<double>(c->stream, shape(0, npt), ig_none(), D.lu, D.lb, w, c->vk, D.h, c->d.omega, pr);
+                }, 20);
+            }
+            D.cpb_res = tr[1] < tr[0] ? 4 : 1;
+            D.cpb_prl = tp[1] < tp[0] ? 4 : 1;
+            D.cpb_fus = tf[1] < tf[0] ? 4 : 1;
+            cache[ks.str()] = bq;
+            cache[ks.str() + ":remap"] = br;
+            cache[ks.str() + ":cpb"] = bc;
+            cache[ks.str() + ":cpb_res"] = D.cpb_res;
+            cache[ks.str() + ":cpb_prl"] = D.cpb_prl;
+            cache[ks.str() + ":cpb_fus"] = D.cpb_fus;
+            if (D.fz_ps) cache[ks.str() + ":fused"] = 0;  // (no cycle on the grid uses the pairs)
+            continue;
+        }
         if (c->gen) {
             // general macro mesh: workgroup size and block order of the class
             // pass (one node per thread); the residual takes the same shape
@@ -3294,6 +3478,7 @@ int hhgr_debug_op(hhgr_ctx *c, int op, int l, const double *in0, const double *i
     const bool fused_op = !c->gen && (op == 9 || op == 10);
     if (l < c->Lc || l > c->L || op < 0 || (op > 7 && !class_op && !fused_op))
         return fail(HHGR_EINVAL, "bad op or level");
+    SlotScratch scratch(*c, l);
     if (fused_op && !fused_ok(*c, global_view<double>(*c, false, 0), l, true))
         return fail(HHGR_EINVAL, "no fused sweeps on this level of this context");
     if (c->gen && (op == 1 || op == 2)) return fail(HHGR_EINVAL, "general_geometry: class passes are op 8 + class mask");

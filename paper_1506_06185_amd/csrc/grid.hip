@@ -5,6 +5,7 @@
 #include <cstdlib>
 #include <type_traits>
 
+#include "elements.hpp"
 #include "grid.hpp"
 #include "kernels.hpp"
 
@@ -27,6 +28,9 @@ __device__ __forceinline__ unsigned grid_xcd(unsigned f, unsigned total) {
 // workgroups of the variants with edge weights: their registers allow 3
 // wavefronts per SIMD
 constexpr int kVkThreads = 512;
+// edges of a launch: weight h everywhere, weights in the vectors' type, or
+// element counts in bytes (GridSweep::code)
+constexpr int kEdgeUniform = 0, kEdgeWeights = 1, kEdgeCodes = 2;
 
 // halo of a launch of K = 2 ns colour passes: nodes below and above a tile
 // along each axis
@@ -73,7 +77,7 @@ __device__ __forceinline__ void block_partial(double sum, double *partial) {
 // and 64 in node order with every pass's weights loaded; loading two steps
 // ahead 43, 62 and 56); bound by the instructions of the passes, of which the
 // halo repeats as many again.
-template <typename T, int NS, int START, int TAIL, bool MASK, bool VK>
+template <typename T, int NS, int START, int TAIL, bool MASK, int VK>
 __global__ void __launch_bounds__(VK ? kVkThreads : 1024) k_grid_sweep(GridSweep<T> g, GridTiles t, T h, T om, T omr) {
     constexpr int K = 2 * NS;
     constexpr bool RES = TAIL != kGridPlain;
@@ -125,7 +129,7 @@ __global__ void __launch_bounds__(VK ? kVkThreads : 1024) k_grid_sweep(GridSweep
     struct Load {
         Pair<T> u, b;
         T e0, e1, e2;
-        unsigned short m;
+        unsigned short m, mu;
     };
     auto plane = [&](int z) { return min(max(z, 0), N); };
     // input of plane z and right-hand side of plane z - 1
@@ -138,6 +142,7 @@ __global__ void __launch_bounds__(VK ? kVkThreads : 1024) k_grid_sweep(GridSweep
             L.e0 = el[cl];
             L.e1 = eh[ch];
             L.e2 = eh[ch + 1];
+            if (MASK) L.mu = *(const unsigned short *)(g.frz + zu * S + off);
         }
         if (MASK) L.m = *(const unsigned short *)(g.frz + zb * S + off);
     };
@@ -159,10 +164,18 @@ __global__ void __launch_bounds__(VK ? kVkThreads : 1024) k_grid_sweep(GridSweep
     Load ld[2];
     issue(zs + 1, ld[1]);
     issue(zs + 2, ld[0]);
+    const T hw = h / T(6);  // weight of one element at an edge (codes)
     // edge weights of a step's passes: along x to the neighbouring thread's
     // column and to the pair's other column, y - 1, y + 1, z - 1, z + 1
+    using W = std::conditional_t<VK == kEdgeCodes, unsigned char, T>;
+    using E = std::conditional_t<VK == kEdgeCodes, unsigned, T>;
+    const W *gw = nullptr;
+    if constexpr (VK == kEdgeCodes)
+        gw = g.code;
+    else
+        gw = g.w;
     struct Edges {
-        T x, o, ym, yp, zm, zp;
+        E x, o, ym, yp, zm, zp;
     };
     Edges ew[VK ? NL : 1] = {}, keep[2] = {};
     auto edges = [&](auto par, int z) {
@@ -178,8 +191,8 @@ __global__ void __launch_bounds__(VK ? kVkThreads : 1024) k_grid_sweep(GridSweep
             for (int k = 0; k < (NL > 2 ? 2 : NL); k++) {
                 const long long zp = (min(max(z - k, 1), N - 1)) * (S >> 1);
                 // the pass's own colour k & 1, and the other one
-                const T *wo = g.w + (k & 1 ? half : 0) + zp, *wn = g.w + (k & 1 ? 0 : half) + zp;
-                const T wr = wo[o], wl = wn[o + (unsigned)xl - 1u];
+                const W *wo = gw + (k & 1 ? half : 0) + zp, *wn = gw + (k & 1 ? 0 : half) + zp;
+                const E wr = wo[o], wl = wn[o + (unsigned)xl - 1u];
                 ew[k].x = right ? wr : wl;
                 ew[k].o = right ? wl : wr;
                 ew[k].yp = wo[g.wstride + o];
@@ -203,8 +216,9 @@ __global__ void __launch_bounds__(VK ? kVkThreads : 1024) k_grid_sweep(GridSweep
             T ul = START == kGridFromZero ? T(0) : L.u.lo, uh = START == kGridFromZero ? T(0) : L.u.hi;
             if (START == kGridProlong) {
                 // a coarse node's own value (twice the half) at even (x, y, z)
-                ul += T(0.5) * (L.e0 + L.e1);
-                uh += T(0.5) * (L.e0 + L.e2);
+                const T el = T(0.5) * (L.e0 + L.e1), eh = T(0.5) * (L.e0 + L.e2);
+                ul += !MASK || !(L.mu & 0xffu) ? el : T(0);
+                uh += !MASK || !(L.mu >> 8) ? eh : T(0);
             }
             in0[0] = yo ? uh : ul;
             in0[1] = yo ? ul : uh;
@@ -246,7 +260,12 @@ __global__ void __launch_bounds__(VK ? kVkThreads : 1024) k_grid_sweep(GridSweep
                 rr = bh[X][0];
             } else {
                 ctr = k == 1 ? uc[X] : pv[X][k - 2];
-                if constexpr (VK) {
+                if constexpr (VK == kEdgeCodes) {
+                    const Edges &e = ew[k - 1];
+                    const T a = ((T(e.x) * nx[k - 1] + T(e.o) * pv[Y][k - 1]) + (T(e.ym) * ny[k - 1] + T(e.yp) * nw[k - 1])) +
+                                (T(e.zp) * res[k - 1] + T(e.zm) * pv[X][k - 1]);
+                    rr = bh[X][k - 1] - hw * (T(e.x + e.o + e.ym + e.yp + e.zm + e.zp) * ctr - a);
+                } else if constexpr (VK) {
                     const Edges &e = ew[k - 1];
                     const T a = ((e.x * nx[k - 1] + e.o * pv[Y][k - 1]) + (e.ym * ny[k - 1] + e.yp * nw[k - 1])) +
                                 (e.zp * res[k - 1] + e.zm * pv[X][k - 1]);
@@ -258,7 +277,10 @@ __global__ void __launch_bounds__(VK ? kVkThreads : 1024) k_grid_sweep(GridSweep
             }
             if (k <= K) {
                 T scale = om;
-                if constexpr (VK) {
+                if constexpr (VK == kEdgeCodes) {
+                    const Edges &e = ew[k - 1];
+                    scale = om / (hw * T(e.x + e.o + e.ym + e.yp + e.zm + e.zp));
+                } else if constexpr (VK) {
                     const Edges &e = ew[k - 1];
                     scale = om / (((e.x + e.o) + (e.ym + e.yp)) + (e.zm + e.zp));
                 }
@@ -439,15 +461,22 @@ __device__ __forceinline__ long long grid_weight(int N, long long ws, int x, int
 }
 
 template <typename T>
-__global__ void __launch_bounds__(256) k_grid_plain_residual(int N, T h, const T *u, const T *b, const T *w, long long ws, T *r) {
+__global__ void __launch_bounds__(256) k_grid_plain_residual(int N, T h, const T *u, const T *b, const T *w,
+                                                             const unsigned char *code, const unsigned char *frz,
+                                                             long long ws, T *r) {
     int x, y, z;
     if (!grid_node(N, x, y, z)) return;
     const int P = N + 16;
     const long long S = (long long)P * N, i = x + (long long)P * y + S * z;
-    if (w) {
+    if (frz && frz[i]) {
+        r[i] = T(0);
+        return;
+    }
+    if (w || code) {
+        auto at = [&](long long q) { return w ? w[q] : h / T(6) * T(code[q]); };
         const long long o = grid_weight(N, ws, x, y, z);
-        const T a = w[grid_weight(N, ws, x - 1, y, z)], c = w[o], d = w[ws + grid_weight(N, ws, x, y - 1, z)], e = w[ws + o];
-        const T f = w[2 * ws + grid_weight(N, ws, x, y, z - 1)], g = w[2 * ws + o];
+        const T a = at(grid_weight(N, ws, x - 1, y, z)), c = at(o), d = at(ws + grid_weight(N, ws, x, y - 1, z)), e = at(ws + o);
+        const T f = at(2 * ws + grid_weight(N, ws, x, y, z - 1)), g = at(2 * ws + o);
         r[i] = b[i] - ((((a + c) + (d + e)) + (f + g)) * u[i] -
                        (((a * u[i - 1] + c * u[i + 1]) + (d * u[i - P] + e * u[i + P])) + (f * u[i - S] + g * u[i + S])));
         return;
@@ -468,13 +497,14 @@ __global__ void __launch_bounds__(256) k_grid_plain_restrict(int N, const T *r, 
 }
 
 template <typename T>
-__global__ void __launch_bounds__(256) k_grid_plain_prolong(int N, const T *u, const T *ec, T *v) {
+__global__ void __launch_bounds__(256) k_grid_plain_prolong(int N, const T *u, const T *ec, const unsigned char *frz,
+                                                             T *v) {
     int x, y, z;
     if (!grid_node(N, x, y, z)) return;
     const long long P = N + 16, i = x + P * (y + (long long)N * z), Pc = N / 2 + 16, Nc = N / 2;
     const T e0 = ec[(x >> 1) + Pc * ((y >> 1) + Nc * (z >> 1))];
     const T e1 = ec[((x + 1) >> 1) + Pc * (((y + 1) >> 1) + Nc * ((z + 1) >> 1))];
-    v[i] = u[i] + T(0.5) * (e0 + e1);
+    v[i] = frz && frz[i] ? u[i] : u[i] + T(0.5) * (e0 + e1);
 }
 
 // ---------------------------------------------------------------------------
@@ -848,8 +878,8 @@ __global__ void __launch_bounds__(1024) k_grid_mass(int N, int vz, double h3, co
 // holds the edge; zero at edges with an end outside the interior's
 // neighbourhood (never read)
 // ---------------------------------------------------------------------------
-template <int A>
-__device__ __forceinline__ double edge_sum(const double *k, int N, int x, int y, int z) {
+template <int A, typename F>
+__device__ __forceinline__ double edge_sum(int N, int x, int y, int z, F element) {
     constexpr int kP[6][3] = {{0, 1, 2}, {0, 2, 1}, {1, 0, 2}, {1, 2, 0}, {2, 0, 1}, {2, 1, 0}};
     double s = 0.0;
 #pragma unroll
@@ -861,22 +891,60 @@ __device__ __forceinline__ double edge_sum(const double *k, int N, int x, int y,
 #pragma unroll
         for (int q = 0; q < 6; q++) {
             if (kP[q][ns] != A || (ns > 0 && !dl[kP[q][0]]) || (ns > 1 && !dl[kP[q][1]])) continue;
-            s += k[6 * cell + q];
+            s += element(cell, x - dl[0], y - dl[1], z - dl[2], kP[q], q);
         }
     }
     return s;
+}
+// the weights v of the edges from a node along x, y and z; element: value of
+// an element of an edge (its cell's index and position, its axis order and
+// number), summed in a fixed order
+template <typename F>
+__device__ __forceinline__ void node_edges(int N, int x, int y, int z, double (&v)[3], F element) {
+    const bool xi = x >= 1 && x < N, yi = y >= 1 && y < N, zi = z >= 1 && z < N;
+    v[0] = x < N && yi && zi ? edge_sum<0>(N, x, y, z, element) : 0.0;
+    v[1] = y < N && xi && zi ? edge_sum<1>(N, x, y, z, element) : 0.0;
+    v[2] = z < N && xi && yi ? edge_sum<2>(N, x, y, z, element) : 0.0;
 }
 __global__ void __launch_bounds__(256) k_grid_weights(int N, double h, const double *k, double *w, float *w32, long long ws) {
     const int x = (int)(blockIdx.x * 64 + (threadIdx.x & 63)), y = (int)(blockIdx.y * 4 + (threadIdx.x >> 6)), z = (int)blockIdx.z;
     if (x >= N || y >= N) return;
     const long long i = grid_weight(N, ws, x, y, z);
-    const bool xi = x >= 1, yi = y >= 1, zi = z >= 1;
-    const double v[3] = {yi && zi ? edge_sum<0>(k, N, x, y, z) * h / 6.0 : 0.0, xi && zi ? edge_sum<1>(k, N, x, y, z) * h / 6.0 : 0.0,
-                         xi && yi ? edge_sum<2>(k, N, x, y, z) * h / 6.0 : 0.0};
+    double v[3];
+    node_edges(N, x, y, z, v, [&](long long cell, int, int, int, const int *, int q) { return k[6 * cell + q]; });
 #pragma unroll
     for (int a = 0; a < 3; a++) {
-        w[a * ws + i] = v[a];
-        if (w32) w32[a * ws + i] = (float)v[a];
+        const double e = v[a] * h / 6.0;
+        w[a * ws + i] = e;
+        if (w32) w32[a * ws + i] = (float)e;
+    }
+}
+
+// dJ/dk of the 6 elements of a cell; the grid holds the Dirichlet zeros
+__global__ void __launch_bounds__(256) k_grid_grad_k(int N, double h, const double *u, const double *lam, double *out) {
+    const long long cell = blockIdx.x * 256LL + threadIdx.x;
+    if (cell >= (long long)N * N * N) return;
+    const int cx = (int)(cell % N), cy = (int)((cell / N) % N), cz = (int)(cell / ((long long)N * N));
+    const long long P = N + 16, S = P * N, i = cx + P * cy + S * cz;
+    double uc[8], lc[8];
+#pragma unroll
+    for (int d = 0; d < 8; d++) {
+        const long long q = i + (d & 1) + ((d & 2) ? P : 0) + ((d & 4) ? S : 0);
+        uc[d] = u[q];
+        lc[d] = lam[q];
+    }
+    constexpr int kP[6][3] = {{0, 1, 2}, {0, 2, 1}, {1, 0, 2}, {1, 2, 0}, {2, 0, 1}, {2, 1, 0}};
+#pragma unroll
+    for (int q = 0; q < 6; q++) {
+        int v = 0;
+        double g = 0.0;
+#pragma unroll
+        for (int s = 0; s < 3; s++) {
+            const int w = v | (1 << kP[q][s]);
+            g += (lc[v] - lc[w]) * (uc[v] - uc[w]);
+            v = w;
+        }
+        out[6 * cell + q] = -(h / 6.0) * g;
     }
 }
 
@@ -886,8 +954,9 @@ __global__ void __launch_bounds__(256) k_grid_weights(int N, double h, const dou
 // tetinfo: subcube corner V (3), first two axes a, b; closure node (i, j, k)
 // at m V + i e_a + j (e_a + e_b) + k (1, 1, 1)
 struct GNode {
-    long long g, s;  // grid index, slot
-    bool interior;
+    int x, y, z;
+    long long w;  // weight slot
+    int tet;
 };
 __device__ __forceinline__ bool closure_node(const GridClosures &c, GNode &o) {
     const unsigned per = ((unsigned)c.nlist + 255u) >> 8;
@@ -903,36 +972,193 @@ __device__ __forceinline__ bool closure_node(const GridClosures &c, GNode &o) {
     const int a = ti[3], b = ti[4];
 #pragma unroll
     for (int q = 0; q < 3; q++) X[q] += (q == a ? i + j : 0) + (q == b ? j : 0);
-    o.g = X[0] + (long long)(c.N + 16) * (X[1] + (long long)c.N * X[2]);
+    o.x = X[0];
+    o.y = X[1];
+    o.z = X[2];
+    o.tet = d.tet;
     const int2 r = c.rowC[k * c.M - ((k * (k - 1)) >> 1) + j];
-    o.s = d.vec + ((((i + k) & 1) ? r.y : r.x) + (i >> 1));
-    o.interior = i > 0 && j > 0 && k > 0 && i + j + k < m;
-    // the plane after the last holds x = N and y = N of the last row: zeros
+    o.w = d.w + (((i + k) & 1) ? r.y : r.x) + (i >> 1);
     return true;
 }
 
-__global__ void __launch_bounds__(256) k_grid_to_closures(GridClosures c, bool zero_interior, const double *grid, double *vec) {
-    GNode o;
-    if (!closure_node(c, o)) return;
-    vec[o.s] = zero_interior && o.interior ? 0.0 : grid[o.g];
+// Grid <-> closures of single tetrahedra.  Slots run along the tetrahedron's
+// first axis a, the grid along x: where the two differ a wavefront takes
+// patches of 8 nodes along x by 8 along a, so that both sides move 64-byte
+// pieces (a node list in slot order reads one 8-byte word of every line).
+// Loads and stores are marked as used once: lines that stay in the L2 of the
+// XCD that converts them slow the local cycles, which go over these vectors
+// from other XCDs (cycle of one tetrahedron at m = 128: 116 to 120 us after
+// plain accesses, 110 to 114 after these, 108 with no conversion before).
+// TO: grid -> u (interior nodes as told) and, if gb is given, the interior of b.
+// A wavefront has four independent pieces in flight: of a row of the grid, or
+// of a patch along a.
+constexpr int kClosureSteps = 4, kClosurePatch = 8 * kClosureSteps;
+__host__ __device__ constexpr int closure_waves(int M) {
+    const int rows = M * M, patches = M * ((M + 7) / 8) * ((M + kClosurePatch - 1) / kClosurePatch);
+    return rows > patches ? rows : patches;
 }
-__global__ void __launch_bounds__(256) k_grid_from_closures(GridClosures c, const double *vec, double *grid) {
-    GNode o;
-    if (closure_node(c, o)) grid[o.g] = vec[o.s];
-}
-__global__ void __launch_bounds__(256) k_grid_to_masters(int n, const int *xyz, int N, const double *grid, double *masters) {
-    const int q = (int)(blockIdx.x * 256 + threadIdx.x);
-    if (q < n) masters[q] = grid[xyz[3 * q] + (long long)(N + 16) * (xyz[3 * q + 1] + (long long)N * xyz[3 * q + 2])];
-}
-__global__ void __launch_bounds__(256) k_grid_from_masters(int n, const int *xyz, int N, const double *masters, double *grid) {
-    const int q = (int)(blockIdx.x * 256 + threadIdx.x);
-    if (q < n) grid[xyz[3 * q] + (long long)(N + 16) * (xyz[3 * q + 1] + (long long)N * xyz[3 * q + 2])] = masters[q];
+// a value that is the same in every lane of a wavefront
+#if __has_builtin(__builtin_amdgcn_readfirstlane)
+__device__ __forceinline__ int wave_uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+#else
+__device__ __forceinline__ int wave_uniform(int v) { return v; }
+#endif
+#if __has_builtin(__builtin_nontemporal_load)
+__device__ __forceinline__ double load_once(const double *p) { return __builtin_nontemporal_load(p); }
+__device__ __forceinline__ void store_once(double *p, double v) { __builtin_nontemporal_store(v, p); }
+#else
+__device__ __forceinline__ double load_once(const double *p) { return *p; }
+__device__ __forceinline__ void store_once(double *p, double v) { *p = v; }
+#endif
+template <bool TO>
+__global__ void __launch_bounds__(256) k_grid_closures(GridLocal c, int interior, const double *gu, double *u, const double *gb,
+                                                       double *b, double *grid) {
+    const int M = c.M, m = M - 1, waves = closure_waves(M), lane = (int)(threadIdx.x & 63);
+    const int wv = wave_uniform((int)(blockIdx.x * 4 + (threadIdx.x >> 6))), t = wv / waves, w = wv - t * waves;
+    if (t >= c.tets.n) return;
+    const int V0 = c.tets.info[t][0], V1 = c.tets.info[t][1], V2 = c.tets.info[t][2], ax = c.tets.info[t][3], bx = c.tets.info[t][4];
+    const int P = c.N + 16, S = P * c.N;  // (offsets within a subcube fit 32 bits)
+    const int pa = ax == 0 ? 1 : ax == 1 ? P : S, pb = bx == 0 ? 1 : bx == 1 ? P : S, pc = ax + bx == 3 ? 1 : ax + bx == 2 ? P : S;
+    // pieces: nodes (A, db, dc) along the axes a, b, c
+    int a0, db, dc, rounds = 1;
+    if (ax == 0) {  // a row along x
+        if (w >= M * M) return;
+        const int y = w % M, z = w / M;
+        db = bx == 1 ? y : z;
+        dc = bx == 1 ? z : y;
+        if (db < dc) return;
+        a0 = db + lane;
+        rounds = (m - db) / (64 * kClosureSteps) + 1;
+    } else {
+        const int p8 = (M + 7) / 8, q = w / p8, pn = (M + kClosurePatch - 1) / kClosurePatch, r = q / pn;
+        const int x0 = 8 * (w - q * p8), x = x0 + (lane & 7);
+        a0 = kClosurePatch * (q - r * pn);
+        // a patch that misses the closure (m >= A >= db >= dc >= 0)
+        if (r >= M || (bx == 0 ? x0 + 7 < r || a0 + kClosurePatch <= x0 : x0 > r || a0 + kClosurePatch <= r)) return;
+        db = bx == 0 ? x : r;
+        dc = bx == 0 ? r : x;
+        a0 += 2 * (lane >> 3);
+    }
+    const bool row = db >= dc && db <= m, face = db == dc || dc == 0;  // face: every node of the row is on the boundary
+    const int *rc = (const int *)(c.rowC + (row ? dc * M - ((dc * (dc - 1)) >> 1) + db - dc : 0));
+    const int red = rc[0], black = rc[1];  // first slots of the row's nodes
+    const long long g0 = m * V0 + (long long)P * (m * V1) + (long long)S * (m * V2), s0 = (long long)t * c.stride;
+    for (int q = 0; q < rounds; q++, a0 += 64 * kClosureSteps) {
+        double uv[kClosureSteps], bv[kClosureSteps];
+        bool in[kClosureSteps], inner[kClosureSteps];
+        int s[kClosureSteps], g[kClosureSteps];
+#pragma unroll
+        for (int e = 0; e < kClosureSteps; e++) {
+            // (a patch: nodes of one colour, consecutive slots, per step)
+            const int A = a0 + (ax == 0 ? 64 * e : 16 * (e >> 1) + (e & 1)), i = A - db;
+            in[e] = row && i >= 0 && A <= m;
+            inner[e] = in[e] && !face && i > 0 && A < m;
+            s[e] = (((i + dc) & 1) ? black : red) + (i >> 1);
+            g[e] = A * pa + db * pb + dc * pc;
+            uv[e] = bv[e] = 0.0;
+            if (TO) {
+                if (in[e] && (!inner[e] || interior == kInteriorCopy)) uv[e] = load_once(gu + g0 + g[e]);
+                if (gb && inner[e]) bv[e] = load_once(gb + g0 + g[e]);
+            } else if (inner[e]) {
+                uv[e] = u[s0 + s[e]];
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < kClosureSteps; e++) {
+            if (TO) {
+                if (in[e] && !(inner[e] && interior == kInteriorKeep)) store_once(u + s0 + s[e], uv[e]);
+                if (gb && inner[e]) store_once(b + s0 + s[e], bv[e]);
+            } else if (inner[e]) {
+                store_once(grid + g0 + g[e], uv[e]);
+            }
+        }
+    }
 }
 
-// nodes of the listed tetrahedra: strictly inside them (zeroed) or their
-// closures (frozen).  A wavefront per grid row of the tetrahedron's
+// per-element k: a node's three edges along its tetrahedron's axes, gathered
+// from the grid's weights
+__global__ void __launch_bounds__(256) k_grid_closure_weights(GridClosures c, const double *w, long long ws, double *w0, double *w1,
+                                                              double *w2) {
+    GNode o;
+    if (!closure_node(c, o)) return;
+    const bool in[3] = {o.x >= 1 && o.x < c.N, o.y >= 1 && o.y < c.N, o.z >= 1 && o.z < c.N};
+    const bool has[3] = {o.x < c.N && in[1] && in[2], o.y < c.N && in[0] && in[2], o.z < c.N && in[0] && in[1]};
+    const long long i = grid_weight(c.N, ws, min(o.x, c.N - 1), min(o.y, c.N - 1), min(o.z, c.N - 1));
+    const double v[3] = {has[0] ? w[i] : 0.0, has[1] ? w[ws + i] : 0.0, has[2] ? w[2 * ws + i] : 0.0};
+    const int *ti = c.tetinfo + 6 * o.tet;
+    const int a = ti[3], b = ti[4], d = ti[5];
+    w0[o.w] = a == 0 ? v[0] : a == 1 ? v[1] : v[2];
+    w1[o.w] = b == 0 ? v[0] : b == 1 ? v[1] : v[2];
+    w2[o.w] = d == 0 ? v[0] : d == 1 ? v[1] : v[2];
+}
+__global__ void __launch_bounds__(256) k_grid_master_weights(int n, const int *xyz, int N, const double *w, long long ws, double *wi) {
+    const int t = (int)(blockIdx.x * 256 + threadIdx.x);
+    if (t >= n) return;
+    const int x = xyz[3 * t], y = xyz[3 * t + 1], z = xyz[3 * t + 2];  // an interior node
+    const long long o = grid_weight(N, ws, x, y, z), m = n;
+    wi[t] = w[o];
+    wi[m + t] = w[grid_weight(N, ws, x - 1, y, z)];
+    wi[2 * m + t] = w[ws + o];
+    wi[3 * m + t] = w[ws + grid_weight(N, ws, x, y - 1, z)];
+    wi[4 * m + t] = w[2 * ws + o];
+    wi[5 * m + t] = w[2 * ws + grid_weight(N, ws, x, y, z - 1)];
+}
+
+// the intact side of a Dirichlet-Neumann recovery (eq. (5)): edge weights over
+// the elements of intact tetrahedra; only edges in the closures of faulty ones
+// lose any
+__global__ void __launch_bounds__(256) k_grid_intact_weights(GridClosures c, int n_sub, double h, const double *k,
+                                                             const unsigned char *faulty, double *w, unsigned char *code,
+                                                             long long ws) {
+    GNode o;
+    if (!closure_node(c, o) || o.x >= c.N || o.y >= c.N || o.z >= c.N) return;
+    const int m = c.M - 1;
+    double v[3];
+    node_edges(c.N, o.x, o.y, o.z, v, [&](long long cell, int cx, int cy, int cz, const int *p, int q) {
+        const bool out = faulty && faulty[macro_tet_of(cx, cy, cz, p[0], p[1], p[2], m, n_sub)];
+        return out ? 0.0 : w ? k[6 * cell + q] : 1.0;
+    });
+    const long long i = grid_weight(c.N, ws, o.x, o.y, o.z);
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        if (w)
+            w[a * ws + i] = v[a] * h / 6.0;
+        else
+            code[a * ws + i] = (unsigned char)v[a];
+    }
+}
+__global__ void __launch_bounds__(256) k_grid_neumann(int n, const int *xyz, int N, const double *wi, const unsigned char *gamma,
+                                                      const double *u, double *b, double *save) {
+    const int t = (int)(blockIdx.x * 256 + threadIdx.x);
+    if (t >= n || !gamma[t]) return;
+    const long long P = N + 16, S = P * N, m = n;
+    const long long i = xyz[3 * t] + P * xyz[3 * t + 1] + S * xyz[3 * t + 2];
+    const double uo = u[i];
+    double s = 0.0;
+    s += wi[t] * (uo - u[i + 1]);
+    s += wi[m + t] * (uo - u[i - 1]);
+    s += wi[2 * m + t] * (uo - u[i + P]);
+    s += wi[3 * m + t] * (uo - u[i - P]);
+    s += wi[4 * m + t] * (uo - u[i + S]);
+    s += wi[5 * m + t] * (uo - u[i - S]);
+    save[t] = b[i];
+    b[i] = s;
+}
+__global__ void __launch_bounds__(256) k_grid_neumann_end(int n, const int *xyz, int N, const unsigned char *gamma, const double *save,
+                                                          double *b) {
+    const int t = (int)(blockIdx.x * 256 + threadIdx.x);
+    if (t < n && gamma[t]) b[xyz[3 * t] + (long long)(N + 16) * (xyz[3 * t + 1] + (long long)N * xyz[3 * t + 2])] = save[t];
+}
+__global__ void __launch_bounds__(256) k_grid_freeze_masters(int n, const int *xyz, int N, const unsigned char *frozen,
+                                                             unsigned char *frz) {
+    const int t = (int)(blockIdx.x * 256 + threadIdx.x);
+    if (t < n && frozen[t]) frz[xyz[3 * t] + (long long)(N + 16) * (xyz[3 * t + 1] + (long long)N * xyz[3 * t + 2])] = 1;
+}
+
+// nodes of the listed tetrahedra: strictly inside them (zeroed, or frozen) or
+// their closures (frozen).  A wavefront per grid row of the tetrahedron's
 // subcube walks the row's nodes of the tetrahedron, an interval along x.
-constexpr int kTetsZero = 0, kTetsFreeze = 1;
+constexpr int kTetsZero = 0, kTetsFreeze = 1, kTetsFreezeInside = 2;
 template <int MODE>
 __global__ void __launch_bounds__(256) k_grid_tets(int N, int m, GridTets t, double *grid, unsigned char *frz) {
     const int w = m + 1, per = (w * w + 3) / 4;
@@ -1033,16 +1259,22 @@ void sweep_mask(hipStream_t s, const GridTiles &t, const GridSweep<T> &g) {
     if constexpr (NS == 1) {
         if (g.w) {
             if (g.frz)
-                hipLaunchKernelGGL((k_grid_sweep<T, 1, START, TAIL, true, true>), grid, block, lds, s, g, t, h, (T)g.omega, omr);
+                hipLaunchKernelGGL((k_grid_sweep<T, 1, START, TAIL, true, kEdgeWeights>), grid, block, lds, s, g, t, h, (T)g.omega, omr);
             else
-                hipLaunchKernelGGL((k_grid_sweep<T, 1, START, TAIL, false, true>), grid, block, lds, s, g, t, h, (T)g.omega, omr);
+                hipLaunchKernelGGL((k_grid_sweep<T, 1, START, TAIL, false, kEdgeWeights>), grid, block, lds, s, g, t, h, (T)g.omega, omr);
             return;
+        }
+        if constexpr (sizeof(T) == 8 && TAIL != kGridNorm) {
+            if (g.code) {
+                hipLaunchKernelGGL((k_grid_sweep<T, 1, START, TAIL, true, kEdgeCodes>), grid, block, lds, s, g, t, h, (T)g.omega, omr);
+                return;
+            }
         }
     }
     if (g.frz)
-        hipLaunchKernelGGL((k_grid_sweep<T, NS, START, TAIL, true, false>), grid, block, lds, s, g, t, h, om, omr);
+        hipLaunchKernelGGL((k_grid_sweep<T, NS, START, TAIL, true, kEdgeUniform>), grid, block, lds, s, g, t, h, om, omr);
     else
-        hipLaunchKernelGGL((k_grid_sweep<T, NS, START, TAIL, false, false>), grid, block, lds, s, g, t, h, om, omr);
+        hipLaunchKernelGGL((k_grid_sweep<T, NS, START, TAIL, false, kEdgeUniform>), grid, block, lds, s, g, t, h, om, omr);
 }
 
 template <typename T>
@@ -1087,7 +1319,12 @@ dim3 node_blocks(int N) { return dim3((unsigned)cdiv(N - 1, 64), (unsigned)cdiv(
 
 template <typename T>
 void plain_residual(hipStream_t s, int N, double h, const T *u, const T *b, const T *w, long long ws, T *r) {
-    hipLaunchKernelGGL((k_grid_plain_residual<T>), node_blocks(N), dim3(256), 0, s, N, (T)h, u, b, w, ws, r);
+    hipLaunchKernelGGL((k_grid_plain_residual<T>), node_blocks(N), dim3(256), 0, s, N, (T)h, u, b, w,
+                       (const unsigned char *)nullptr, (const unsigned char *)nullptr, ws, r);
+}
+void plain_residual_intact(hipStream_t s, int N, double h, const double *u, const double *b, const double *w,
+                           const unsigned char *code, long long ws, const unsigned char *frz, double *r) {
+    hipLaunchKernelGGL((k_grid_plain_residual<double>), node_blocks(N), dim3(256), 0, s, N, h, u, b, w, code, frz, ws, r);
 }
 void weights(hipStream_t s, int N, double h, const double *k, double *w, float *w32, long long ws) {
     hipLaunchKernelGGL(k_grid_weights, dim3((unsigned)cdiv(N, 64), (unsigned)cdiv(N, 4), (unsigned)N), dim3(256), 0, s, N, h, k, w,
@@ -1099,7 +1336,10 @@ void plain_restrict(hipStream_t s, int N, const T *r, T *bc) {
 }
 template <typename T>
 void plain_prolong(hipStream_t s, int N, const T *u, const T *ec, T *v) {
-    hipLaunchKernelGGL((k_grid_plain_prolong<T>), node_blocks(N), dim3(256), 0, s, N, u, ec, v);
+    hipLaunchKernelGGL((k_grid_plain_prolong<T>), node_blocks(N), dim3(256), 0, s, N, u, ec, (const unsigned char *)nullptr, v);
+}
+void plain_prolong_intact(hipStream_t s, int N, const double *u, const double *ec, const unsigned char *frz, double *v) {
+    hipLaunchKernelGGL((k_grid_plain_prolong<double>), node_blocks(N), dim3(256), 0, s, N, u, ec, frz, v);
 }
 template <typename T>
 void coarse(hipStream_t s, int N, const double *st, const T *b, T *u) {
@@ -1162,19 +1402,38 @@ void mass_user(hipStream_t s, int N, double h, const double *grid, double *user)
     mass<true, false>(s, N, h, grid, user, nullptr);
 }
 unsigned closure_blocks(const GridClosures &c) { return (unsigned)(((c.nlist + 255) / 256) * c.nvol); }
-void to_closures(hipStream_t s, const GridClosures &c, bool zero_interior, const double *grid, double *vec) {
+dim3 closure_grid(const GridLocal &c) { return dim3((unsigned)((closure_waves(c.M) * c.tets.n + 3) / 4)); }
+void to_closures(hipStream_t s, const GridLocal &c, int interior, const double *gu, double *u, const double *gb, double *b) {
+    if (c.tets.n > 0)
+        hipLaunchKernelGGL(k_grid_closures<true>, closure_grid(c), dim3(256), 0, s, c, interior, gu, u, gb, b, (double *)nullptr);
+}
+void from_closures(hipStream_t s, const GridLocal &c, const double *vec, double *grid) {
+    if (c.tets.n > 0)
+        hipLaunchKernelGGL(k_grid_closures<false>, closure_grid(c), dim3(256), 0, s, c, kInteriorCopy, (const double *)nullptr,
+                           (double *)vec, (const double *)nullptr, (double *)nullptr, grid);
+}
+void closure_weights(hipStream_t s, const GridClosures &c, const double *w, long long ws, double *w0, double *w1, double *w2) {
     if (closure_blocks(c))
-        hipLaunchKernelGGL(k_grid_to_closures, dim3(closure_blocks(c)), dim3(256), 0, s, c, zero_interior, grid, vec);
+        hipLaunchKernelGGL(k_grid_closure_weights, dim3(closure_blocks(c)), dim3(256), 0, s, c, w, ws, w0, w1, w2);
 }
-void from_closures(hipStream_t s, const GridClosures &c, const double *vec, double *grid) {
-    if (closure_blocks(c)) hipLaunchKernelGGL(k_grid_from_closures, dim3(closure_blocks(c)), dim3(256), 0, s, c, vec, grid);
+void intact_weights(hipStream_t s, const GridClosures &c, int n_sub, double h, const double *k, const unsigned char *faulty, double *w,
+                    unsigned char *code, long long ws) {
+    if (closure_blocks(c))
+        hipLaunchKernelGGL(k_grid_intact_weights, dim3(closure_blocks(c)), dim3(256), 0, s, c, n_sub, h, k, faulty, w, code, ws);
 }
-void to_masters(hipStream_t s, int n, const int *xyz, int N, const double *grid, double *masters) {
-    if (n > 0) hipLaunchKernelGGL(k_grid_to_masters, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, s, n, xyz, N, grid, masters);
+dim3 master_blocks(int n) { return dim3((unsigned)cdiv(n, 256)); }
+void master_weights(hipStream_t s, int n, const int *xyz, int N, const double *w, long long ws, double *wi) {
+    if (n > 0) hipLaunchKernelGGL(k_grid_master_weights, master_blocks(n), dim3(256), 0, s, n, xyz, N, w, ws, wi);
 }
-void from_masters(hipStream_t s, int n, const int *xyz, int N, const double *masters, double *grid) {
-    if (n > 0)
-        hipLaunchKernelGGL(k_grid_from_masters, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, s, n, xyz, N, masters, grid);
+void neumann(hipStream_t s, int n, const int *xyz, int N, const double *wi, const unsigned char *gamma, const double *u, double *b,
+             double *save) {
+    if (n > 0) hipLaunchKernelGGL(k_grid_neumann, master_blocks(n), dim3(256), 0, s, n, xyz, N, wi, gamma, u, b, save);
+}
+void neumann_end(hipStream_t s, int n, const int *xyz, int N, const unsigned char *gamma, const double *save, double *b) {
+    if (n > 0) hipLaunchKernelGGL(k_grid_neumann_end, master_blocks(n), dim3(256), 0, s, n, xyz, N, gamma, save, b);
+}
+void grad_k(hipStream_t s, int N, double h, const double *u, const double *lam, double *out) {
+    hipLaunchKernelGGL(k_grid_grad_k, dim3((unsigned)(((long long)N * N * N + 255) / 256)), dim3(256), 0, s, N, h, u, lam, out);
 }
 template <int MODE>
 void tets(hipStream_t s, int N, int m, const GridTets &t, double *grid, unsigned char *frz) {
@@ -1184,9 +1443,18 @@ void tets(hipStream_t s, int N, int m, const GridTets &t, double *grid, unsigned
 void zero_tets(hipStream_t s, int N, int m, const GridTets &t, double *grid) {
     tets<kTetsZero>(s, N, m, t, grid, nullptr);
 }
-void freeze_tets(hipStream_t s, int N, int m, const GridTets &t, unsigned char *frz) {
+void freeze_none(hipStream_t s, int N, unsigned char *frz) {
     hipLaunchKernelGGL(k_grid_zero32, dim3(1024), dim3(256), 0, s, (unsigned *)frz, (grid_len(N) + 3) / 4);
+}
+void freeze_tets(hipStream_t s, int N, int m, const GridTets &t, unsigned char *frz) {
+    freeze_none(s, N, frz);
     tets<kTetsFreeze>(s, N, m, t, nullptr, frz);
+}
+void freeze_inside(hipStream_t s, int N, int m, const GridTets &t, int n, const int *xyz, const unsigned char *frozen,
+                   unsigned char *frz) {
+    freeze_none(s, N, frz);
+    tets<kTetsFreezeInside>(s, N, m, t, nullptr, frz);
+    if (n > 0) hipLaunchKernelGGL(k_grid_freeze_masters, master_blocks(n), dim3(256), 0, s, n, xyz, N, frozen, frz);
 }
 
 // Tile choice.  The time of a launch is modelled as the larger of two bounds
@@ -1257,6 +1525,8 @@ const GridOps kOps = {tiles,
                       residual_any,
                       plain_residual<double>,
                       plain_residual<float>,
+                      plain_residual_intact,
+                      plain_prolong_intact,
                       plain_restrict<double>,
                       plain_restrict<float>,
                       plain_prolong<double>,
@@ -1273,12 +1543,17 @@ const GridOps kOps = {tiles,
                       mass_load,
                       mass_user,
                       weights,
+                      closure_weights,
+                      master_weights,
+                      intact_weights,
+                      grad_k,
                       to_closures,
                       from_closures,
-                      to_masters,
-                      from_masters,
+                      neumann,
+                      neumann_end,
                       zero_tets,
-                      freeze_tets};
+                      freeze_tets,
+                      freeze_inside};
 
 }  // namespace
 

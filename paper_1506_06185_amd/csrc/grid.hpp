@@ -41,14 +41,18 @@ struct GridTiles {
 // interpolation of the coarse grid ec).  tail kGridRestrict also writes
 // bc = P^T (b - A v) at the interior coarse nodes, kGridNorm leaves
 // per-workgroup sums of (b - A v)^2 in partial.  frz (optional): one byte per
-// node of the grid; nonzero nodes keep their values and do not count.
+// node of the grid; nonzero nodes keep their values (take no correction) and
+// do not count.
 // w (optional): per-element k, the weight of the edge from each node along
 // +x, then (w + wstride) +y, then +z; else k = 1.  Each of the three arrays
 // holds the nodes of even x + y + z, then (wstride / 2 on) the odd ones, node
 // (x, y, z) at (x >> 1) + (P / 2) (y + N z).
+// code (optional, k = 1 with elements left out): weights as above, in bytes
+// that count the elements of the edge: weight = code h / 6, 6 where none is
+// left out.
 // Built: ns = 1 from u (any tail), from zero (plain, restrict) and
 // interpolating (plain, norm); ns = 2 from zero with k = 1 (plain, restrict);
-// norms in FP64 only.
+// norms in FP64 only; code in FP64 with frz and without norms.
 template <typename T>
 struct GridSweep {
     int N = 0;
@@ -61,6 +65,7 @@ struct GridSweep {
     const unsigned char *frz = nullptr;
     double *partial = nullptr;
     const T *w = nullptr;
+    const unsigned char *code = nullptr;
     long long wstride = 0;
 };
 
@@ -91,11 +96,23 @@ struct GridClosures {
     const int *tetinfo = nullptr;
     int M = 0, N = 0;
 };
+// what a transfer from the grid does with the interior nodes of the closures
+constexpr int kInteriorCopy = 0, kInteriorZero = 1, kInteriorKeep = 2;
 
 // faulty tetrahedra (subcube corner, axis order), passed by value
 struct GridTets {
     int n = 0;
     int info[8][6];
+};
+
+// closures of the local hierarchy on the finest level: container f (slots from
+// f stride on) holds tetrahedron f of tets; rowC: first red and black slot of
+// the rows of a container (M nodes per edge)
+struct GridLocal {
+    GridTets tets;
+    long long stride = 0;
+    const int2 *rowC = nullptr;
+    int M = 0, N = 0;
 };
 
 // tiles of vp x vy x vz own pairs, rows and planes (rows and planes rounded up
@@ -119,6 +136,11 @@ struct GridOps {
                              long long wstride, double *r);
     void (*plain_residual32)(hipStream_t, int N, double h, const float *u, const float *b, const float *w,
                              long long wstride, float *r);
+    // ... of an intact side whose frozen nodes do not hold their coarse
+    // parents' zero: r = 0 and no correction there; weights w, or code
+    void (*plain_residual_intact)(hipStream_t, int N, double h, const double *u, const double *b, const double *w,
+                                  const unsigned char *code, long long wstride, const unsigned char *frz, double *r);
+    void (*plain_prolong_intact)(hipStream_t, int N, const double *u, const double *ec, const unsigned char *frz, double *v);
     void (*plain_restrict64)(hipStream_t, int N, const double *r, double *bc);
     void (*plain_restrict32)(hipStream_t, int N, const float *r, float *bc);
     void (*plain_prolong64)(hipStream_t, int N, const double *u, const double *ec, double *v);
@@ -152,15 +174,37 @@ struct GridOps {
     // edge weights of a level from its k per element (w, and rounded to w32 if
     // not null)
     void (*weights)(hipStream_t, int N, double h, const double *k, double *w, float *w32, long long wstride);
-    // grid -> closures (list: every node; interior nodes get zero if
-    // zero_interior), closures -> grid (list: interior nodes)
-    void (*to_closures)(hipStream_t, const GridClosures &, bool zero_interior, const double *grid, double *vec);
-    void (*from_closures)(hipStream_t, const GridClosures &, const double *vec, double *grid);
-    void (*to_masters)(hipStream_t, int n, const int *xyz, int N, const double *grid, double *masters);
-    void (*from_masters)(hipStream_t, int n, const int *xyz, int N, const double *masters, double *grid);
-    // grid = 0 strictly inside the tetrahedra; frz = 1 on their closures, else 0
+    // the same weights in slot space: from a node of the closures (list: every
+    // node) along the tetrahedron's three axes, to w0, w1, w2 at the closures'
+    // weight slots; and of a master's edges along +x, -x, +y, -y, +z, -z, to
+    // [6][n] (weights of edges on the cube's boundary, which nothing reads: 0)
+    void (*closure_weights)(hipStream_t, const GridClosures &, const double *w, long long wstride, double *w0, double *w1,
+                            double *w2);
+    void (*master_weights)(hipStream_t, int n, const int *xyz, int N, const double *w, long long wstride, double *wi);
+    // weights of the edges from the nodes of the closures (list: every node)
+    // over the elements whose macro tetrahedron is not flagged in faulty (null:
+    // over all): w from the level's k per element, or code (w null)
+    void (*intact_weights)(hipStream_t, const GridClosures &, int n_sub, double h, const double *k,
+                           const unsigned char *faulty, double *w, unsigned char *code, long long wstride);
+    // dJ/dk_T = -(h/6) sum over the path edges (a, b) of T of (lam_a - lam_b)
+    // (u_a - u_b), element order
+    void (*grad_k)(hipStream_t, int N, double h, const double *u, const double *lam, double *out);
+    // grid -> closures: u (interior nodes: kInterior...) and the interior nodes
+    // of b (optional); interior nodes of the closures -> grid
+    void (*to_closures)(hipStream_t, const GridLocal &, int interior, const double *gu, double *u, const double *gb,
+                        double *b);
+    void (*from_closures)(hipStream_t, const GridLocal &, const double *vec, double *grid);
+    // at the masters flagged in gamma: save = b, then b = A u with the masters'
+    // weights wi [6][n] (+x, -x, +y, -y, +z, -z); and b = save
+    void (*neumann)(hipStream_t, int n, const int *xyz, int N, const double *wi, const unsigned char *gamma, const double *u,
+                    double *b, double *save);
+    void (*neumann_end)(hipStream_t, int n, const int *xyz, int N, const unsigned char *gamma, const double *save, double *b);
+    // grid = 0 strictly inside the tetrahedra; frz = 1 on their closures, or
+    // strictly inside them and at the masters flagged in frozen, else 0
     void (*zero_tets)(hipStream_t, int N, int m, const GridTets &, double *grid);
     void (*freeze_tets)(hipStream_t, int N, int m, const GridTets &, unsigned char *frz);
+    void (*freeze_inside)(hipStream_t, int N, int m, const GridTets &, int n, const int *xyz, const unsigned char *frozen,
+                          unsigned char *frz);
 };
 const GridOps *grid_ops() __attribute__((weak));
 

@@ -21,6 +21,7 @@
 
 #include <cstdint>
 
+#include "elements.hpp"
 #include "grid.hpp"
 #include "kernels.hpp"
 
@@ -1288,11 +1289,6 @@ __global__ void __launch_bounds__(256) k_update_add(const VolDesc *__restrict__ 
 // ---------------------------------------------------------------------------
 __device__ __constant__ int kPermD[6][3] = {{0, 1, 2}, {0, 2, 1}, {1, 0, 2}, {1, 2, 0}, {2, 0, 1}, {2, 1, 0}};
 
-__device__ __forceinline__ int perm_id(int a, int b) {
-    // third axis is implied
-    return a == 0 ? (b == 1 ? 0 : 1) : a == 1 ? (b == 0 ? 2 : 3) : (b == 0 ? 4 : 5);
-}
-
 // Bey children of coarse element (C, p) with a = e_p0, b = e_p1, c = e_p2:
 // (2C,p) (2C+a,p) (2C+a+b,p) (2C+a+b+c,p) (2C+a,(p1,p2,p0)) (2C+a,(p1,p0,p2))
 // (2C+a+b,(p2,p0,p1)) (2C+a+b,(p0,p2,p1)); coarse k = their mean.
@@ -1428,21 +1424,8 @@ __global__ void k_dirichlet_load(int N, double h, const double *__restrict__ k, 
 
 // Dirichlet-Neumann recovery (Sec. 4.3, eq. (5)): the intact side's
 // sub-stencils are the stiffness assembled over the elements of intact macro
-// tetrahedra only.  Fine element (cell c, permutation q) at a level with m
-// segments per macro edge lies in the macro tetrahedron of macro cell c / m
-// whose axis order sorts the element's centroid offsets in that macro cell.
-__device__ __forceinline__ int macro_tet_of(int cx, int cy, int cz, int p0, int p1, int p2, int m, int n_sub) {
-    const int C0 = cx / m, C1 = cy / m, C2 = cz / m;
-    // centroid offsets in quarter units: 3, 2, 1 along the element's axes p0, p1, p2
-    const int D0 = 4 * (cx - m * C0) + (p0 == 0 ? 3 : p1 == 0 ? 2 : 1);
-    const int D1 = 4 * (cy - m * C1) + (p0 == 1 ? 3 : p1 == 1 ? 2 : 1);
-    const int D2 = 4 * (cz - m * C2) + (p0 == 2 ? 3 : p1 == 2 ? 2 : 1);
-    const int a0 = D0 > D1 ? (D0 > D2 ? 0 : 2) : (D1 > D2 ? 1 : 2);
-    const int a2 = D0 < D1 ? (D0 < D2 ? 0 : 2) : (D1 < D2 ? 1 : 2);
-    const int a1 = 3 - a0 - a2;
-    return 6 * (C0 + n_sub * (C1 + n_sub * C2)) + perm_id(a0, a1);
-}
-__device__ __forceinline__ int macro_tet_of(int cx, int cy, int cz, int q, int m, int n_sub) {
+// tetrahedra only.
+__device__ __forceinline__ int macro_tet_of_q(int cx, int cy, int cz, int q, int m, int n_sub) {
     return macro_tet_of(cx, cy, cz, kPermD[q][0], kPermD[q][1], kPermD[q][2], m, n_sub);
 }
 
@@ -1555,7 +1538,7 @@ __device__ double gen_entry(const GenK &G, const int X[3], int dx, int dy, int d
             }
             if (rr < 0) continue;
             const long long e = 6 * (c[0] + (long long)G.N * (c[1] + (long long)G.N * c[2])) + q;
-            const int t = macro_tet_of(c[0], c[1], c[2], q, G.m, G.n_sub);
+            const int t = macro_tet_of_q(c[0], c[1], c[2], q, G.m, G.n_sub);
             if (G.faulty && G.faulty[t]) continue;
             s += (G.k ? G.k[e] : 1.0) * G.kel[(6LL * t + q) * 16 + 4 * r + rr];
         }
@@ -1599,7 +1582,7 @@ __global__ void k_grad_k15(int N, int m, int n_sub, const double *__restrict__ k
         ul[v] = in ? u[d] : 0.0;
         ll[v] = in ? lam[d] : 0.0;
     }
-    const double *K = kel + (6LL * macro_tet_of(c[0], c[1], c[2], q, m, n_sub) + q) * 16;
+    const double *K = kel + (6LL * macro_tet_of_q(c[0], c[1], c[2], q, m, n_sub) + q) * 16;
     double g = 0.0;
     for (int a = 0; a < 4; a++)
         for (int b = 0; b < 4; b++) g += ll[a] * K[4 * a + b] * ul[b];

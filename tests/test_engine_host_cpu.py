@@ -10,6 +10,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 @pytest.mark.parametrize("check,link", [
     ("engine_batch_check", []),
+    ("engine_grid_check", []),
     ("engine_mass_check", ["-Wl,--wrap=_ZN4hhgr16launch_mass_gridEP11mock_streamidPKdPd"]),
 ])
 def test_engine_host_logic(check, link, tmp_path):
