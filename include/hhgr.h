@@ -343,10 +343,10 @@ int hhgr_set_graph(hhgr_ctx *ctx, int use_graph);
  * (level, precision, coefficient mode) for all volume kernels of that level;
  * at that shape it then picks 1 or 4 nodes per thread separately for the
  * residual, the prolongation and the red post-smoothing pass that adds the
- * coarse-grid correction.  On the cube these launches are the recoveries'
- * (Dirichlet-Neumann, single tetrahedra); global cycles there choose their
- * tiles by a model, tuned or not.  cache_path (optional) is a text file read before
- * and written after tuning, keyed by device name.  Enqueues work and
+ * coarse-grid correction.  On the cube these launches are those of the local
+ * cycles (FP64, timed on one tetrahedron); global cycles there choose their
+ * tiles by a model, tuned or not.  cache_path (optional) is a text file read
+ * before and written after tuning, keyed by device name.  Enqueues work and
  * synchronises. */
 int hhgr_autotune(hhgr_ctx *ctx, const char *cache_path);
 
@@ -356,16 +356,13 @@ int hhgr_autotune(hhgr_ctx *ctx, const char *cache_path);
  * coarse_level+1..level. */
 int hhgr_tuning_info(const hhgr_ctx *ctx, int level, int *block_size, int *xcd_order, int *nodes_per_thread);
 
-/* Fused red-black sweeps (cube, k = 1; Sec. 2.1 smoother): on level
- * `level` (coarse_level < level <= level of the context), on = 1 runs every
- * two consecutive sweeps of an unmasked cycle as a pair of single-launch
- * sweeps (red and black of each plane in one kernel, planes marched through
- * LDS), on = 0 as two colour passes per sweep.  The iterates are the same
- * bit for bit.  The cube's global cycles, whose sweeps are single launches on
- * the grid anyway, do not depend on it.  hhgr_autotune sets it where the pair is faster; this call
- * overrides that (e.g. to time the kernel).  EINVAL where the fused kernel
- * cannot take the level (general or unstructured meshes, variable k, levels
- * with fewer than 8 segments per edge). */
+/* Fused red-black sweeps in slot space (cube, k = 1; Sec. 2.1 smoother): a pair
+ * of single-launch sweeps (red and black of each plane in one kernel, planes
+ * marched through LDS), which hhgr_debug_op 9 and 10 run.  The cube's cycles,
+ * whose sweeps are single launches on the grid, do not use the pair, so this
+ * call changes nothing; it is EINVAL where the fused kernel cannot take the
+ * level (general or unstructured meshes, variable k, levels with fewer than 8
+ * segments per edge). */
 int hhgr_set_fused_sweeps(hhgr_ctx *ctx, int level, int on);
 
 /* Set the tuning choices of one level (level = 0: every level above the

@@ -125,18 +125,14 @@ struct LevelDev {
     double *mw15 = nullptr, *mwtab = nullptr;  // finest level: mass stencils (indexed like w15, wtab)
     double *mwi = nullptr;                     // ... the masters' own mass rows (unstructured meshes)
     float *w15f = nullptr, *wtabf = nullptr, *wvf = nullptr, *wi15f = nullptr;  // FP32 copies (mixed precision)
-    // fused red-black sweeps (cube, k = 1, unmasked cycles): a second slot
-    // vector of u in the cycle's precision (the pair of sweeps goes u -> ualt
-    // -> u), plane starts and tiles (FusedGeom)
-    double *ualt = nullptr;
-    float *u32alt = nullptr;
+    // fused red-black sweeps in slot space (cube, k = 1; single operators
+    // only): plane starts and tiles (FusedGeom)
     int *fz_ps = nullptr;
     int4 *fz_tiles = nullptr;
     std::vector<int> fz_ps_host;
     std::vector<int4> fz_tiles_host;
     int fz_TJ = 0, fz_TK = 0;
     long long fz_black0 = 0;
-    bool fz_on = false;  // the cycles use fused pairs on this level (autotuner: where faster)
     // the cube: u (two buffers, a sweep goes from one to the other) and b on
     // the grid (grid.hpp), the frozen nodes of a recovery's intact side, and
     // the tiles of each kind of launch.  Slot vectors are scratch memory that
@@ -156,7 +152,6 @@ struct LevelDev {
 template <typename T>
 struct LevView {
     T *u = nullptr, *b = nullptr, *r = nullptr;
-    T *ualt = nullptr;  // second buffer of fused sweep pairs (unmasked cube cycles with k = 1), or nullptr
     Weights<T> w;
     const VolDesc *vd = nullptr;
     int nvol = 0;
@@ -495,11 +490,6 @@ void carve(hhgr_ctx &c, Carver &cv) {
         if (!c.gen && !c.vk && l > c.Lc && T.m >= 8 && fused_tables(T, D)) {
             D.fz_ps = cv.take<int>(D.fz_ps_host.size());
             D.fz_tiles = cv.take<int4>(D.fz_tiles_host.size());
-            if (c.go) {
-            } else if (c.mixed)
-                D.u32alt = cv.take<float>(T.n_slots);
-            else
-                D.ualt = cv.take<double>(T.n_slots);
         }
         D.nilist = (int)T.ilist.size();
         D.nrlist = (int)T.rlist.size();
@@ -823,11 +813,11 @@ template <typename T>
 T *lvec(LevelDev &D, int which);
 template <>
 double *lvec<double>(LevelDev &D, int which) {
-    return which == 0 ? D.u : which == 1 ? D.b : which == 2 ? D.r : D.ualt;
+    return which == 0 ? D.u : which == 1 ? D.b : D.r;
 }
 template <>
 float *lvec<float>(LevelDev &D, int which) {
-    return which == 0 ? D.u32 : which == 1 ? D.b32 : which == 2 ? D.r32 : D.u32alt;
+    return which == 0 ? D.u32 : which == 1 ? D.b32 : D.r32;
 }
 
 // global (all tetrahedra) or masked (intact tetrahedra, frozen interface) view
@@ -847,7 +837,6 @@ HView<T> global_view(hhgr_ctx &c, bool masked, int stream_idx) {
         v.u = lvec<T>(D, 0);
         v.b = lvec<T>(D, 1);
         v.r = lvec<T>(D, 2);
-        v.ualt = masked ? nullptr : lvec<T>(D, 3);
         v.w = weights<T>(D);
         v.vd = masked ? D.vd_masked : D.vd_all;
         v.nvol = masked ? D.n_masked : c.n_tets;
@@ -919,9 +908,6 @@ struct NormOut {
     double *partial = nullptr;
     int blocks = 0;
 };
-
-template <typename T>
-bool fused_ok(const hhgr_ctx &c, const HView<T> &V, int l, bool any = false);
 
 // general macro meshes: one 4-colour sweep, classes 0, 1, 2, 3 (a start
 // from zero clears the level's vector first).  The class-3 pass also sums
@@ -998,30 +984,20 @@ void sweep(hhgr_ctx &c, const HView<T> &V, int l, bool zero, hipStream_t s, cons
             launch_colour_res<T>(s, vg, ig, v.u, v.b, v.w, c.vk, D.h, c.d.omega, rout);
             continue;
         }
-        const bool timed = c.timing && V.timed && l == c.L && !fused_ok(c, V, l);
+        const bool timed = c.timing && V.timed && l == c.L;
         if (timed) timed_begin(c, s);
         launch_colour<T>(s, vg, ig, v.u, v.b, v.w, c.vk, D.h, c.d.omega, zero, zero && colour == 0);
         if (timed) timed_end(c, s);
     }
 }
 
-// the fused kernels apply: the cube with k = 1, every tetrahedron and
-// every master of the level (no frozen nodes, no intact-side stencils), a
-// second buffer for the level; and the level uses them (any = true: whether
-// or not the autotuner chose them)
-template <typename T>
-bool fused_ok(const hhgr_ctx &c, const HView<T> &V, int l, bool any) {
-    const LevelDev &D = c.lev[l];
-    const LevView<T> &v = V.lv[l];
-    return !c.gen && !c.vk && !V.local && v.ualt && v.ifc && !v.frozen && !v.w.wi && !v.gptr && D.fz_ps &&
-           v.vd == D.vd_all && v.nvol == c.n_tets && (any || D.fz_on);
-}
-
-template <typename T>
-FusedGeom fgeom(const LevelDev &D, const LevView<T> &v) {
+// one red-black sweep of a level of the cube (k = 1, every tetrahedron) from
+// us into ud in slot space: red masters, the volume interiors in one launch
+// (fused kernel), black masters.  zero: from u = 0.
+void fused_sweep(hhgr_ctx &c, const LevelDev &D, const double *us, double *ud, const double *b, bool zero, hipStream_t s) {
     FusedGeom g;
-    g.vd = v.vd;
-    g.nvol = v.nvol;
+    g.vd = D.vd_all;
+    g.nvol = c.n_tets;
     g.tiles = D.fz_tiles;
     g.ntiles = (int)D.fz_tiles_host.size();
     g.m = D.m;
@@ -1030,41 +1006,21 @@ FusedGeom fgeom(const LevelDev &D, const LevView<T> &v) {
     g.black0 = D.fz_black0;
     g.ps = D.fz_ps;
     g.remap = D.remap;
-    return g;
-}
-
-// one red-black sweep from us into ud: red masters, the volume interiors
-// (fused kernel), black masters.  zero: from u = 0; rout: black residual tail.
-template <typename T>
-void fused_sweep(hhgr_ctx &c, const HView<T> &V, int l, const T *us, T *ud, bool zero, hipStream_t s, T *rout) {
-    const LevelDev &D = c.lev[l];
-    const LevView<T> &v = V.lv[l];
+    double *const no_residual = nullptr;
     const IfcGeom red = igeom(D, 0, D.n_ifc_red, nullptr, true), black = igeom(D, D.n_ifc_red, D.n_ifc, nullptr, true);
-    launch_ifc_sor<T>(s, red, us, us, ud, v.b, D.h, c.d.omega, zero, zero, (T *)nullptr);
-    const bool timed = c.timing && V.timed && l == c.L && !zero && !rout;
-    if (timed) timed_begin(c, s);
-    launch_sweep_fused_vol<T>(s, fgeom(D, v), us, ud, v.b, D.h, c.d.omega, zero, rout);
-    if (timed) timed_end(c, s);
-    launch_ifc_sor<T>(s, black, us, ud, ud, v.b, D.h, c.d.omega, zero, false, rout);
+    launch_ifc_sor<double>(s, red, us, us, ud, b, D.h, c.d.omega, zero, zero, no_residual);
+    launch_sweep_fused_vol<double>(s, g, us, ud, b, D.h, c.d.omega, zero, no_residual);
+    launch_ifc_sor<double>(s, black, us, ud, ud, b, D.h, c.d.omega, zero, false, no_residual);
 }
 
-// nsweeps red-black sweeps in place.  Two sweeps in a row run fused where
-// fused_ok holds, the first into the level's second buffer and the second
-// back (the first sweep may start from zero, the second may write the
-// residual tail); a sweep that adds the coarse-grid correction (pr) or sums
-// the squared residual (nout) runs as two colour passes.
+// nsweeps red-black (4-class) sweeps in place: the first may start from zero
+// or add the coarse-grid correction (pr), the last may sum the squared
+// residual (nout) or write its black (class-3) part (rout)
 template <typename T>
 void smooth(hhgr_ctx &c, const HView<T> &V, int l, int nsweeps, bool zero, hipStream_t s,
-            const Prol<T> *pr = nullptr, NormOut *nout = nullptr, T *rout = nullptr, bool force_fused = false) {
-    const LevView<T> &v = V.lv[l];
+            const Prol<T> *pr = nullptr, NormOut *nout = nullptr, T *rout = nullptr) {
     for (int k = 0; k < nsweeps; k++) {
         const bool last = k == nsweeps - 1;
-        if (k + 1 < nsweeps && fused_ok(c, V, l, force_fused) && !(k == 0 && pr) && !(k + 1 == nsweeps - 1 && nout)) {
-            fused_sweep<T>(c, V, l, v.u, v.ualt, zero && k == 0, s, (T *)nullptr);
-            fused_sweep<T>(c, V, l, v.ualt, v.u, false, s, k + 1 == nsweeps - 1 ? rout : nullptr);
-            k++;
-            continue;
-        }
         sweep(c, V, l, zero && k == 0, s, k == 0 ? pr : nullptr, last ? nout : nullptr, last ? rout : nullptr);
     }
 }
@@ -1471,8 +1427,7 @@ void grid_from_local(hhgr_ctx &c, hipStream_t s) {
 }
 
 // Slot vectors of a grid context's levels l and l - 1 for single operators:
-// u, b (or either of the coarser level) and r (or the fused sweeps' second u)
-// in the scratch vectors and the idle buffer of the finest u, which is zero
+// u, b (or either of the coarser level) and r in the scratch vectors and the idle buffer of the finest u, which is zero
 // again at the end.
 struct SlotScratch {
     hhgr_ctx &c;
@@ -1484,7 +1439,6 @@ struct SlotScratch {
         D.u = c.aux_u;
         D.b = c.aux_b;
         D.r = idle;
-        if (D.fz_ps && !c.mixed) D.ualt = idle;
         if (l > c.Lc) c.lev[l - 1].u = c.lev[l - 1].b = c.aux_b;
         for (double *v : {c.aux_u, c.aux_b, idle}) launch_fill<double>(c.stream, v, D.n_slots, 0.0);
     }
@@ -1492,7 +1446,7 @@ struct SlotScratch {
         if (!c.go) return;
         LevelDev &D = c.lev[l];
         launch_fill<double>(c.stream, D.r, D.n_slots, 0.0);
-        D.u = D.b = D.r = D.ualt = nullptr;
+        D.u = D.b = D.r = nullptr;
         if (l > c.Lc) c.lev[l - 1].u = c.lev[l - 1].b = nullptr;
     }
 };
@@ -2288,8 +2242,6 @@ int create_ctx(const hhgr_desc *desc, std::shared_ptr<const Topology> mesh_topo,
             rc = rc ? rc : upload(*c, D.fz_tiles, D.fz_tiles_host.data(), D.fz_tiles_host.size() * sizeof(int4));
         }
         // zero every vector (also the Dirichlet ghosts and the zero slot)
-        if (D.ualt) launch_fill<double>(c->stream, D.ualt, T.n_slots, 0.0);
-        if (D.u32alt) launch_fill<float>(c->stream, D.u32alt, T.n_slots, 0.0f);
         if (!c->go) {
             launch_fill<double>(c->stream, D.u, T.n_slots, 0.0);
             launch_fill<double>(c->stream, D.b, T.n_slots, 0.0);
@@ -3119,10 +3071,8 @@ int hhgr_tuning_info(const hhgr_ctx *c, int level, int *block_size, int *xcd_ord
 int hhgr_set_fused_sweeps(hhgr_ctx *c, int level, int on) {
     if (!c) return fail(HHGR_EINVAL, "null context");
     if (level <= c->Lc || level > c->L) return fail(HHGR_EINVAL, "level outside coarse_level+1..level");
-    LevelDev &D = c->lev[level];
+    const LevelDev &D = c->lev[level];
     if (on && !D.fz_ps) return fail(HHGR_EINVAL, "no fused sweeps on this level of this context");
-    D.fz_on = on != 0;
-    invalidate_graph(*c);
     return HHGR_OK;
 }
 
@@ -3177,15 +3127,9 @@ int hhgr_kernel_stats(hhgr_ctx *c, long long *launches, double *mean_ms, double 
     // class pass of the 4-colour sweep reads the other 3 classes' u
     // (3/4 word per unknown) and 3 words per node of its class (1/4)
     const double w = c->mixed ? 4.0 : 8.0;
-    const LevelDev &F = c->lev[c->L];
     if (c->go) {
         // counted launch by launch
         if (alg_bytes) *alg_bytes = c->tev_used ? c->tev_bytes / (0.5 * (double)c->tev_used) : 0.0;
-    } else if (F.fz_on && (c->mixed ? F.u32alt != nullptr : F.ualt != nullptr)) {
-        // the fused sweep's volume kernel: u (both colours) and b read once,
-        // u written once, over the volume-interior nodes
-        const double mm = F.m;
-        if (alg_bytes) *alg_bytes = 3.0 * w * (double)c->n_tets * (mm - 1) * (mm - 2) * (mm - 3) / 6.0;
     } else if (alg_bytes) {
         *alg_bytes = (c->gen ? 1.5 : 2.0) * w * (double)c->n_dofs;
     }
@@ -3223,16 +3167,14 @@ int hhgr_autotune(hhgr_ctx *c, const char *cache_path) {
         auto itcr = cache.find(ks.str() + ":cpb_res");
         auto itcp = cache.find(ks.str() + ":cpb_prl");
         auto itcf = cache.find(ks.str() + ":cpb_fus");
-        auto itfz = cache.find(ks.str() + ":fused");
         if (it != cache.end() && itr != cache.end() && itc != cache.end() && itcr != cache.end() &&
-            itcp != cache.end() && itcf != cache.end() && (itfz != cache.end() || !D.fz_ps)) {
+            itcp != cache.end() && itcf != cache.end()) {
             D.bs_sel = it->second;
             D.remap = itr->second;
             D.cpb = itc->second;
             D.cpb_res = itcr->second;
             D.cpb_prl = itcp->second;
             D.cpb_fus = itcf->second;
-            D.fz_on = D.fz_ps && itfz->second != 0;
             continue;
         }
         auto time_it = [&](auto run, int reps) -> float {
@@ -3245,13 +3187,15 @@ int hhgr_autotune(hhgr_ctx *c, const char *cache_path) {
         };
         double best = 1e30;
         int bq = 1, br = 1, bc = 1;
-        if (c->go) {
-            // the launches of the local cycles, on one tetrahedron of the local
-            // hierarchy (global cycles run on the grid): workgroup size and
-            // block order of the red pass, then nodes per thread of the
-            // residual, the prolongation and the pass that adds the correction
+        if (!c->gen) {
+            // the cube: the launches of the local cycles, on the first container
+            // of the local hierarchy (global cycles run on the grid): workgroup
+            // size and block order of the red pass, then nodes per thread of
+            // the residual, the prolongation and the pass that adds the correction
             const LevelDev &Dc = c->lev[l - 1];
-            for (double *v : {D.lu, D.lb, D.lr, Dc.lu}) launch_fill<double>(c->stream, v, v == Dc.lu ? Dc.C_pad : D.C_pad, 0.0);
+            double *const u = D.lu ? D.lu : D.r, *const b = D.lb ? D.lb : D.b, *const r = D.lr;
+            for (double *v : {u, D.lb}) launch_fill<double>(c->stream, v, v ? D.C_pad : 0, 0.0);
+            launch_fill<double>(c->stream, Dc.lu, Dc.C_pad, 0.0);
             const Weights<double> w = weights<double>(D);
             auto shape = [&](int colour, int npt) {
                 VolGeom vg = vgeom(D, D.vd_all, 1, false, -1, colour);
@@ -3263,7 +3207,7 @@ int hhgr_autotune(hhgr_ctx *c, const char *cache_path) {
                 D.remap = (rq / 3) % 2 == 0 ? 1 : 0;
                 const int npt = rq < 6 ? 1 : 4;
                 const float ms = time_it([&]() {
-                    launch_colour<double>(c->stream, shape(0, npt), ig_none(), D.lu, D.lb, w, c->vk, D.h, c->d.omega, false,
+                    launch_colour<double>(c->stream, shape(0, npt), ig_none(), u, b, w, c->vk, D.h, c->d.omega, false,
                                           false);
                 }, 20);
                 if (ms < best) {
@@ -3280,11 +3224,11 @@ int hhgr_autotune(hhgr_ctx *c, const char *cache_path) {
             for (int qc = 0; qc < 2; qc++) {
                 const int npt = qc ? 4 : 1;
                 tr[qc] = time_it([&]() {
-                    launch_residual<double, double>(c->stream, shape(-1, npt), ig_none(), D.lu, D.lb, w, c->vk, D.h, D.lr,
-                                                    nullptr);
+                    launch_residual<double, double>(c->stream, shape(-1, npt), ig_none(), u, b, w, c->vk, D.h, r,
+                                                    r ? nullptr : c->partial[0]);
                 }, 20);
                 tp[qc] = time_it([&]() {
-                    launch_prolong<double>(c->stream, shape(1, npt), Dc.vd_all, Dc.rowC, Dc.M, ig_none(), D.prl, Dc.lu, D.lu);
+                    launch_prolong<double>(c->stream, shape(1, npt), Dc.vd_all, Dc.rowC, Dc.M, ig_none(), D.prl, Dc.lu, u);
                 }, 20);
                 Prol<double> pr;
                 pr.vdc = Dc.vd_all;
@@ -3293,7 +3237,7 @@ int hhgr_autotune(hhgr_ctx *c, const char *cache_path) {
                 pr.prl = D.prl;
                 pr.ec = Dc.lu;
                 tf[qc] = time_it([&]() {
-                    launch_colour_prol<double>(c->stream, shape(0, npt), ig_none(), D.lu, D.lb, w, c->vk, D.h, c->d.omega, pr);
+                    launch_colour_prol<double>(c->stream, shape(0, npt), ig_none(), u, b, w, c->vk, D.h, c->d.omega, pr);
                 }, 20);
             }
             D.cpb_res = tr[1] < tr[0] ? 4 : 1;
@@ -3305,161 +3249,37 @@ int hhgr_autotune(hhgr_ctx *c, const char *cache_path) {
             cache[ks.str() + ":cpb_res"] = D.cpb_res;
             cache[ks.str() + ":cpb_prl"] = D.cpb_prl;
             cache[ks.str() + ":cpb_fus"] = D.cpb_fus;
-            if (D.fz_ps) cache[ks.str() + ":fused"] = 0;  // (no cycle on the grid uses the pairs)
+            launch_fill<double>(c->stream, u, D.C_pad, 0.0);
             continue;
         }
-        if (c->gen) {
-            // general macro mesh: workgroup size and block order of the class
-            // pass (one node per thread); the residual takes the same shape
-            for (int rq = 0; rq < 6; rq++) {
-                const int q = rq % 3;
-                D.remap = rq < 3 ? 1 : 0;
-                VolGeom vg = vgeom(D, D.vd_all, c->n_tets, false, q);
-                vg.list = D.qlist[0];
-                vg.nlist = D.nqlist[0];
-                const float ms = time_it([&]() {
-                    launch_colour15(c->stream, vg, igeom(D, 0, D.n_ifc, nullptr, true), gen15(D, 0, true), D.r, D.b,
-                                    c->d.omega);
-                }, l >= 6 ? 5 : 20);
-                if (ms < best) {
-                    best = ms;
-                    bq = q;
-                    br = D.remap;
-                }
-            }
-            D.bs_sel = bq;
-            D.remap = br;
-            D.cpb = D.cpb_res = D.cpb_prl = D.cpb_fus = 1;
-            cache[ks.str()] = bq;
-            cache[ks.str() + ":remap"] = br;
-            cache[ks.str() + ":cpb"] = 1;
-            cache[ks.str() + ":cpb_res"] = 1;
-            cache[ks.str() + ":cpb_prl"] = 1;
-            cache[ks.str() + ":cpb_fus"] = 1;
-            launch_fill<double>(c->stream, D.r, D.n_slots, 0.0);
-            continue;
-        }
-        for (int rq = 0; rq < 12; rq++) {
+        // general macro mesh: workgroup size and block order of the class
+        // pass (one node per thread); the residual takes the same shape
+        for (int rq = 0; rq < 6; rq++) {
             const int q = rq % 3;
-            D.remap = (rq / 3) % 2 == 0 ? 1 : 0;
-            D.cpb = rq < 6 ? 1 : 4;
-            const VolGeom vg = vgeom(D, D.vd_all, c->n_tets, false, q, 0);
-            const IfcGeom ig = igeom(D, 0, D.n_ifc_red, nullptr, false);
-            auto run = [&]() {
-                if (c->mixed)
-                    launch_colour<float>(c->stream, vg, ig, D.r32, D.b32, weights<float>(D), c->vk, D.h, c->d.omega,
-                                         false, false);
-                else
-                    launch_colour<double>(c->stream, vg, ig, D.r, D.b, weights<double>(D), c->vk, D.h, c->d.omega,
-                                          false, false);
-            };
-            run();
-            HIPCHK(hipEventRecord(e0, c->stream));
-            const int reps = l >= 6 ? 5 : 20;
-            for (int r = 0; r < reps; r++) run();
-            HIPCHK(hipEventRecord(e1, c->stream));
-            HIPCHK(hipEventSynchronize(e1));
-            float ms = 0;
-            HIPCHK(hipEventElapsedTime(&ms, e0, e1));
+            D.remap = rq < 3 ? 1 : 0;
+            VolGeom vg = vgeom(D, D.vd_all, c->n_tets, false, q);
+            vg.list = D.qlist[0];
+            vg.nlist = D.nqlist[0];
+            const float ms = time_it([&]() {
+                launch_colour15(c->stream, vg, igeom(D, 0, D.n_ifc, nullptr, true), gen15(D, 0, true), D.r, D.b,
+                                c->d.omega);
+            }, l >= 6 ? 5 : 20);
             if (ms < best) {
                 best = ms;
                 bq = q;
                 br = D.remap;
-                bc = D.cpb;
             }
         }
         D.bs_sel = bq;
         D.remap = br;
-        D.cpb = bc;
+        D.cpb = D.cpb_res = D.cpb_prl = D.cpb_fus = 1;
         cache[ks.str()] = bq;
         cache[ks.str() + ":remap"] = br;
-        cache[ks.str() + ":cpb"] = bc;
-        // nodes per thread of the residual (norm form), of the prolongation
-        // (black nodes, as in the cycle) and of the red pass that adds the
-        // correction, at that workgroup size and block order; the scratch
-        // vectors r of this level and of the next coarser one stand in for
-        // u and the coarse correction
-        const int reps = l >= 6 ? 5 : 20;
-        float tr[2], tp[2], tf[2];
-        const LevelDev &Dc = c->lev[l - 1];
-        for (int qc = 0; qc < 2; qc++) {
-            VolGeom vg = vgeom(D, D.vd_all, c->n_tets, false);
-            vg.cpb = qc ? 4 : 1;
-            VolGeom vgb = vgeom(D, D.vd_all, c->n_tets, false, -1, 1);
-            vgb.cpb = vg.cpb;
-            VolGeom vgr = vgeom(D, D.vd_all, c->n_tets, false, -1, 0);
-            vgr.cpb = vg.cpb;
-            tr[qc] = time_it([&]() {
-                if (c->mixed)
-                    launch_residual<float, float>(c->stream, vg, igeom(D, 0, D.n_ifc, nullptr, false), D.r32, D.b32,
-                                                  weights<float>(D), c->vk, D.h, (float *)nullptr, c->partial[0]);
-                else
-                    launch_residual<double, double>(c->stream, vg, igeom(D, 0, D.n_ifc, nullptr, false), D.r, D.b,
-                                                    weights<double>(D), c->vk, D.h, (double *)nullptr, c->partial[0]);
-            }, reps);
-            tp[qc] = time_it([&]() {
-                const IfcGeom igb = igeom(D, D.n_ifc_red, D.n_ifc, nullptr, true);
-                if (c->mixed)
-                    launch_prolong<float>(c->stream, vgb, Dc.vd_all, Dc.rowC, Dc.M, igb, D.prl, Dc.r32, D.r32);
-                else
-                    launch_prolong<double>(c->stream, vgb, Dc.vd_all, Dc.rowC, Dc.M, igb, D.prl, Dc.r, D.r);
-            }, reps);
-            tf[qc] = time_it([&]() {
-                const IfcGeom igr = igeom(D, 0, D.n_ifc_red, nullptr, true);
-                if (c->mixed) {
-                    Prol<float> pr;
-                    pr.vdc = Dc.vd_all;
-                    pr.cC = Dc.rowC;
-                    pr.Mc = Dc.M;
-                    pr.prl = D.prl;
-                    pr.ec = Dc.r32;
-                    launch_colour_prol<float>(c->stream, vgr, igr, D.r32, D.b32, weights<float>(D), c->vk, D.h,
-                                              c->d.omega, pr);
-                } else {
-                    Prol<double> pr;
-                    pr.vdc = Dc.vd_all;
-                    pr.cC = Dc.rowC;
-                    pr.Mc = Dc.M;
-                    pr.prl = D.prl;
-                    pr.ec = Dc.r;
-                    launch_colour_prol<double>(c->stream, vgr, igr, D.r, D.b, weights<double>(D), c->vk, D.h,
-                                               c->d.omega, pr);
-                }
-            }, reps);
-        }
-        D.cpb_res = tr[1] < tr[0] ? 4 : 1;
-        D.cpb_prl = tp[1] < tp[0] ? 4 : 1;
-        D.cpb_fus = tf[1] < tf[0] ? 4 : 1;
-        cache[ks.str() + ":cpb_res"] = D.cpb_res;
-        cache[ks.str() + ":cpb_prl"] = D.cpb_prl;
-        cache[ks.str() + ":cpb_fus"] = D.cpb_fus;
-        // two sweeps as a fused pair (through the level's second buffer)
-        // against two sweeps of two colour passes each, from the scratch
-        // vector r; the cycles use the pair only where it is faster
-        if (D.fz_ps && (c->mixed ? D.u32alt != nullptr : D.ualt != nullptr)) {
-            HView<double> V64 = global_view<double>(*c, false, 0);
-            HView<float> V32 = global_view<float>(*c, false, 0);
-            V64.lv[l].u = D.r;
-            V32.lv[l].u = D.r32;
-            V64.timed = V32.timed = false;
-            const float t_pair = time_it([&]() {
-                if (c->mixed)
-                    smooth<float>(*c, V32, l, 2, false, c->stream, nullptr, nullptr, nullptr, true);
-                else
-                    smooth<double>(*c, V64, l, 2, false, c->stream, nullptr, nullptr, nullptr, true);
-            }, reps);
-            const float t_plain = time_it([&]() {
-                if (c->mixed)
-                    for (int q = 0; q < 2; q++) sweep<float>(*c, V32, l, false, c->stream);
-                else
-                    for (int q = 0; q < 2; q++) sweep<double>(*c, V64, l, false, c->stream);
-            }, reps);
-            D.fz_on = t_pair < t_plain;
-            cache[ks.str() + ":fused"] = D.fz_on ? 1 : 0;
-        }
-        // scratch vector used for timing goes back to zero
+        cache[ks.str() + ":cpb"] = 1;
+        cache[ks.str() + ":cpb_res"] = 1;
+        cache[ks.str() + ":cpb_prl"] = 1;
+        cache[ks.str() + ":cpb_fus"] = 1;
         launch_fill<double>(c->stream, D.r, D.n_slots, 0.0);
-        if (c->mixed) launch_fill<float>(c->stream, D.r32, D.n_slots, 0.0f);
     }
     hipEventDestroy(e0);
     hipEventDestroy(e1);
@@ -3479,7 +3299,7 @@ int hhgr_debug_op(hhgr_ctx *c, int op, int l, const double *in0, const double *i
     if (l < c->Lc || l > c->L || op < 0 || (op > 7 && !class_op && !fused_op))
         return fail(HHGR_EINVAL, "bad op or level");
     SlotScratch scratch(*c, l);
-    if (fused_op && !fused_ok(*c, global_view<double>(*c, false, 0), l, true))
+    if (fused_op && (!c->lev[l].fz_ps || c->mixed))
         return fail(HHGR_EINVAL, "no fused sweeps on this level of this context");
     if (c->gen && (op == 1 || op == 2)) return fail(HHGR_EINVAL, "general_geometry: class passes are op 8 + class mask");
     if ((op == 4 || op == 5) && l <= c->Lc) return fail(HHGR_EINVAL, "transfer needs level > coarse_level");
@@ -3591,8 +3411,8 @@ int hhgr_debug_op(hhgr_ctx *c, int op, int l, const double *in0, const double *i
         // two sweeps as a fused pair (op 10: the first from u = 0)
         to_slots(in0, D.u, D);
         to_slots(in1, D.b, D);
-        HView<double> V = global_view<double>(*c, false, 0);
-        smooth<double>(*c, V, l, 2, op == 10, s, nullptr, nullptr, nullptr, true);
+        fused_sweep(*c, D, D.u, D.r, D.b, op == 10, s);
+        fused_sweep(*c, D, D.r, D.u, D.b, false, s);
         to_user(D.u, out, D);
         break;
     }
