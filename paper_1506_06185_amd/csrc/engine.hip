@@ -1294,7 +1294,8 @@ int grid_cycle(hhgr_ctx &c, int l, bool zero, int q, int side, bool norm, hipStr
     };
     for (int k = 0; k < c.d.nu_pre;) {
         // two sweeps in one launch only from zero: there the first pass reads
-        // b alone (N = 256: 105 us against 67 + 110; from u 275 against 105 + 110)
+        // b alone (N = 256: 90 us against 57 + 102; from u 275 against 105 + 110
+        // when that was built)
         const int start = zero && k == 0 ? kGridFromZero : kGridFromU;
         // (with edge weights the second sweep's registers do not fit)
         const int ns = start == kGridFromZero && c.d.nu_pre >= 2 && !c.vk && !dn ? 2 : 1;

@@ -72,11 +72,14 @@ __device__ __forceinline__ void block_partial(double sum, double *partial) {
 // VK (per-element k): a pass needs the 6 edge weights of its node, which it
 // loads one step ahead; the residual of a red node reuses those of its red
 // pass two steps before.  The weights are stored split by colour (grid.hpp),
-// so the nodes of one pass read whole lines.  N = 128: 37, 61 and 55 us for a
-// plain sweep, one with restriction, one with interpolation and norm (39, 71
-// and 64 in node order with every pass's weights loaded; loading two steps
-// ahead 43, 62 and 56); bound by the instructions of the passes, of which the
-// halo repeats as many again.
+// so the nodes of one pass read whole lines.  N = 128: 33, 63 and 47 us for a
+// plain sweep, one with restriction, one with interpolation and norm (when the
+// layout was chosen 37, 61 and 55, against 39, 71 and 64 in node order with
+// every pass's weights loaded, and 43, 62 and 56 loading two steps ahead);
+// bound by the instructions of the passes, of which the halo repeats as many
+// again.  Bytes that count elements (k = 1, Dirichlet-Neumann) take 3 B per
+// node in place of 24: 28, 60 and 32 us, at N = 256 184, 296 and 230 (edge
+// weights 270, 391 and 361; one stencil with frozen nodes 99, 110 and 113).
 template <typename T, int NS, int START, int TAIL, bool MASK, int VK>
 __global__ void __launch_bounds__(VK ? kVkThreads : 1024) k_grid_sweep(GridSweep<T> g, GridTiles t, T h, T om, T omr) {
     constexpr int K = 2 * NS;
@@ -1469,7 +1472,7 @@ void freeze_inside(hipStream_t s, int N, int m, const GridTets &t, int n, const 
 //     thin tiles on many CUs.  A residual with edge weights waits for them in
 //     every step, 0.7 to 0.9 us (N = 64, 96, 128: 5.5, 11 and 21 us, against
 //     9, 18 and 32 with the tiles of a plain residual's step).
-// At N = 256 a plain sweep takes 100 us (98 by the bounds), at N = 512 730.
+// At N = 256 a plain sweep takes 91 us, at N = 512 680.
 GridTiles tiles(int N, int ns, int start, int tail, int word, bool vk) {
     const int K = tail == kGridResidual ? 0 : 2 * ns, np = N / 2;
     const int hl = halo_lo(K, tail), hh = halo_hi(K, tail);

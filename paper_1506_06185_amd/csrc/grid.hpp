@@ -2,8 +2,9 @@
 //
 // The Kuhn tetrahedra tile the N^3 grid and the operator couples a node to
 // its 6 axis neighbours (k = 1: one stencil everywhere; per-element k: a
-// weight per edge), so the unmasked and the Dirichlet-Dirichlet cycles keep u
-// and b of every level as one grid, x fastest: node (x, y, z) at
+// weight per edge), so a context on the cube keeps u and b of every level as
+// one grid, x fastest, and all its global cycles, a recovery's intact side
+// included, run there (faulty tetrahedra recover in slot space): node (x, y, z) at
 // x + P (y + N z), 0 <= x, y < N, 0 <= z <= N, with the Dirichlet nodes stored
 // as zeros.  The row pitch P exceeds N, and row y = N of a plane is row y = 0
 // of the next one, so every neighbour of an interior node is a plain offset

@@ -820,105 +820,68 @@ __global__ void __launch_bounds__(64 * NW) k_coarse_pcg(int n, const long long *
     if (tid == 0 && iters) *iters = it;
 }
 
-// the same Jacobi-PCG in a single wavefront (n <= 64 NPT): reductions are
-// wave shuffles and the only barrier is the one that publishes p in LDS
-template <typename T, int NPT, int NB = 6>
+// the same Jacobi-PCG in a single wavefront, one row per lane (n <= 64):
+// reductions are wave shuffles and the only barrier is the one that publishes
+// p in LDS
+template <typename T, int NB = 6>
 __global__ void __launch_bounds__(64) k_coarse_pcg_wave(int n, const long long *__restrict__ slot,
                                                         const int *__restrict__ col, const double *__restrict__ val,
                                                         const unsigned char *__restrict__ frozen,
                                                         const T *__restrict__ b, T *__restrict__ u,
                                                         const int *__restrict__ cptr, const int *__restrict__ cidx,
                                                         double rtol, int maxit, int *__restrict__ iters) {
-    __shared__ double p_sh[64 * NPT];
-    const int tid = threadIdx.x;
-    double x[NPT], r[NPT], p[NPT], dinv[NPT], dg[NPT], av[NPT][NB];
-    int ac[NPT][NB];
-    bool act[NPT];
+    __shared__ double p_sh[64];
+    const int q = threadIdx.x;
+    const bool act = q < n && !(frozen && frozen[q]);
+    double x = 0.0, r = 0.0, dinv = 0.0, dg = 0.0, av[NB];
+    int ac[NB];
 #pragma unroll
-    for (int s = 0; s < NPT; s++) {
-        const int q = tid + 64 * s;
-        act[s] = q < n && !(frozen && frozen[q]);
-        x[s] = 0.0;
-        r[s] = 0.0;
-        p[s] = 0.0;
-        dinv[s] = 0.0;
-        dg[s] = 0.0;
+    for (int e = 0; e < NB; e++) {
+        ac[e] = 0;
+        av[e] = 0.0;
+    }
+    if (act) {
+        dg = val[(NB + 1) * q];
+        dinv = 1.0 / dg;
+        r = (double)b[slot[q]];
 #pragma unroll
         for (int e = 0; e < NB; e++) {
-            ac[s][e] = 0;
-            av[s][e] = 0.0;
+            const int c = col[(NB + 1) * q + 1 + e];
+            ac[e] = c >= 0 ? c : 0;
+            av[e] = c >= 0 ? val[(NB + 1) * q + 1 + e] : 0.0;
         }
-        if (act[s]) {
-            dg[s] = val[(NB + 1) * q];
-            dinv[s] = 1.0 / dg[s];
-            r[s] = (double)b[slot[q]];
-#pragma unroll
-            for (int e = 0; e < NB; e++) {
-                const int c = col[(NB + 1) * q + 1 + e];
-                ac[s][e] = c >= 0 ? c : 0;
-                av[s][e] = c >= 0 ? val[(NB + 1) * q + 1 + e] : 0.0;
-            }
-        }
-        p[s] = r[s] * dinv[s];
-        p_sh[q] = p[s];
     }
-    double rz = 0.0, rr0 = 0.0;
-#pragma unroll
-    for (int s = 0; s < NPT; s++) {
-        rz += r[s] * p[s];
-        rr0 += r[s] * r[s];
-    }
-    rz = wave_sum_dpp(rz);
-    rr0 = wave_sum_dpp(rr0);
+    double p = r * dinv;
+    p_sh[q] = p;
+    double rz = wave_sum_dpp(r * p);
+    const double rr0 = wave_sum_dpp(r * r);
     int it = 0;
     if (rr0 > 0.0) {
         const double stop = rtol * rtol * rr0;
         for (it = 1; it <= maxit; it++) {
             __syncthreads();
-            double qv[NPT];
-            double pq = 0.0;
+            double a = 0.0;
+            if (act) {
+                a = dg * p;
 #pragma unroll
-            for (int s = 0; s < NPT; s++) {
-                double a = 0.0;
-                if (act[s]) {
-                    a = dg[s] * p[s];
-#pragma unroll
-                    for (int e = 0; e < NB; e++) a += av[s][e] * p_sh[ac[s][e]];
-                }
-                qv[s] = a;
-                pq += p[s] * a;
+                for (int e = 0; e < NB; e++) a += av[e] * p_sh[ac[e]];
             }
-            pq = wave_sum_dpp(pq);
-            const double alpha = rz / pq;
-            double rr = 0.0, rz1 = 0.0;
-#pragma unroll
-            for (int s = 0; s < NPT; s++) {
-                x[s] += alpha * p[s];
-                r[s] -= alpha * qv[s];
-                rr += r[s] * r[s];
-                rz1 += r[s] * r[s] * dinv[s];
-            }
-            rr = wave_sum_dpp(rr);
-            rz1 = wave_sum_dpp(rz1);
+            const double alpha = rz / wave_sum_dpp(p * a);
+            x += alpha * p;
+            r -= alpha * a;
+            const double rr = wave_sum_dpp(r * r);
+            const double rz1 = wave_sum_dpp(r * r * dinv);
             if (rr <= stop) break;
             const double beta = rz1 / rz;
             rz = rz1;
             __syncthreads();  // every lane has finished reading p_sh
-#pragma unroll
-            for (int s = 0; s < NPT; s++) {
-                p[s] = r[s] * dinv[s] + beta * p[s];
-                p_sh[tid + 64 * s] = p[s];
-            }
+            p = r * dinv + beta * p;
+            p_sh[q] = p;
         }
     }
-#pragma unroll
-    for (int s = 0; s < NPT; s++) {
-        const int q = tid + 64 * s;
-        if (!act[s]) continue;
-        const T xv = (T)x[s];
-        for (int c = cptr[q]; c < cptr[q + 1]; c++) u[cidx[c]] = xv;
-    }
-    if (tid == 0 && iters) *iters = it;
+    if (act)
+        for (int c = cptr[q]; c < cptr[q + 1]; c++) u[cidx[c]] = (T)x;
+    if (q == 0 && iters) *iters = it;
 }
 
 // PCG of the coarsest level of a cube on the grid (grid.hpp), preconditioned
@@ -926,7 +889,7 @@ __global__ void __launch_bounds__(64) k_coarse_pcg_wave(int n, const long long *
 // inverse is sine transforms along x, y and z.  The coarsest k is a mean over
 // many elements, so few iterations are left (Jacobi: 35 and more), each with
 // six short products in LDS.  ord: unknown of every interior grid node (x
-// fastest).  Latency binds it: about 12 barriers per iteration.  343 unknowns,
+// fastest).  Latency binds it: 9 barriers per iteration.  343 unknowns,
 // log-normal k: 25.5 us, with the Jacobi PCG above 45 (one block of 512
 // threads: a second workgroup would need grid-wide waits, dearer than the work)
 template <typename T, int NPT>
@@ -1972,7 +1935,7 @@ void launch_coarse_pcg(hipStream_t s, int n, const long long *slot, const int *c
                            maxit, iters);
     };
     if (n <= 64)
-        run(k_coarse_pcg_wave<T, 1>, 64);
+        run(k_coarse_pcg_wave<T>, 64);
     else if (n <= 256)
         run(k_coarse_pcg<T, 4, 1>, 256);
     else if (n <= 512)
@@ -2216,7 +2179,7 @@ void launch_coarse_pcg15(hipStream_t s, int n, const long long *slot, const int 
                            maxit, iters);
     };
     if (n <= 64)
-        run(k_coarse_pcg_wave<T, 1, 14>, 64);
+        run(k_coarse_pcg_wave<T, 14>, 64);
     else if (n <= 256)
         run(k_coarse_pcg<T, 4, 1, 14>, 256);
     else if (n <= 512)
