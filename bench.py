@@ -626,8 +626,8 @@ def main():
     ap.add_argument("--no-general", action="store_true", help="skip the general-macro-mesh leg")
     ap.add_argument("--no-mesh", action="store_true", help="skip the unstructured-macro-mesh leg")
     ap.add_argument("--fused-sweeps", choices=("auto", "on", "off"), default="auto",
-                    help="slot-space smoother: fused red-black sweep pairs or two colour "
-                         "passes per sweep (default: the autotuner's choice)")
+                    help="passed to set_fused_sweeps; the cube's cycles run on their grid and "
+                         "take no slot-space sweep pairs")
     ap.add_argument("--graph", action="store_true", help="replay captured graphs (disables kernel timing)")
     ap.add_argument("--tune-cache", default=None,
                     help="autotuner cache file, read before and written after tuning and kept (default: a "
