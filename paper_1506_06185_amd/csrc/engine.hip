@@ -1428,8 +1428,8 @@ void grid_from_local(hhgr_ctx &c, hipStream_t s) {
 }
 
 // Slot vectors of a grid context's levels l and l - 1 for single operators:
-// u, b (or either of the coarser level) and r in the scratch vectors and the idle buffer of the finest u, which is zero
-// again at the end.
+// u, b (or either of the coarser level) and r in the scratch vectors and the
+// idle buffer of the finest u, which is zero again at the end.
 struct SlotScratch {
     hhgr_ctx &c;
     int l;
